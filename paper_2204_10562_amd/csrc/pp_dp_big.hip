@@ -1,23 +1,17 @@
-// Partition DP for 128 < L <= 2048 with 32-bit keys: one wavefront per candidate, the cells of
-// a row in super-rows of 128, the (cell, split) plane in blocks of 32 x 32 that the 64 lanes
-// cover as 4 x 4 tiles of 8 x 8.
+// Partition DP for 128 < L <= 2048 with 32-bit keys: one wavefront per candidate, the rows as in
+// pp_dp_row.h, up to four chunks of 64 cells side by side.
 //
-// Recursion for W(l, xi, r, i) of Sec. IV-B / the PRM listing with one replica per stage:
-//   W[n][l] = min_{n<=k<l} max(g_n[k], P[l] - P[k]),   g_n[k] = max(W[n-1][k], X_n[k]).
-//
-// Same key representation and lane layout as the kernel for L <= 128 (lane (a, b) owns cells
-// 128I + 8i + a + 1 and splits 128J + 8j + b; a cell is (time << K) | k, so max keeps the
-// split index and min returns the smallest time with the lowest split), but the difference
-// term ((P[l] - P[k]) << K) | k is too large to keep in registers for the whole plane, so it
-// is formed on the fly: subtract, max and half a three-operand min per pair.  The cells are
-// taken in groups of 32 (four tiles); a group visits the blocks of 32 splits on or below the
-// diagonal, from the diagonal leftwards, and stops as soon as the difference term alone rules
-// out everything further left for its cells; the last super-row has NTL <= 16 cell tiles,
-// fixed at compile time, so a model of 300 layers does not pay for 384.
+// What bounds it: the latency of the searches' LDS reads, then instruction issue (vector unit busy
+// 59 % at L = 1024, where the LDS holds three waves per SIMD; four chunks side by side give each
+// wave four reads in flight).  About 33 K vector instructions per candidate at L = 1024, S = 32,
+// against 125 K when every (cell, split) pair up to an exact early exit was evaluated: 2^20
+// candidates 275 -> 88 ms; L = 300, S = 16, 15 751 representatives 297 -> 210 us.  (One lane per row
+// and one step per cell with a monotone queue was measured too: 345 ms at L = 1024, a serial chain of
+// LDS trips per cell.)
 //
 // Per wave in LDS: two rows of keys (the row being read, rewritten in place as g, and the row
-// being produced).  Split indices go to a per-wave table in global memory while the next row's
-// g is built (one coalesced pass), and the plan is read back from there with cache-bypassing
+// being produced) and h.  Split indices go to a per-wave table in global memory while the next
+// row's g is built (coalesced), and the plan is read back from there with cache-bypassing
 // loads.  Waves are persistent and walk candidates wave, wave + nwaves, ...; where groups of
 // candidates are the same problem (pp_share.hip) a wave instead takes a run of consecutive
 // entries of the sorted list of representatives, keeps every row it computes in the workspace
@@ -25,13 +19,10 @@
 #include "pp_common.h"
 #include "pp_dp_flat.h"
 #include "pp_dp_generic.h"
-
-#define DPP_QUAD_XOR1 0xB1     // quad_perm:[1,0,3,2]
-#define DPP_QUAD_XOR2 0x4E     // quad_perm:[2,3,0,1]
-#define DPP_HALF_MIRROR 0x141  // row_half_mirror: lane b <-> 7-b within each 8 lanes
+#include "pp_dp_row.h"
 
 struct dp_big_args {
-    int NI;      // super-rows: ceil(L / 128)
+    int NC;      // chunks of 64 cells: ceil(L / 64)
     int waves;   // working waves (each owns one backtrack table)
     size_t arg_stride;  // entries of one wave's backtrack table: S * Lp
     // non-NULL: if the workspace header says so, walk this list of representatives (one per
@@ -44,134 +35,30 @@ struct dp_big_args {
     dp_args g;
 };
 
-__device__ __forceinline__ int bmin(int a, int b) { return a < b ? a : b; }
-__device__ __forceinline__ int bmax(int a, int b) { return a > b ? a : b; }
-
-template <int CTRL>
-__device__ __forceinline__ int big_dpp_min(int v) {
-    int o = __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, true);
-    return bmin(v, o);
+// Where the split of cell k of a row stands in its row of the backtrack table: the four chunks of a
+// whole group of 256 cells lane by lane (one store of 8 bytes per lane), the rest cell by cell.
+__device__ __forceinline__ int big_arg_at(int k, int Lp) {
+    return k < (Lp & ~255) ? (k & ~255) | (k & 63) << 2 | (k >> 6 & 3) : k;
 }
 
-__device__ __forceinline__ int big_min_over_b(int v) {
-    v = big_dpp_min<DPP_QUAD_XOR1>(v);
-    v = big_dpp_min<DPP_QUAD_XOR2>(v);
-    v = big_dpp_min<DPP_HALF_MIRROR>(v);
-    return v;
-}
-
-__device__ __forceinline__ void big_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
-// The g row and the table (P[k] << K) - k at the 4 split tiles of one block, as lane (a, b)
-// needs them: splits 8 j + b.
-struct big_splits {
-    int g[4], pk[4];
-};
-
-__device__ __forceinline__ void big_load(big_splits &s, const int *G, const int *Pk, int lb) {
+// The chunks c0 .. c0 + 64 U - 1 of a row being built (c0 a multiple of 256).  xv: the link's times;
+// arow: where the previous row's split indices go (NULL: nowhere).
+template <int U>
+__device__ __forceinline__ void big_build(dp_row &r, int c0, const int (&xv)[4], unsigned short *arow) {
+    int w[U];
+    row_build<U>(r, c0, xv, w);
+    if (!arow) return;
+    if (U == 4) {
+        const unsigned lo = (unsigned)(w[0] & r.kmask) | (unsigned)(w[U > 1 ? 1 : 0] & r.kmask) << 16;
+        const unsigned hi = (unsigned)(w[U > 2 ? 2 : 0] & r.kmask) | (unsigned)(w[U > 3 ? 3 : 0] & r.kmask) << 16;
+        *(uint2 *)(arow + c0 + 4 * r.lane) = make_uint2(lo, hi);
+    } else {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) { s.g[j] = G[8 * j + lb]; s.pk[j] = Pk[8 * j + lb]; }
-}
-
-// One block: NI4 (<= 4) cell tiles against 4 split tiles.  DIAG: the split tiles are the cell
-// tiles' own: tiles above the diagonal are skipped, those on it are valid for lanes with b <= a.
-template <int NI4, bool DIAG>
-__device__ __forceinline__ void big_block(int (&acc)[4], const int (&Pl)[4], const big_splits &s,
-                                          int la, int lb) {
-#pragma unroll
-    for (int i = 0; i < NI4; ++i) {
-        int v = acc[i];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (DIAG && j > i) continue;
-            int d = Pl[i] - s.pk[j];
-            if (DIAG && j == i) d = lb <= la ? d : PP_INF32;
-            v = bmin(v, bmax(s.g[j], d));
-        }
-        acc[i] = v;
+        for (int u = 0; u < U; ++u) arow[c0 + 64 * u + r.lane] = (unsigned short)(w[u] & r.kmask);
     }
 }
 
-// (cell, split) pairs with cell in [a, b], split in [klo, cell - 1] (at most L^2 / 2 < 2^22)
-__device__ __forceinline__ unsigned big_pairs(int a, int b, int klo) {
-    if (a <= klo) a = klo + 1;
-    if (b < a) return 0;
-    const unsigned lo = (unsigned)(a - klo), hi = (unsigned)(b - klo);
-    return (lo + hi) * (hi - lo + 1) / 2;
-}
-
-// A group of NI4 cell tiles (cells c0+1 .. c0+8 NI4, c0 a multiple of 32) of row n: the block on
-// the diagonal, then the blocks of 32 splits to its left from the nearest on, then the
-// reduction over the 8 lanes that share a cell, then the cells go to the next row.
-// P[l] - P[k] grows as k falls, so once the smallest difference of the next block (first cell
-// of the group against the block's last split) exceeds every value a lane still holds for a
-// cell of the group, neither that block nor any further left can lower or tie one of them:
-// the scan stops there.  The test costs a scalar subtraction, two maxima and one compare:
-// pend holds (P[32 s + 31] << K) in lane s.  Returns the pairs evaluated (for the work counter).
-template <int NI4>
-__device__ __forceinline__ unsigned big_cell_group(int c0, int n, int L, const int *G,
-                                                             const int *sPk, int *nxt, int la,
-                                                             int lb, int pend) {
-    int acc[4], Pl[4];
-#pragma unroll
-    for (int i = 0; i < NI4; ++i) {
-        const int l = c0 + 8 * i + la + 1;
-        Pl[i] = sPk[l] + l;  // P[l] << K
-        acc[i] = PP_INF32;
-    }
-    big_splits s;
-    big_load(s, G + c0, sPk + c0, lb);
-    big_block<NI4, true>(acc, Pl, s, la, lb);
-    const int first = __builtin_amdgcn_readlane(Pl[0], 0);  // lane 0 holds cell c0 + 1
-    const int sg_lo = n >> 5;  // blocks wholly below split n hold nothing feasible
-    int sg = (c0 >> 5) - 1;
-    for (; sg >= sg_lo; --sg) {
-        // ((P[c0 + 1] - P[32 sg + 31]) << K) is the smallest difference key of block sg: it can
-        // still lower or tie a cell of the group only if some lane holds a key that is not below it
-        // (fetching the next block's splits ahead of this test was measured: no gain)
-        const int dkey = first - __builtin_amdgcn_readlane(pend, sg);
-        int m = acc[0];
-#pragma unroll
-        for (int i = 1; i < NI4; ++i) m = bmax(m, acc[i]);
-        if (!__ballot(m >= dkey)) break;
-        big_load(s, G + 32 * sg, sPk + 32 * sg, lb);
-        big_block<NI4, false>(acc, Pl, s, la, lb);
-    }
-#pragma unroll
-    for (int i = 0; i < NI4; ++i) {
-        acc[i] = big_min_over_b(acc[i]);
-        asm volatile("" : "+v"(acc[i]));
-    }
-    if (lb == 0) {
-#pragma unroll
-        for (int i = 0; i < NI4; ++i) nxt[c0 + 8 * i + la + 1] = acc[i];
-    }
-    const int a0 = c0 + 1 > n + 1 ? c0 + 1 : n + 1, b0 = c0 + 8 * NI4 < L ? c0 + 8 * NI4 : L;
-    const int klo = 32 * (sg + 1) > n ? 32 * (sg + 1) : n;
-    return big_pairs(a0, b0, klo);
-}
-
-// One super-row of NTI cell tiles of row n, in groups of four.
-template <int NTI>
-__device__ __forceinline__ unsigned big_super_row(int I, int n, int L, const int *G,
-                                                            const int *sPk, int *nxt, int la,
-                                                            int lb, int pend) {
-    unsigned pairs = 0;
-    constexpr int REST = (NTI & 3) ? (NTI & 3) : 4;
-#pragma unroll
-    for (int cg = 0; cg < (NTI + 3) / 4; ++cg) {
-        const int c0 = 128 * I + 32 * cg;
-        if (NTI - 4 * cg >= 4) pairs += big_cell_group<4>(c0, n, L, G, sPk, nxt, la, lb, pend);
-        else pairs += big_cell_group<REST>(c0, n, L, G, sPk, nxt, la, lb, pend);
-    }
-    return pairs;
-}
-
-template <int NTL>
-__global__ __launch_bounds__(256) void k_dp_big(dp_big_args b) {
+__global__ __launch_bounds__(256, 4) void k_dp_big(dp_big_args b) {
     extern __shared__ __align__(16) unsigned char smem[];
     const dp_args &a = b.g;
     if (pp_is_flat(a.hdr)) {
@@ -186,20 +73,32 @@ __global__ __launch_bounds__(256) void k_dp_big(dp_big_args b) {
     const int lane = threadIdx.x & 63;
     const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wpb = blockDim.x >> 6;
-    const int la = lane >> 3, lb = lane & 7;
-    const int S = a.S, K = a.K, L = a.L, D = a.D, NI = b.NI;
-    const int Lp = 128 * NI, RS = Lp + 4;
+    const int S = a.S, K = a.K, L = a.L, D = a.D;
+    const int Lp = 64 * b.NC, RS = Lp + 4;
     const int kmask = (1 << K) - 1;
-    int *sPk = (int *)smem;                       // (P[k] << K) - k, k = 0..Lp (P padded with P[L])
-    int *bufA = sPk + RS + (size_t)wib * 2 * RS;  // this wave's two rows
+    // (P[k] << K) - k, k = 0..Lp (P padded with P[L]); this wave's two rows and h.  Every array has
+    // an entry of padding in front (index -1).
+    int *sPk = (int *)smem + 1;
+    int *bufA = sPk + RS + (size_t)wib * 3 * RS;
     int *bufB = bufA + RS;
     const long long wave = (long long)blockIdx.x * wpb + wib;
 
     for (int k = threadIdx.x; k <= Lp; k += blockDim.x) sPk[k] = (a.p32[k < L ? k : L] << K) - k;
+    if (threadIdx.x == 0) sPk[-1] = 0;
     __syncthreads();
     if (wave >= b.waves) return;
-    // lane s: (P[32 s + 31] << K), the last split of block s (for the early exit's test)
-    const int pend = 32 * lane + 31 <= Lp ? sPk[32 * lane + 31] + 32 * lane + 31 : 0;
+    dp_row row;
+    row.h = (unsigned *)(bufB + RS);
+    row.PK = sPk;
+    row.L = L;
+    row.K = K;
+    row.kmask = kmask;
+    row.strict = a.hdr->strict != 0;
+    row.lane = lane;
+    // lane n: steps of a search in row n.  With balanced stages a cell of row n chooses among the
+    // splits within P[l] / (n + 1) of it; a row that needs more gets a step more from then on.
+    int v_steps = 1;
+    while ((1 << v_steps) - 1 < L / (lane + 1) + L / (8 * (lane + 1)) + 2) ++v_steps;
     unsigned short *arg = a.arg + (size_t)wave * b.arg_stride;
     unsigned long long pairs = 0, nrows = 0;
     const int tri = S * (S + 1) / 2;
@@ -318,7 +217,7 @@ __global__ __launch_bounds__(256) void k_dp_big(dp_big_args b) {
         if (p == 0) {
             // row 0: one stage holding the first l layers
             for (int l = lane; l <= Lp; l += 64) cur[l] = l ? sPk[l] + l : PP_INF32;
-            big_lds_sync();
+            row_lds_sync();
             top = cur[L];  // S == 1: C = P[L]
             v_tops = top;
         } else {
@@ -328,43 +227,60 @@ __global__ __launch_bounds__(256) void k_dp_big(dp_big_args b) {
             const int *from = save + (size_t)(p - 1) * RS;
             for (int l = lane; l <= Lp; l += 64)
                 cur[l] = __hip_atomic_load(from + l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            big_lds_sync();
+            row_lds_sync();
         }
 
-        for (int n = p + 1; n < S; ++n) {
-            const int *xrow = a.x32 + (size_t)__builtin_amdgcn_readlane(v_link, n) * L;
-            // Rewrite the previous row in place as g; on the way its split indices (the low
-            // key bits) go to the backtrack table.
-            unsigned short *arow = arg + (size_t)(n - 1) * Lp;
-            // (the link's times are requested eight steps at a time, ahead of the stores they
-            // could otherwise not be moved across: one trip per 512 splits instead of eight)
-            for (int k0 = lane; k0 < Lp; k0 += 512) {
-                int xv[8];
+        // the links' times are requested 256 splits ahead (from row to row as well)
+        const int c_last = (Lp - 1) & ~255;  // first split of the last group of four chunks
+        int xv[4], xn[4];
+        auto fetch_x = [&](int (&x)[4], const int *xrow, int c0) {
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int k = k0 + 64 * u;
-                    xv[u] = (k >= 1 && k < L) ? xrow[k] : 0;
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int k = k0 + 64 * u;
-                    if (k < Lp) {
-                        const int w = cur[k];
-                        if (n >= 2) arow[k] = (unsigned short)(w & kmask);
-                        int xk = PP_INF32;
-                        if (k >= 1 && k < L) xk = (xv[u] << K) | k;
-                        int wk = (w & ~kmask) | (xk & kmask);
-                        cur[k] = bmax(wk, xk);
-                    }
-                }
+            for (int u = 0; u < 4; ++u) {
+                const int k = c0 + 64 * u + lane;
+                x[u] = k < L ? xrow[k] : 0;
             }
-            big_lds_sync();
+        };
+        fetch_x(xv, a.x32 + (size_t)__builtin_amdgcn_readlane(v_link, p + 1 < S ? p + 1 : p) * L, c_last);
+        for (int n = p + 1; n < S; ++n) {
+            // The previous row's split indices (the low key bits) go to the backtrack table.
+            unsigned short *arow = n >= 2 ? arg + (size_t)(n - 1) * Lp : NULL;
+            const int *xrow = a.x32 + (size_t)__builtin_amdgcn_readlane(v_link, n) * L;
+            const int *xnext = a.x32 + (size_t)__builtin_amdgcn_readlane(v_link, n + 1 < S ? n + 1 : n) * L;
+            // (the times of the splits c0 .. c0 + 255 of this row, or the last ones of the next row)
+            auto fetch_from = [&](int c0) {
+                const bool here = c0 >= 0;
+                fetch_x(xn, here ? xrow : xnext, here ? c0 : c_last);
+            };
             if (n < S - 1) {
-                for (int I = 0; I < NI; ++I)
-                    pairs += I + 1 < NI ? big_super_row<16>(I, n, L, cur, sPk, nxt, la, lb, pend)
-                                        : big_super_row<NTL>(I, n, L, cur, sPk, nxt, la, lb, pend);
-                if (lane == 0) nxt[0] = PP_INF32;
-                big_lds_sync();
+                row.W = row.g = cur;
+                row.out = nxt;
+                row.n = n;
+                row.steps = __builtin_amdgcn_readlane(v_steps, n);
+                row.carry = PP_INF32;
+                row.again = false;
+                for (int c0 = c_last; c0 >= 0; c0 -= 256) {
+                    const int left = (Lp - c0) >> 6;
+                    if (left >= 4) big_build<4>(row, c0, xv, arow);
+                    else if (left == 3) big_build<3>(row, c0, xv, arow);
+                    else if (left == 2) big_build<2>(row, c0, xv, arow);
+                    else big_build<1>(row, c0, xv, arow);
+                    // (after the stores, so that the wait for the times does not have to be one for
+                    // younger stores)
+                    fetch_from(c0 - 256);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) xv[u] = xn[u];
+                }
+                row_lds_sync();
+                for (int c0 = 0; c0 < Lp; c0 += 256) {
+                    const int left = (Lp - c0) >> 6;
+                    if (left >= 4) row_search<4>(row, c0);
+                    else if (left == 3) row_search<3>(row, c0);
+                    else if (left == 2) row_search<2>(row, c0);
+                    else row_search<1>(row, c0);
+                }
+                pairs += (unsigned long long)(L - n) * (unsigned)(row.steps + 1);
+                if (row.again && lane == n && v_steps < K) ++v_steps;
+                row_lds_sync();
                 int *t = cur; cur = nxt; nxt = t;
                 const int top_n = cur[L];
                 if (lane == n) v_tops = top_n;
@@ -377,8 +293,22 @@ __global__ __launch_bounds__(256) void k_dp_big(dp_big_args b) {
                 // only W[S-1][L] is needed of the last row
                 const int PL = sPk[L] + L;
                 int v = PP_INF32;
-                for (int k = lane; k < L; k += 64) v = bmin(v, bmax(cur[k], PL - sPk[k]));
-                for (int off = 32; off; off >>= 1) v = bmin(v, __shfl_xor(v, off));
+                for (int c0 = c_last; c0 >= 0; c0 -= 256) {
+                    fetch_from(c0 - 256);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int k = c0 + 64 * u + lane;
+                        if (k >= L) continue;
+                        const int w = cur[k];
+                        if (arow) arow[big_arg_at(k, Lp)] = (unsigned short)(w & kmask);
+                        const int xk = (int)((unsigned)xv[u] << K) | k, wk = (w & ~kmask) | k;
+                        const int t = row_imax(row_imax(wk, xk), PL - sPk[k]);
+                        v = k >= n ? row_imin(v, t) : v;
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) xv[u] = xn[u];
+                }
+                for (int off = 32; off; off >>= 1) v = row_imin(v, __shfl_xor(v, off));
                 top = v;
                 if (lane == n) v_tops = v;
                 pairs += (unsigned long long)(L - n);
@@ -402,7 +332,7 @@ __global__ __launch_bounds__(256) void k_dp_big(dp_big_args b) {
                         e = v_tops & kmask;
                         e = e < Lp ? e : Lp - 1;  // stays inside the table whatever the data
                     } else {
-                        const size_t at = (size_t)m * Lp + e;
+                        const size_t at = (size_t)m * Lp + big_arg_at(e, Lp);
                         const unsigned *word = (const unsigned *)(arg + (at & ~(size_t)1));
                         unsigned w2 = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         e = (int)((at & 1) ? (w2 >> 16) : (w2 & 0xffffu));
@@ -418,7 +348,7 @@ __global__ __launch_bounds__(256) void k_dp_big(dp_big_args b) {
             if (m == S - 1) {
                 e = top & kmask;
             } else {
-                const size_t at = (size_t)m * Lp + e;
+                const size_t at = (size_t)m * Lp + big_arg_at(e, Lp);
                 const unsigned *word = (const unsigned *)(arg + (at & ~(size_t)1));
                 unsigned w2 = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 e = (int)((at & 1) ? (w2 >> 16) : (w2 & 0xffffu));
@@ -430,19 +360,13 @@ __global__ __launch_bounds__(256) void k_dp_big(dp_big_args b) {
     if (lane == 0) pp_count_work(a.hdr, pairs, nrows, (unsigned)wave);
 }
 
-template <int NTL>
-static int launch_big(const dp_big_args &b, int grid, int wpb, size_t lds, hipStream_t st) {
-    hipLaunchKernelGGL(k_dp_big<NTL>, dim3(grid), dim3(64 * wpb), lds, st, b);
-    return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_HIP;
-}
-
 // LDS of a workgroup and waves per workgroup for this shape (0 if it does not fit).
 static size_t big_lds(int L, int D, int S, int &wpb) {
-    const int Lp = 128 * ((L + 127) / 128), RS = Lp + 4;
-    wpb = 4;  // waves per workgroup: table + two rows per wave within 64 KiB of LDS
-    while (wpb > 1 && (size_t)(1 + 2 * wpb) * RS * 4 > 64 * 1024) wpb >>= 1;
-    size_t lds = (size_t)(1 + 2 * wpb) * RS * 4;
-    const size_t generic = (size_t)3 * (L + 1) * 8;  // the int64 fallback's rows
+    const int Lp = 64 * ((L + 63) / 64), RS = Lp + 4;
+    wpb = 4;  // waves per workgroup: table + two rows and h per wave within 64 KiB of LDS
+    while (wpb > 1 && (size_t)(1 + 3 * wpb) * RS * 4 > 64 * 1024) wpb >>= 1;
+    size_t lds = (size_t)(1 + 3 * wpb) * RS * 4;
+    const size_t generic = dp_generic_lds_bytes(L);  // the int64 fallback's rows
     if (lds < generic) lds = generic;
     const size_t flat = pp_flat_lds_wanted(L, D, S, wpb);  // the closed-form body's tables
     if (lds < flat) lds = flat;
@@ -454,7 +378,8 @@ int pp_dp_big_waves(int L, int D, int S, int max_waves, int cus) {
     const size_t lds = big_lds(L, D, S, wpb);
     if (!lds) return 1;
     // resident waves: 4 per SIMD by registers, and what 160 KiB of LDS per CU allow
-    long long per_cu = (long long)(160 * 1024 / lds) * wpb;
+    // (given out in pieces of 1280 bytes)
+    long long per_cu = (long long)(160 * 1024 / ((lds + 1279) / 1280 * 1280)) * wpb;
     if (per_cu > 16) per_cu = 16;
     if (per_cu < 1) per_cu = 1;
     long long waves = per_cu * cus;
@@ -471,10 +396,8 @@ int pp_launch_dp_big(const dp_args &g, int max_waves, int cus, const pp_share_li
     b.start = list ? list->start : NULL;
     b.rows = list ? list->rows : NULL;
     b.row_slots = list ? list->row_slots : 0;
-    b.NI = (g.L + 127) / 128;
-    const int Lp = 128 * b.NI, RS = Lp + 4;
-    b.arg_stride = (size_t)g.S * Lp;
-    const int ntl = (g.L - 128 * (b.NI - 1) + 7) / 8;
+    b.NC = (g.L + 63) / 64;
+    b.arg_stride = (size_t)g.S * 64 * b.NC;
     int wpb;
     const size_t lds = big_lds(g.L, g.D, g.S, wpb);
     if (!lds) return PP_ERR_INVALID_ARG;
@@ -483,11 +406,6 @@ int pp_launch_dp_big(const dp_args &g, int max_waves, int cus, const pp_share_li
     b.waves = (int)waves;
     const int grid = (int)((waves + wpb - 1) / wpb);
     b.g.nblocks = g.nblocks < grid ? g.nblocks : grid;
-    switch (ntl) {
-#define CASE(n) case n: return launch_big<n>(b, grid, wpb, lds, st);
-        CASE(1) CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8)
-        CASE(9) CASE(10) CASE(11) CASE(12) CASE(13) CASE(14) CASE(15) CASE(16)
-#undef CASE
-    }
-    return PP_ERR_INVALID_ARG;
+    hipLaunchKernelGGL(k_dp_big, dim3(grid), dim3(64 * wpb), lds, st, b);
+    return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_HIP;
 }

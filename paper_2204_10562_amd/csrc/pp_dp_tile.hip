@@ -488,7 +488,7 @@ static int launch_nt(const dp_tile_args &a, int grid, int wpb, size_t lds, hipSt
 
 int pp_launch_dp_tile(const dp_tile_args &a, int nt, int grid, int wpb, hipStream_t st) {
     size_t lds = (size_t)wpb * pp_dp_tile_lds_per_wave(a.S, nt);
-    const size_t generic = (size_t)3 * (a.L + 1) * 8;  // the int64 fallback's rows
+    const size_t generic = dp_generic_lds_bytes(a.L);  // the int64 fallback's rows
     if (lds < generic) lds = generic;
     const size_t flat = pp_flat_lds_wanted(a.L, a.D, a.S, wpb);  // the closed-form body's tables
     if (lds < flat) lds = flat;
