@@ -18,97 +18,13 @@
 // ramp-down sweeps are compile-time constants, otherwise every block is computed in every
 // sweep and its update kept or dropped; 32-bit when the bound (M+4S-4) * largest block of
 // Lemma 1 fits, else 64-bit, decided per wave; several microbatch counts run side by side,
-// one wave each, in workgroups that share the gather of the block durations); for larger S
-// they live in the lane's own LDS column.
+// one wave each, in workgroups that share the gather of the block durations).  For larger S the
+// resources of a candidate are spread over a few lanes (pp_makespan_split.hip) when the times fit
+// 30 bits; otherwise they live in the lane's own LDS column (k_makespan_lds).
 // When asked to, each wave also reduces (T, candidate) to its minimum, and a one-workgroup
 // kernel launched next reduces the per-wave minima to the winner record.
-#include "pp_common.h"
 #include "pp_dp_flat.h"
-
-struct tc_pair { long long T, c; };
-
-struct mk_args {
-    int L, D, S, nM;
-    int Ms[PP_MAX_M_LIST];  // microbatch counts; the plans are evaluated once per entry
-    // k_makespan_regs: wave slot i (blockIdx.y * waves + wave) serves count Ms[order[i]]
-    unsigned char order[PP_MAX_M_LIST];
-    // k_makespan_regs8: a workgroup holds `groups` groups of waves, each group one wave per
-    // microbatch count for its own 64 candidates; wave w of group g takes slot
-    // (slot_perm >> 2 (4 g + w)) & 3 of its four
-    int groups;
-    unsigned slot_perm;
-    // k_makespan_regs8: nonzero = blockIdx.z + 1 is the number of stages xi, the plan with xi
-    // stages is read from the triangular bounds array and T goes to column xi-1 (S, bnd_off and
-    // t_off are then ignored)
-    int all_xi;
-    // With all_xi and the library's own list of all D! orderings in lexicographic order:
-    // share[xi] = (D - xi)! consecutive candidates share their first xi devices and with them
-    // the plan of xi stages, so it is scheduled once per such block (share[xi] = 1: no sharing)
-    long long share[9];
-    long long N;
-    const long long *PF, *PB, *XF, *XB;
-    const int *orderings;  // NULL = all D! orderings, candidate index = lexicographic rank
-    const int *bounds;
-    long long *T_out;      // [nM][N]; may be NULL when only the winners are wanted
-    // Where candidate c's data lie: devices at orderings[c*ord_stride + n], bounds at
-    // bounds[c*bnd_stride + bnd_off + n], T of microbatch count q at
-    // T_out[(q*N + c)*t_stride + t_off].  (ord_stride, bnd_stride, bnd_off, t_stride, t_off)
-    // = (S, S, 0, 1, 0) for plain lists; the stage-count search evaluates the plans with S = xi
-    // stages out of rows that hold search = S_max devices and all S_max plans.
-    int ord_stride, bnd_off, t_off;
-    long long bnd_stride, t_stride;
-    // search > 0 (arg-min only): the N entries are (candidate, stage count) pairs, entry
-    // i = c*search + xi-1; the record of the winner is decoded accordingly
-    int search;
-    int variant;  // k_makespan_variant only: PP_SCHED_*
-    // k_makespan_mid / k_makespan_lds launched together without a header (17..32 stages, no
-    // workspace): nonzero = every block of 64 candidates decides for itself which of the two
-    // kernels schedules it (see mid_takes_block)
-    int by_block;
-    // workspace header with the largest time of the tables (NULL if there is none): lets every
-    // wave of a launch take the same decision between 32-bit and 64-bit finish times
-    const pp_ws_header *hdr;
-    // k_makespan_regs8 inside pp_best_plan: nonzero = when no link's channel time depends on the
-    // cut position and every finish time of the launch fits 32 bits (both read from hdr), the
-    // partition DP kernel has left the plans to this kernel, which builds them in closed form
-    // from the channel-free tables bfl (pp_dp_flat.h) and writes C_w [N] and bounds_w [N][S].
-    // fuse_mmax: the largest microbatch count of the call (the DP kernel tests the same bound).
-    int fuse, fuse_mmax, fuse_validate;
-    const long long *bfl;
-    long long *C_w;
-    int *bounds_w;
-    int32_t *status;
-    // replicated stages (k_rep_makespan and the record of its arg-min; NULL otherwise): replica
-    // counts laid out like bounds, prefix sums of the parameter sizes, activation sizes, the
-    // bandwidth matrix, and W per (candidate, stage count) (PP_INF64 = no such plan)
-    const int *reps;
-    const long long *PA, *actf, *actb, *bw, *W;
-    // k_makespan_regs<S> inside pp_best_plan: non-NULL = if the workspace header says that
-    // candidates share their partition DP (pp_share.hip), this is the list of the candidates
-    // that stand for all others; only they are scheduled (entry i by lane i of the launch), and
-    // the slots of the partials no wave writes hold "none" already
-    const int *rlist;
-    pp_rep_result *rout;   // [nM] winner records with replica counts (instead of out)
-    // arg-min (all NULL when not wanted)
-    tc_pair *part;         // [nM][waves]: every wave's minimum, reduced by k_pick
-    long long n_part;      // k_pick: partials per microbatch count
-    const long long *C;
-    pp_result *out;        // [nM]
-};
-
-__device__ __forceinline__ tc_pair tc_min(tc_pair a, tc_pair b) {
-    return (b.T < a.T || (b.T == a.T && b.c < a.c)) ? b : a;
-}
-
-__device__ __forceinline__ tc_pair wave_tc_min(tc_pair v) {
-    for (int off = 32; off; off >>= 1) {
-        tc_pair o;
-        o.T = __shfl_xor(v.T, off);
-        o.c = __shfl_xor(v.c, off);
-        v = tc_min(v, o);
-    }
-    return v;
-}
+#include "pp_makespan.h"
 
 // Checks candidate c's ordering and bounds and gathers its block durations through `put`
 // (called as put(block j (1-based), duration)).  Returns fault bits; on a fault or for a
@@ -189,28 +105,6 @@ template <int ST, typename Put>
 __device__ __forceinline__ int gather_durations(const mk_args &a, long long c, bool live,
                                                 long long &worst, Put put) {
     return gather_durations<ST>(a, c, live, worst, put, [](long long, long long) {});
-}
-
-// The schedule is no longer than (M + 4S - 4) * C (Lemma 1): fault if that bound reaches 2^62.
-__device__ __forceinline__ int overflow_fault(long long worst, int M, int S) {
-    return worst > (PP_CAP62 - 1) / ((long long)M + 4 * S - 4) ? PP_FAULT_OVERFLOW : 0;
-}
-
-// Writes T of microbatch count q, raises faults, and (if wanted) leaves the wave's minimum in
-// its slot of the partials; k_pick, launched next on the same stream, reduces the partials.
-// (Plain stores and a kernel boundary: earlier versions let the last wave to arrive do the
-// final reduction, but the returned atomics and arrival counters that needs cost more than
-// the schedule itself once a launch has thousands of waves.)
-__device__ __forceinline__ void emit(const mk_args &a, int q, long long c, bool live, int fault,
-                                     long long T, long long wave_id, long long n_waves, int t_off) {
-    if (live) {
-        if (fault) { T = PP_INF64; pp_raise(a.status, fault); }
-        if (a.T_out) a.T_out[((long long)q * a.N + c) * a.t_stride + t_off] = T;
-    }
-    if (!a.part) return;
-    tc_pair v = {live ? T : PP_INF64, live ? c : INT64_MAX};
-    v = wave_tc_min(v);
-    if ((threadIdx.x & 63) == 0 && wave_id < n_waves) a.part[(long long)q * n_waves + wave_id] = v;
 }
 
 // The winner record of microbatch count q from the minimum w over all entries.
@@ -915,88 +809,15 @@ __global__ __launch_bounds__(64) void k_rep_makespan(mk_args a) {
 
 // ---------------------------------------------------------------- LDS columns, any S
 
-// True if no finish time of any candidate of the launch can reach 2^31 for any of its
-// microbatch counts (Lemma 1's bound with the largest time of the tables); the same for every
-// lane of every wave.  False without a header.
+// True if every finish time of the launch fits k_makespan_split, from the largest time in the
+// workspace header; the same for every lane of every wave.  False without a header.
 __device__ __forceinline__ bool launch_is_narrow(const mk_args &a) {
     if (!a.hdr) return false;
     unsigned long long vmax = 0;
     for (int b = 0; b < PP_PACK_BLOCKS; ++b) vmax = a.hdr->pmax[b] > vmax ? a.hdr->pmax[b] : vmax;
     int mmax = 1;
     for (int q = 0; q < a.nM; ++q) mmax = a.Ms[q] > mmax ? a.Ms[q] : mmax;
-    return vmax <= 0x7fffffffull / (unsigned long long)(mmax + 4 * a.S - 4);
-}
-
-// Without a header the same question per block of 64 candidates, from the largest per-resource
-// time of each of them (`worst` as gather_durations reports it; ok = this lane's candidates fit,
-// dead and faulty ones count as fitting): both kernels evaluate this on the same values, so
-// exactly one of them schedules the block.
-__device__ __forceinline__ bool fits_narrow(const mk_args &a, long long worst) {
-    int mmax = 1;
-    for (int q = 0; q < a.nM; ++q) mmax = a.Ms[q] > mmax ? a.Ms[q] : mmax;
-    return worst <= (long long)(0x7fffffffull / (unsigned long long)(mmax + 4 * a.S - 4));
-}
-
-// 16 < S <= 32 with 32-bit times: the 4S-3 finish times of a lane in registers (blocks
-// unrolled, each update selected by a per-lane test of the sweep's window), the durations in
-// the lane's LDS column.  Runs only if the whole launch is narrow; k_makespan_lds, launched
-// with it, runs otherwise.
-template <int S>
-__global__ __launch_bounds__(64) void k_makespan_mid(mk_args a) {
-    constexpr int R = 2 * S - 1, J = 2 * R - 1;
-    extern __shared__ int smi[];
-    if (!a.by_block && !launch_is_narrow(a)) return;
-    const int lane = threadIdx.x;
-    int *dur = smi + lane;  // [J][64]
-    const long long c = (long long)blockIdx.x * 64 + lane;
-    const bool live = c < a.N;
-    long long worst;
-    const int fault = gather_durations<S>(a, c, live, worst,
-                                          [&](int j, long long d) { dur[(j - 1) * 64] = (int)d; });
-    // (by block: this kernel takes the block iff all of its 64 candidates fit 32 bits)
-    if (a.by_block && !__all(!live || fault || fits_narrow(a, worst))) return;
-    for (int q = 0; q < a.nM; ++q) {
-        const int M = a.Ms[q];
-        const int fq = (live && !fault) ? overflow_fault(worst, M, S) : fault;
-        int fin[J + 1];
-#pragma unroll
-        for (int j = 0; j <= J; ++j) fin[j] = 0;
-        const int sweeps = M + 2 * R - 2;
-        const unsigned width = (unsigned)(M - 1);
-        for (int t = 1; t <= sweeps; ++t) {
-            const int jlo_s = t - M + 1;  // the sweep's window is blocks jlo_s .. t
-            int jlo = jlo_s;
-            asm volatile("" : "+v"(jlo));
-            const int finR_prev = fin[R];
-            // groups of eight blocks; one that lies wholly outside the window is jumped over
-            // (while the pipeline fills and drains that is about half of them)
-#pragma unroll
-            for (int jb = R; jb >= 1; jb -= 8) {
-                const int ja = jb - 7 > 1 ? jb - 7 : 1;
-                if (jb < jlo_s || ja > t) continue;
-#pragma unroll
-                for (int j = jb; j >= ja; --j) {
-                    int idle = fin[j] > fin[2 * R - j] ? fin[j] : fin[2 * R - j];
-                    int ready = j > 1 ? fin[j - 1] : 0;
-                    int nv = (idle > ready ? idle : ready) + dur[(j - 1) * 64];
-                    fin[j] = (unsigned)(j - jlo) <= width ? nv : fin[j];
-                }
-            }
-#pragma unroll
-            for (int jb = J; jb >= R + 1; jb -= 8) {
-                const int ja = jb - 7 > R + 1 ? jb - 7 : R + 1;
-                if (jb < jlo_s || ja > t) continue;
-#pragma unroll
-                for (int j = jb; j >= ja; --j) {
-                    int idle = fin[j] > fin[2 * R - j] ? fin[j] : fin[2 * R - j];
-                    int ready = j == R + 1 ? finR_prev : fin[j - 1];
-                    int nv = (idle > ready ? idle : ready) + dur[(j - 1) * 64];
-                    fin[j] = (unsigned)(j - jlo) <= width ? nv : fin[j];
-                }
-            }
-        }
-        emit(a, q, c, live, fq, (long long)fin[J], blockIdx.x, gridDim.x, a.t_off);
-    }
+    return vmax <= MK_SPLIT_CAP && mk_split_fits((long long)vmax, mmax, a.S);
 }
 
 // blockDim.x = lanes in use (64, or fewer when 2 * (4S-3) rows of 64 int64 would not fit in
@@ -1006,21 +827,9 @@ __global__ __launch_bounds__(64) void k_makespan_lds(mk_args a) {
     extern __shared__ long long sm[];
     const int lane = threadIdx.x, W = blockDim.x;
     const int S = a.S;
-    if (S > 16 && S <= 32 && !a.by_block && launch_is_narrow(a)) return;  // k_makespan_mid does this launch
-    if (a.by_block) {
-        // k_makespan_mid takes the block of 64 candidates this workgroup's W lie in iff all 64
-        // fit 32 bits: the same test here, every lane looking at 64 / W of them
-        const long long c0 = ((long long)blockIdx.x * W / 64) * 64;
-        bool ok = true;
-        for (int i = lane; i < 64; i += W) {
-            const long long cc = c0 + i;
-            const bool lv = cc < a.N;
-            long long w2;
-            const int f2 = gather_durations<0>(a, cc, lv, w2, [](int, long long) {});
-            ok = ok && (!lv || f2 || fits_narrow(a, w2));
-        }
-        if (__all(ok)) return;
-    }
+    if (!a.by_block && launch_is_narrow(a)) return;  // k_makespan_split does this launch
+    // (by block: it has marked the candidates that it leaves to this kernel)
+    if (a.by_block && a.T_out[(long long)blockIdx.x * W * a.t_stride + a.t_off] != MK_NOT_TAKEN) return;
     const int R = 2 * S - 1, J = 2 * R - 1;
     // rows 0..J-1: duration of block j = row+1; rows J..2J-1: its latest finish time
     long long *dur = sm + lane;
@@ -1134,13 +943,6 @@ static int launch_regs(const mk_args &a, hipStream_t st) {
     return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_HIP;
 }
 
-template <int S>
-static int launch_mid(const mk_args &a, hipStream_t st) {
-    unsigned grid = (unsigned)((a.N + 63) / 64);
-    hipLaunchKernelGGL(k_makespan_mid<S>, dim3(grid), dim3(64), (size_t)(4 * S - 3) * 64 * 4, st, a);
-    return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_HIP;
-}
-
 static void plain_layout(mk_args &a, int S) {
     a.ord_stride = S; a.bnd_stride = S; a.bnd_off = 0; a.t_stride = 1; a.t_off = 0; a.search = 0;
     a.reps = NULL; a.PA = a.actf = a.actb = a.bw = a.W = NULL; a.rout = NULL;
@@ -1165,33 +967,13 @@ static int launch_makespan(const mk_args &a, hipStream_t st) {
         CASE(9) CASE(10) CASE(11) CASE(12) CASE(13) CASE(14) CASE(15) CASE(16)
 #undef CASE
     }
+    // Both kernels are enqueued.  With a header the data decide for the whole launch which of them
+    // works; without one (no workspace) every block of 64 candidates goes to one of them.
     const int W = lds_lanes(a.S);
     mk_args b = a;
-    b.by_block = 0;
-    if (!a.hdr && !a.part && a.S <= 32) {
-        // no workspace header to tell whether the times fit 32 bits: both kernels are enqueued
-        // and every block of 64 candidates goes to one of them (W divides 64)
-        b.by_block = 1;
-        int rc = PP_ERR_INVALID_ARG;
-        switch (a.S) {
-#define CASE(n) case n: rc = launch_mid<n>(b, st); break;
-            CASE(17) CASE(18) CASE(19) CASE(20) CASE(21) CASE(22) CASE(23) CASE(24)
-            CASE(25) CASE(26) CASE(27) CASE(28) CASE(29) CASE(30) CASE(31) CASE(32)
-#undef CASE
-        }
-        if (rc) return rc;
-    }
-    if (a.hdr && a.S <= 32 && (W == 64 || !a.part)) {
-        // both kernels are enqueued; which one works depends on the data (see launch_is_narrow)
-        int rc = PP_ERR_INVALID_ARG;
-        switch (a.S) {
-#define CASE(n) case n: rc = launch_mid<n>(a, st); break;
-            CASE(17) CASE(18) CASE(19) CASE(20) CASE(21) CASE(22) CASE(23) CASE(24)
-            CASE(25) CASE(26) CASE(27) CASE(28) CASE(29) CASE(30) CASE(31) CASE(32)
-#undef CASE
-        }
-        if (rc) return rc;
-    }
+    b.by_block = !a.hdr;
+    int rc = pp_launch_makespan_split(b, st);
+    if (rc) return rc;
     const size_t lds = (size_t)2 * (4 * a.S - 3) * W * 8;
     unsigned grid = (unsigned)((a.N + W - 1) / W);
     hipLaunchKernelGGL(k_makespan_lds, dim3(grid), dim3(W), lds, st, b);
@@ -1235,27 +1017,31 @@ int pp_launch_makespan(int L, int D, int S, int64_t N, int nM, const int *Ms, co
         a.C_w = (long long *)fuse->C;
         a.bounds_w = fuse->bounds;
     }
-    if (S > 16 && lds_lanes(S) != 64 && part) {
-        // narrow workgroups: per microbatch count, T goes to memory and a separate pass finds
-        // the minimum
-        for (int q = 0; q < nM; ++q) {
+    if (S > 16 && part) {
+        // the LDS kernel's workgroups are narrower than 64 lanes here: T goes to memory and a
+        // separate pass finds the minimum, per microbatch count if the caller does not want T
+        const int each = T_out ? nM : 1;
+        for (int q = 0; q < nM; q += each) {
             mk_args b = a;
-            b.nM = 1; b.Ms[0] = Ms[q];
+            b.nM = each;
+            for (int i = 0; i < each; ++i) b.Ms[i] = Ms[q + i];
             b.part = NULL; b.C = NULL; b.out = NULL;
-            b.T_out = T_out ? (long long *)T_out + (long long)q * N : (long long *)T_scratch;
+            b.T_out = T_out ? (long long *)T_out : (long long *)T_scratch;
             if (!b.T_out) return PP_ERR_INVALID_ARG;
             int rc = launch_makespan(b, st);
             if (rc) return rc;
-            rc = pp_launch_argmin(D, S, N, (const int64_t *)b.T_out, C, bounds, orderings, part,
-                                  out + q, st);
-            if (rc) return rc;
+            for (int i = 0; i < each; ++i) {
+                rc = pp_launch_argmin(D, S, N, (const int64_t *)b.T_out + (size_t)i * N, C, bounds, orderings, part,
+                                      out + q + i, st);
+                if (rc) return rc;
+            }
         }
         return PP_OK;
     }
     int rc = launch_makespan(a, st);
     if (rc || !part) return rc;
     // one partial per wave of 64 candidates and microbatch count
-    return launch_pick(a, nM, S <= 16 ? regs_waves(N) : (N + 63) / 64, st);
+    return launch_pick(a, nM, regs_waves(N), st);
 }
 
 // ---------------------------------------------------------------- stand-alone arg-min
