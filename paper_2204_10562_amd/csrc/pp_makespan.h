@@ -121,5 +121,39 @@ __device__ __forceinline__ bool mk_split_fits(long long worst, int M, int S) {
     return worst <= (long long)MK_SPLIT_CAP / ((long long)M + 4 * S + 64);
 }
 
-// Any number of stages >= 9 with times below MK_SPLIT_CAP (pp_makespan_split.hip).
+// Fault bits of a candidate whose devices and bounds lie in LDS (o: filled in for the list of all D!
+// orderings).  A bad ordering is reported alone: its plan is not looked at.
+__device__ __forceinline__ int mk_check_rows(const mk_args &a, long long c, int *o, const int *e) {
+    const int S = a.S, L = a.L, D = a.D;
+    if (a.orderings) {
+        unsigned long long seen = 0;
+        bool bad = false;
+        for (int n = 0; n < S; ++n) {
+            const int d = o[n];
+            bad |= d < 0 || d >= D;
+            if (D <= 64) {
+                bad |= (seen >> (d & 63)) & 1;
+                seen |= 1ull << (d & 63);
+            } else {
+                for (int q = 0; q < n; ++q) bad |= o[q] == d;
+            }
+        }
+        if (bad) return PP_FAULT_ORDERING;
+    } else {
+        unsigned long long rem = (unsigned long long)c;
+        unsigned used = 0;
+        for (int n = 0; n < S; ++n) o[n] = pp_unrank_next(D, n, rem, used);
+    }
+    int prev = 0, fault = 0;
+    for (int n = 0; n < S; ++n) {
+        if (e[n] <= prev || e[n] > L) fault = PP_FAULT_BOUNDS;
+        prev = e[n];
+    }
+    return prev != L ? PP_FAULT_BOUNDS : fault;
+}
+
+// Resources over lanes (pp_makespan_split.hip): times below MK_SPLIT_CAP, a.variant any but
+// PP_SCHED_FIFO.  With a.by_block it marks the candidates it leaves alone.
 int pp_launch_makespan_split(const mk_args &a, hipStream_t st);
+// PP_SCHED_FIFO for at most 32 stages (pp_makespan_fifo.hip); marks the candidates it leaves alone.
+int pp_launch_makespan_fifo(const mk_args &a, hipStream_t st);

@@ -1215,15 +1215,19 @@ int pp_launch_rep_makespan(int L, int D, int64_t N, int M, const int64_t *PF, co
 //     with the transfers over the stage's inbound link added to its duration.
 //   PP_SCHED_FIFO: Alg. 1 with channels that serve by readiness instead of by list (only
 //     computation blocks enter the lists U_s in the listing): an event simulation.
+// It does the candidates that the faster kernels (pp_makespan_split.hip, pp_makespan_fifo.hip, launched
+// before it) have marked: 64-bit times, and for PP_SCHED_FIFO zero durations and more than 32 stages
+// (by_block == 0: all candidates).
 __global__ __launch_bounds__(64) void k_makespan_variant(mk_args a) {
     extern __shared__ long long sm[];
     const int lane = threadIdx.x, W = blockDim.x;
+    const long long c = (long long)blockIdx.x * W + lane;
+    const bool live = c < a.N && (!a.by_block || a.T_out[c] == MK_NOT_TAKEN);
+    if (!__ballot(live)) return;
     const int S = a.S, M = a.Ms[0];
     const int R = 2 * S - 1, J = 2 * R - 1;
     long long *dur = sm + lane;                    // rows 0..J-1: duration of block j = row + 1
     long long *fin = sm + (size_t)J * W + lane;    // rows J..2J-1: finish times / busy-until times
-    const long long c = (long long)blockIdx.x * W + lane;
-    const bool live = c < a.N;
     long long worst, lastF = 0, lastB = 0;
     const int fault0 = gather_durations<0>(a, c, live, worst,
                                            [&](int j, long long d) { dur[(size_t)(j - 1) * W] = d; },
@@ -1374,6 +1378,11 @@ int pp_launch_makespan_variant(int variant, int L, int D, int S, int64_t N, int 
     a.variant = variant;
     a.T_out = (long long *)T_out; a.status = status;
     a.part = NULL; a.C = NULL; a.out = NULL;
+    a.by_block = variant != PP_SCHED_FIFO || S <= 32;
+    if (a.by_block) {
+        const int rc = variant == PP_SCHED_FIFO ? pp_launch_makespan_fifo(a, st) : pp_launch_makespan_split(a, st);
+        if (rc) return rc;
+    }
     int W = lds_lanes(S);
     const int J = 4 * S - 3, R = 2 * S - 1;
     size_t rows = (size_t)2 * J;

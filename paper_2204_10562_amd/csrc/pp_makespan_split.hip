@@ -1,4 +1,5 @@
-// Makespan for more than 16 stages with times below 2^30: the resources of a candidate spread over
+// Makespan for more than 16 stages, and the comparison schedules for any number but PP_SCHED_FIFO, with
+// times below 2^30: the resources of a candidate spread over
 // 1, 2, 4 or 8 neighbouring lanes, every finish time and duration in a register.
 //
 // The recurrence is that of pp_makespan.hip: in sweep t resource r = 1..R (R = 2S - 1; odd: stages,
@@ -28,6 +29,8 @@
 // lane per candidate with the durations in LDS (what this replaces, for up to 32 stages) held one
 // wave per SIMD and issued 5 vector instructions and an LDS read per block update, and its check of
 // an ordering read every pair of devices from memory; beyond 32 stages everything was 64-bit in LDS.
+// Comparison schedules of 40 320 plans of 8 stages, M = 64: full-duplex channels 221 -> 30 us, GPipe's
+// order 131 -> 34 us, transfers added to the stages 137 -> 22 us (64-bit in LDS before).
 #include "pp_makespan.h"
 
 #define DPP_WAVE_SHL1 0x130  // lane i takes lane i + 1's value
@@ -41,7 +44,10 @@ __device__ __forceinline__ int with_sign(int from, int u) { return (from & (int)
 
 enum { SPLIT_FILL, SPLIT_FULL, SPLIT_DRAIN, SPLIT_BOTH };
 
-template <int RL, int KIND>
+// MODE: PP_SCHED_PE; PP_SCHED_DUPLEX: the two transfers of a channel (even places) do not wait for
+// each other, so a channel's sides are idle from their own last items; PP_SCHED_ADDITIVE: the PE
+// schedule of stages alone; PP_SCHED_GPIPE: see split_wave.
+template <int RL, int KIND, int MODE>
 __device__ __forceinline__ void split_sweep(int (&f)[RL], int (&b)[RL], int (&idle)[RL], const int (&df)[RL],
                                             const int (&db)[RL], int source, bool is_first, bool is_last) {
     int rf = __builtin_amdgcn_update_dpp(0, f[RL - 1], DPP_WAVE_SHR1, 0xf, 0xf, false);
@@ -51,7 +57,9 @@ __device__ __forceinline__ void split_sweep(int (&f)[RL], int (&b)[RL], int (&id
 #pragma unroll
     for (int i = RL - 1; i >= 0; --i) {
         const int in = i ? f[i - 1] : rf;
-        if (KIND == SPLIT_FILL) {
+        if (MODE == PP_SCHED_DUPLEX && !(i & 1)) {
+            f[i] = with_sign(in, smax(f[i], in) + df[i]);
+        } else if (KIND == SPLIT_FILL) {
             f[i] = smax(smax(f[i], b[i]), in) + df[i];
         } else if (KIND == SPLIT_FULL) {
             f[i] = smax(b[i], in) + df[i];
@@ -67,7 +75,9 @@ __device__ __forceinline__ void split_sweep(int (&f)[RL], int (&b)[RL], int (&id
 #pragma unroll
     for (int i = 0; i < RL; ++i) {
         const int in = i + 1 < RL ? b[i + 1 < RL ? i + 1 : i] : rb;
-        if (KIND == SPLIT_FILL) {
+        if (MODE == PP_SCHED_DUPLEX && !(i & 1)) {
+            b[i] = with_sign(in, smax(b[i], in) + db[i]);
+        } else if (KIND == SPLIT_FILL) {
             b[i] = with_sign(in, smax(f[i], in) + db[i]);
         } else if (KIND == SPLIT_FULL) {
             b[i] = smax(f[i], in) + db[i];
@@ -80,8 +90,25 @@ __device__ __forceinline__ void split_sweep(int (&f)[RL], int (&b)[RL], int (&id
     }
 }
 
+// GPipe's order: a forward wave over all microbatches, then a backward wave, each resource continuing
+// from the end of its last forward item.  One sweep of one of them (a place whose input is negative
+// has no item).
+template <int RL, bool FORWARD>
+__device__ __forceinline__ void split_wave(int (&x)[RL], int (&idle)[RL], const int (&d)[RL], int source, bool at_source) {
+    int edge = FORWARD ? __builtin_amdgcn_update_dpp(0, x[RL - 1], DPP_WAVE_SHR1, 0xf, 0xf, false)
+                       : __builtin_amdgcn_update_dpp(0, x[0], DPP_WAVE_SHL1, 0xf, 0xf, false);
+    edge = at_source ? source : edge;
+#pragma unroll
+    for (int j = 0; j < RL; ++j) {
+        const int i = FORWARD ? RL - 1 - j : j;
+        const int in = FORWARD ? (i ? x[i ? i - 1 : 0] : edge) : (i + 1 < RL ? x[i + 1 < RL ? i + 1 : i] : edge);
+        x[i] = with_sign(in, smax(idle[i], in) + d[i]);
+        idle[i] = smax(idle[i], x[i]);
+    }
+}
+
 // 64 candidates per workgroup of G waves, G = a.lanes_per.
-template <int RL>
+template <int RL, int MODE>
 __global__ __launch_bounds__(512) void k_makespan_split(mk_args a) {
     extern __shared__ int rows[];  // devices and bounds of 64 candidates, rows of SP; then 64 fault words
     // (with a header the data decide for the whole launch: k_makespan_lds does the others)
@@ -91,7 +118,8 @@ __global__ __launch_bounds__(512) void k_makespan_split(mk_args a) {
         for (int q = 0; q < a.nM; ++q) mmax = a.Ms[q] > mmax ? a.Ms[q] : mmax;
         if (__ballot(!(vmax <= MK_SPLIT_CAP && mk_split_fits((long long)vmax, mmax, a.S)))) return;
     }
-    const int S = a.S, L = a.L, D = a.D, R = 2 * S - 1, G = a.lanes_per, SP = S | 1;
+    // (resources: stages and channels, or stages alone)
+    const int S = a.S, L = a.L, D = a.D, R = MODE == PP_SCHED_ADDITIVE ? S : 2 * S - 1, G = a.lanes_per, SP = S | 1;
     const int tid = threadIdx.x, T = blockDim.x;
     int *so = rows, *sb = rows + 64 * SP, *sf = sb + 64 * SP;
     const long long c0 = (long long)blockIdx.x * 64;
@@ -107,44 +135,11 @@ __global__ __launch_bounds__(512) void k_makespan_split(mk_args a) {
         sb[i * SP + n] = e;
     }
     __syncthreads();
-    if (tid < 64) {
-        // a bad ordering is reported alone: its plan is not looked at
-        int fault = 0;
-        if (c0 + tid < a.N) {
-            int *o = so + tid * SP;
-            const int *e = sb + tid * SP;
-            if (a.orderings) {
-                unsigned long long seen = 0;
-                bool bad = false;
-                for (int n = 0; n < S; ++n) {
-                    const int d = o[n];
-                    bad |= d < 0 || d >= D;
-                    if (D <= 64) {
-                        bad |= (seen >> (d & 63)) & 1;
-                        seen |= 1ull << (d & 63);
-                    } else {
-                        for (int q = 0; q < n; ++q) bad |= o[q] == d;
-                    }
-                }
-                if (bad) fault = PP_FAULT_ORDERING;
-            } else {
-                unsigned long long rem = (unsigned long long)(c0 + tid);
-                unsigned used = 0;
-                for (int n = 0; n < S; ++n) o[n] = pp_unrank_next(D, n, rem, used);
-            }
-            int prev = 0, fb = 0;
-            for (int n = 0; n < S; ++n) {
-                if (e[n] <= prev || e[n] > L) fb = PP_FAULT_BOUNDS;
-                prev = e[n];
-            }
-            if (prev != L) fb = PP_FAULT_BOUNDS;
-            fault = fault ? fault : fb;
-        }
-        sf[tid] = fault;
-    }
+    if (tid < 64) sf[tid] = c0 + tid < a.N ? mk_check_rows(a, c0 + tid, so + tid * SP, sb + tid * SP) : 0;
     __syncthreads();
     // lane q of candidate i holds the places q RL .. q RL + RL - 1 of G RL; place p is resource
-    // p + 1 - pad.  RL is even and R odd, so pad is odd: odd places are stages, even ones channels.
+    // p + 1 - pad.  RL is even and 2 S - 1 odd, so pad is odd: odd places are stages, even ones
+    // channels.  (Stages alone: place p is stage p - pad.)
     const int lg = __builtin_ctz(G), i = tid >> lg, q = tid & (G - 1);
     const int pad = G * RL - R;
     const long long c = c0 + i;
@@ -154,29 +149,45 @@ __global__ __launch_bounds__(512) void k_makespan_split(mk_args a) {
     const int *o = so + i * SP, *e = sb + i * SP;
     int df[RL], db[RL];
     long long worst = 0;
+    auto stage = [&](int n, long long &x, long long &y) {
+        const int e1 = e[n], e0 = n ? e[n - 1] : 0;
+        x = a.PF[e1] - a.PF[e0];
+        y = a.PB[e1] - a.PB[e0];
+        worst = x + y > worst ? x + y : worst;
+    };
+    auto channel = [&](int n, long long &x, long long &y) {  // between stages n - 1 and n
+        const size_t at = ((size_t)o[n - 1] * D + o[n]) * L + (size_t)(e[n - 1] - 1);
+        x = a.XF[at];
+        y = a.XB[at];
+        worst = x + y > worst ? x + y : worst;
+    };
 #pragma unroll
     for (int k = 0; k < RL; ++k) {
         const int p = q * RL + k;
         long long x = 0, y = 0;
         bool empty = p < pad;
-        if (k & 1) {
-            const int n = (p - pad) >> 1;  // stage n
+        if (MODE == PP_SCHED_ADDITIVE) {
+            // the transfers over a stage's inbound link are part of its passes
+            const int n = p - pad;
             if (ok && !empty) {
-                const int e1 = e[n], e0 = n ? e[n - 1] : 0;
-                x = a.PF[e1] - a.PF[e0];
-                y = a.PB[e1] - a.PB[e0];
+                stage(n, x, y);
+                if (n) {
+                    long long cx, cy;
+                    channel(n, cx, cy);
+                    x += cx;
+                    y += cy;
+                }
+                worst = x + y > worst ? x + y : worst;
             }
-            worst = x + y > worst ? x + y : worst;
             if (n == S - 1) { x += y; y = 0; }
+        } else if (k & 1) {
+            const int n = (p - pad) >> 1;
+            if (ok && !empty) stage(n, x, y);
+            if (n == S - 1 && MODE != PP_SCHED_GPIPE) { x += y; y = 0; }
         } else {
-            const int n = (p + 1 - pad) >> 1;  // channel between stages n - 1 and n
+            const int n = (p + 1 - pad) >> 1;
             empty |= n < 1;
-            if (ok && !empty) {
-                const size_t at = ((size_t)o[n - 1] * D + o[n]) * L + (size_t)(e[n - 1] - 1);
-                x = a.XF[at];
-                y = a.XB[at];
-            }
-            worst = x + y > worst ? x + y : worst;
+            if (ok && !empty) channel(n, x, y);
         }
         df[k] = (int)x;
         db[k] = empty ? SPLIT_NEG : (int)y;
@@ -188,7 +199,8 @@ __global__ __launch_bounds__(512) void k_makespan_split(mk_args a) {
     if (a.by_block) {
         int mmax = 1;
         for (int m = 0; m < a.nM; ++m) mmax = a.Ms[m] > mmax ? a.Ms[m] : mmax;
-        const bool fits = !ok || mk_split_fits(worst, mmax, S);
+        // (GPipe's two waves take up to M + R - 1 of the largest forward and backward times each)
+        const bool fits = !ok || mk_split_fits(worst, MODE == PP_SCHED_GPIPE ? 2 * mmax + 4 * S : mmax, S);
         if (!__syncthreads_and(fits)) {
             if (live && q == 0) a.T_out[c * a.t_stride + a.t_off] = MK_NOT_TAKEN;
             return;
@@ -200,18 +212,26 @@ __global__ __launch_bounds__(512) void k_makespan_split(mk_args a) {
         int f[RL], b[RL], idle[RL];
 #pragma unroll
         for (int k = 0; k < RL; ++k) f[k] = b[k] = SPLIT_NEG;
+        if constexpr (MODE == PP_SCHED_GPIPE) {
+#pragma unroll
+            for (int k = 0; k < RL; ++k) idle[k] = 0;
+            const int waves = M + R - 1 + pad;
+            for (int t = 1; t <= waves; ++t) split_wave<RL, true>(f, idle, df, t <= M ? 0 : SPLIT_NEG, is_first);
+            for (int t = 1; t <= waves - pad; ++t) split_wave<RL, false>(b, idle, db, t <= M ? 0 : SPLIT_NEG, is_last);
+        } else {
         // sweeps: resource 1 serves microbatch m in sweep m + pad, its last backward item ends in
         // sweep M + J - 1 + pad; after sweep J + pad every resource has had a backward item
         const int full = J + pad, end = M + J - 1 + pad;
         int t = 1;
-        for (; t <= full && t <= M; ++t) split_sweep<RL, SPLIT_FILL>(f, b, idle, df, db, 0, is_first, is_last);
+        for (; t <= full && t <= M; ++t) split_sweep<RL, SPLIT_FILL, MODE>(f, b, idle, df, db, 0, is_first, is_last);
         if (t <= full) {
 #pragma unroll
             for (int k = 0; k < RL; ++k) idle[k] = smax(smax(f[k], b[k]), 0);
-            for (; t <= full; ++t) split_sweep<RL, SPLIT_BOTH>(f, b, idle, df, db, SPLIT_NEG, is_first, is_last);
+            for (; t <= full; ++t) split_sweep<RL, SPLIT_BOTH, MODE>(f, b, idle, df, db, SPLIT_NEG, is_first, is_last);
         }
-        for (; t <= M; ++t) split_sweep<RL, SPLIT_FULL>(f, b, idle, df, db, 0, is_first, is_last);
-        for (; t <= end; ++t) split_sweep<RL, SPLIT_DRAIN>(f, b, idle, df, db, SPLIT_NEG, is_first, is_last);
+        for (; t <= M; ++t) split_sweep<RL, SPLIT_FULL, MODE>(f, b, idle, df, db, 0, is_first, is_last);
+        for (; t <= end; ++t) split_sweep<RL, SPLIT_DRAIN, MODE>(f, b, idle, df, db, SPLIT_NEG, is_first, is_last);
+        }
         // resource 1 sits at place `pad`
         int Tv = 0;
 #pragma unroll
@@ -227,14 +247,21 @@ __global__ __launch_bounds__(512) void k_makespan_split(mk_args a) {
 template <int RL>
 static int launch_split(const mk_args &a, hipStream_t st) {
     const size_t lds = ((size_t)2 * 64 * (a.S | 1) + 64) * 4;
-    hipLaunchKernelGGL(k_makespan_split<RL>, dim3((unsigned)((a.N + 63) / 64)), dim3(64 * a.lanes_per), lds, st, a);
+    const dim3 grid((unsigned)((a.N + 63) / 64)), block(64 * a.lanes_per);
+    switch (a.variant) {
+        case PP_SCHED_PE: hipLaunchKernelGGL((k_makespan_split<RL, PP_SCHED_PE>), grid, block, lds, st, a); break;
+        case PP_SCHED_DUPLEX: hipLaunchKernelGGL((k_makespan_split<RL, PP_SCHED_DUPLEX>), grid, block, lds, st, a); break;
+        case PP_SCHED_GPIPE: hipLaunchKernelGGL((k_makespan_split<RL, PP_SCHED_GPIPE>), grid, block, lds, st, a); break;
+        case PP_SCHED_ADDITIVE: hipLaunchKernelGGL((k_makespan_split<RL, PP_SCHED_ADDITIVE>), grid, block, lds, st, a); break;
+        default: return PP_ERR_INVALID_ARG;
+    }
     return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_HIP;
 }
 
 int pp_launch_makespan_split(const mk_args &a, hipStream_t st) {
     // As few lanes per candidate as 32 places each allow (the two shifts per sweep are shared by
     // more resources), twice as many while the launch would leave SIMDs without a second wave.
-    const int R = 2 * a.S - 1;
+    const int R = a.variant == PP_SCHED_ADDITIVE ? a.S : 2 * a.S - 1;
     mk_args b = a;
     int G = 1;
     while (G * 32 < R) G <<= 1;

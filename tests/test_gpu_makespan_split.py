@@ -58,3 +58,30 @@ def test_makespan_many_stages_around_the_limit(ppo, S, M):
     check(ppo, w, bounds, [M])
     w.fwd[0] = 8 * cap
     check(ppo, w, bounds, [M, 1])
+
+
+@pytest.mark.parametrize("times", ["positive", "zeros", "wide", "mixed"])
+@pytest.mark.parametrize("S,M", [(1, 3), (2, 1), (3, 40), (8, 64), (9, 5), (16, 70), (17, 9), (32, 20), (33, 6), (64, 4)])
+def test_variants_over_lanes(ppo, S, M, times):
+    # the comparison schedules: positive times go over lanes, zero-length items under FIFO and times
+    # beyond 30 bits to the general kernel, candidate by candidate
+    from paper_2204_10562_amd.problem import GpuProblem
+    L, D, N = S + 7, max(S, 4), 130
+    w = workloads.random_small(8300 + S, L, D, S, N, zero_frac=0.3 if times == "zeros" else 0.0, hi_time=60, hi_act=6000)
+    w.actf[:] = np.maximum(w.actf, 0 if times == "zeros" else 1)
+    w.actb[:] = np.maximum(w.actb, 0 if times == "zeros" else 1)
+    if times == "mixed":
+        w.fwd[L - 1] = w.bwd[L - 1] = 0   # some plans have a stage of nothing else
+    if times == "wide":
+        w.fwd[0] = 1 << 33
+    bounds = plans(np.random.Generator(np.random.PCG64(S)), N, S, L)
+    rc, PF, PB, XF, XB = ppo.prefix_costs(w.fwd, w.bwd, w.actf, w.actb, w.bw)
+    assert rc == 0
+    g = GpuProblem(w)
+    g.set_tables(PF, PB, XF, XB)
+    for v in range(5):
+        print("[case]", v, S, M, times, flush=True)
+        st, T = g.makespan_variant(v, M, bounds)
+        rc, T0 = ppo.schedule_makespan_variant(v, L, D, S, N, M, PF, PB, XF, XB, w.orderings, bounds)
+        assert st == 0 and rc == 0
+        np.testing.assert_array_equal(T, T0)
