@@ -16,6 +16,7 @@
 // enqueued after it branches on that.
 #include "pp_common.h"
 #include "pp_dp_generic.h"
+#include "pp_dp_rows.h"
 #include "pp_dp_tile.h"
 
 // ---------------------------------------------------------------- pack
@@ -361,48 +362,63 @@ int pp_launch_dp(int L, int D, int S, int64_t N, const int64_t *PF, const int64_
     a.bfl = (const long long *)(base + lay.bfl);
     a.defer_mmax = defer_mmax;
 
+    int cus = 256;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        cus = 256;
+    // Priority levels of the waves that share a SIMD end when a tenth, a quarter and half of the chunk
+    // are left: they drift apart while they are on the same level and are pulled together at each
+    // boundary, so the levels get shorter towards the end (measured for the kernel that evaluates all
+    // pairs, L = 128, all 8! orderings, against equal quarters: 65.8 against 67.1 us).
+    auto levels = [](long long chunk, int (&left)[3]) {
+        const long long frac[3] = {10, 4, 2};
+        for (int k = 0; k < 3; ++k) {
+            const long long v = chunk / frac[k];
+            left[k] = (int)(v > 0x3fffffff ? 0x3fffffff : v);
+        }
+    };
+    if (L > PP_PAIRS_MAX_L && L <= PP_TILE_MAX_L) {
+        dp_rows_args t;
+        t.L = L; t.D = D; t.S = S; t.K = a.K; t.N = N;
+        t.validate = a.validate;
+        const size_t lds_wave = pp_dp_rows_lds_per_wave(S), table = (size_t)DPR_RS * 4;
+        int wpb = 4;  // waves per workgroup, limited by 64 KiB of LDS
+        while (wpb > 1 && table + lds_wave * wpb > 64 * 1024) wpb >>= 1;
+        if (table + lds_wave * wpb > 64 * 1024) return PP_ERR_INVALID_ARG;  // cannot happen for S <= 64
+        // waves that fit a SIMD's share of the LDS (given out in pieces of 1280 bytes)
+        int waves_per_simd = (int)(160 * 1024 / ((table + lds_wave * wpb + 1279) / 1280 * 1280)) * wpb / 4;
+        waves_per_simd = waves_per_simd < 1 ? 1 : (waves_per_simd > 4 ? 4 : waves_per_simd);
+        t.chunk = choose_chunk(N, D, lex_ord != NULL, (long long)cus * 4, waves_per_simd);
+        levels(t.chunk, t.prio_left);
+        const long long nchunks = (N + t.chunk - 1) / t.chunk;
+        const int grid = (int)((nchunks + wpb - 1) / wpb);
+        if (a.nblocks > grid) a.nblocks = grid;
+        t.g = a;
+        return pp_launch_dp_rows(t, grid, wpb, st);
+    }
     if (lay.nt) {
-        // L <= 128: register-tiled kernel, one wave per candidate (falls back to the generic
+        // L <= 88: register-tiled kernel, one wave per candidate (falls back to the generic
         // int64 body inside the same launch when the times do not fit 32-bit keys)
         dp_tile_args t;
         t.L = L; t.D = D; t.S = S; t.K = a.K; t.N = N;
         t.validate = a.validate;
         t.xkt = (const int *)(base + lay.xkt);
         t.xct = (const int *)(base + lay.xct);
-        int cus = 256;
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-            cus = 256;
         const size_t lds_wave = pp_dp_tile_lds_per_wave(S, lay.nt);
         int wpb = 4;  // waves per workgroup, limited by 64 KiB of LDS
         while (wpb > 1 && lds_wave * wpb > 64 * 1024) wpb >>= 1;
         if (lds_wave * wpb > 64 * 1024) return PP_ERR_INVALID_ARG;  // cannot happen for S <= 64
-        const int waves_per_simd = lay.nt >= 14 ? 2 : (lay.nt >= 12 ? 3 : 4);
+        const int waves_per_simd = 4;
         t.chunk = choose_chunk(N, D, lex_ord != NULL, (long long)cus * 4, waves_per_simd);
-        {
-            // Priority levels end when a tenth, a quarter and half of the chunk are left: the
-            // two waves of a SIMD drift apart while they are on the same level and are pulled
-            // together at each boundary, so the levels get shorter towards the end (measured at
-            // GPT size against equal quarters: 65.8 against 67.1 us).
-            const long long frac[3] = {10, 4, 2};
-            for (int k = 0; k < 3; ++k) {
-                long long v = t.chunk / frac[k];
-                t.prio_left[k] = (int)(v > 0x3fffffff ? 0x3fffffff : v);
-            }
-        }
+        levels(t.chunk, t.prio_left);
         const long long nchunks = (N + t.chunk - 1) / t.chunk;
         const int grid = (int)((nchunks + wpb - 1) / wpb);
         if (a.nblocks > grid) a.nblocks = grid;
         t.g = a;
         return pp_launch_dp_tile(t, lay.nt, grid, wpb, st);
     }
-    // L > 128: super-tiled kernel, one persistent wave per candidate slot
-    int cus = 256;
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        cus = 256;
+    // L > 128: one persistent wave per candidate slot
     long long waves = lay.slots < N ? lay.slots : N;
     if (!lay.sh_table) return pp_launch_dp_big(a, (int)waves, cus, NULL, st);
     // candidates whose links have the same channel times share one DP: the kernel walks the

@@ -67,7 +67,7 @@ __global__ __launch_bounds__(256, 4) void k_dp_big(dp_big_args b) {
         return;
     }
     if (!(pp_vmax(a.hdr) < a.fit_limit)) {
-        dp_generic_body<true>(a, smem);  // times too large for 32-bit keys
+        dp_generic_body<true>(a, smem, *(dp_generic_small *)(smem + dp_generic_rows_bytes(a.L)));  // times too large for 32-bit keys
         return;
     }
     const int lane = threadIdx.x & 63;
@@ -95,10 +95,7 @@ __global__ __launch_bounds__(256, 4) void k_dp_big(dp_big_args b) {
     row.kmask = kmask;
     row.strict = a.hdr->strict != 0;
     row.lane = lane;
-    // lane n: steps of a search in row n.  With balanced stages a cell of row n chooses among the
-    // splits within P[l] / (n + 1) of it; a row that needs more gets a step more from then on.
-    int v_steps = 1;
-    while ((1 << v_steps) - 1 < L / (lane + 1) + L / (8 * (lane + 1)) + 2) ++v_steps;
+    int v_steps = row_first_steps(L, lane);  // lane n: steps of a search in row n
     unsigned short *arg = a.arg + (size_t)wave * b.arg_stride;
     unsigned long long pairs = 0, nrows = 0;
     const int tri = S * (S + 1) / 2;
@@ -273,10 +270,10 @@ __global__ __launch_bounds__(256, 4) void k_dp_big(dp_big_args b) {
                 row_lds_sync();
                 for (int c0 = 0; c0 < Lp; c0 += 256) {
                     const int left = (Lp - c0) >> 6;
-                    if (left >= 4) row_search<4>(row, c0);
-                    else if (left == 3) row_search<3>(row, c0);
-                    else if (left == 2) row_search<2>(row, c0);
-                    else row_search<1>(row, c0);
+                    if (left >= 4) { int w[4]; row_search<4>(row, c0, w); }
+                    else if (left == 3) { int w[3]; row_search<3>(row, c0, w); }
+                    else if (left == 2) { int w[2]; row_search<2>(row, c0, w); }
+                    else { int w[1]; row_search<1>(row, c0, w); }
                 }
                 pairs += (unsigned long long)(L - n) * (unsigned)(row.steps + 1);
                 if (row.again && lane == n && v_steps < K) ++v_steps;

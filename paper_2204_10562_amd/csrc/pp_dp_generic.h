@@ -75,17 +75,23 @@ __device__ inline bool load_ordering(const dp_args &a, long long c, int *s_o, in
     return *s_ok != 0;
 }
 
-// LDS the generic body needs: three rows, the tops of all rows, an ordering, a flag.  (All of it
-// dynamic: a static array would be added to every launch of the kernels that contain this body.)
+// The small arrays of the generic body.  A kernel whose occupancy is bound by LDS keeps them in its
+// dynamic part (dp_generic_lds_bytes), because a static array is added to every launch.
+struct dp_generic_small {
+    long long top[PP_MAX_STAGES];  // W[n][L] of every row (stage-count search)
+    int o[PP_MAX_STAGES];
+    int ok;
+};
+__host__ __device__ static inline size_t dp_generic_rows_bytes(int L) { return (size_t)3 * (L + 1) * 8; }
 __host__ __device__ static inline size_t dp_generic_lds_bytes(int L) {
-    return (size_t)3 * (L + 1) * 8 + PP_MAX_STAGES * 12 + 16;
+    return dp_generic_rows_bytes(L) + sizeof(dp_generic_small);
 }
 
 // One workgroup per candidate (workgroup b walks candidates b, b + nblocks, ...), cells
-// spread over the threads, rows in LDS (smem: dp_generic_lds_bytes), backtrack
+// spread over the threads, rows in LDS (smem: dp_generic_rows_bytes), backtrack
 // table in the workgroup's slice of a.arg.  Must be entered by whole workgroups.
 template <bool WIDE>
-__device__ void dp_generic_body(const dp_args &a, unsigned char *smem) {
+__device__ void dp_generic_body(const dp_args &a, unsigned char *smem, dp_generic_small &small) {
     if ((int)blockIdx.x >= a.nblocks) return;
     using V = typename std::conditional<WIDE, long long, int>::type;
     const V INF = WIDE ? (V)PP_INF64 : (V)PP_INF32;
@@ -95,10 +101,9 @@ __device__ void dp_generic_body(const dp_args &a, unsigned char *smem) {
     V *sP = (V *)smem;      // WIDE: P[l];  keys: (P[l] << K) - l
     V *sW = sP + (L + 1);   // row n-1, then row n: W[.][l] (keys: time << K in the high bits)
     V *sG = sW + (L + 1);   // g[k] = max(W[n-1][k], X_n[k])  (keys: | k)
-    // (behind the rows: dp_generic_lds_bytes)
-    long long *s_top = (long long *)(smem + (size_t)3 * (L + 1) * 8);  // W[n][L] of every row (stage-count search)
-    int *s_o = (int *)(s_top + PP_MAX_STAGES);
-    int &s_ok = s_o[PP_MAX_STAGES];
+    long long *s_top = small.top;
+    int *s_o = small.o;
+    int &s_ok = small.ok;
     unsigned short *arg = a.arg + (size_t)blockIdx.x * S * (L + 1);
 
     for (int l = tid; l <= L; l += B) {

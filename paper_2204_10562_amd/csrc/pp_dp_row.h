@@ -59,6 +59,14 @@ struct dp_row {
     bool again;  // a search needed a second round
 };
 
+// Steps of a search in row n for a start.  With balanced stages a cell of row n chooses among the
+// splits within P[l] / (n + 1) of it; a row that needs more gets a step more from then on.
+__device__ __forceinline__ int row_first_steps(int L, int n) {
+    int s = 1;
+    while ((1 << s) - 1 < L / (n + 1) + L / (8 * (n + 1)) + 2) ++s;
+    return s;
+}
+
 // Minima over the lanes from each lane on (and over `carry`).
 __device__ __forceinline__ int row_suffix_min(int v, int carry, int lane) {
     v = row_imin(v, __builtin_amdgcn_update_dpp(v, v, DPP_ROW_SHL(1), 0xf, 0xf, false));
@@ -154,10 +162,25 @@ __device__ __forceinline__ int row_on_peak(const dp_row &r, int j, int l, unsign
     return best;
 }
 
+// One step of U searches: back by s bytes where that split is not done for (CLAMP: not below `low`).
+template <int U, bool CLAMP>
+__device__ __forceinline__ void row_step(int s, int (&pos)[U], const unsigned (&Pl)[U], int low) {
+    int j[U];
+    unsigned hv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        j[u] = CLAMP ? row_imax(pos[u] - s, low) : pos[u] - s;
+        hv[u] = row_at(j[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) pos[u] = hv[u] >= Pl[u] ? j[u] : pos[u];
+}
+
 // Cells c0 + 1 .. c0 + 64 U (cells beyond L repeat cell L, those up to n are infinite).
+// w receives them too.
 template <int U>
-__device__ __forceinline__ void row_search(dp_row &r, int c0) {
-    int pos[U], w[U];
+__device__ __forceinline__ void row_search(dp_row &r, int c0, int (&w)[U]) {
+    int pos[U];
     unsigned Pl[U];
     const int h0 = row_addr(r.h), low = h0 + 4 * r.n, reach = (4 << r.steps) - 4;
 #pragma unroll
@@ -171,24 +194,11 @@ __device__ __forceinline__ void row_search(dp_row &r, int c0) {
         int from[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) from[u] = pos[u];
+        // (loops: straight-line code entered at the first step was measured 5 % slower)
         if (first && limit >= reach) {
-            // (no lane can get below split n)
-            for (int s = 2 << r.steps; s >= 4; s >>= 1) {
-                unsigned hv[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) hv[u] = row_at(pos[u] - s);
-#pragma unroll
-                for (int u = 0; u < U; ++u) pos[u] = hv[u] >= Pl[u] ? pos[u] - s : pos[u];
-            }
+            for (int s = 2 << r.steps; s >= 4; s >>= 1) row_step<U, false>(s, pos, Pl, low);  // no lane can get below split n
         } else {
-            for (int s = 2 << r.steps; s >= 4; s >>= 1) {
-                int j[U];
-                unsigned hv[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) { j[u] = row_imax(pos[u] - s, low); hv[u] = row_at(j[u]); }
-#pragma unroll
-                for (int u = 0; u < U; ++u) pos[u] = hv[u] >= Pl[u] ? j[u] : pos[u];
-            }
+            for (int s = 2 << r.steps; s >= 4; s >>= 1) row_step<U, true>(s, pos, Pl, low);
         }
         bool more = false;
 #pragma unroll

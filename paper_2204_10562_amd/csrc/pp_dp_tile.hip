@@ -1,4 +1,4 @@
-// Partition DP for L <= 128: one wavefront per candidate, cells and splits tiled over the
+// Partition DP for L <= 88: one wavefront per candidate, cells and splits tiled over the
 // 64 lanes, everything that does not depend on the candidate kept in registers.
 //
 // Recursion for W(l, xi, r, i) of Sec. IV-B / the PRM listing with one replica per stage:
@@ -97,13 +97,14 @@ __device__ __forceinline__ void lds_sync() {
 template <int NT>
 __global__ __launch_bounds__(256) void k_dp_tile(dp_tile_args a) {
     extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ dp_generic_small s_generic;
     if (pp_is_flat(a.g.hdr)) {
         // no channel time depends on the cut position: closed form, here or in the makespan kernel
         if (!dp_flat_deferred(a.g)) dp_flat_body(a.g, smem, a.g.lds_bytes);
         return;
     }
     if (!(pp_vmax(a.g.hdr) < a.g.fit_limit)) {
-        dp_generic_body<true>(a.g, smem);  // times too large for 32-bit keys
+        dp_generic_body<true>(a.g, smem, s_generic);  // times too large for 32-bit keys
         return;
     }
 
@@ -488,7 +489,7 @@ static int launch_nt(const dp_tile_args &a, int grid, int wpb, size_t lds, hipSt
 
 int pp_launch_dp_tile(const dp_tile_args &a, int nt, int grid, int wpb, hipStream_t st) {
     size_t lds = (size_t)wpb * pp_dp_tile_lds_per_wave(a.S, nt);
-    const size_t generic = dp_generic_lds_bytes(a.L);  // the int64 fallback's rows
+    const size_t generic = dp_generic_rows_bytes(a.L);  // the int64 fallback's rows
     if (lds < generic) lds = generic;
     const size_t flat = pp_flat_lds_wanted(a.L, a.D, a.S, wpb);  // the closed-form body's tables
     if (lds < flat) lds = flat;
@@ -497,7 +498,7 @@ int pp_launch_dp_tile(const dp_tile_args &a, int nt, int grid, int wpb, hipStrea
     switch (nt) {
 #define CASE(n) case n: return launch_nt<n>(b, grid, wpb, lds, st);
         CASE(1) CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8)
-        CASE(9) CASE(10) CASE(11) CASE(12) CASE(13) CASE(14) CASE(15) CASE(16)
+        CASE(9) CASE(10) CASE(11)
 #undef CASE
     }
     return PP_ERR_INVALID_ARG;

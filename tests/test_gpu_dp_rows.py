@@ -30,7 +30,8 @@ def shaped(kind, seed, L, D, S, N):
 
 
 @pytest.mark.parametrize("kind", ["rising", "peaks", "falling", "zero", "skewed"])
-@pytest.mark.parametrize("L,D,S,N", [(129, 5, 2, 20), (191, 7, 7, 30), (192, 6, 3, 30), (193, 9, 8, 30), (256, 4, 4, 24),
+@pytest.mark.parametrize("L,D,S,N", [(88, 6, 6, 40), (89, 6, 3, 40), (96, 5, 2, 40), (97, 70, 34, 70), (127, 9, 9, 40), (128, 64, 64, 34), (128, 4, 1, 9),
+                                     (129, 5, 2, 20), (191, 7, 7, 30), (192, 6, 3, 30), (193, 9, 8, 30), (256, 4, 4, 24),
                                      (257, 12, 12, 20), (320, 65, 6, 20), (449, 20, 17, 12), (512, 8, 5, 20),
                                      (1025, 40, 33, 6), (2048, 64, 64, 3)])
 def test_partition_rows(ppo, kind, L, D, S, N):
