@@ -22,13 +22,26 @@
 // too.  Neither the sub-problem nor the channel term depends on l, and the last stage's term
 // does not depend on r'; max with the latter commutes with the minimum over r', so per state
 //   Gmin[l'] = min over r' of max(W(l', xi-1, r', i-r), X[r'][l'])
-// is built once in LDS and a cell costs one pass over l' only:
+// is built once in LDS and a cell is
 //   W(l, xi, r, i) = min over l' of max(Gmin[l'], last stage [l', l)).
-// The r' that goes with the chosen l' is then the first one whose value reaches the minimum.
+// The last stage's term falls as l' grows, so with int32 values the cell is found by a binary
+// search (see the cells); int64 values pass over l' from l - 1 down with an early exit.  The r'
+// that goes with the chosen l' is the first one whose value reaches the minimum; with int32
+// values it is worked out for the plans' cells only.
 // States that use all D GPUs are needed at l = L only and are reduced by the whole workgroup.
+//
+// Bound by vector instructions (issue slots about half busy) and the barriers between the short
+// phases of a state.  L = 128, D = 8, all 40320 orderings, whole call: 9.40 ms with a pass over
+// l' per cell and 64-bit divisions, 8.37 ms with the divisions in doubles, 5.17 ms with the
+// search (82 K, 70 K and 33 K vector instructions per candidate).
 #include "pp_common.h"
+#include "pp_dp_row.h"
 
 #define PRM_THREADS 128
+// Fewest layers for which a cell's split is searched rather than scanned for (int32 values).  All
+// 40320 orderings of 8 GPUs, whole call, scan / search in ms: 3.17 / 3.57 at L = 8, 3.79 / 4.02 at
+// 32, 4.26 / 4.35 at 64, 5.15 / 4.78 at 72 (a second chunk of positions), 5.39 / 4.85 at 96.
+#define PRM_SEARCH_MIN_L 72
 
 struct prm_args {
     int L, D, M;
@@ -80,8 +93,28 @@ __device__ __forceinline__ bool prm_less(const prm_key &a, const prm_key &b) {
 
 __device__ __forceinline__ long long cdiv64(long long a, long long b) { return a / b + (a % b != 0); }
 
+// Quotients of whole numbers below 2^53 by double arithmetic (instead of 64-bit integer division,
+// about 100 instructions each and 14 % of the kernel's).  `inv` is the reciprocal
+// of den to 40 bits or more and the quotient is below 2^31, so the truncated product is off by one
+// at most; the remainder (exact by the fused multiply-add) says which way.
+__device__ __forceinline__ double prm_inv(double den) {
+    const double r = __builtin_amdgcn_rcp(den);
+    return __builtin_fma(r, __builtin_fma(-den, r, 1.0), r);
+}
+__device__ __forceinline__ int prm_ceil_div(double a, double den, double inv) {
+    const double q = __builtin_trunc(a * inv), rem = __builtin_fma(-q, den, a);
+    return (int)q + (rem > 0.0) + (rem > den);
+}
+__device__ __forceinline__ int prm_floor_div(double a, double den, double inv, int &rest) {
+    const double q = __builtin_trunc(a * inv), rem = __builtin_fma(-q, den, a);
+    const int up = rem >= den, down = rem < 0.0;
+    rest = (int)(rem + (down ? den : up ? -den : 0.0));
+    return (int)q + up - down;
+}
+
 // Values are int64, or int32 when every finite value of the launch is known to stay below
-// 2^30 (decided on the device from bounds on the stage and channel terms).
+// 2^30 (decided on the device from bounds on the stage and channel terms) and every size below
+// 2^53, so that quotients can be had by double arithmetic.
 template <bool WIDE> struct prm_val { using V = int; };
 template <> struct prm_val<true> { using V = long long; };
 
@@ -121,6 +154,32 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
     long long *bfwd = (long long *)((char *)At + pp_align256((size_t)NS * L1 * 4));  // [p][rp][r]
     long long *bbwd = bfwd + (size_t)D1 * D1 * D1;
     long long *bin = bbwd + (size_t)D1 * D1 * D1;                        // [n][r]
+    // int32 values: the minima are kept as the denominators they end up in (doubles in the same
+    // places); the arrays of prefix sums in LDS hold the activation sizes at the cuts and the prefix
+    // sums of the parameter sizes as doubles; and what the last stage's compute terms are at every
+    // position (M (QF + QB), one-hot remainders) is tabled per number of replicas behind the table of
+    // W, which leaves half of its area.  (D >= 2.)
+    double *dfwd = (double *)bfwd, *dbwd = (double *)bbwd, *din = (double *)bin;
+    double *AF = (double *)PF, *AB = (double *)PB, *PAd = (double *)PA;
+    int2 *UT = (int2 *)(slot + (((size_t)NS * L1 * 4 + 7) & ~(size_t)7));  // [r - 1][L1]
+    if constexpr (!WIDE) {
+        for (int r = 1; r <= D; ++r)
+            for (int l = tid; l <= L; l += B) {
+                const long long qf = PF[l] / r, qb = PB[l] / r;
+                UT[(size_t)(r - 1) * L1 + l] = make_int2((int)(M * (qf + qb)), (1 << (int)(PF[l] - qf * r)) | (1 << (16 + (int)(PB[l] - qb * r))));
+            }
+        __syncthreads();
+        for (int l = tid; l <= L; l += B) {
+            AF[l] = l >= 1 && l < L ? (double)a.actf[l - 1] : 0.0;
+            AB[l] = l >= 1 && l < L ? (double)a.actb[l - 1] : 0.0;
+            PAd[l] = (double)PA[l];
+        }
+        if (tid == 0) { Q[0].u = 0; Q[0].ra = 0; Q[0].oh = 0x10001; }
+        __syncthreads();
+    }
+    int *Gr = (int *)(Q + L1);  // int32 values: Gmin; the g field of a record holds H(l' + 1) (see the cells)
+    const int lane = tid & 63, wib = tid >> 6;
+    const bool search = !WIDE && L >= PRM_SEARCH_MIN_L;
 
     // A workgroup walks a contiguous chunk of candidates.  State (xi, r, i) depends only on the
     // first i devices of the ordering, so whatever the previous candidate shares as a prefix is
@@ -168,8 +227,13 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
                     mf = x < mf ? x : mf;
                     mb = y < mb ? y : mb;
                 }
-            bfwd[t] = mf;
-            bbwd[t] = mb;
+            if constexpr (WIDE) {
+                bfwd[t] = mf;
+                bbwd[t] = mb;
+            } else {
+                dfwd[t] = (double)(rp * r) * (double)mf;
+                dbwd[t] = (double)(rp * r) * (double)mb;
+            }
         }
         // bin[n][r]: ordered pairs inside ranks [n-r, n)
         for (int t = tid; t < D1 * D1; t += B) {
@@ -182,7 +246,8 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
                         long long x = a.bw[(size_t)o[u] * D + o[v]];
                         m = x < m ? x : m;
                     }
-            bin[t] = m;
+            if constexpr (WIDE) bin[t] = m;
+            else din[t] = (double)r * (double)m;
         }
         __syncthreads();
 
@@ -193,25 +258,45 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
                 // Last stage on r replicas, ranks [i-r, i): division-free form of its terms, and
                 // the channel term X[r'][l'] = M (c^f + c^b) towards r' replicas on ranks
                 // [i-r-r', i-r); both are shared by every stage count.
-                const long long den = r > 1 ? (long long)r * bin[i * D1 + r] : 1;
-                for (int l = tid; l <= L; l += B) {
-                    long long qf = PF[l] / r, qb = PB[l] / r;
-                    long long num = 2 * (long long)(r - 1) * PA[l];
-                    long long qa = num / den;
-                    Q[l].u = (V)(M * (qf + qb) + qa);
-                    Q[l].ra = (V)(num - qa * den);
-                    Q[l].oh = (1 << (int)(PF[l] - qf * r)) | (1 << (16 + (int)(PB[l] - qb * r)));
-                }
                 const int n0 = i - r;  // GPUs of the sub-problem
-                for (int t = tid; t < n0 * L1; t += B) {
-                    const int rp = 1 + t / L1, lp = t % L1;
-                    V x = INF;
-                    if (lp >= 1 && lp <= L - 1) {
-                        const size_t at = ((size_t)n0 * D1 + rp) * D1 + r;
-                        x = (V)(M * (cdiv64(a.actf[lp - 1], (long long)rp * r * bfwd[at]) +
-                                     cdiv64(a.actb[lp - 1], (long long)rp * r * bbwd[at])));
+                if constexpr (WIDE) {
+                    const long long den = r > 1 ? (long long)r * bin[i * D1 + r] : 1;
+                    for (int l = tid; l <= L; l += B) {
+                        long long qf = PF[l] / r, qb = PB[l] / r;
+                        long long num = 2 * (long long)(r - 1) * PA[l];
+                        long long qa = num / den;
+                        Q[l].u = (V)(M * (qf + qb) + qa);
+                        Q[l].ra = (V)(num - qa * den);
+                        Q[l].oh = (1 << (int)(PF[l] - qf * r)) | (1 << (16 + (int)(PB[l] - qb * r)));
                     }
-                    X[(size_t)(rp - 1) * L1 + lp] = x;
+                    for (int t = tid; t < n0 * L1; t += B) {
+                        const int rp = 1 + t / L1, lp = t % L1;
+                        V x = INF;
+                        if (lp >= 1 && lp <= L - 1) {
+                            const size_t at = ((size_t)n0 * D1 + rp) * D1 + r;
+                            x = (V)(M * (cdiv64(a.actf[lp - 1], (long long)rp * r * bfwd[at]) +
+                                         cdiv64(a.actb[lp - 1], (long long)rp * r * bbwd[at])));
+                        }
+                        X[(size_t)(rp - 1) * L1 + lp] = x;
+                    }
+                } else {
+                    const double den = r > 1 ? din[i * D1 + r] : 1.0, inv = prm_inv(den), times = 2.0 * (r - 1);
+                    const int2 *ut = UT + (size_t)(r - 1) * L1;
+                    for (int l = tid + 1; l <= L; l += B) {
+                        const int2 u = ut[l];
+                        int ra = 0;
+                        const int qa = r > 1 ? prm_floor_div(times * PAd[l], den, inv, ra) : 0;
+                        Q[l].u = u.x + qa;
+                        Q[l].ra = ra;
+                        Q[l].oh = u.y;
+                    }
+                    for (int rp = 1; rp <= n0; ++rp) {
+                        const size_t at = ((size_t)n0 * D1 + rp) * D1 + r;
+                        const double f = dfwd[at], b = dbwd[at], finv = prm_inv(f), binv = prm_inv(b);
+                        V *Xr = X + (size_t)(rp - 1) * L1;
+                        for (int lp = tid; lp < L; lp += B)
+                            Xr[lp] = (int)M * (prm_ceil_div(AF[lp], f, finv) + prm_ceil_div(AB[lp], b, binv));
+                    }
                 }
                 __syncthreads();
                 // the last stage [l', l): M (F + B) + A, from the records of l' and l
@@ -230,8 +315,8 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
                     unsigned *As = At + (size_t)sid * L1;
                     if (xi == 1) {
                         // a single stage must take all i GPUs
-                        for (int l = top ? L + tid : tid; l <= L; l += B) {
-                            Ws[l] = (r == i && l >= 1) ? last_stage(Q[0], Q[l], mask_of(Q[l].oh)) : INF;
+                        for (int l = top ? L + tid : tid + 1; l <= L; l += B) {
+                            Ws[l] = (r == i) ? last_stage(Q[0], Q[l], mask_of(Q[l].oh)) : INF;
                             As[l] = 0;
                         }
                         continue;  // touches no LDS array that the next state rewrites
@@ -239,9 +324,9 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
                     const int nrp = n0 - (xi - 2);  // r' = 1..nrp leave >= 1 GPU per earlier stage
                     // Gmin[l'] = min over r' of max(W(l', xi-1, r', n0), X[r'][l']).  The last
                     // stage's term does not depend on r', and max with it commutes with this min.
-                    for (int lp = tid; lp <= L; lp += B) {
+                    for (int lp = tid; lp < L; lp += B) {
                         V g = INF;
-                        if (lp >= xi - 1 && lp <= L - 1) {
+                        if (lp >= xi - 1) {
                             // four loads in flight at a time; a clamped r' repeats the last one
                             const V *Wsub = Wt + (size_t)prm_sid(n0, xi - 1, 1) * L1 + lp;  // r' = 1, 2, ...
                             for (int rp0 = 1; rp0 <= nrp; rp0 += 4) {
@@ -259,7 +344,8 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
                                 }
                             }
                         }
-                        Q[lp].g = g;
+                        if (search) Gr[lp] = (int)g;
+                        else Q[lp].g = g;
                     }
                     __syncthreads();
                     // first r' (ascending) whose value reaches the minimum v found at l'
@@ -273,8 +359,69 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
                         }
                         return 0;
                     };
-                    if (!top) {
-                        for (int l = tid; l <= L; l += B) {
+                    if (!top && search) {
+                        // The minimum over l' of max(G[l'], last stage [l', l)) by a search, as in
+                        // pp_dp_row.h: G = Gmin, and the last stage's term falls as l' grows.  With
+                        // H(j) = min_{k>=j} G[k] over the whole row, split j is done for iff its last
+                        // stage exceeds H(j + 1); the first that is not is the crossing.  Here the last
+                        // stage's term can be equal at neighbouring splits (quotients): the lowest of
+                        // those with G no larger is taken.
+                        int carry = PP_INF32;
+                        for (int c = L & ~63; c >= 0; c -= 64) {
+                            const int lp = c + lane;
+                            const int m = row_suffix_min(lp >= xi - 1 && lp < L ? Gr[lp] : PP_INF32, carry, lane);
+                            carry = __builtin_amdgcn_readlane(m, 0);
+                            if (((c >> 6) & 1) == wib && lp >= 1 && lp <= L) Q[lp - 1].g = m;
+                        }
+                        __syncthreads();
+                        const int lo = xi - 1;
+                        int steps = 1;
+                        while ((1 << steps) - 1 < L / xi + L / (8 * xi) + 3) ++steps;
+                        for (int l = tid + 1; l <= L; l += B) {
+                            const Row ql = Q[l];
+                            const int mask = mask_of(ql.oh);
+                            int pos = l - 1;
+                            for (;;) {
+                                const int from = pos;
+                                for (int st = 1 << (steps - 1); st; st >>= 1) {
+                                    const int k = row_imax(pos - st, lo);
+                                    const Row q = Q[k];
+                                    pos = k < pos && last_stage(q, ql, mask) <= q.g ? k : pos;
+                                }
+                                if (!__ballot(pos > lo && pos == from - ((1 << steps) - 1))) break;
+                            }
+                            V best = INF;
+                            int blp = 0;
+                            if (l > lo) {
+                                const Row q = Q[pos];
+                                const V last = last_stage(q, ql, mask), g = Gr[pos];
+                                if (g <= q.g) {
+                                    best = g > last ? g : last;
+                                    blp = pos;
+                                    for (int k = pos - 1; k >= lo && best != INF && last_stage(Q[k], ql, mask) <= best; --k)
+                                        blp = Gr[k] <= best ? k : blp;
+                                } else {
+                                    int e = pos + 1;
+                                    while (e < l && Gr[e] > q.g) ++e;
+                                    if (e < l) {
+                                        best = q.g;
+                                        blp = e;
+                                    } else {
+                                        for (int k = l - 1; k >= lo; --k) {
+                                            const V lk = last_stage(Q[k], ql, mask), gk = Gr[k];
+                                            if (lk > best) break;
+                                            const V t = gk > lk ? gk : lk;
+                                            if (t <= best) { best = t; blp = k; }
+                                        }
+                                    }
+                                }
+                            }
+                            // (which r' goes with it is worked out for the plans only)
+                            Ws[l] = best;
+                            As[l] = (unsigned)blp;
+                        }
+                    } else if (!top) {
+                        for (int l = tid + 1; l <= L; l += B) {
                             const Row ql = Q[l];
                             const int mask = mask_of(ql.oh);
                             V best = INF;
@@ -305,7 +452,9 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
                                 if (t <= best) { best = t; blp = lp; }
                             }
                             Ws[l] = best;
-                            As[l] = best == INF ? 0u : ((unsigned)blp | ((unsigned)first_rp(blp, l, best) << 16));
+                            As[l] = (unsigned)blp;
+                            if constexpr (WIDE)
+                                if (best != INF) As[l] |= (unsigned)first_rp(blp, l, best) << 16;
                         }
                     } else {
                         // the workgroup shares the scan of l' for the single cell L
@@ -314,8 +463,8 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
                         prm_key best = {PP_INF64, 0, 0};
                         for (int lp = xi - 1 + tid; lp < L; lp += B) {
                             const Row q = Q[lp];
-                            const V last = last_stage(q, ql, mask);
-                            const V t = q.g > last ? q.g : last;
+                            const V last = last_stage(q, ql, mask), g = search ? (V)Gr[lp] : q.g;
+                            const V t = g > last ? g : last;
                             prm_key k = {t == INF ? PP_INF64 : (long long)t, lp, 0};
                             if (prm_less(k, best)) best = k;
                         }
@@ -333,7 +482,8 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
                                 if (prm_less(sh.red[w], best)) best = sh.red[w];
                             const bool none = best.v == PP_INF64;
                             Ws[L] = none ? INF : (V)best.v;
-                            As[L] = none ? 0u : ((unsigned)best.lp | ((unsigned)first_rp(best.lp, L, (V)best.v) << 16));
+                            if constexpr (WIDE) As[L] = none ? 0u : ((unsigned)best.lp | ((unsigned)first_rp(best.lp, L, (V)best.v) << 16));
+                            else As[L] = none ? 0u : (unsigned)best.lp;
                         }
                     }
                     __syncthreads();  // the g fields (and sh.red) are rewritten by the next state
@@ -360,10 +510,37 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
                 if (wbest == INF) { bo[s] = 0; ro[s] = 0; continue; }
                 bo[s] = l;
                 ro[s] = r;
-                unsigned arg = At[(size_t)prm_sid(n, s + 1, r) * L1 + l];
-                n -= r;
-                l = (int)(arg & 0xffffu);
-                r = (int)(arg >> 16);
+                const size_t at = (size_t)prm_sid(n, s + 1, r) * L1 + l;
+                const unsigned arg = At[at];
+                const int lp = (int)(arg & 0xffffu);
+                if constexpr (WIDE) {
+                    n -= r;
+                    r = (int)(arg >> 16);
+                } else if (s > 0) {
+                    // the first r' whose value reaches the cell's (the last stage's term is the same
+                    // for all of them)
+                    const V v = Wt[at];
+                    const int n0 = n - r, nrp = n0 - (s - 1);
+                    const double den = r > 1 ? din[n * D1 + r] : 1.0, inv = prm_inv(den), times = 2.0 * (r - 1);
+                    const int2 ul = UT[(size_t)(r - 1) * L1 + l], up = UT[(size_t)(r - 1) * L1 + lp];
+                    int ral = 0, rap = 0;
+                    const int qal = r > 1 ? prm_floor_div(times * PAd[l], den, inv, ral) : 0;
+                    const int qap = r > 1 ? prm_floor_div(times * PAd[lp], den, inv, rap) : 0;
+                    const V last = ul.x + qal - (up.x + qap) +
+                                   (V)((int)M * __popc((unsigned)(up.y & (ul.y - 0x10001)))) + (ral > rap);
+                    int rp = 1;
+                    for (; rp < nrp; ++rp) {
+                        const size_t m = ((size_t)n0 * D1 + rp) * D1 + r;
+                        const V x = (int)M * (prm_ceil_div(AF[lp], dfwd[m], prm_inv(dfwd[m])) +
+                                              prm_ceil_div(AB[lp], dbwd[m], prm_inv(dbwd[m])));
+                        V w = Wt[(size_t)prm_sid(n0, s, rp) * L1 + lp];
+                        w = w > x ? w : x;
+                        if ((w > last ? w : last) == v) break;
+                    }
+                    n = n0;
+                    r = rp;
+                }
+                l = lp;
             }
         }
     }
@@ -434,6 +611,9 @@ __global__ __launch_bounds__(PRM_THREADS) void k_prm(prm_args a) {
                      2 * al / bmin + 1 < lim / 2;
         }
         narrow = narrow && f + b + 2 < lim / (2 * M);
+        // (sizes and the multiples of them that are divided must be exact in double arithmetic)
+        const unsigned long long exact = 1ull << 53;
+        narrow = narrow && D > 1 && sh.amax_f < exact && sh.amax_b < exact && (unsigned long long)al < exact / (2 * D);
         sh.wide = !narrow;
     }
     __syncthreads();
