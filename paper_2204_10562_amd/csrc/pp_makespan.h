@@ -157,3 +157,7 @@ __device__ __forceinline__ int mk_check_rows(const mk_args &a, long long c, int 
 int pp_launch_makespan_split(const mk_args &a, hipStream_t st);
 // PP_SCHED_FIFO for at most 32 stages (pp_makespan_fifo.hip); marks the candidates it leaves alone.
 int pp_launch_makespan_fifo(const mk_args &a, hipStream_t st);
+
+// The schedules of all plans with replicated stages: 1..a.D stages, a.N candidates
+// (pp_makespan_rep.hip).
+int mk_launch_replicated(const mk_args &a, hipStream_t st);

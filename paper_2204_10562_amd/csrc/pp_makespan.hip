@@ -25,6 +25,7 @@
 // kernel launched next reduces the per-wave minima to the winner record.
 #include "pp_dp_flat.h"
 #include "pp_makespan.h"
+#include "pp_makespan_sweep.h"
 
 // Checks candidate c's ordering and bounds and gathers its block durations through `put`
 // (called as put(block j (1-based), duration)).  Returns fault bits; on a fault or for a
@@ -190,191 +191,6 @@ static int launch_pick(mk_args a, int nM, long long n_part, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------- registers, S <= 16
-
-// med3(old, fresh, sel) for 0 <= old <= fresh < 2^31: fresh if the scalar sel is all ones, old if it is 0.
-__device__ __forceinline__ int keep_or_take(int old, int fresh, unsigned sel) {
-    int r;
-    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(old), "v"(fresh), "s"(sel));
-    return r;
-}
-__device__ __forceinline__ long long keep_or_take(long long old, long long fresh, unsigned sel) {
-    return sel ? fresh : old;
-}
-
-// One sweep restricted to blocks LO..HI (compile-time), no validity tests.
-template <int S, typename V, int LO, int HI>
-__device__ __forceinline__ void sweep_blocks(V (&fin)[4 * S - 3 + 1], const V (&dur)[4 * S - 3 + 1]) {
-    constexpr int R = 2 * S - 1, J = 2 * R - 1;
-    const V finR_prev = fin[R];
-    // forward blocks and the merged block R, descending so that fin[j-1] is still the
-    // previous sweep's value
-#pragma unroll
-    for (int j = R; j >= 1; --j) {
-        if (j < LO || j > HI) continue;
-        V idle = fin[j] > fin[2 * R - j] ? fin[j] : fin[2 * R - j];
-        V ready = j > 1 ? fin[j - 1] : (V)0;
-        fin[j] = (idle > ready ? idle : ready) + dur[j];
-    }
-    // backward blocks: the resource may just have been used by this sweep's forward block
-#pragma unroll
-    for (int j = J; j >= R + 1; --j) {
-        if (j < LO || j > HI) continue;
-        V idle = fin[j] > fin[2 * R - j] ? fin[j] : fin[2 * R - j];
-        V ready = j == R + 1 ? finR_prev : fin[j - 1];
-        fin[j] = (idle > ready ? idle : ready) + dur[j];
-    }
-}
-
-template <int S, typename V, int T>
-__device__ __forceinline__ void ramp_up(V (&fin)[4 * S - 3 + 1], const V (&dur)[4 * S - 3 + 1]) {
-    if constexpr (T <= 4 * S - 4) {
-        sweep_blocks<S, V, 1, T>(fin, dur);
-        ramp_up<S, V, T + 1>(fin, dur);
-    }
-}
-
-template <int S, typename V, int U>
-__device__ __forceinline__ void ramp_down(V (&fin)[4 * S - 3 + 1], const V (&dur)[4 * S - 3 + 1]) {
-    if constexpr (U <= 4 * S - 4) {
-        sweep_blocks<S, V, U + 1, 4 * S - 3>(fin, dur);
-        ramp_down<S, V, U + 1>(fin, dur);
-    }
-}
-
-// All M + 4S - 4 sweeps with the finish times in registers; returns the finish of the last
-// backward block on stage 0.  Block j works in sweep t iff t-M+1 <= j <= t.  When the
-// pipeline fills completely (M >= J-1) the sweeps split into a ramp-up (blocks 1..t), a
-// steady phase (all blocks) and a ramp-down (blocks t-M+1..J) whose block ranges are known at
-// compile time.  A shorter pipeline still has such a ramp-up (its first M sweeps) and ramp-down
-// (its last M-1); in the sweeps between them, and in every sweep for S > 8 (where unrolling
-// every sweep would be too much code), every block is computed and the update is kept or
-// dropped by a select: with 32-bit times a median of three against a per-block scalar that is
-// 0 or all ones (finish times never decrease, so med3(old, new, ~0) = new and
-// med3(old, new, 0) = old), with 64-bit times a per-lane compare.
-// `result(fin)` turns the final finish times into the value returned.
-// Sweep t with every block computed and the update of the blocks outside [t-M+1, t] dropped.
-template <int S, typename V>
-__device__ __forceinline__ void sweep_selected(V (&fin)[4 * S - 3 + 1], const V (&dur)[4 * S - 3 + 1], int t, int M) {
-    constexpr int R = 2 * S - 1, J = 2 * R - 1;
-    const V finR_prev = fin[R];
-    if constexpr (sizeof(V) == 4) {
-        // bit j of `act`: block j works in this sweep
-        const int jlo = t - M + 1 > 1 ? t - M + 1 : 1, jhi = t < J ? t : J;
-        const unsigned long long act = ((2ull << jhi) - 1) & ~((1ull << jlo) - 1);
-        // groups of G blocks without an active one are skipped altogether
-        constexpr int G = 5;
-#pragma unroll
-        for (int jh = R; jh >= 1; jh -= G) {
-            const int jl = jh - G + 1 > 1 ? jh - G + 1 : 1;
-            if (!(act & (((2ull << jh) - 1) & ~((1ull << jl) - 1)))) continue;
-#pragma unroll
-            for (int j = jh; j >= jl; --j) {
-                V idle = fin[j] > fin[2 * R - j] ? fin[j] : fin[2 * R - j];
-                V ready = j > 1 ? fin[j - 1] : (V)0;
-                V nv = (idle > ready ? idle : ready) + dur[j];
-                fin[j] = keep_or_take(fin[j], nv, (act >> j) & 1 ? ~0u : 0u);
-            }
-        }
-#pragma unroll
-        for (int jh = J; jh >= R + 1; jh -= G) {
-            const int jl = jh - G + 1 > R + 1 ? jh - G + 1 : R + 1;
-            if (!(act & (((2ull << jh) - 1) & ~((1ull << jl) - 1)))) continue;
-#pragma unroll
-            for (int j = jh; j >= jl; --j) {
-                V idle = fin[j] > fin[2 * R - j] ? fin[j] : fin[2 * R - j];
-                V ready = j == R + 1 ? finR_prev : fin[j - 1];
-                V nv = (idle > ready ? idle : ready) + dur[j];
-                fin[j] = keep_or_take(fin[j], nv, (act >> j) & 1 ? ~0u : 0u);
-            }
-        }
-    } else {
-        // j is in [t-M+1, t] iff (unsigned)(j - (t-M+1)) <= M-1; kept in a vector register so
-        // that the tests run on the vector unit next to the arithmetic
-        const unsigned width = (unsigned)(M - 1);
-        int jlo = t - M + 1;
-        asm volatile("" : "+v"(jlo));
-#pragma unroll
-        for (int j = R; j >= 1; --j) {
-            V idle = fin[j] > fin[2 * R - j] ? fin[j] : fin[2 * R - j];
-            V ready = j > 1 ? fin[j - 1] : (V)0;
-            V nv = (idle > ready ? idle : ready) + dur[j];
-            fin[j] = (unsigned)(j - jlo) <= width ? nv : fin[j];
-        }
-#pragma unroll
-        for (int j = J; j >= R + 1; --j) {
-            V idle = fin[j] > fin[2 * R - j] ? fin[j] : fin[2 * R - j];
-            V ready = j == R + 1 ? finR_prev : fin[j - 1];
-            V nv = (idle > ready ? idle : ready) + dur[j];
-            fin[j] = (unsigned)(j - jlo) <= width ? nv : fin[j];
-        }
-    }
-}
-
-// The first M sweeps of a pipeline that never fills (M <= J-2): blocks 1..t.
-template <int S, typename V, int T>
-__device__ __forceinline__ void ramp_up_to(V (&fin)[4 * S - 3 + 1], const V (&dur)[4 * S - 3 + 1], int M) {
-    if constexpr (T <= 4 * S - 5) {
-        if (T > M) return;
-        sweep_blocks<S, V, 1, T>(fin, dur);
-        ramp_up_to<S, V, T + 1>(fin, dur, M);
-    }
-}
-
-// The last sweeps of a pipeline, blocks U+1..J for every U+1 >= lo.
-template <int S, typename V, int U>
-__device__ __forceinline__ void ramp_down_from(V (&fin)[4 * S - 3 + 1], const V (&dur)[4 * S - 3 + 1], int lo) {
-    if constexpr (U <= 4 * S - 4) {
-        if (U + 1 >= lo) sweep_blocks<S, V, U + 1, 4 * S - 3>(fin, dur);
-        ramp_down_from<S, V, U + 1>(fin, dur, lo);
-    }
-}
-
-// Sweeps M+1..J of a pipeline that never fills, for a microbatch count known at compile time:
-// the window of M blocks moves up by one block per sweep.
-template <int S, typename V, int M, int T>
-__device__ __forceinline__ void slide_window(V (&fin)[4 * S - 3 + 1], const V (&dur)[4 * S - 3 + 1]) {
-    if constexpr (T <= 4 * S - 3) {
-        sweep_blocks<S, V, T - M + 1, T>(fin, dur);
-        slide_window<S, V, M, T + 1>(fin, dur);
-    }
-}
-
-// Picks the instance of slide_window for the run-time microbatch count m (1 <= m <= J-2).
-template <int S, typename V, int M>
-__device__ __forceinline__ void slide_window_for(V (&fin)[4 * S - 3 + 1], const V (&dur)[4 * S - 3 + 1], int m) {
-    if constexpr (M <= 4 * S - 5) {
-        if (m == M) {
-            slide_window<S, V, M, M + 1>(fin, dur);
-            return;
-        }
-        slide_window_for<S, V, M + 1>(fin, dur, m);
-    }
-}
-
-template <int S, typename V, typename Result>
-__device__ __forceinline__ long long sweep_regs(const long long (&dur64)[4 * S - 3 + 1], int M, Result result) {
-    constexpr int R = 2 * S - 1, J = 2 * R - 1;
-    V dur[J + 1], fin[J + 1];
-#pragma unroll
-    for (int j = 1; j <= J; ++j) { dur[j] = (V)dur64[j]; fin[j] = 0; }
-    dur[0] = fin[0] = 0;
-    if constexpr (S <= 8) {
-        if (M >= J - 1) {
-            ramp_up<S, V, 1>(fin, dur);
-            for (int t = J; t <= M; ++t) sweep_blocks<S, V, 1, J>(fin, dur);
-            ramp_down<S, V, 1>(fin, dur);
-        } else {
-            ramp_up_to<S, V, 1>(fin, dur, M);                                   // sweeps 1..M
-            if constexpr (sizeof(V) == 4) slide_window_for<S, V, 1>(fin, dur, M);       // sweeps M+1..J
-            else for (int t = M + 1; t <= J; ++t) sweep_selected<S, V>(fin, dur, t, M);
-            ramp_down_from<S, V, 1>(fin, dur, J - M + 2);                       // sweeps J+1..J+M-1
-        }
-        return result(fin);
-    }
-    const int sweeps = M + 2 * R - 2;
-    for (int t = 1; t <= sweeps; ++t) sweep_selected<S, V>(fin, dur, t, M);
-    return result(fin);
-}
 
 // Microbatch counts handled by one group of waves of k_makespan_regs (one wave each), and the
 // most groups a workgroup of k_makespan_regs8 holds.
@@ -686,124 +502,6 @@ __global__ __launch_bounds__(64 * MK_REGS_WAVES) void k_makespan_regs8_shared(mk
         case 6: regs_body<6, true>(a); break;
         case 7: regs_body<7, true>(a); break;
         case 8: regs_body<8, true>(a); break;
-    }
-}
-
-// ---------------------------------------------------------------- replicated stages, S <= 16
-
-__device__ __forceinline__ long long ceil_div64(long long x, long long y) { return x / y + (x % y != 0); }
-
-// Plans with replicated stages (Sec. III-B): stage s runs on reps[s] GPUs of consecutive ranks,
-// a replica takes ceil(p / k) per microbatch, a transfer between stages of k' and k replicas
-// ceil(d / (k' k min b)) with the minimum over the links between the two GPU sets, and a
-// replicated stage ends with a ring AllReduce of ceil(2 (k-1) sum alpha / (k min b)) (Eq. 1)
-// that starts when its last backward pass has finished.  T is the later of the last backward
-// block on stage 0 and the end of the last AllReduce (Eq. 2).  One lane per candidate; the
-// plan with S stages of candidate c is read from the triangular arrays.
-template <int S>
-__global__ __launch_bounds__(64) void k_rep_makespan(mk_args a) {
-    constexpr int R = 2 * S - 1, J = 4 * S - 3;
-    const int lane = threadIdx.x, L = a.L, D = a.D;
-    const long long c = (long long)blockIdx.x * 64 + lane;
-    const bool live = c < a.N;
-    const int M = a.Ms[0];
-    long long dur[J + 1], A[S];
-    long long worst = 0, amax = 0;
-    int fault = 0;
-    const bool none = live && a.W[c * a.t_stride + a.t_off] == PP_INF64;  // no plan with S stages
-    const bool work = live && !none;
-    const int *bd = a.bounds + c * a.bnd_stride + a.bnd_off;
-    const int *rp = a.reps + c * a.bnd_stride + a.bnd_off;
-    const int *o = a.orderings + c * a.ord_stride;
-    if (work) {
-        int prev = 0, used = 0;
-        for (int s = 0; s < S; ++s) {
-            int e = bd[s], k = rp[s];
-            if (e <= prev || e > L || k < 1 || k > D) fault |= PP_FAULT_BOUNDS;
-            prev = e;
-            used += k;
-        }
-        if (prev != L || used != D) fault |= PP_FAULT_BOUNDS;
-        for (int n = 0; n < D; ++n) {
-            int d = o[n];
-            bool bad = d < 0 || d >= D;
-            for (int q = 0; q < n; ++q) bad |= (o[q] == d);
-            if (bad) fault |= PP_FAULT_ORDERING;
-        }
-    }
-    const bool ok = work && !fault;
-    int e0 = 0, n = 0, kprev = 0;
-#pragma unroll
-    for (int s = 0; s < S; ++s) {
-        long long F = 0, Bk = 0, cf = 0, cb = 0, As = 0;
-        if (ok) {
-            const int e = bd[s], k = rp[s];
-            F = ceil_div64(a.PF[e] - a.PF[e0], k);
-            Bk = ceil_div64(a.PB[e] - a.PB[e0], k);
-            if (k > 1) {
-                long long m = PP_INF64;
-                for (int u = n; u < n + k; ++u)
-                    for (int v = n; v < n + k; ++v)
-                        if (u != v) {
-                            long long x = a.bw[(size_t)o[u] * D + o[v]];
-                            m = x < m ? x : m;
-                        }
-                As = ceil_div64(2 * (long long)(k - 1) * (a.PA[e] - a.PA[e0]), (long long)k * m);
-            }
-            if (s) {
-                long long mf = PP_INF64, mb = PP_INF64;
-                for (int u = n - kprev; u < n; ++u)
-                    for (int v = n; v < n + k; ++v) {
-                        long long x = a.bw[(size_t)o[u] * D + o[v]], y = a.bw[(size_t)o[v] * D + o[u]];
-                        mf = x < mf ? x : mf;
-                        mb = y < mb ? y : mb;
-                    }
-                cf = ceil_div64(a.actf[e0 - 1], (long long)kprev * k * mf);
-                cb = ceil_div64(a.actb[e0 - 1], (long long)kprev * k * mb);
-            }
-            e0 = e;
-            n += k;
-            kprev = k;
-        }
-        A[s] = As;
-        amax = As > amax ? As : amax;
-        long long w = F + Bk > cf + cb ? F + Bk : cf + cb;
-        worst = w > worst ? w : worst;
-        const int r = 2 * s + 1;
-        if (s == S - 1) {
-            dur[R] = F + Bk;
-        } else {
-            dur[r] = F;
-            dur[2 * R - r] = Bk;
-        }
-        if (s) {
-            dur[r - 1] = cf;
-            dur[2 * R - (r - 1)] = cb;
-        }
-    }
-    dur[0] = 0;
-    if (ok) {
-        fault |= overflow_fault(worst, M, S);
-        if (amax >= PP_CAP62 / 2) fault |= PP_FAULT_OVERFLOW;
-    }
-    // the later of the last backward block on stage 0 and the end of every AllReduce
-    auto finish = [&](auto &fin) {
-        long long T = (long long)fin[J];
-#pragma unroll
-        for (int s = 0; s < S; ++s) {
-            const int jb = s == S - 1 ? R : 2 * R - (2 * s + 1);
-            const long long t = (long long)fin[jb] + A[s];
-            T = (A[s] > 0 && t > T) ? t : T;
-        }
-        return T;
-    };
-    const bool narrow = !ok || fault || worst <= (long long)0x7fffffff / ((long long)M + 4 * S - 4);
-    long long T;
-    if (__all(narrow)) T = sweep_regs<S, int>(dur, M, finish);
-    else T = sweep_regs<S, long long>(dur, M, finish);
-    if (live) {
-        if (fault) pp_raise(a.status, fault);
-        a.T_out[c * a.t_stride + a.t_off] = (none || fault) ? PP_INF64 : T;
     }
 }
 
@@ -1151,13 +849,6 @@ int pp_launch_makespan_stages(int L, int D, int S, int64_t N, int nM, const int 
 
 // ---------------------------------------------------------------- replicated stages: launch
 
-template <int S>
-static int launch_rep(const mk_args &a, hipStream_t st) {
-    unsigned grid = (unsigned)((a.N + 63) / 64);
-    hipLaunchKernelGGL(k_rep_makespan<S>, dim3(grid), dim3(64), 0, st, a);
-    return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_HIP;
-}
-
 int pp_launch_rep_makespan(int L, int D, int64_t N, int M, const int64_t *PF, const int64_t *PB,
                            const int64_t *PA, const int64_t *actf, const int64_t *actb,
                            const int64_t *bw, const int32_t *orderings, const int32_t *bounds,
@@ -1175,19 +866,11 @@ int pp_launch_rep_makespan(int L, int D, int64_t N, int M, const int64_t *PF, co
     a.T_out = (long long *)T_out; a.status = status;
     a.part = NULL; a.C = NULL; a.out = NULL; a.rout = NULL;
     a.ord_stride = D; a.bnd_stride = (long long)D * (D + 1) / 2; a.t_stride = D; a.search = 0;
-    for (int xi = 1; xi <= D; ++xi) {
-        a.S = xi;
-        a.bnd_off = xi * (xi - 1) / 2;
-        a.t_off = xi - 1;
-        int rc = PP_ERR_INVALID_ARG;
-        switch (xi) {
-#define CASE(n) case n: rc = launch_rep<n>(a, st); break;
-            CASE(1) CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8)
-            CASE(9) CASE(10) CASE(11) CASE(12) CASE(13) CASE(14) CASE(15) CASE(16)
-#undef CASE
-        }
-        if (rc) return rc;
-    }
+    a.S = D;
+    a.bnd_off = D * (D - 1) / 2;
+    a.t_off = D - 1;
+    int rc = mk_launch_replicated(a, st);
+    if (rc) return rc;
     // smallest T over all (candidate, stage count) pairs, lowest c*D + xi-1 on ties
     mk_args m = a;
     m.S = D; m.N = N * D; m.search = D;
