@@ -13,8 +13,9 @@
 // The listing scans l' ascending, then r' ascending, and replaces its best only on strict
 // improvement: the minimiser kept is the first in (l', r') order.
 //
-// One workgroup per candidate (persistent over candidates), one thread per cell l.  State
-// (xi, r, i) depends only on states with fewer GPUs, so states are visited by ascending i.
+// One workgroup of two waves per candidate (persistent over candidates), one lane per cell l.  State
+// (xi, r, i) depends only on states with fewer GPUs, so states are visited by ascending i, and with
+// int32 values each wave does half of the states of an i on its own, without barriers.
 // All states with the same (r, i) share the last stage's terms, which are made division-free:
 // with Q[l] = floor(P[l] / r), R[l] = P[l] mod r,  ceil((P[l] - P[l']) / r) =
 // Q[l] - Q[l'] + (R[l] > R[l']); so the stage term is U[l] - U[l'] + (remainder compares) with
@@ -28,23 +29,25 @@
 // search (see the cells); int64 values pass over l' from l - 1 down with an early exit.  The r'
 // that goes with the chosen l' is the first one whose value reaches the minimum; with int32
 // values it is worked out for the plans' cells only.
-// States that use all D GPUs are needed at l = L only and are reduced by the whole workgroup.
+// States that use all D GPUs are needed at l = L only: the lanes share the scan of l'.
 //
-// Bound by vector instructions (issue slots about half busy) and the barriers between the short
-// phases of a state.  L = 128, D = 8, all 40320 orderings, whole call: 9.40 ms with a pass over
-// l' per cell and 64-bit divisions, 8.37 ms with the divisions in doubles, 5.17 ms with the
-// search (82 K, 70 K and 33 K vector instructions per candidate).
+// Bound by vector instructions and the latency of the short phases of a state.  L = 128, D = 8, all
+// 40320 orderings, whole call: 9.40 ms with a pass over l' per cell and 64-bit divisions, 8.37 ms with
+// the divisions in doubles, 5.11 ms with the search (82 K, 70 K and 33 K vector instructions per
+// candidate), 3.95 ms with a wave per state instead of a workgroup per state and three barriers in
+// it (L = 8, where one wave was idle: 3.2 -> 2.2 ms).
 #include "pp_common.h"
 #include "pp_dp_row.h"
 
 #define PRM_THREADS 128
 // Fewest layers for which a cell's split is searched rather than scanned for (int32 values).  All
-// 40320 orderings of 8 GPUs, whole call, scan / search in ms: 3.17 / 3.57 at L = 8, 3.79 / 4.02 at
-// 32, 4.26 / 4.35 at 64, 5.15 / 4.78 at 72 (a second chunk of positions), 5.39 / 4.85 at 96.
-#define PRM_SEARCH_MIN_L 72
+// 40320 orderings of 8 GPUs, whole call, scan / search in ms: 2.60 / 2.65 at L = 32, 2.80 / 2.73 at
+// 48, 2.99 / 2.87 at 64, 4.29 / 3.68 at 72 (a second chunk of positions), 4.82 / 3.85 at 112.
+#define PRM_SEARCH_MIN_L 40
 
 struct prm_args {
     int L, D, M;
+    int search;  // nonzero: the launch has LDS for the minima apart from the records
     long long N;
     const long long *fwd, *bwd, *actf, *actb, *alpha, *bw;
     const int *ord;  // [N][D]
@@ -78,6 +81,12 @@ static inline size_t prm_lds_bytes(int L, int D) {
     // X (int64, D-1 rows)
     // (the three prefix arrays are padded to an even length so that the records are 16-byte aligned)
     return (size_t)(L + 2) * (3 * 8) + (size_t)(L + 1) * 32 + (size_t)(D > 1 ? D - 1 : 1) * (L + 1) * 8 + 64;
+}
+
+// The int32 form: two sets of records (16 bytes) and channel terms (one row less in the second), and of
+// Gmin where cells are searched for.  Without those it is less than the above.
+static inline size_t prm_search_lds_bytes(int L, int D) {
+    return (size_t)(L + 2) * (3 * 8) + (size_t)(L + 1) * (2 * 16 + (2 * D - 1) * 4);
 }
 
 struct prm_key {
@@ -128,7 +137,7 @@ template <bool WIDE> struct alignas(16) prm_row { int g, u, ra, oh; };
 template <> struct alignas(16) prm_row<true> { long long g, u, ra; int oh, pad; };
 
 struct prm_shared {
-    int o[PP_MAX_STAGES];
+    int o[16];
     int fault, keep, wide;
     unsigned long long amax_f, amax_b, bmin, bmax;
     prm_key red[PRM_THREADS / 64];
@@ -145,8 +154,15 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
     const int L1 = L + 1, D1 = D + 1;
     const int L1p = (L1 + 1) & ~1;  // even, so that what follows the int64 arrays is 16-byte aligned
     long long *PF = (long long *)smem, *PB = PF + L1p, *PA = PB + L1p;
-    Row *Q = (Row *)(PA + L1p);                          // [L1]
-    V *X = (V *)((long long *)(PA + L1p) + 4 * (size_t)L1);  // [D-1][L1], after 32 bytes per record
+    // int32 values: every wave does states of its own (see the states), with its own records, channel
+    // terms and minima (WV); int64 values: the workgroup does one state at a time
+    constexpr int WV = WIDE ? 1 : 2;
+    const int lane = tid & 63, wib = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tl = WIDE ? tid : lane, BL = WIDE ? B : 64, part = WIDE ? 0 : wib;
+    Row *Q = (Row *)(PA + L1p) + (size_t)part * L1;                                     // [L1]
+    V *X = (V *)((Row *)(PA + L1p) + (size_t)WV * L1) + (size_t)part * (D - 1) * L1;    // [D-1][L1] (part 1: [D-2])
+    // int32 values, cells searched for: Gmin; the g field of a record then holds H(l' + 1) (see the cells)
+    int *Gr = (int *)((Row *)(PA + L1p) + (size_t)WV * L1) + (size_t)(2 * D - 3 + part) * L1;
     const int NS = prm_states(D), tri = D * (D + 1) / 2;
     char *slot = a.scratch + (size_t)blockIdx.x * a.slot_bytes;
     V *Wt = (V *)slot;                                                   // [NS][L1]
@@ -174,12 +190,14 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
             AB[l] = l >= 1 && l < L ? (double)a.actb[l - 1] : 0.0;
             PAd[l] = (double)PA[l];
         }
-        if (tid == 0) { Q[0].u = 0; Q[0].ra = 0; Q[0].oh = 0x10001; }
+        if (lane == 0) { Q[0].u = 0; Q[0].ra = 0; Q[0].oh = 0x10001; }
         __syncthreads();
     }
-    int *Gr = (int *)(Q + L1);  // int32 values: Gmin; the g field of a record holds H(l' + 1) (see the cells)
-    const int lane = tid & 63, wib = tid >> 6;
-    const bool search = !WIDE && L >= PRM_SEARCH_MIN_L;
+    auto sync = [&]() {
+        if constexpr (WIDE) __syncthreads();
+        else row_lds_sync();
+    };
+    const bool search = !WIDE && L >= PRM_SEARCH_MIN_L && a.search;
 
     // A workgroup walks a contiguous chunk of candidates.  State (xi, r, i) depends only on the
     // first i devices of the ordering, so whatever the previous candidate shares as a prefix is
@@ -255,13 +273,15 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
         for (int i = keep + 1; i <= D; ++i) {
             const bool top = i == D;  // all GPUs in use: only cell L is needed
             for (int r = 1; r <= i; ++r) {
+                // r = 1, 4, 5, 8, .. by wave 0 and 2, 3, 6, 7, .. by wave 1: about as many states each
+                if (!WIDE && ((r >> 1) & 1) != part) continue;
                 // Last stage on r replicas, ranks [i-r, i): division-free form of its terms, and
                 // the channel term X[r'][l'] = M (c^f + c^b) towards r' replicas on ranks
                 // [i-r-r', i-r); both are shared by every stage count.
                 const int n0 = i - r;  // GPUs of the sub-problem
                 if constexpr (WIDE) {
                     const long long den = r > 1 ? (long long)r * bin[i * D1 + r] : 1;
-                    for (int l = tid; l <= L; l += B) {
+                    for (int l = tl; l <= L; l += BL) {
                         long long qf = PF[l] / r, qb = PB[l] / r;
                         long long num = 2 * (long long)(r - 1) * PA[l];
                         long long qa = num / den;
@@ -269,7 +289,7 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
                         Q[l].ra = (V)(num - qa * den);
                         Q[l].oh = (1 << (int)(PF[l] - qf * r)) | (1 << (16 + (int)(PB[l] - qb * r)));
                     }
-                    for (int t = tid; t < n0 * L1; t += B) {
+                    for (int t = tl; t < n0 * L1; t += BL) {
                         const int rp = 1 + t / L1, lp = t % L1;
                         V x = INF;
                         if (lp >= 1 && lp <= L - 1) {
@@ -282,7 +302,7 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
                 } else {
                     const double den = r > 1 ? din[i * D1 + r] : 1.0, inv = prm_inv(den), times = 2.0 * (r - 1);
                     const int2 *ut = UT + (size_t)(r - 1) * L1;
-                    for (int l = tid + 1; l <= L; l += B) {
+                    for (int l = tl + 1; l <= L; l += BL) {
                         const int2 u = ut[l];
                         int ra = 0;
                         const int qa = r > 1 ? prm_floor_div(times * PAd[l], den, inv, ra) : 0;
@@ -294,11 +314,11 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
                         const size_t at = ((size_t)n0 * D1 + rp) * D1 + r;
                         const double f = dfwd[at], b = dbwd[at], finv = prm_inv(f), binv = prm_inv(b);
                         V *Xr = X + (size_t)(rp - 1) * L1;
-                        for (int lp = tid; lp < L; lp += B)
+                        for (int lp = tl; lp < L; lp += BL)
                             Xr[lp] = (int)M * (prm_ceil_div(AF[lp], f, finv) + prm_ceil_div(AB[lp], b, binv));
                     }
                 }
-                __syncthreads();
+                sync();
                 // the last stage [l', l): M (F + B) + A, from the records of l' and l
                 auto last_stage = [&](const Row &q, const Row &ql, int mask) -> V {
                     const int flags = __popc((unsigned)(q.oh & mask));  // 0, 1 or 2
@@ -315,7 +335,7 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
                     unsigned *As = At + (size_t)sid * L1;
                     if (xi == 1) {
                         // a single stage must take all i GPUs
-                        for (int l = top ? L + tid : tid + 1; l <= L; l += B) {
+                        for (int l = top ? L + tl : tl + 1; l <= L; l += BL) {
                             Ws[l] = (r == i) ? last_stage(Q[0], Q[l], mask_of(Q[l].oh)) : INF;
                             As[l] = 0;
                         }
@@ -324,7 +344,7 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
                     const int nrp = n0 - (xi - 2);  // r' = 1..nrp leave >= 1 GPU per earlier stage
                     // Gmin[l'] = min over r' of max(W(l', xi-1, r', n0), X[r'][l']).  The last
                     // stage's term does not depend on r', and max with it commutes with this min.
-                    for (int lp = tid; lp < L; lp += B) {
+                    for (int lp = tl; lp < L; lp += BL) {
                         V g = INF;
                         if (lp >= xi - 1) {
                             // four loads in flight at a time; a clamped r' repeats the last one
@@ -347,7 +367,7 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
                         if (search) Gr[lp] = (int)g;
                         else Q[lp].g = g;
                     }
-                    __syncthreads();
+                    sync();
                     // first r' (ascending) whose value reaches the minimum v found at l'
                     auto first_rp = [&](int lp, int l, V v) -> int {
                         const V last = last_stage(Q[lp], Q[l], mask_of(Q[l].oh));
@@ -371,13 +391,13 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
                             const int lp = c + lane;
                             const int m = row_suffix_min(lp >= xi - 1 && lp < L ? Gr[lp] : PP_INF32, carry, lane);
                             carry = __builtin_amdgcn_readlane(m, 0);
-                            if (((c >> 6) & 1) == wib && lp >= 1 && lp <= L) Q[lp - 1].g = m;
+                            if (lp >= 1 && lp <= L) Q[lp - 1].g = m;
                         }
-                        __syncthreads();
+                        sync();
                         const int lo = xi - 1;
                         int steps = 1;
                         while ((1 << steps) - 1 < L / xi + L / (8 * xi) + 3) ++steps;
-                        for (int l = tid + 1; l <= L; l += B) {
+                        for (int l = tl + 1; l <= L; l += BL) {
                             const Row ql = Q[l];
                             const int mask = mask_of(ql.oh);
                             int pos = l - 1;
@@ -421,7 +441,7 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
                             As[l] = (unsigned)blp;
                         }
                     } else if (!top) {
-                        for (int l = tid + 1; l <= L; l += B) {
+                        for (int l = tl + 1; l <= L; l += BL) {
                             const Row ql = Q[l];
                             const int mask = mask_of(ql.oh);
                             V best = INF;
@@ -457,11 +477,11 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
                                 if (best != INF) As[l] |= (unsigned)first_rp(blp, l, best) << 16;
                         }
                     } else {
-                        // the workgroup shares the scan of l' for the single cell L
+                        // the lanes share the scan of l' for the single cell L
                         const Row ql = Q[L];
                         const int mask = mask_of(ql.oh);
                         prm_key best = {PP_INF64, 0, 0};
-                        for (int lp = xi - 1 + tid; lp < L; lp += B) {
+                        for (int lp = xi - 1 + tl; lp < L; lp += BL) {
                             const Row q = Q[lp];
                             const V last = last_stage(q, ql, mask), g = search ? (V)Gr[lp] : q.g;
                             const V t = g > last ? g : last;
@@ -475,21 +495,25 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
                             ok.rp = 0;
                             if (prm_less(ok, best)) best = ok;
                         }
-                        if ((tid & 63) == 0) sh.red[tid >> 6] = best;
-                        __syncthreads();
-                        if (tid == 0) {
-                            for (int w = 1; w < B / 64; ++w)
-                                if (prm_less(sh.red[w], best)) best = sh.red[w];
+                        if constexpr (WIDE) {
+                            if (lane == 0) sh.red[wib] = best;
+                            __syncthreads();
+                            if (tid == 0)
+                                for (int w = 1; w < B / 64; ++w)
+                                    if (prm_less(sh.red[w], best)) best = sh.red[w];
+                        }
+                        if (tl == 0) {
                             const bool none = best.v == PP_INF64;
                             Ws[L] = none ? INF : (V)best.v;
                             if constexpr (WIDE) As[L] = none ? 0u : ((unsigned)best.lp | ((unsigned)first_rp(best.lp, L, (V)best.v) << 16));
                             else As[L] = none ? 0u : (unsigned)best.lp;
                         }
                     }
-                    __syncthreads();  // the g fields (and sh.red) are rewritten by the next state
+                    sync();  // the g fields (and sh.red) are rewritten by the next state
                 }
-                __syncthreads();  // the records and X are rewritten by the next (r, i)
+                sync();  // the records and X are rewritten by the next (r, i)
             }
+            __syncthreads();  // the states with more GPUs read these
         }
 
         // ---- per stage count: the first r with the smallest W (Alg. 3), and its plan
@@ -724,7 +748,10 @@ extern "C" int pp_plan_replicated(int L, int D, int64_t N, int M, const int64_t 
     a.W_out = (long long *)W; a.bounds_out = bounds; a.reps_out = reps;
     a.pre_out = (long long *)pre;
     a.status = status;
-    hipLaunchKernelGGL(k_prm, dim3(lay.slots), dim3(PRM_THREADS), prm_lds_bytes(L, D), st, a);
+    size_t lds = prm_lds_bytes(L, D);
+    a.search = prm_search_lds_bytes(L, D) <= 64 * 1024;
+    if (a.search && prm_search_lds_bytes(L, D) > lds) lds = prm_search_lds_bytes(L, D);
+    hipLaunchKernelGGL(k_prm, dim3(lay.slots), dim3(PRM_THREADS), lds, st, a);
     if (hipGetLastError() != hipSuccess) return PP_ERR_HIP;
     return pp_launch_rep_makespan(L, D, N, M, pre, pre + (L + 1), pre + 2 * (L + 1), act_fwd_bytes,
                                   actb, bw, ord, bounds, reps, W, T, status, base + lay.part,

@@ -13,8 +13,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("seed,L,D,N", [
-    (601, 2, 8, 6), (602, 8, 8, 12), (603, 63, 3, 6), (604, 64, 5, 8), (605, 65, 8, 8), (606, 127, 4, 8), (610, 71, 6, 8),
-    (611, 72, 6, 8), (607, 128, 6, 8), (608, 129, 3, 6), (609, 193, 4, 4),
+    (601, 2, 8, 6), (602, 8, 8, 12), (603, 63, 3, 6), (604, 64, 5, 8), (605, 65, 8, 8), (606, 127, 4, 8), (610, 39, 6, 8),
+    (611, 40, 6, 8), (607, 128, 6, 8), (608, 129, 3, 6), (609, 193, 4, 4),
+    (612, 962, 2, 2), (613, 1021, 2, 2),
 ])
 def test_search_edges(ppo, G, seed, L, D, N):
     rng = np.random.Generator(np.random.PCG64(seed))
