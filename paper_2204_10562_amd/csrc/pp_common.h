@@ -44,9 +44,7 @@ struct pp_ws_header {
     // share_active: the sorted representatives are cut into share_nchunks runs of about equal
     // work (rows to compute); run w is entries start[w] .. start[w + 1] - 1 of the list
     unsigned share_nchunks;
-    // strict != 0: P[k] < P[k + 1] for every layer
-    unsigned strict;
-    unsigned pad0[54];
+    unsigned pad0[55];
     // byte 1024: work the partition DP actually did in this call, in 64 records of 128 bytes
     // (atomics that hit one cache line are served one after another, so every record has a
     // line of its own): (cell, split) pairs evaluated (rows shared between candidates are

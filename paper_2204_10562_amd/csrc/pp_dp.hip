@@ -220,19 +220,16 @@ __device__ void flat_table(const pack_args &a, long long *sh) {
 __global__ __launch_bounds__(256) void k_prep(pack_args a) {
     extern __shared__ __align__(16) long long dyn[];
     __shared__ unsigned long long sh[4];
-    __shared__ int shf[4], shs[4];
+    __shared__ int shf[4];
     const int tid = threadIdx.x;
     if (blockIdx.x < PP_PACK_BLOCKS) {
         const unsigned first = blockIdx.x * 256 + tid, stride = PP_PACK_BLOCKS * 256;
         unsigned long long m = 0;
-        bool strict = true;
         if (blockIdx.x == 0) {
             // P as int32, padded with P[L] up to a whole tile
             for (int l = tid; l <= a.L + 16; l += 256) {
                 int q = l < a.L ? l : a.L;
-                const long long p = a.PF[q] + a.PB[q];
-                a.p32[l] = (int)p;
-                if (l >= 1 && l <= a.L) strict &= a.PF[l - 1] + a.PB[l - 1] < p;
+                a.p32[l] = (int)(a.PF[q] + a.PB[q]);
             }
             long long pl = a.PF[a.L] + a.PB[a.L];
             m = pl < 0 ? ~0ull : (unsigned long long)pl;
@@ -248,14 +245,12 @@ __global__ __launch_bounds__(256) void k_prep(pack_args a) {
             m = o > m ? o : m;
         }
         const int wflat = __ballot(!flat) == 0;
-        const int wstrict = __ballot(!strict) == 0;
-        if ((tid & 63) == 0) { sh[tid >> 6] = m; shf[tid >> 6] = wflat; shs[tid >> 6] = wstrict; }
+        if ((tid & 63) == 0) { sh[tid >> 6] = m; shf[tid >> 6] = wflat; }
         __syncthreads();
         if (tid == 0) {
             for (int w = 1; w < 4; ++w) m = sh[w] > m ? sh[w] : m;
             a.hdr->pmax[blockIdx.x] = m;
             a.hdr->flat[blockIdx.x] = (unsigned)(shf[0] & shf[1] & shf[2] & shf[3]);
-            if (blockIdx.x == 0) a.hdr->strict = (unsigned)(shs[0] & shs[1] & shs[2] & shs[3]);
         }
     } else if (blockIdx.x == PP_PACK_BLOCKS) {
         flat_table(a, dyn);

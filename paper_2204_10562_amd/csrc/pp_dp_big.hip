@@ -93,7 +93,7 @@ __global__ __launch_bounds__(256, 4) void k_dp_big(dp_big_args b) {
     row.L = L;
     row.K = K;
     row.kmask = kmask;
-    row.strict = a.hdr->strict != 0;
+    row.strict = row_is_strict(sPk, L, lane);
     row.lane = lane;
     int v_steps = row_first_steps(L, lane);  // lane n: steps of a search in row n
     unsigned short *arg = a.arg + (size_t)wave * b.arg_stride;

@@ -87,7 +87,7 @@ __global__ __launch_bounds__(256) void k_dp_rows(dp_rows_args a) {
     r.L = L;
     r.K = K;
     r.kmask = kmask;
-    r.strict = a.g.hdr->strict != 0;
+    r.strict = row_is_strict(sPk, L, lane);
     r.lane = lane;
     int v_steps = row_first_steps(L, lane);
     const unsigned long long smask = S >= 64 ? ~0ull : ((1ull << S) - 1);
