@@ -1,4 +1,4 @@
-// Arguments of the register-tiled partition DP kernel (L <= 128).
+// Arguments of the register-tiled partition DP kernel (L <= 88).
 #pragma once
 
 #include "pp_common.h"

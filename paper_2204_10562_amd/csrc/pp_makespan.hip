@@ -13,7 +13,7 @@
 // anti-diagonal t = m + j - 1 of the (block, microbatch) grid), so one lane carries one
 // candidate and all lanes run the same uniform loop.
 //
-// Two kernels: for S <= 16 the 4S-3 durations and finish times of a lane live in registers
+// For S <= 16 the 4S-3 durations and finish times of a lane live in registers
 // (blocks unrolled; for S <= 8 the block ranges of the ramp-up, steady or sliding-window and
 // ramp-down sweeps are compile-time constants, otherwise every block is computed in every
 // sweep and its update kept or dropped; 32-bit when the bound (M+4S-4) * largest block of
