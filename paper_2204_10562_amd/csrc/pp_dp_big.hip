@@ -2,10 +2,10 @@
 // pp_dp_row.h, up to four chunks of 64 cells side by side.
 //
 // What bounds it: the latency of the searches' LDS reads, then instruction issue (vector unit busy
-// 59 % at L = 1024, where the LDS holds three waves per SIMD; four chunks side by side give each
-// wave four reads in flight).  About 33 K vector instructions per candidate at L = 1024, S = 32,
+// 61 % at L = 1024, where the LDS holds three waves per SIMD; four chunks side by side give each
+// wave four reads in flight).  About 36 K vector instructions per candidate at L = 1024, S = 32,
 // against 125 K when every (cell, split) pair up to an exact early exit was evaluated: 2^20
-// candidates 275 -> 88 ms; L = 300, S = 16, 15 751 representatives 297 -> 210 us.  (One lane per row
+// candidates 275 -> 96 ms; L = 300, S = 16, 15 751 representatives 297 -> 210 us.  (One lane per row
 // and one step per cell with a monotone queue was measured too: 345 ms at L = 1024, a serial chain of
 // LDS trips per cell.)
 //

@@ -16,10 +16,10 @@
 // arena rows make up its path, and the plans of up to DPR_PENDING finished candidates are read
 // back together, one candidate per lane.
 //
-// What bounds it: instruction issue (166 vector and 129 scalar instructions per row, vector unit busy
-// 60 %), then the latency of the searches' LDS reads at three waves per SIMD.  L = 128, S = 8, all 8!
-// orderings: 64 us with every (cell, split) pair evaluated from registers, 50 us here; L = 97, S = 11,
-// 200 003 sampled orderings: 1.02 -> 0.90 ms.
+// What bounds it: instruction issue (107 vector and 85 scalar instructions per row, all told; vector unit
+// busy 51 %) and the latency of the searches' LDS reads at three waves per SIMD.  L = 128, S = 8, all 8!
+// orderings: 63 us with every (cell, split) pair evaluated from registers, 46 us here; L = 97, S = 11,
+// 200 003 sampled orderings, whole call: 1.18 -> 0.93 ms.
 #include "pp_common.h"
 #include "pp_dp_flat.h"
 #include "pp_dp_row.h"
