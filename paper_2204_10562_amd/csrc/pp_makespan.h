@@ -43,7 +43,8 @@ struct mk_args {
     // workspace): nonzero = every block of 64 candidates decides for itself which of the two
     // kernels schedules it; k_makespan_split leaves MK_NOT_TAKEN in T_out of those it does not take
     int by_block;
-    int lanes_per;  // k_makespan_split: lanes per candidate (1, 2, 4 or 8)
+    int lanes_per;  // lanes per candidate of k_makespan_split (1, 2, 4 or 8) and k_makespan_fifo (1 .. 64)
+    long long first;  // k_makespan_fifo: the launch's first candidate
     // workspace header with the largest time of the tables (NULL if there is none): lets every
     // wave of a launch take the same decision between 32-bit and 64-bit finish times
     const pp_ws_header *hdr;

@@ -35,7 +35,7 @@ __global__ __launch_bounds__(FIFO_THREADS) void k_makespan_fifo(mk_args a) {
     int Q = 1;
     while (Q < J) Q <<= 1;
     int *so = lds, *sb = so + per * SP, *sf = sb + per * SP, *rings = sf + per;
-    const long long c0 = (long long)blockIdx.x * per;
+    const long long c0 = a.first + (long long)blockIdx.x * per;
     for (int t = tid; t < per * S; t += FIFO_THREADS) {
         const int i = t / S, n = t - i * S;
         const long long c = c0 + i;
@@ -163,6 +163,13 @@ int pp_launch_makespan_fifo(const mk_args &a, hipStream_t st) {
     while (Q < J) Q <<= 1;
     const int per = FIFO_THREADS / b.lanes_per;
     const size_t lds = (size_t)per * (2 * (a.S | 1) + 1 + Q) * 4;
-    hipLaunchKernelGGL(k_makespan_fifo, dim3((unsigned)((a.N + per - 1) / per)), dim3(FIFO_THREADS), lds, st, b);
-    return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_HIP;
+    // A launch has fewer than 2^32 threads.  At up to 64 lanes per candidate that is fewer candidates than
+    // a list may hold (all 12! orderings, 32 lanes each), so long lists take several launches.
+    const long long groups = (a.N + per - 1) / per, most = ((1ll << 32) - 1) / FIFO_THREADS;
+    for (long long g = 0; g < groups; g += most) {
+        b.first = g * per;
+        hipLaunchKernelGGL(k_makespan_fifo, dim3((unsigned)(groups - g < most ? groups - g : most)), dim3(FIFO_THREADS), lds, st, b);
+        if (hipGetLastError() != hipSuccess) return PP_ERR_HIP;
+    }
+    return PP_OK;
 }

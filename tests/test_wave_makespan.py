@@ -1,0 +1,57 @@
+"""The schedules' kernels that spread a candidate over lanes, run lane by lane on the CPU (their own
+sources, built with g++ and UndefinedBehaviorSanitizer against tests/wave_cpu/hip/hip_runtime.h)."""
+import math
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from conftest import ROOT
+
+PE, DUPLEX, GPIPE, ADDITIVE, FIFO = range(5)
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+
+
+def build(out, name):
+    exe = str(out / name)
+    here = os.path.join(ROOT, "tests", "wave_cpu")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-no-pie", "-Wno-attributes", "-fsanitize=undefined", "-I", here,
+                    "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2204_10562_amd", "csrc"),
+                    os.path.join(here, name + ".cpp"), "-o", exe], check=True)
+    return exe
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    exe = build(tmp_path_factory.mktemp("wave"), "makespan_driver")
+
+    def ask(lines, timeout=300):
+        env = dict(os.environ)
+        env.pop("LD_PRELOAD", None)  # the sanitizer's runtime must come first in the library list
+        res = subprocess.run([exe], input="".join(l + "\n" for l in lines), stdout=subprocess.PIPE,
+                             stderr=subprocess.PIPE, text=True, timeout=timeout, env=env)
+        assert res.returncode == 0, res.stderr[-2000:]
+        out = [[int(x) for x in l.split()] for l in res.stdout.splitlines()]
+        assert len(out) == len(lines)
+        return out, res.stderr
+    return ask
+
+
+@pytest.mark.parametrize("variant", [PE, DUPLEX, GPIPE, ADDITIVE, FIFO])
+def test_schedules_lane_by_lane(driver, variant):
+    sizes = [(1, 3), (2, 1), (3, 9), (5, 20), (8, 33), (9, 2), (16, 20)]
+    if variant != FIFO:
+        sizes += [(17, 5), (20, 90), (32, 7), (33, 140), (64, 3)]
+    lines = ["run %d %d %d %d %d" % (variant, S, M, S + M, hi) for S, M in sizes for hi in (3, 100000)]
+    out, _ = driver(lines)
+    for line, got in zip(lines, out):
+        assert got == [0, 0, 0], line
+
+
+@pytest.mark.parametrize("S,N", [(1, 1000), (12, math.factorial(12)), (32, 1 << 26), (32, (1 << 26) - 1), (17, (1 << 26) + 70),
+                                 (9, (1 << 27) + 70), (5, (1 << 28) + 70), (2, (1 << 30) + 70)])
+def test_readiness_order_takes_long_lists(driver, S, N):
+    # HIP refuses launches of 2^32 threads; the readiness order uses up to 64 lanes per candidate
+    (got,), _ = driver(["launch %d %d %d" % (FIFO, S, N)])
+    assert got[0] == 0 and N <= got[1] < N + 256

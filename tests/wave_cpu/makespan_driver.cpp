@@ -1,0 +1,181 @@
+// Runs the schedules' kernels that spread a candidate over lanes (their own sources) on the CPU.
+// Reads cases from stdin, one per line:
+//   run VARIANT S M SEED HI     40 random plans of S stages with times up to HI under the schedule
+//                               VARIANT, against Alg. 1's rules written out in 64 bits
+//   taken VARIANT S M TIME      how many of 64 plans whose times are all TIME the 30-bit kernel takes
+//   launch VARIANT S N          the launches for N candidates (nothing runs): the return value, and how
+//                               many candidates they have lanes for
+// and prints one line per case.
+#include "../../paper_2204_10562_amd/csrc/pp_makespan_split.hip"
+#undef DPP_WAVE_SHL1
+#undef DPP_WAVE_SHR1
+#include "../../paper_2204_10562_amd/csrc/pp_makespan_fifo.hip"
+
+#include <string.h>
+
+#include <algorithm>
+#include <random>
+
+alignas(16) int rows[16384], lds[16384];  // the kernels' LDS
+
+typedef long long ll;
+
+// Durations: d[j], j = 1..J (block R: the last stage's passes together); lastF, lastB: apart.
+static ll reference(int variant, int S, int M, std::vector<ll> d, ll lastF, ll lastB) {
+    int R = 2 * S - 1, J = 2 * R - 1;
+    if (variant == PP_SCHED_GPIPE) {
+        std::vector<ll> busy(R + 2, 0);
+        for (int m = 0; m < M; ++m)
+            for (int r = 1; r <= R; ++r) busy[r] = std::max(busy[r], r > 1 ? busy[r - 1] : 0) + (r == R ? lastF : d[r]);
+        for (int m = 0; m < M; ++m)
+            for (int r = R; r >= 1; --r) busy[r] = std::max(busy[r], r < R ? busy[r + 1] : 0) + (r == R ? lastB : d[2 * R - r]);
+        return busy[1];
+    }
+    if (variant == PP_SCHED_ADDITIVE) {
+        std::vector<ll> e(2 * S, 0);
+        for (int n = 0; n < S; ++n) {
+            const int r = 2 * n + 1, in = r - 1, out = 2 * R - in;
+            if (n == S - 1) e[S] = d[R] + (n ? d[in] + d[out] : 0);
+            else { e[n + 1] = d[r] + (n ? d[in] : 0); e[2 * S - 1 - n] = d[2 * R - r] + (n ? d[out] : 0); }
+        }
+        d = e; R = S; J = 2 * R - 1;
+    }
+    if (variant == PP_SCHED_FIFO) {
+        // (one item at a time: the earliest start, then the lowest resource; a channel takes the head
+        // that was ready first, then the earlier in list order)
+        std::vector<int> next(J + 1, 1);
+        std::vector<ll> idle(R + 1, 0);
+        std::vector<std::vector<ll>> left(J + 1, std::vector<ll>(M + 1, 0));
+        for (ll todo = (ll)J * M; todo; --todo) {
+            ll first = INT64_MAX;
+            int br = 0, bj = 0;
+            for (int r = 1; r <= R; ++r) {
+                const int ja = r, jb = 2 * R - r, ma = next[ja], mb = jb == ja ? M + 1 : next[jb];
+                const bool atA = ma <= M && (ja == 1 || next[ja - 1] > ma), atB = mb <= M && next[jb - 1] > mb;
+                const ll ra = atA && ja > 1 ? left[ja - 1][ma] : 0, rb = atB ? left[jb - 1][mb] : 0;
+                int j = 0;
+                if (r & 1) {
+                    if (ma <= M && (mb > M || ma + ja <= mb + jb)) j = atA ? ja : 0;
+                    else if (mb <= M) j = atB ? jb : 0;
+                } else if (atA && (!atB || ra < rb || (ra == rb && ma + ja <= mb + jb))) j = ja;
+                else if (atB) j = jb;
+                const ll start = std::max(idle[r], j == ja ? ra : rb);
+                if (j && start < first) { first = start; br = r; bj = j; }
+            }
+            idle[br] = left[bj][next[bj]] = first + d[bj];
+            ++next[bj];
+        }
+        return left[J][M];
+    }
+    std::vector<ll> fin(J + 2, 0);
+    for (int t = 1; t <= M + J - 1; ++t) {
+        const std::vector<ll> was = fin;
+        for (int pass = 0; pass < 2; ++pass)  // a resource's forward block is served before its backward block
+            for (int j = std::max(1, t - M + 1); j <= std::min(J, t); ++j) {
+                if ((j > R) != (pass == 1)) continue;
+                ll idle = fin[j];
+                if (variant != PP_SCHED_DUPLEX || (j & 1)) idle = std::max(idle, fin[2 * R - j]);
+                fin[j] = std::max(idle, j > 1 ? was[j - 1] : 0) + d[j];
+            }
+    }
+    return fin[J];
+}
+
+struct problem {
+    int L, D, S, N;
+    std::vector<ll> PF, PB, XF, XB, T;
+    std::vector<int> o, e;
+    int status = 0;
+    mk_args a = {};
+    problem(int variant, int S_, int N_, int M, unsigned seed, ll lo, ll hi) : L(S_ + 5), D(S_), S(S_), N(N_) {
+        std::mt19937_64 g(seed);
+        auto time = [&] { return lo + (ll)(g() % (unsigned long long)(hi - lo + 1)); };
+        PF.resize(L + 1);
+        PB.resize(L + 1);
+        for (int l = 0; l < L; ++l) { PF[l + 1] = PF[l] + time(); PB[l + 1] = PB[l] + time(); }
+        XF.resize((size_t)D * D * L);
+        XB.resize((size_t)D * D * L);
+        for (ll &x : XF) x = time();
+        for (ll &x : XB) x = time();
+        for (int c = 0; c < N; ++c) {
+            std::vector<int> dev(D), cut;
+            for (int i = 0; i < D; ++i) dev[i] = i;
+            std::shuffle(dev.begin(), dev.end(), g);
+            o.insert(o.end(), dev.begin(), dev.begin() + S);
+            for (int l = 1; l < L; ++l) cut.push_back(l);
+            std::shuffle(cut.begin(), cut.end(), g);
+            cut.resize(S - 1);
+            std::sort(cut.begin(), cut.end());
+            e.insert(e.end(), cut.begin(), cut.end());
+            e.push_back(L);
+        }
+        T.assign(N, -77);
+        a.L = L; a.D = D; a.S = S; a.N = N; a.nM = 1;
+        for (int &m : a.Ms) m = M;
+        a.PF = PF.data(); a.PB = PB.data(); a.XF = XF.data(); a.XB = XB.data();
+        a.orderings = o.data(); a.bounds = e.data(); a.T_out = T.data(); a.status = &status;
+        a.ord_stride = S; a.bnd_stride = S; a.t_stride = 1;
+        a.variant = variant;
+        a.by_block = 1;
+    }
+    ll want(int c, int M) const {
+        const int R = 2 * S - 1, J = 2 * R - 1;
+        std::vector<ll> d(J + 2, 0);
+        ll lastF = 0, lastB = 0;
+        for (int n = 0; n < S; ++n) {
+            const int e1 = e[c * S + n], e0 = n ? e[c * S + n - 1] : 0, r = 2 * n + 1;
+            const ll F = PF[e1] - PF[e0], B = PB[e1] - PB[e0];
+            if (n == S - 1) { d[R] = F + B; lastF = F; lastB = B; }
+            else { d[r] = F; d[2 * R - r] = B; }
+            if (n) {
+                const size_t at = ((size_t)o[c * S + n - 1] * D + o[c * S + n]) * L + e0 - 1;
+                d[r - 1] = XF[at];
+                d[2 * R - r + 1] = XB[at];
+            }
+        }
+        return reference(a.variant, S, M, d, lastF, lastB);
+    }
+    int launch() { return a.variant == PP_SCHED_FIFO ? pp_launch_makespan_fifo(a, NULL) : pp_launch_makespan_split(a, NULL); }
+};
+
+int main() {
+    char what[16];
+    while (scanf("%15s", what) == 1) {
+        int variant, S;
+        ll M, x;
+        if (scanf("%d %d %lld", &variant, &S, &M) != 3) return 2;
+        if (!strcmp(what, "run")) {
+            int seed;
+            if (scanf("%d %lld", &seed, &x) != 2) return 2;
+            problem p(variant, S, 40, (int)M, seed, variant == PP_SCHED_FIFO ? 1 : 0, x);
+            const int rc = p.launch();
+            int differ = 0;
+            for (int c = 0; c < p.N; ++c) differ += p.T[c] != p.want(c, (int)M);
+            printf("%d %d %d\n", rc, p.status, differ);
+        } else if (!strcmp(what, "taken")) {
+            if (scanf("%lld", &x) != 1) return 2;
+            problem p(variant, S, 64, (int)M, 1, x, x);
+            const int rc = p.launch();
+            int taken = 0;
+            for (int c = 0; c < p.N; ++c) taken += p.T[c] != MK_NOT_TAKEN;
+            printf("%d %d\n", rc, taken);
+        } else {
+            problem p(variant, S, 1, 8, 1, 1, 1);
+            p.a.N = M;
+            p.a.orderings = NULL;
+            wave::dry = true;
+            wave::launches.clear();
+            const int rc = p.launch();
+            wave::dry = false;
+            // (lanes per candidate: one per resource, rounded up to a power of two, or what the launch says)
+            ll lanes = 0;
+            for (auto &l : wave::launches) lanes += (ll)l.grid.x * l.block.x;
+            int each = 1;
+            while (variant == PP_SCHED_FIFO && each < 2 * S - 1) each <<= 1;
+            if (variant != PP_SCHED_FIFO) each = (int)wave::launches[0].block.x / 64;
+            printf("%d %lld\n", rc, lanes / each);
+        }
+        fflush(stdout);
+    }
+    return 0;
+}
