@@ -117,9 +117,10 @@ __device__ __forceinline__ void emit(const mk_args &a, int q, long long c, bool 
 // Largest finish time k_makespan_split works with.
 #define MK_SPLIT_CAP 0x3fffffff
 // True if every finish time of a pipeline of S stages whose largest per-resource time is `worst`
-// stays below MK_SPLIT_CAP for M microbatches (Lemma 1, with the sweeps of the padded pipeline).
-__device__ __forceinline__ bool mk_split_fits(long long worst, int M, int S) {
-    return worst <= (long long)MK_SPLIT_CAP / ((long long)M + 4 * S + 64);
+// stays below MK_SPLIT_CAP for M microbatches (Lemma 1, with the sweeps of the padded pipeline), and
+// the number of sweeps fits an int also where all times are zero.
+__device__ __forceinline__ bool mk_split_fits(long long worst, long long M, int S) {
+    return M + 4 * S + 64 <= MK_SPLIT_CAP && worst <= MK_SPLIT_CAP / (M + 4 * S + 64);
 }
 
 // Fault bits of a candidate whose devices and bounds lie in LDS (o: filled in for the list of all D!

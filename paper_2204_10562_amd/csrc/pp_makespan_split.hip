@@ -200,7 +200,7 @@ __global__ __launch_bounds__(512) void k_makespan_split(mk_args a) {
         int mmax = 1;
         for (int m = 0; m < a.nM; ++m) mmax = a.Ms[m] > mmax ? a.Ms[m] : mmax;
         // (GPipe's two waves take up to M + R - 1 of the largest forward and backward times each)
-        const bool fits = !ok || mk_split_fits(worst, MODE == PP_SCHED_GPIPE ? 2 * mmax + 4 * S : mmax, S);
+        const bool fits = !ok || mk_split_fits(worst, MODE == PP_SCHED_GPIPE ? 2ll * mmax + 4 * S : mmax, S);
         if (!__syncthreads_and(fits)) {
             if (live && q == 0) a.T_out[c * a.t_stride + a.t_off] = MK_NOT_TAKEN;
             return;

@@ -55,3 +55,23 @@ def test_readiness_order_takes_long_lists(driver, S, N):
     # HIP refuses launches of 2^32 threads; the readiness order uses up to 64 lanes per candidate
     (got,), _ = driver(["launch %d %d %d" % (FIFO, S, N)])
     assert got[0] == 0 and N <= got[1] < N + 256
+
+
+@pytest.mark.parametrize("variant", [PE, DUPLEX, GPIPE, ADDITIVE])
+@pytest.mark.parametrize("S", [1, 4, 17, 64])
+def test_microbatch_counts_next_to_the_largest_int(driver, variant, S):
+    # left to the 64-bit kernel, whatever the times: neither the limit on the times nor a number of
+    # sweeps may wrap around
+    Ms = [2**31 - 1 - d for d in (0, 1, 2 * S, 4 * S + 32, 4 * S + 33)] + [2**30, 2**30 - 1, 2**30 - 64]
+    lines = ["taken %d %d %d %d" % (variant, S, M, time) for M in Ms for time in (0, 1, 7)]
+    out, errors = driver(lines, timeout=60)
+    for line, got in zip(lines, out):
+        assert got == [0, 0], line
+    assert "runtime error" not in errors, errors[-2000:]
+
+
+def test_taken_where_the_times_fit(driver):
+    # one stage of all layers against the limit: 6 + 6 layers' times in 30 bits with the padded sweeps
+    fits = (2**30 - 1) // (100 + 4 + 64) // 12
+    out, _ = driver(["taken %d 1 100 %d" % (PE, fits), "taken %d 1 100 %d" % (PE, fits + 1)])
+    assert out == [[0, 64], [0, 0]]
