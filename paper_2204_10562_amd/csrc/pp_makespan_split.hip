@@ -16,8 +16,9 @@
 // places, and the kinds of sweeps differ in where they can be:
 //   filling (t <= M, not every resource has a backward item yet): forward places that are not
 //     reached yet run through negative numbers by themselves (they start at -2^30 and the sums of
-//     durations stay below 2^30); a backward place whose input is negative hands its sign on.  The
-//     resource is idle from max(f, b): 5 instructions per resource.
+//     durations stay below 2^30); a backward place whose input is negative hands its sign on (a time
+//     with that sign is a number from -2^31 up).  The resource is idle from max(f, b): 5 instructions
+//     per resource.
 //   full: 4 instructions per resource, f = max(b, f') + df, b = max(f, b') + db.
 //   draining (t > M, the source gives -2^30): a forward place whose input is negative hands its sign
 //     on; b, which is served in every sweep by now, says when the resource is idle: 5 instructions.
@@ -71,18 +72,21 @@ __device__ __forceinline__ void split_sweep(int (&f)[RL], int (&b)[RL], int (&id
         }
     }
     rb = is_last ? f[RL - 1] : rb;
-    // backward side, upwards: b[i + 1] is still the previous sweep's
+    // backward side, upwards: b[i + 1] is still the previous sweep's.  (The two sides of a channel do not
+    // hold each other's values up under DUPLEX: marks can lie below -2^30 there, and an empty place must not
+    // take its -2^30 from those.)
+    constexpr int low = SPLIT_NEG;
 #pragma unroll
     for (int i = 0; i < RL; ++i) {
         const int in = i + 1 < RL ? b[i + 1 < RL ? i + 1 : i] : rb;
         if (MODE == PP_SCHED_DUPLEX && !(i & 1)) {
-            b[i] = with_sign(in, smax(b[i], in) + db[i]);
+            b[i] = with_sign(in, smax(smax(b[i], in), low) + db[i]);
         } else if (KIND == SPLIT_FILL) {
             b[i] = with_sign(in, smax(f[i], in) + db[i]);
         } else if (KIND == SPLIT_FULL) {
             b[i] = smax(f[i], in) + db[i];
         } else if (KIND == SPLIT_DRAIN) {
-            b[i] = smax(smax(b[i], f[i]), in) + db[i];
+            b[i] = smax(smax(b[i], f[i]), MODE == PP_SCHED_DUPLEX ? smax(in, low) : in) + db[i];
         } else {
             b[i] = with_sign(in, smax(idle[i], in) + db[i]);
             idle[i] = smax(idle[i], b[i]);
