@@ -138,9 +138,9 @@ __global__ __launch_bounds__(256) void k_dp_rows(dp_rows_args a) {
         // a single stage: nothing to compute, C = P[L]
         const int key = rows[L];
         for (long long c = c0; c < c1; ++c) {
-            int d = lane == 0 ? ord[c] : 0;
+            const int d = ord[c];
             const bool bad = a.validate && (d < 0 || d >= D);
-            if (lane == pending) v_top = __builtin_amdgcn_readfirstlane(bad) ? -1 : key;
+            if (lane == pending) v_top = bad ? -1 : key;
             if (++pending == DPR_PENDING) flush();
         }
         if (pending) flush();
