@@ -237,7 +237,7 @@ def main():
                 "workload": "gpt_varied: the GPT shape with activation sizes 16 MiB x U[0.5, 2) per boundary",
                 "achieved": ach / 1e12, "peak": ALU_PEAK_OPS / 1e12, "unit": "TOP/s (32-bit integer lane-ops)",
                 "frac": ach / ALU_PEAK_OPS, "ops_per_pair": OPS_PER_PAIR,
-                "peak_measured": peak4 / 1e12, "peak_measured_at": "4 waves per SIMD (the kernel runs 3)",
+                "peak_measured": peak4 / 1e12, "peak_measured_at": "4 waves per SIMD (the kernel's occupancy)",
                 "launch": us(t_dpv), "pair_evals_executed_per_launch": sv["pairs_executed"],
                 "pair_evals_nominal_per_launch": pairs, "rows_executed_per_launch": sv["rows_executed"],
                 "dp_cells_per_s": N * S * L / t_dpv["mean"], "dp_nominal_pair_evals_per_s": pairs / t_dpv["mean"],

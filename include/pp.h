@@ -103,9 +103,10 @@ int pp_prefix_costs(int L, int D, const int64_t *fwd_us, const int64_t *bwd_us,
  * split) pairs the dynamic program actually evaluated in that call, the
  * uint64 after it to the number of DP rows it computed.  Rows that
  * consecutive candidates share (equal ordering prefixes) are computed and
- * counted once, and the kernels for L > 88 search for a cell's split (counted:
- * the steps of the search and its result, not the few splits looked at where a
- * search has to be mended), so these can be far below N * pairs-per-candidate.
+ * counted once, and for L > 128, and for longer lists of 88 < L <= 128, a cell's
+ * split is searched for (counted: the steps of the search and its result; for
+ * L > 128 not the few splits looked at where a search has to be mended), so
+ * these can be far below N * pairs-per-candidate.
  *
  * For L > 128 and D <= 64 the dynamic program is computed once for every
  * group of candidates whose links have the same transfer times at every cut

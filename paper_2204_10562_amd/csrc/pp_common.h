@@ -71,15 +71,12 @@ struct pp_ws_layout {
     size_t sh_hash, sh_rep, sh_table, sh_keys, sh_reps, sh_cnt, sh_start, sh_rows;
     long long sh_row_slots;  // DP rows (of pp_share_row_stride(L) keys) the area sh_rows holds
     int slots;  // resident workgroups of the generic DP kernel (one backtrack table each)
-    int nt;     // 8-cell tiles per row of the register-tiled DP kernel, 0 if it is not used
+    int nt;     // 8-cell tiles per row of the register-tiled DP kernel, 0 if it cannot be used
 };
 
 #define PP_TILE_MAX_L 128
-// Up to here every (cell, split) pair is evaluated from registers (pp_dp_tile.hip), beyond it a cell is
-// searched for (pp_dp_rows.hip): the pairs grow with L^2, the search's two chunks of 64 lanes do not.
-// Measured with 50 000 sampled orderings of 11 devices / all 8! orderings, whole search: L = 65 235 / 80 us
-// pairs, 287 / 83 searched; L = 80 249 / 92, 272 / 84; L = 88 270 / 96, 272 / 84; L = 96 319 / 107, 270 / 85;
-// L = 128 345 / 102, 292 / 86.
+// Up to here the register-tiled kernel always does the DP, beyond it and up to PP_TILE_MAX_L where
+// pp_dp_tiled says so.
 #define PP_PAIRS_MAX_L 88
 #define PP_DP_SLOTS 4096
 // Sharing of one partition DP between the candidates whose links have the same channel times
@@ -108,14 +105,11 @@ static inline pp_ws_layout pp_layout(int L, int D, int S, int64_t N) {
     pp_ws_layout w;
     size_t off = 0;
     w.hdr = off;    off += pp_align256(sizeof(pp_ws_header));
-    const size_t tiles = L <= PP_TILE_MAX_L ? (size_t)(L + 7) / 8 : 0;
-    w.nt = L <= PP_PAIRS_MAX_L ? (int)tiles : 0;
+    w.nt = L <= PP_TILE_MAX_L ? (L + 7) / 8 : 0;
     w.p32 = off;    off += pp_align256((size_t)(L + 17) * 4);  // padded to a whole tile
     w.x32 = off;    off += pp_align256((size_t)D * D * L * 4);
-    // (not used between PP_PAIRS_MAX_L and PP_TILE_MAX_L, but kept there: the sizes callers have been
-    // told, and which problems fit the static workspace, stay what they were)
-    w.xkt = off;    off += pp_align256((size_t)D * D * 8 * tiles * 4);
-    w.xct = off;    off += pp_align256((size_t)D * D * 16 * ((tiles + 1) / 2) * 4);
+    w.xkt = off;    off += pp_align256((size_t)D * D * 8 * w.nt * 4);
+    w.xct = off;    off += pp_align256((size_t)D * D * 16 * ((w.nt + 1) / 2) * 4);
     // channel-free DP table: values [S][L+1] int64, then lowest minimising splits [S][L+1] int32
     w.bfl = off;    off += pp_align256((size_t)S * (L + 1) * 12);
     w.ord = off;    off += pp_align256((size_t)N * S * 4);

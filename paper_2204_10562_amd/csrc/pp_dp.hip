@@ -260,12 +260,35 @@ __global__ __launch_bounds__(256) void k_prep(pack_args a) {
     }
 }
 
+// 8-cell tiles per row of the register-tiled kernel where it does the DP, 0 where another kernel does.
+//
+// For 88 < L <= 128 the pairs the tiled kernel evaluates (two waves per SIMD by its registers, fewer by LDS)
+// stand against the latency of the row kernel's searches, which more resident waves hide.  Measured for
+// S = 2 .. 64 with 50 000 sampled orderings, DP alone, tiled / rows in us: 16 against 8 waves per compute
+// unit 189 / 142 (L = 89, S = 8), 206 / 145 (L = 128, S = 8); 12 against 8: 288 / 236 (L = 97, S = 11);
+// 8 against 6: 846 / 473 (L = 128, S = 16), but 480 / 432 and, with links that bind everywhere, 479 / 544
+// (30 000, L = 97, S = 24); 8 against 8: 332 / 376 (L = 89, S = 13), 289 / 349 (L = 112, S = 12).
+// Short lists leave SIMDs without a second wave: 1000 candidates 18 / 24 (L = 89, S = 8), 4000 26 / 28, 8000
+// 46 / 38; L = 128: 4000 30 / 26; one wave of the tiled kernel per SIMD: 2000 56 / 39 (L = 128, S = 16).
+static int pp_dp_tiles(int L, int D, int S, int64_t N, const pp_ws_layout &lay) {
+    if (!lay.nt || L <= PP_PAIRS_MAX_L) return lay.nt;
+    size_t lds;
+    const int wpb = pp_dp_tile_shape(L, D, S, lay.nt, &lds);
+    lds = (lds + sizeof(dp_generic_small) + 1279) / 1280 * 1280;
+    int tiled = (int)(160 * 1024 / lds) * wpb;
+    tiled = tiled < 8 ? tiled : 8;
+    // (with the room the stage-count search needs, so that preparation and search agree)
+    const int rows = pp_dp_rows_shape(L, D, S, 1).waves_per_cu;
+    const int least = tiled <= 6 ? 2048 : (L > 104 ? 4096 : 6144);
+    return N >= least && (L > 104 ? rows > tiled : 3 * rows > 4 * tiled) ? 0 : lay.nt;
+}
+
 int pp_launch_pack(int L, int D, int S, int64_t N, const int64_t *PF, const int64_t *PB,
                    const int64_t *XF, const int64_t *XB, const int32_t *orderings, void *ws,
                    const pp_ws_layout &lay, const int32_t **ord, hipStream_t st) {
     char *base = (char *)ws;
     pack_args a;
-    a.L = L; a.D = D; a.S = S; a.K = pp_index_bits(L); a.nt = lay.nt; a.N = N;
+    a.L = L; a.D = D; a.S = S; a.K = pp_index_bits(L); a.nt = pp_dp_tiles(L, D, S, N, lay); a.N = N;
     a.total = (size_t)D * D * L;
     a.PF = (const long long *)PF; a.PB = (const long long *)PB;
     a.XF = (const long long *)XF; a.XB = (const long long *)XB;
@@ -364,8 +387,8 @@ int pp_launch_dp(int L, int D, int S, int64_t N, const int64_t *PF, const int64_
         cus = 256;
     // Priority levels of the waves that share a SIMD end when a tenth, a quarter and half of the chunk
     // are left: they drift apart while they are on the same level and are pulled together at each
-    // boundary, so the levels get shorter towards the end (measured for the kernel that evaluates all
-    // pairs, L = 128, all 8! orderings, against equal quarters: 65.8 against 67.1 us).
+    // boundary, so the levels get shorter towards the end (the tiled kernel, L = 128, all 8! orderings,
+    // against equal quarters: 65.8 against 67.1 us).
     auto levels = [](long long chunk, int (&left)[3]) {
         const long long frac[3] = {10, 4, 2};
         for (int k = 0; k < 3; ++k) {
@@ -373,45 +396,43 @@ int pp_launch_dp(int L, int D, int S, int64_t N, const int64_t *PF, const int64_
             left[k] = (int)(v > 0x3fffffff ? 0x3fffffff : v);
         }
     };
-    if (L > PP_PAIRS_MAX_L && L <= PP_TILE_MAX_L) {
+    const int nt = pp_dp_tiles(L, D, S, N, lay);
+    if (lay.nt && !nt) {
         dp_rows_args t;
         t.L = L; t.D = D; t.S = S; t.K = a.K; t.N = N;
         t.validate = a.validate;
-        const size_t lds_wave = pp_dp_rows_lds_per_wave(S), table = (size_t)DPR_RS * 4;
-        int wpb = 4;  // waves per workgroup, limited by 64 KiB of LDS
-        while (wpb > 1 && table + lds_wave * wpb > 64 * 1024) wpb >>= 1;
-        if (table + lds_wave * wpb > 64 * 1024) return PP_ERR_INVALID_ARG;  // cannot happen for S <= 64
-        // waves that fit a SIMD's share of the LDS (given out in pieces of 1280 bytes)
-        int waves_per_simd = (int)(160 * 1024 / ((table + lds_wave * wpb + 1279) / 1280 * 1280)) * wpb / 4;
-        waves_per_simd = waves_per_simd < 1 ? 1 : (waves_per_simd > 4 ? 4 : waves_per_simd);
-        t.chunk = choose_chunk(N, D, lex_ord != NULL, (long long)cus * 4, waves_per_simd);
+        const dpr_shape sh = pp_dp_rows_shape(L, D, S, stages);
+        if (!sh.wpb) return PP_ERR_INVALID_ARG;  // cannot happen for S <= 64
+        // the list split evenly over the resident waves, also where neighbours share rows: the kernel
+        // is bound by latency, and with all 8! orderings of L = 128 runs of 4! (two waves per SIMD)
+        // took 110 us for the whole search, runs of 10 (four) 78 us
+        t.chunk = (N + (long long)cus * sh.waves_per_cu - 1) / ((long long)cus * sh.waves_per_cu);
         levels(t.chunk, t.prio_left);
         const long long nchunks = (N + t.chunk - 1) / t.chunk;
-        const int grid = (int)((nchunks + wpb - 1) / wpb);
+        const int grid = (int)((nchunks + sh.wpb - 1) / sh.wpb);
         if (a.nblocks > grid) a.nblocks = grid;
         t.g = a;
-        return pp_launch_dp_rows(t, grid, wpb, st);
+        return pp_launch_dp_rows(t, grid, sh, st);
     }
-    if (lay.nt) {
-        // L <= 88: register-tiled kernel, one wave per candidate (falls back to the generic
+    if (nt) {
+        // register-tiled kernel, one wave per candidate (falls back to the generic
         // int64 body inside the same launch when the times do not fit 32-bit keys)
         dp_tile_args t;
         t.L = L; t.D = D; t.S = S; t.K = a.K; t.N = N;
         t.validate = a.validate;
         t.xkt = (const int *)(base + lay.xkt);
         t.xct = (const int *)(base + lay.xct);
-        const size_t lds_wave = pp_dp_tile_lds_per_wave(S, lay.nt);
-        int wpb = 4;  // waves per workgroup, limited by 64 KiB of LDS
-        while (wpb > 1 && lds_wave * wpb > 64 * 1024) wpb >>= 1;
-        if (lds_wave * wpb > 64 * 1024) return PP_ERR_INVALID_ARG;  // cannot happen for S <= 64
-        const int waves_per_simd = 4;
+        size_t lds;
+        const int wpb = pp_dp_tile_shape(L, D, S, nt, &lds);
+        if (!wpb) return PP_ERR_INVALID_ARG;  // cannot happen for S <= 64
+        const int waves_per_simd = nt >= 14 ? 2 : (nt >= 12 ? 3 : 4);
         t.chunk = choose_chunk(N, D, lex_ord != NULL, (long long)cus * 4, waves_per_simd);
         levels(t.chunk, t.prio_left);
         const long long nchunks = (N + t.chunk - 1) / t.chunk;
         const int grid = (int)((nchunks + wpb - 1) / wpb);
         if (a.nblocks > grid) a.nblocks = grid;
         t.g = a;
-        return pp_launch_dp_tile(t, lay.nt, grid, wpb, st);
+        return pp_launch_dp_tile(t, nt, grid, wpb, st);
     }
     // L > 128: one persistent wave per candidate slot
     long long waves = lay.slots < N ? lay.slots : N;

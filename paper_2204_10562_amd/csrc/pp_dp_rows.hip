@@ -1,5 +1,26 @@
-// Partition DP for 88 < L <= 128: one wavefront per candidate, the rows as in pp_dp_row.h (one lane
-// per cell and a search per cell, two chunks of 64 cells side by side).
+// Partition DP for 88 < L <= 128 and lists long enough to fill the chip: one wavefront per candidate, one
+// lane per cell (two chunks of 64 side by side) and a binary search per cell.
+//
+// Recursion for W(l, xi, r, i) of Sec. IV-B / the PRM listing with one replica per stage:
+//   W[n][l] = min_{n<=k<l} max(g[k], P[l] - P[k]),   g[k] = max(W[n-1][k], X_n[k]),
+// lowest minimising k kept; cells and splits are 32-bit keys (time << K) | k.
+//
+// With G(j) = min_{j<k<l} g[k] (infinite for j = l - 1) a split j is alive iff P[l] - P[j] <= G(j).  G rises
+// with j and P[l] - P[j] falls, so the alive splits are those from some j* on.  A split left of j* costs more
+// than the one whose g its difference exceeds; among the alive ones no difference exceeds a later g, so
+//   W[n][l] = min(G(j*), max(g[j*], P[l] - P[j*])),
+// and with keys for times this is the lowest split too (P strictly rising; where layers of length zero make
+// lower splits with j*'s P tie, the lowest of their run is looked up).  j* is found from l - 1 downwards by
+// powers of two, G growing along: T[s][k] = min g[k+1 .. k+2^s] gives the minimum over a jump.  The tables
+// for s = 0 .. steps - 1 take a pass each over the row (two passes per trip to LDS) and lie in the rows that
+// are computed after this one.
+//
+// The minima end at the cell itself, so the work does not depend on where the links bind.  (Minima over the
+// whole row, one table, and a walk over the splits wherever a later g undercuts the cell's, as pp_dp_row.h
+// has it, took 46 us where this takes 47 - L = 128, S = 8, all 8! orderings, channel times that seldom bind;
+// 63 us with all pairs from registers - but with activations that shrink from layer to layer and 1.25 GB/s
+// links 341 us for the whole search, against 90 us with all pairs and 78 us here; L = 89, S = 16, 24 000
+// orderings 2.4 ms, 0.30 ms, and the tiled kernel's 0.30 ms by pp_dp_tiles.)
 //
 // The rows of the current candidate live in LDS, one private slice per wave, so there are no
 // barriers.  The single cell of the last row that is needed is worked out at the end of row S-2,
@@ -16,10 +37,10 @@
 // arena rows make up its path, and the plans of up to DPR_PENDING finished candidates are read
 // back together, one candidate per lane.
 //
-// What bounds it: instruction issue (107 vector and 85 scalar instructions per row, all told; vector unit
-// busy 51 %) and the latency of the searches' LDS reads at three waves per SIMD.  L = 128, S = 8, all 8!
-// orderings: 63 us with every (cell, split) pair evaluated from registers, 46 us here; L = 97, S = 11,
-// 200 003 sampled orderings, whole call: 1.18 -> 0.93 ms.
+// What bounds it: instruction issue (187 vector and 154 scalar instructions per row, all told; vector unit
+// busy 67 %) and the latency of a row's two chains through LDS, the tables' and the search's: a row takes
+// 5 200 clocks with four waves per SIMD.  L = 97, S = 11, 200 003 sampled orderings, whole
+// call: 1.18 ms with all pairs, 0.96 ms here.
 #include "pp_common.h"
 #include "pp_dp_flat.h"
 #include "pp_dp_row.h"
@@ -35,6 +56,114 @@ __device__ __forceinline__ int wave_min(int v) {
                     row_imin(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
 }
 
+// One row n (xv: the link's times at the splits 64 u + lane + 1): W[n] to row n of the wave's rows, and to w.
+// Returns the number of rounds the searches took.
+struct rows_row {
+    int *rows;      // the wave's rows, RS entries each
+    const int *PK;  // (P[k] << K) - k, k = 0 .. 128
+    int RS, L, K, kmask, lane;
+    bool strict;    // no layer has length zero
+    const unsigned char *run;  // the first split of every split's run of equal P, k = 0 .. 127
+    // of the cells 64 u + lane + 1: P, and the entry of PK of their last split (the cells beyond L repeat L)
+    unsigned Pl[2];
+    int last[2];
+};
+__device__ __forceinline__ int rows_compute(const rows_row &r, int n, int steps, const int (&xv)[2], int (&w)[2]) {
+    const int lane = r.lane, RS = r.RS;
+    int *T = r.rows + n * RS;
+    // T[s RS + k] = min g[k + 1 .. k + 2^s] (what a search in front of split k + 2^s asks for), 0 for k < n.
+    // (Only entries whose whole range lies below L are read back, whatever the others hold.)
+    int m[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int k = 64 * u + lane + 1;
+        m[u] = row_imax((T[k - RS] & ~r.kmask) | k, (int)((unsigned)xv[u] << r.K) | k);
+    }
+    const int g_n = __builtin_amdgcn_readlane(m[0], n - 1);
+    m[0] = lane >= n ? m[0] : 0;
+    T += lane;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) T[64 * u] = m[u];
+    row_lds_sync();
+    int *t = T;
+    for (int s = 0, by = 1; s + 1 < steps; s += 2, by *= 4) {
+        int x[2], y[2], z[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) { x[u] = t[by + 64 * u]; y[u] = t[2 * by + 64 * u]; z[u] = t[3 * by + 64 * u]; }
+        t += RS;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) { x[u] = row_imin(m[u], x[u]); m[u] = row_imin(row_imin(x[u], y[u]), z[u]); }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) t[64 * u] = x[u];
+        t += RS;
+        row_lds_sync();  // (other lanes' spills before this table's entries)
+        if (s + 2 < steps) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) t[64 * u] = m[u];
+        }
+        row_lds_sync();
+    }
+    // at[u]: (address of) the entry of P of the split each cell has got back to, low[u]: min g over the
+    // splits right of it
+    const int pk0 = row_addr(r.PK), to_t = row_addr(T - lane) - pk0, reach = (4 << steps) - 4;
+    int at[2];
+    unsigned low[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) { at[u] = r.last[u]; low[u] = PP_INF32; }
+    int rounds = 0;
+    for (bool more = true; more; ++rounds) {
+        int from[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) from[u] = at[u];
+        for (int by = 2 << steps, to = to_t + 4 * (steps - 1) * RS; by >= 4; by >>= 1, to -= 4 * RS) {
+            int j[2];
+            unsigned p[2], q[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) { j[u] = at[u] - by; p[u] = row_at(j[u]); q[u] = row_at(j[u] + to); }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const unsigned h = q[u] < low[u] ? q[u] : low[u];
+                const bool back = r.Pl[u] - p[u] < h;  // (equal keys cannot be: the split's index is in them)
+                at[u] = back ? j[u] : at[u];
+                low[u] = back ? h : low[u];
+            }
+        }
+        bool whole = false;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) whole |= at[u] == from[u] - reach;
+        more = __ballot(whole) != 0;
+    }
+    unsigned g[2], p[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) { g[u] = row_at(at[u] + to_t - 4); p[u] = row_at(at[u]); }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int d = (int)(r.Pl[u] - p[u]), gk = at[u] == pk0 + 4 * n ? g_n : (int)g[u];
+        w[u] = row_imin((int)low[u], row_imax(gk, d));
+    }
+    if (!r.strict) {
+        // the lowest split of a run of equal P whose g does not exceed the value (others cannot tie)
+        const int *G = T - lane - 1;  // G[k] = g[k], k > n
+        int a[2], v[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            a[u] = row_imax(r.run[(at[u] - pk0) >> 2], n);
+            v[u] = w[u] | r.kmask;
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int j = (at[u] - pk0) >> 2;
+            while (a[u] < j && (a[u] > n ? G[a[u]] : g_n) > v[u]) ++a[u];
+            w[u] = a[u] < j ? (w[u] & ~r.kmask) | a[u] : w[u];
+        }
+    }
+    row_lds_sync();
+    w[0] = lane >= n ? w[0] : PP_INF32;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) T[64 * u + 1] = w[u];
+    return rounds;
+}
+
 __global__ __launch_bounds__(256) void k_dp_rows(dp_rows_args a) {
     extern __shared__ __align__(16) unsigned char smem[];
     if (pp_is_flat(a.g.hdr)) {
@@ -47,24 +176,33 @@ __global__ __launch_bounds__(256) void k_dp_rows(dp_rows_args a) {
         return;
     }
 
-    constexpr int U = 2, RS = DPR_RS;  // two chunks of 64 cells; row stride: keys in dwords, arena rows in bytes
+    constexpr int U = 2;  // two chunks of 64 cells
     const int lane = threadIdx.x & 63;
     const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int S = a.S, K = a.K, L = a.L, D = a.D;
+    const int RS = dpr_stride(L);  // row stride: keys in dwords, arena rows in bytes
     const int kmask = (1 << K) - 1;
-    // (P[k] << K) - k, k = 0..64 U (P padded with P[L]), shared by the workgroup, with an entry of padding in front
-    int *sPk = (int *)smem + 1;
+    const size_t lds_wave = dpr_lds_per_wave(L, S, a.rows, a.g.stages);
+    // (P[k] << K) - k, k = 0..128 (P padded with P[L]), shared by the workgroup.  A search looks up to 64
+    // entries below split 0: what stands there ends it.  It lies behind the waves' parts, because the search
+    // looks as far below their rows.
+    int *sPk = (int *)(smem + lds_wave * (blockDim.x >> 6)) + 64;
+    for (int k = threadIdx.x; k < 64; k += blockDim.x) sPk[k - 64] = (int)0x80000001;
     for (int k = threadIdx.x; k <= 64 * U; k += blockDim.x) sPk[k] = (a.g.p32[k < L ? k : L] << K) - k;
-    if (threadIdx.x == 0) sPk[-1] = 0;
     __syncthreads();
-    unsigned char *mine = smem + RS * 4 + (size_t)wib * pp_dp_rows_lds_per_wave(S);
-    int *rows = (int *)mine;              // [S][RS] keys of the current path's rows
-    int *sg = rows + S * RS;              // g and h of the row being computed
-    unsigned *sh = (unsigned *)(sg + RS) + 1;
-    int *tops = sg + 2 * RS;              // [pending][S] key of cell (n, L)
-    unsigned char *arena = (unsigned char *)(tops + DPR_PENDING * S);
-    unsigned char *slots = arena + (size_t)dpr_arena_rows(S) * RS;  // [pending][S] arena row of row n
-    const int arena_rows = dpr_arena_rows(S);
+    unsigned char *run = (unsigned char *)(sPk + 64 * U + 1);
+    for (int k = threadIdx.x; k < 64 * U; k += blockDim.x) {
+        int a = k;
+        while (a > 0 && sPk[a - 1] + (a - 1) == sPk[k] + k) --a;
+        run[k] = (unsigned char)a;
+    }
+    __syncthreads();
+    unsigned char *mine = smem + (size_t)wib * lds_wave;
+    const int arena_rows = dpr_arena_rows(S, a.g.stages), key_rows = a.rows;
+    int *rows = (int *)mine;                           // [key_rows][RS]: the current path's rows
+    int *tops = rows + key_rows * RS + (128 - L);      // [pending][S] key of cell (n, L)
+    unsigned char *arena = (unsigned char *)(tops + (a.g.stages ? DPR_PENDING * S : 0));
+    unsigned char *slots = arena + (size_t)arena_rows * RS + (128 - L);  // [pending][S] arena row of row n
     const bool stages = a.g.stages != 0;
     const int tri = S * (S + 1) / 2;
     long long *C_out = a.g.C_out;
@@ -80,16 +218,25 @@ __global__ __launch_bounds__(256) void k_dp_rows(dp_rows_args a) {
     for (int l = lane; l <= 64 * U; l += 64) rows[l] = sPk[l] + l;
     row_lds_sync();
     const int PLk = sPk[L] + L;
-    dp_row r;
-    r.g = sg;
-    r.h = sh;
+    rows_row r;
+    r.rows = rows;
     r.PK = sPk;
+    r.RS = RS;
     r.L = L;
     r.K = K;
     r.kmask = kmask;
-    r.strict = row_is_strict(sPk, L, lane);
     r.lane = lane;
-    int v_steps = row_first_steps(L, lane);
+    r.strict = row_is_strict(sPk, L, lane);
+    r.run = run;
+    int to_end[U];  // P[L] - P[l] of the lane's cells, infinite from L on
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int l = 64 * u + lane + 1;
+        r.Pl[u] = (unsigned)(sPk[l] + l);
+        r.last[u] = row_addr(sPk) + 4 * row_imin(l - 1, L - 1);
+        to_end[u] = l < L ? PLk - sPk[l] : PP_INF32;
+    }
+    int v_steps = dpr_steps(L, lane);  // lane n: steps of a search in row n
     const unsigned long long smask = S >= 64 ? ~0ull : ((1ull << S) - 1);
     const int top_lane = (L - 1) & 63;  // the lane of cell L (in the last chunk)
 
@@ -181,8 +328,8 @@ __global__ __launch_bounds__(256) void k_dp_rows(dp_rows_args a) {
         const int *xp = a.g.x32 + (size_t)link * L;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int k = 64 * u + lane;
-            x[u] = xp[k];  // (beyond L: whatever follows the row in the workspace; not used)
+            const int k = 64 * u + lane + 1;
+            x[u] = xp[k];  // (from L on: whatever follows the row in the workspace; not used)
         }
     };
 
@@ -270,20 +417,13 @@ __global__ __launch_bounds__(256) void k_dp_rows(dp_rows_args a) {
             }
             fetch_x(xf, next_link);
 
-            r.W = rows + (n - 1) * RS;
             if (n < S - 1) {
-                r.out = rows + n * RS;
-                r.n = n;
-                r.steps = __builtin_amdgcn_readlane(v_steps, n);
-                r.carry = PP_INF32;
-                r.again = false;
                 int w[U];
-                row_build<U>(r, 0, xc, w);
-                row_lds_sync();
-                row_search<U>(r, 0, w);
-                pairs += (unsigned long long)((L - n) * (r.steps + 1));
+                const int steps = __builtin_amdgcn_readlane(v_steps, n);
+                const int rounds = rows_compute(r, n, steps, xc, w);
+                pairs += (unsigned long long)((L - n) * (rounds * steps + 1));
                 ++nrows;
-                if (r.again && lane == n && v_steps < K) ++v_steps;
+                if (rounds > 1 && lane == n && v_steps < key_rows - n && v_steps < DPR_MAX_STEPS) ++v_steps;
                 const int slot = arena_used++;
                 const int top_n = __builtin_amdgcn_readlane(w[U - 1], top_lane);
                 if (lane == n) { v_cur = slot; v_tops = top_n; }
@@ -299,8 +439,7 @@ __global__ __launch_bounds__(256) void k_dp_rows(dp_rows_args a) {
                     for (int u = 0; u < U; ++u) {
                         const int l = 64 * u + lane + 1;
                         const int xk2 = (int)((unsigned)xl[u] << K) | l, wk = (w[u] & ~kmask) | l;
-                        const int t = row_imax(row_imax(wk, xk2), PLk - sPk[l]);
-                        m = l < L ? row_imin(m, t) : m;
+                        m = row_imin(m, row_imax(row_imax(wk, xk2), to_end[u]));
                     }
                     const int top = wave_min(m);
                     pairs += (unsigned long long)(L - (S - 1));
@@ -313,10 +452,10 @@ __global__ __launch_bounds__(256) void k_dp_rows(dp_rows_args a) {
                 int m = PP_INF32;
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const int k = 64 * u + lane;
-                    const int xk2 = (int)((unsigned)xc[u] << K) | k, wk = (r.W[k] & ~kmask) | k;
-                    const int t = row_imax(row_imax(wk, xk2), PLk - sPk[k]);
-                    m = (k >= n && k < L) ? row_imin(m, t) : m;
+                    const int k = 64 * u + lane + 1;
+                    const int xk2 = (int)((unsigned)xc[u] << K) | k, wk = (rows[(n - 1) * RS + k] & ~kmask) | k;
+                    const int t = row_imax(row_imax(wk, xk2), to_end[u]);
+                    m = k >= n ? row_imin(m, t) : m;
                 }
                 pairs += (unsigned long long)(L - n);
                 ++nrows;
@@ -369,14 +508,34 @@ __global__ __launch_bounds__(256) void k_dp_rows(dp_rows_args a) {
     if (lane == 0) pp_count_work(a.g.hdr, pairs, nrows, (unsigned)wave);
 }
 
-int pp_launch_dp_rows(const dp_rows_args &a, int grid, int wpb, hipStream_t st) {
-    size_t lds = (size_t)DPR_RS * 4 + (size_t)wpb * pp_dp_rows_lds_per_wave(a.S);
-    const size_t generic = dp_generic_lds_bytes(a.L);  // the int64 fallback's rows
+static size_t rows_lds(int L, int D, int S, int rows, int stages, int wpb) {
+    size_t lds = DPR_TABLE + (size_t)wpb * dpr_lds_per_wave(L, S, rows, stages);
+    const size_t generic = dp_generic_lds_bytes(L);  // the int64 fallback's rows
     if (lds < generic) lds = generic;
-    const size_t flat = pp_flat_lds_wanted(a.L, a.D, a.S, wpb);  // the closed-form body's tables
-    if (lds < flat) lds = flat;
+    const size_t flat = pp_flat_lds_wanted(L, D, S, wpb);  // the closed-form body's tables
+    return lds < flat ? flat : lds;
+}
+
+dpr_shape pp_dp_rows_shape(int L, int D, int S, int stages) {
+    dpr_shape s = {4, dpr_min_rows(L, S), 1, 0};
+    while (s.wpb && rows_lds(L, D, S, s.rows, stages, s.wpb) > 64 * 1024) s.wpb >>= 1;
+    if (!s.wpb) return s;
+    // workgroups on a compute unit: 160 KiB of LDS, given out in pieces of 1280 bytes
+    auto groups = [&](int rows) {
+        const size_t lds = rows_lds(L, D, S, rows, stages, s.wpb);
+        return lds > 64 * 1024 ? 0 : (int)(160 * 1024 / ((lds + 1279) / 1280 * 1280));
+    };
+    const int g = groups(s.rows);
+    while (S > 2 && s.rows < S - 2 + DPR_MAX_STEPS && groups(s.rows + 1) == g) ++s.rows;
+    s.lds = rows_lds(L, D, S, s.rows, stages, s.wpb);
+    s.waves_per_cu = g * s.wpb > 16 ? 16 : g * s.wpb;
+    return s;
+}
+
+int pp_launch_dp_rows(const dp_rows_args &a, int grid, const dpr_shape &sh, hipStream_t st) {
     dp_rows_args b = a;
-    b.g.lds_bytes = lds;
-    hipLaunchKernelGGL(k_dp_rows, dim3(grid), dim3(64 * wpb), lds, st, b);
+    b.g.lds_bytes = sh.lds;
+    b.rows = sh.rows;
+    hipLaunchKernelGGL(k_dp_rows, dim3(grid), dim3(64 * sh.wpb), sh.lds, st, b);
     return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_HIP;
 }

@@ -1,4 +1,4 @@
-// Arguments of the register-tiled partition DP kernel (L <= 88).
+// Arguments of the register-tiled partition DP kernel (L <= 128).
 #pragma once
 
 #include "pp_common.h"
@@ -27,6 +27,9 @@ __host__ __device__ static inline size_t pp_dp_tile_lds_per_wave(int S, int nt) 
     size_t tops = (size_t)DPT_PENDING * S * 4;
     return (rows + arena + slots + tops + 15) & ~(size_t)15;
 }
+
+// Waves per workgroup for this shape (0: it does not fit) and the workgroup's dynamic LDS.
+int pp_dp_tile_shape(int L, int D, int S, int nt, size_t *lds);
 
 // grid workgroups of wpb waves; wave w walks candidates [w*chunk, (w+1)*chunk)
 int pp_launch_dp_tile(const dp_tile_args &a, int nt, int grid, int wpb, hipStream_t st);

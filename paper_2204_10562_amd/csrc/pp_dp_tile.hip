@@ -1,4 +1,4 @@
-// Partition DP for L <= 88: one wavefront per candidate, cells and splits tiled over the
+// Partition DP for L <= 128: one wavefront per candidate, cells and splits tiled over the
 // 64 lanes, everything that does not depend on the candidate kept in registers.
 //
 // Recursion for W(l, xi, r, i) of Sec. IV-B / the PRM listing with one replica per stage:
@@ -487,18 +487,27 @@ static int launch_nt(const dp_tile_args &a, int grid, int wpb, size_t lds, hipSt
     return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_HIP;
 }
 
+int pp_dp_tile_shape(int L, int D, int S, int nt, size_t *lds) {
+    const size_t lds_wave = pp_dp_tile_lds_per_wave(S, nt);
+    int wpb = 4;  // waves per workgroup, limited by 64 KiB of LDS
+    while (wpb && lds_wave * wpb > 64 * 1024) wpb >>= 1;
+    *lds = (size_t)wpb * lds_wave;
+    const size_t generic = dp_generic_rows_bytes(L);  // the int64 fallback's rows
+    if (*lds < generic) *lds = generic;
+    const size_t flat = pp_flat_lds_wanted(L, D, S, wpb);  // the closed-form body's tables
+    if (*lds < flat) *lds = flat;
+    return wpb;
+}
+
 int pp_launch_dp_tile(const dp_tile_args &a, int nt, int grid, int wpb, hipStream_t st) {
-    size_t lds = (size_t)wpb * pp_dp_tile_lds_per_wave(a.S, nt);
-    const size_t generic = dp_generic_rows_bytes(a.L);  // the int64 fallback's rows
-    if (lds < generic) lds = generic;
-    const size_t flat = pp_flat_lds_wanted(a.L, a.D, a.S, wpb);  // the closed-form body's tables
-    if (lds < flat) lds = flat;
+    size_t lds;
+    pp_dp_tile_shape(a.L, a.D, a.S, nt, &lds);
     dp_tile_args b = a;
     b.g.lds_bytes = lds;
     switch (nt) {
 #define CASE(n) case n: return launch_nt<n>(b, grid, wpb, lds, st);
         CASE(1) CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8)
-        CASE(9) CASE(10) CASE(11)
+        CASE(9) CASE(10) CASE(11) CASE(12) CASE(13) CASE(14) CASE(15) CASE(16)
 #undef CASE
     }
     return PP_ERR_INVALID_ARG;

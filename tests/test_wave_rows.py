@@ -1,0 +1,52 @@
+"""The partition DP's row kernel for 88 < L <= 128, run lane by lane on the CPU (its own source, with
+UndefinedBehaviorSanitizer) against the recursion over all splits: values, the lowest split among equal
+ones, every number of stages.  The LDS is filled with different bytes beforehand, so nothing may depend on
+what an earlier launch left there."""
+import os
+import subprocess
+
+import pytest
+
+from test_wave_makespan import build
+
+pytestmark = pytest.mark.skipif(__import__("shutil").which("g++") is None, reason="needs g++")
+
+KINDS = {"free": 0, "one zero layer": 1, "half zero layers": 2, "last layer outweighs": 3, "skewed": 4,
+         "falling transfers": 5, "random transfers": 6, "all zero": 7}
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    exe = build(tmp_path_factory.mktemp("rows"), "rows_driver")
+
+    def ask(cases):
+        env = dict(os.environ)
+        env.pop("LD_PRELOAD", None)  # the sanitizer's runtime must come first in the library list
+        res = subprocess.run([exe], input="".join(" ".join(str(x) for x in c) + "\n" for c in cases),
+                             stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=300, env=env)
+        assert res.returncode == 0 and "runtime error" not in res.stderr, res.stderr[-2000:]
+        out = [[int(x) for x in l.split()] for l in res.stdout.splitlines()]
+        assert len(out) == len(cases)
+        return out
+    return ask
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_rows_lane_by_lane(driver, kind):
+    sizes = [(89, 4, 2, 6), (89, 3, 3, 6), (90, 7, 1, 5), (97, 12, 11, 9), (100, 5, 5, 14), (111, 17, 16, 6),
+             (127, 8, 8, 12), (128, 8, 8, 12), (128, 33, 32, 4), (113, 40, 33, 4), (128, 64, 64, 3)]
+    cases = [(L, D, S, N, L + S, KINDS[kind], stages, fill) for L, D, S, N in sizes for stages in (0, 1) for fill in (0, 255, 85)]
+    out = driver(cases)
+    for case, got in zip(cases, out):
+        assert got[:3] == [0, 0, 0], case
+    # the same work whatever the LDS held
+    for i in range(0, len(out), 3):
+        assert out[i] == out[i + 1] == out[i + 2], cases[i]
+
+
+@pytest.mark.parametrize("L,D,S,N", [(97, 12, 11, 30), (128, 8, 8, 40), (128, 17, 16, 20)])
+def test_steps_do_not_depend_on_binding_links(driver, L, D, S, N):
+    # all trips of the searches are counted, those of repeated rounds too: links that bind at every cut
+    # may widen the windows, but never make a cell look at its splits one by one
+    free, falling, wild = (driver([(L, D, S, N, 5, k, 0, 0)])[0][3] for k in (0, 5, 6))
+    assert falling < 1.7 * free and wild < 1.7 * free, (free, falling, wild)

@@ -22,11 +22,16 @@
 #define __shared__
 #define __forceinline__ inline
 #define __launch_bounds__(...)
+#define __align__(n) alignas(n)
 
 struct dim3 {
     unsigned x, y, z;
     dim3(unsigned x_ = 1, unsigned y_ = 1, unsigned z_ = 1) : x(x_), y(y_), z(z_) {}
 };
+struct int2 { int x, y; };
+struct int4 { int x, y, z, w; };
+inline int2 make_int2(int x, int y) { return {x, y}; }
+inline int4 make_int4(int x, int y, int z, int w) { return {x, y, z, w}; }
 typedef void *hipStream_t;
 typedef int hipError_t;
 enum { hipSuccess = 0, hipErrorInvalidConfiguration = 9 };
@@ -34,7 +39,7 @@ enum { hipSuccess = 0, hipErrorInvalidConfiguration = 9 };
 inline dim3 threadIdx, blockIdx, blockDim, gridDim;
 
 namespace wave {
-enum op { NONE, BALLOT, SHFL_XOR, DPP, READLANE, WAVE_BARRIER, BLOCK_BARRIER };
+enum op { NONE, BALLOT, SHFL_XOR, SHFL_UP, DPP, READLANE, WAVE_BARRIER, BLOCK_BARRIER };
 struct lane {
     ucontext_t at;
     std::vector<char> stack;
@@ -94,6 +99,7 @@ inline void serve(int a, int b) {
         auto of = [&](int j) { return j >= 0 && a + j < b && !lanes[a + j].done; };
         if (o == BALLOT) l.out = (long long)vote;
         else if (o == SHFL_XOR) l.out = of((i - a) ^ l.arg) ? lanes[a + ((i - a) ^ l.arg)].v : l.v;
+        else if (o == SHFL_UP) l.out = i - a >= l.arg ? lanes[i - l.arg].v : l.v;
         else if (o == READLANE) l.out = lanes[a + l.arg].v;
         else if (o == DPP) {
             const int j = dpp_source(l.arg, i - a);
@@ -174,10 +180,13 @@ inline unsigned long long __builtin_amdgcn_ballot_w64(bool v) { return __ballot(
 inline int __shfl_xor(int v, int m) { return (int)wave::meet(wave::SHFL_XOR, v, m); }
 inline long long __shfl_xor(long long v, int m) { return wave::meet(wave::SHFL_XOR, v, m); }
 inline unsigned long long __shfl_xor(unsigned long long v, int m) { return (unsigned long long)wave::meet(wave::SHFL_XOR, (long long)v, m); }
+inline int __shfl_up(int v, int d) { return (int)wave::meet(wave::SHFL_UP, v, d); }
 inline int __builtin_amdgcn_update_dpp(int old, int v, int ctrl, int, int, bool) { return (int)wave::meet(wave::DPP, v, ctrl, old); }
+inline int __builtin_amdgcn_readfirstlane(int v) { return (int)wave::meet(wave::READLANE, v, 0); }
 inline int __builtin_amdgcn_readlane(int v, int i) { return (int)wave::meet(wave::READLANE, v, i); }
 inline void __builtin_amdgcn_wave_barrier() { wave::meet(wave::WAVE_BARRIER, 0); }
 #define __builtin_amdgcn_fence(...) ((void)0)
+#define __builtin_amdgcn_s_setprio(...) ((void)0)
 inline void __syncthreads() { wave::meet(wave::BLOCK_BARRIER, 1); }
 inline int __syncthreads_and(int v) { return (int)wave::meet(wave::BLOCK_BARRIER, v); }
 template <typename T, typename V> T atomicOr(T *p, V v) { T o = *p; *p |= (T)v; return o; }
