@@ -93,8 +93,8 @@ __global__ __launch_bounds__(256, 4) void k_dp_big(dp_big_args b) {
     row.L = L;
     row.K = K;
     row.kmask = kmask;
-    row.strict = row_is_strict(sPk, L, lane);
     row.lane = lane;
+    row_begin(row);
     int v_steps = row_first_steps(L, lane);  // lane n: steps of a search in row n
     unsigned short *arg = a.arg + (size_t)wave * b.arg_stride;
     unsigned long long pairs = 0, nrows = 0;

@@ -67,6 +67,15 @@ __device__ __forceinline__ bool row_is_strict(const int *PK, int L, int lane) {
     return __ballot(!rises) == 0;
 }
 
+// Once per wave, with everything above but W, g, out and n set: whether P rises strictly, and what row_build
+// does not write where the last chunk ends with the row (L a multiple of 64): nothing is right of split
+// L - 1, so nothing undercuts it.
+__device__ __forceinline__ void row_begin(dp_row &r) {
+    r.strict = row_is_strict(r.PK, r.L, r.lane);
+    if (r.lane == 0) r.h[r.L - 1] = (unsigned)(PP_INF32 & ~r.kmask) + (unsigned)(r.PK[r.L - 1] + (r.L - 1));
+    row_lds_sync();
+}
+
 // Steps of a search in row n for a start.  With balanced stages a cell of row n chooses among the
 // splits within P[l] / (n + 1) of it; a row that needs more gets a step more from then on.
 __device__ __forceinline__ int row_first_steps(int L, int n) {

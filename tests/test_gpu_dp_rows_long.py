@@ -45,3 +45,21 @@ def test_partition_rows_of_long_lists(ppo, kind, L, D, S, N):
         assert rc == 0
         np.testing.assert_array_equal(Cs[:, x - 1], C0)
         np.testing.assert_array_equal(bs[:, x * (x - 1) // 2:x * (x + 1) // 2], b0)
+
+
+@pytest.mark.parametrize("L", [128, 191, 192, 193, 256, 1024])
+def test_last_layer_that_outweighs_the_others(ppo, L):
+    # cell L rests on its last split: nothing stands right of it in the row
+    from paper_2204_10562_amd.problem import GpuProblem
+    w = workloads.random_small(8700 + L, L, 6, 5, 40, hi_time=300, hi_act=3000)
+    w.fwd[L - 1] = 2 * int((w.fwd + w.bwd).sum())
+    rc, PF, PB, XF, XB = ppo.prefix_costs(w.fwd, w.bwd, w.actf, w.actb, w.bw)
+    assert rc == 0
+    g = GpuProblem(w)
+    g.set_tables(PF, PB, XF, XB)
+    print("[case]", L, flush=True)
+    st, C, b = g.dp()
+    rc, C0, b0 = ppo.partition_dp(L, 6, 5, 40, PF, PB, XF, XB, w.orderings)
+    assert st == 0 and rc == 0
+    np.testing.assert_array_equal(C, C0)
+    np.testing.assert_array_equal(b, b0)

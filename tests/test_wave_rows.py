@@ -1,7 +1,7 @@
-"""The partition DP's row kernel for 88 < L <= 128, run lane by lane on the CPU (its own source, with
-UndefinedBehaviorSanitizer) against the recursion over all splits: values, the lowest split among equal
-ones, every number of stages.  The LDS is filled with different bytes beforehand, so nothing may depend on
-what an earlier launch left there."""
+"""The partition DP's kernels that search for a cell's split, run lane by lane on the CPU (their own sources,
+with UndefinedBehaviorSanitizer) against the recursion over all splits: values, the lowest split among
+equal ones, every number of stages.  The LDS is filled with different bytes beforehand: neither results nor
+any vote of a wave may depend on what an earlier launch left there."""
 import os
 import subprocess
 
@@ -34,12 +34,13 @@ def driver(tmp_path_factory):
 @pytest.mark.parametrize("kind", KINDS)
 def test_rows_lane_by_lane(driver, kind):
     sizes = [(89, 4, 2, 6), (89, 3, 3, 6), (90, 7, 1, 5), (97, 12, 11, 9), (100, 5, 5, 14), (111, 17, 16, 6),
-             (127, 8, 8, 12), (128, 8, 8, 12), (128, 33, 32, 4), (113, 40, 33, 4), (128, 64, 64, 3)]
+             (127, 8, 8, 12), (128, 8, 8, 12), (128, 33, 32, 4), (113, 40, 33, 4), (128, 64, 64, 3),
+             (129, 5, 5, 6), (192, 6, 5, 6), (200, 9, 8, 5), (256, 4, 4, 6), (321, 7, 7, 4)]
     cases = [(L, D, S, N, L + S, KINDS[kind], stages, fill) for L, D, S, N in sizes for stages in (0, 1) for fill in (0, 255, 85)]
     out = driver(cases)
     for case, got in zip(cases, out):
         assert got[:3] == [0, 0, 0], case
-    # the same work whatever the LDS held
+    # the same way there whatever the LDS held
     for i in range(0, len(out), 3):
         assert out[i] == out[i + 1] == out[i + 2], cases[i]
 

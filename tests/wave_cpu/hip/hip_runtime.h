@@ -29,6 +29,8 @@ struct dim3 {
     dim3(unsigned x_ = 1, unsigned y_ = 1, unsigned z_ = 1) : x(x_), y(y_), z(z_) {}
 };
 struct int2 { int x, y; };
+struct uint2 { unsigned x, y; };
+inline uint2 make_uint2(unsigned x, unsigned y) { return {x, y}; }
 struct int4 { int x, y, z, w; };
 inline int2 make_int2(int x, int y) { return {x, y}; }
 inline int4 make_int4(int x, int y, int z, int w) { return {x, y, z, w}; }
@@ -52,6 +54,7 @@ inline std::vector<lane> lanes;
 inline ucontext_t scheduler;
 inline int me;
 inline const std::function<void()> *body;
+inline unsigned long long votes = 1;  // changes with every vote's outcome
 
 inline long long meet(op o, long long v, int arg = 0, long long old = 0) {
     lane &l = lanes[me];
@@ -93,6 +96,10 @@ inline void serve(int a, int b) {
             if (lanes[i].waits != o) { fprintf(stderr, "the lanes of a wave meet different operations\n"); abort(); }
             if (lanes[i].v) vote |= 1ull << (i - a);
         }
+    if (o == BALLOT) {
+        votes = (votes ^ vote) * 0x9e3779b97f4a7c15ull;
+        votes ^= votes >> 32;
+    }
     for (int i = a; i < b; ++i) {
         lane &l = lanes[i];
         if (l.done) continue;
@@ -189,5 +196,7 @@ inline void __builtin_amdgcn_wave_barrier() { wave::meet(wave::WAVE_BARRIER, 0);
 #define __builtin_amdgcn_s_setprio(...) ((void)0)
 inline void __syncthreads() { wave::meet(wave::BLOCK_BARRIER, 1); }
 inline int __syncthreads_and(int v) { return (int)wave::meet(wave::BLOCK_BARRIER, v); }
+#define __HIP_MEMORY_SCOPE_AGENT 0
+#define __hip_atomic_load(p, order, scope) (*(p))
 template <typename T, typename V> T atomicOr(T *p, V v) { T o = *p; *p |= (T)v; return o; }
 template <typename T, typename V> T atomicAdd(T *p, V v) { T o = *p; *p += (T)v; return o; }

@@ -1,10 +1,12 @@
-// Runs the partition DP's kernel for 88 < L <= 128 (its own source) on the CPU.  Reads cases from stdin,
-// one per line:
+// Runs the partition DP's kernels that search for a cell's split (their own sources) on the CPU: the row
+// kernel for L <= 128, the one for longer rows beyond.  Reads cases from stdin, one per line:
 //   L D S N SEED KIND STAGES FILL
 // KIND: what the layer and transfer times look like (see problem below); STAGES: plans of every number
 // of stages; FILL: the byte the LDS is filled with before the launch.  Prints, per case, the return value,
-// the status, how many results differ from the recursion over all splits, and the steps the kernel counted.
+// the status, how many results differ from the recursion over all splits, the steps the kernel counted, and
+// a number that depends on all votes its waves took.
 #include "../../paper_2204_10562_amd/csrc/pp_dp_rows.hip"
+#include "../../paper_2204_10562_amd/csrc/pp_dp_big.hip"
 
 #include <string.h>
 
@@ -68,16 +70,29 @@ int main() {
         std::vector<ll> C((size_t)N * nc, -7);
         std::vector<int> bounds((size_t)N * tri, -7);
         int status = 0;
-        dp_rows_args t = {};
-        t.L = t.g.L = L; t.D = t.g.D = D; t.S = t.g.S = S; t.K = t.g.K = pp_index_bits(L); t.N = t.g.N = N;
-        t.validate = 1;
-        t.g.fit_limit = (1ull << (31 - t.K)) - 1;
-        t.g.hdr = &hdr; t.g.p32 = p32.data(); t.g.x32 = x32.data(); t.g.ord = ord.data();
-        t.g.stages = stages; t.g.C_out = C.data(); t.g.bounds_out = bounds.data(); t.g.status = &status;
-        const dpr_shape sh = pp_dp_rows_shape(L, D, S, stages);
-        t.chunk = (N + 2) / 3;                                     // three waves share the list
+        dp_args a = {};
+        a.L = L; a.D = D; a.S = S; a.K = pp_index_bits(L); a.N = N;
+        a.validate = 1;
+        a.fit_limit = (1ull << (31 - a.K)) - 1;
+        a.hdr = &hdr; a.p32 = p32.data(); a.x32 = x32.data(); a.ord = ord.data();
+        a.stages = stages; a.C_out = C.data(); a.bounds_out = bounds.data(); a.status = &status;
+        a.nblocks = 3;
+        std::vector<unsigned short> arg((size_t)3 * S * (L + 128));
+        a.arg = arg.data();
         memset(smem, fill, sizeof smem);
-        const int rc = pp_launch_dp_rows(t, (3 + sh.wpb - 1) / sh.wpb, sh, NULL);
+        wave::votes = 1;
+        int rc;
+        if (L > PP_TILE_MAX_L) {
+            rc = pp_launch_dp_big(a, 3, 256, NULL, NULL);          // three waves share the list
+        } else {
+            dp_rows_args t = {};
+            t.L = L; t.D = D; t.S = S; t.K = a.K; t.N = N;
+            t.validate = 1;
+            t.chunk = (N + 2) / 3;
+            t.g = a;
+            const dpr_shape sh = pp_dp_rows_shape(L, D, S, stages);
+            rc = pp_launch_dp_rows(t, (3 + sh.wpb - 1) / sh.wpb, sh, NULL);
+        }
         int differ = 0;
         for (int c = 0; c < N; ++c) {
             std::vector<std::vector<ll>> W(S, std::vector<ll>(L + 1));
@@ -103,7 +118,7 @@ int main() {
         }
         ll pairs = 0;
         for (auto &r : hdr.work) pairs += (ll)r.pairs;
-        printf("%d %d %d %lld\n", rc, status, differ, pairs);
+        printf("%d %d %d %lld %llu\n", rc, status, differ, pairs, wave::votes);
         fflush(stdout);
     }
     return 0;
