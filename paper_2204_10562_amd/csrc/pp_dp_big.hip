@@ -254,7 +254,7 @@ __global__ __launch_bounds__(256, 4) void k_dp_big(dp_big_args b) {
                 row.n = n;
                 row.steps = __builtin_amdgcn_readlane(v_steps, n);
                 row.carry = PP_INF32;
-                row.again = false;
+                row.again = 0;
                 for (int c0 = c_last; c0 >= 0; c0 -= 256) {
                     const int left = (Lp - c0) >> 6;
                     if (left >= 4) big_build<4>(row, c0, xv, arow);
@@ -275,7 +275,7 @@ __global__ __launch_bounds__(256, 4) void k_dp_big(dp_big_args b) {
                     else if (left == 2) { int w[2]; row_search<2>(row, c0, w); }
                     else { int w[1]; row_search<1>(row, c0, w); }
                 }
-                pairs += (unsigned long long)(L - n) * (unsigned)(row.steps + 1);
+                pairs += (unsigned long long)(L - n) * (unsigned)(row.steps + 1) + (unsigned)(64 * row.again * row.steps);
                 if (row.again && lane == n && v_steps < K) ++v_steps;
                 row_lds_sync();
                 int *t = cur; cur = nxt; nxt = t;

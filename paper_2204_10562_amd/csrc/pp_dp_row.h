@@ -56,7 +56,7 @@ struct dp_row {
     bool strict;
     int lane;
     int carry;   // min g over the splits to the right of what row_build has done
-    bool again;  // a search needed a second round
+    int again;   // rounds of `steps` steps the searches took beyond the first, over all chunks of 64 cells
 };
 
 // Whether P rises strictly (PK as above); once per wave: the preparation kernel, which could leave it in
@@ -136,7 +136,8 @@ __device__ __forceinline__ void row_build(dp_row &r, int c0, const int *xv, int 
     }
 }
 
-// The cell whose crossing lies on a peak, or any cell of a model with zero-length layers.
+// The cell whose crossing lies on a peak or, where layers have length zero, on a split that shares its P
+// with the one before.
 __device__ __forceinline__ int row_on_peak(const dp_row &r, int j, int l, unsigned Pl) {
     const unsigned t = ~(unsigned)r.kmask, Pj = (unsigned)(r.PK[j] + j);
     const unsigned d = Pl - Pj, gj = (unsigned)r.g[j] & t, nx = r.h[j] - Pj;
@@ -221,25 +222,30 @@ __device__ __forceinline__ void row_search(dp_row &r, int c0, int (&w)[U]) {
 #pragma unroll
         for (int u = 0; u < U; ++u) more |= pos[u] > low && pos[u] == from[u] - reach;
         if (!__ballot(more)) break;
-        r.again = true;
+        r.again += U;
     }
     const int to_g = row_addr(r.g) - h0, to_pk = row_addr(r.PK) - h0;
     unsigned gv[U], pv[U], hv[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) { gv[u] = row_at(pos[u] + to_g); pv[u] = row_at(pos[u] + to_pk); hv[u] = row_at(pos[u]); }
-    bool odd = !r.strict;
+    bool odd = false, peak[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         w[u] = row_imax((int)gv[u], (int)(Pl[u] - pv[u]));
-        // g[j] > H(j+1), the key's low bits being j on both sides
-        odd |= gv[u] + pv[u] > hv[u] && (u || c0 + r.lane >= r.n);
+        peak[u] = gv[u] + pv[u] > hv[u];  // g[j] > H(j+1), the key's low bits being j on both sides
     }
+    if (!r.strict) {
+        // splits left of j tie only where they have its P
+#pragma unroll
+        for (int u = 0; u < U; ++u) peak[u] |= row_at(pos[u] + to_pk - 4) == pv[u] + 1;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) odd |= peak[u] && (u || c0 + r.lane >= r.n);
     if (__ballot(odd)) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int l = c0 + 64 * u + r.lane + 1;
-            const bool on_peak = !r.strict || gv[u] + pv[u] > hv[u];
-            if (on_peak && l > r.n && l <= r.L) w[u] = row_on_peak(r, (pos[u] - h0) >> 2, l, Pl[u]);
+            if (peak[u] && l > r.n && l <= r.L) w[u] = row_on_peak(r, (pos[u] - h0) >> 2, l, Pl[u]);
         }
     }
     w[0] = c0 + r.lane >= r.n ? w[0] : PP_INF32;
