@@ -5,7 +5,9 @@
 // 61 % at L = 1024, where the LDS holds three waves per SIMD; four chunks side by side give each
 // wave four reads in flight).  About 36 K vector instructions per candidate at L = 1024, S = 32,
 // against 125 K when every (cell, split) pair up to an exact early exit was evaluated: 2^20
-// candidates 275 -> 96 ms; L = 300, S = 16, 15 751 representatives 297 -> 210 us.  (One lane per row
+// candidates 275 -> 96 ms; L = 300, S = 16, 15 751 representatives 297 -> 210 us.  Where links bind at
+// every cut (1.25 GB/s, activations that shrink; DP alone): L = 1024, S = 16 522 -> 280 us for 500
+// candidates, L = 300, S = 16 176 -> 143 us for 2 777.  (One lane per row
 // and one step per cell with a monotone queue was measured too: 345 ms at L = 1024, a serial chain of
 // LDS trips per cell.)
 //
@@ -21,6 +23,13 @@
 #include "pp_dp_generic.h"
 #include "pp_dp_row.h"
 
+// Rows in which more than one split in ROW_FALLS is undercut by a later one are searched with minima that end
+// at the cell (row_jump).  DP alone against a kernel that evaluates all (cell, split) pairs up to an early
+// exit, thresholds of no row / L/4 / L/16 / L/64 / every row with one: links that bind everywhere (1.25 GB/s,
+// activations that shrink) L = 300, S = 16 0.54x / 0.53x / 1.23x / 1.22x / 1.23x; channel times of about a
+// stage's, in no order, L = 192, S = 64 0.81x / 0.98x / 1.13x / 1.23x / 1.23x, L = 1024, S = 16 1.88x / 1.88x /
+// 2.02x / 1.88x / 1.75x; times that seldom bind, L = 1024, S = 32 2.18x / 2.17x / 2.17x / 2.16x / 1.83x.
+#define ROW_FALLS 32
 struct dp_big_args {
     int NC;      // chunks of 64 cells: ceil(L / 64)
     int waves;   // working waves (each owns one backtrack table)
@@ -255,6 +264,7 @@ __global__ __launch_bounds__(256, 4) void k_dp_big(dp_big_args b) {
                 row.steps = __builtin_amdgcn_readlane(v_steps, n);
                 row.carry = PP_INF32;
                 row.again = 0;
+                row.falls = 0;
                 for (int c0 = c_last; c0 >= 0; c0 -= 256) {
                     const int left = (Lp - c0) >> 6;
                     if (left >= 4) big_build<4>(row, c0, xv, arow);
@@ -268,14 +278,27 @@ __global__ __launch_bounds__(256, 4) void k_dp_big(dp_big_args b) {
                     for (int u = 0; u < 4; ++u) xv[u] = xn[u];
                 }
                 row_lds_sync();
-                for (int c0 = 0; c0 < Lp; c0 += 256) {
-                    const int left = (Lp - c0) >> 6;
-                    if (left >= 4) { int w[4]; row_search<4>(row, c0, w); }
-                    else if (left == 3) { int w[3]; row_search<3>(row, c0, w); }
-                    else if (left == 2) { int w[2]; row_search<2>(row, c0, w); }
-                    else { int w[1]; row_search<1>(row, c0, w); }
+                if (row.falls * ROW_FALLS > L) {
+                    row_tables(row);
+                    int trips = 0;  // of 64 cells
+                    for (int c0 = c_last; c0 >= 0; c0 -= 256) {
+                        const int left = (Lp - c0) >> 6;
+                        if (left >= 4) trips += 4 * row_jump<4>(row, c0);
+                        else if (left == 3) trips += 3 * row_jump<3>(row, c0);
+                        else if (left == 2) trips += 2 * row_jump<2>(row, c0);
+                        else trips += row_jump<1>(row, c0);
+                    }
+                    pairs += (unsigned long long)(64 * trips);
+                } else {
+                    for (int c0 = 0; c0 < Lp; c0 += 256) {
+                        const int left = (Lp - c0) >> 6;
+                        if (left >= 4) { int w[4]; row_search<4>(row, c0, w); }
+                        else if (left == 3) { int w[3]; row_search<3>(row, c0, w); }
+                        else if (left == 2) { int w[2]; row_search<2>(row, c0, w); }
+                        else { int w[1]; row_search<1>(row, c0, w); }
+                    }
+                    pairs += (unsigned long long)(L - n) * (unsigned)(row.steps + 1) + (unsigned)(64 * row.again * row.steps);
                 }
-                pairs += (unsigned long long)(L - n) * (unsigned)(row.steps + 1) + (unsigned)(64 * row.again * row.steps);
                 if (row.again && lane == n && v_steps < K) ++v_steps;
                 row_lds_sync();
                 int *t = cur; cur = nxt; nxt = t;

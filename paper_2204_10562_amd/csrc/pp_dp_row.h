@@ -17,12 +17,12 @@
 // (row_build, right to left) leaves h[j] = H(j+1) + P[j] for all cells, and the search is for the
 // first j >= n with h[j] >= P[l] (or j = l-1): one LDS read per step.  What it finds is exact
 // whenever g[j] <= H(j+1), i.e. nothing later undercuts split j: then G(j) = g[j] = H(j), and W =
-// max(g[j], P[l] - P[j]).  That is almost always so (W[n-1] rises, and few links are slow enough to
-// put peaks into g).  Otherwise (the crossing is on a peak) a split after j and before l that
+// max(g[j], P[l] - P[j]).  That is almost always so where links are fast (W[n-1] rises, and few
+// transfers put peaks into g).  Otherwise (the crossing is on a peak) a split after j and before l that
 // attains H(j+1) proves G(j) = H(j) too, and it is the answer; failing that the undercutting split
 // is not the cell's yet, and the cell looks at its splits one by one from l-1 leftwards until the
-// difference term alone exceeds the best value.  On the workloads' rows 0..4 % of the cells get
-// there, for 4..10 splits each.
+// difference term alone exceeds the best value: 0..4 % of the cells with links from 10 GB/s, for 4..10
+// splits each.  Rows with many such splits (row_build counts them) are searched by row_jump instead.
 //
 // Zero-length layers (strict == 0): P is equal at neighbouring cuts, and a split left of j with the
 // same P can tie; the lowest split of the run of equal P whose g does not exceed the value is kept.
@@ -56,6 +56,7 @@ struct dp_row {
     bool strict;
     int lane;
     int carry;   // min g over the splits to the right of what row_build has done
+    int falls;   // splits whose g a later one undercuts, as far as row_build has looked
     int again;   // rounds of `steps` steps the searches took beyond the first, over all chunks of 64 cells
 };
 
@@ -125,7 +126,9 @@ __device__ __forceinline__ void row_build(dp_row &r, int c0, const int *xv, int 
     for (int u = U - 1; u >= 0; --u) {
         int m = g[u];
         const int next = __builtin_amdgcn_update_dpp(r.carry, g[u], DPP_WAVE_SHL1, 0xf, 0xf, false);
-        if (__ballot(next < m)) m = row_suffix_min(m, r.carry, r.lane);
+        const unsigned long long falls = __ballot(next < m);
+        r.falls += __builtin_popcountll(falls);
+        if (falls) m = row_suffix_min(m, r.carry, r.lane);
         r.carry = __builtin_amdgcn_readlane(m, 0);
         g[u] = m;
     }
@@ -251,4 +254,79 @@ __device__ __forceinline__ void row_search(dp_row &r, int c0, int (&w)[U]) {
     w[0] = c0 + r.lane >= r.n ? w[0] : PP_INF32;
 #pragma unroll
     for (int u = 0; u < U; ++u) r.out[c0 + 64 * u + r.lane + 1] = w[u];
+}
+
+// Rows in which g falls often (links that bind): what undercuts a split lies beyond the cell then, and the
+// search above would send most cells to row_on_peak.  The same crossing with minima that end at the cell:
+// back from split l - 1 by 16, 4 and 1 while the split in front costs no more than the least g in between
+// (pp_dp_rows.hip has the reasoning; keys for times).  T16[j] = min g[j+1 .. j+16] in the place of h and
+// T4[j] = min g[j+1 .. j+4] in the row being produced, both 0 for j < n; the row's cells are therefore
+// worked out from the right, where they overwrite what no cell left of them needs.
+__device__ __forceinline__ void row_tables(const dp_row &r) {
+    row_lds_sync();
+    for (int j = r.lane; j < r.L; j += 64) {
+        const int a = r.g[j + 1], b = r.g[j + 2], c = r.g[j + 3], d = r.g[j + 4];
+        r.out[j] = j < r.n ? 0 : row_imin(row_imin(a, b), row_imin(c, d));
+    }
+    row_lds_sync();
+    for (int j = r.lane; j < r.L; j += 64) {
+        const int a = r.out[j], b = r.out[j + 4], c = r.out[j + 8], d = r.out[j + 12];
+        r.h[j] = (unsigned)row_imin(row_imin(a, b), row_imin(c, d));
+    }
+    row_lds_sync();
+}
+
+// Cells c0 + 1 .. c0 + 64 U; returns the trips to LDS it took.
+template <int U>
+__device__ __forceinline__ int row_jump(const dp_row &r, int c0) {
+    int pos[U];
+    unsigned low[U], Pl[U];
+    const int p0 = row_addr(r.PK), to_16 = row_addr(r.h) - p0, to_4 = row_addr(r.out) - p0, to_g = row_addr(r.g) - p0;
+    const int first = p0 + 4 * r.n;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int k = c0 + 64 * u + r.lane;
+        Pl[u] = (unsigned)(r.PK[k + 1] + (k + 1));
+        pos[u] = p0 + 4 * row_imin(k, r.L - 1);
+        low[u] = PP_INF32;
+    }
+    // (split 0 stands for all in front of it: its minima are 0)
+    auto step = [&](int by, int to, bool check) {
+        int j[U];
+        unsigned p[U], q[U];
+        bool any = false;
+#pragma unroll
+        for (int u = 0; u < U; ++u) { j[u] = row_imax(pos[u] - by, p0); p[u] = row_at(j[u]); q[u] = row_at(j[u] + to); }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const unsigned m = q[u] < low[u] ? q[u] : low[u];
+            const bool back = Pl[u] - p[u] < m && (!check || j[u] >= first);
+            pos[u] = back ? j[u] : pos[u];
+            low[u] = back ? m : low[u];
+            any |= back;
+        }
+        return any;
+    };
+    int trips = 7;
+    while (__ballot(step(64, to_16, false))) ++trips;
+    for (int i = 0; i < 3; ++i) step(16, to_4, false);
+    for (int i = 0; i < 3; ++i) step(4, to_g + 4, true);
+    int w[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) w[u] = row_imin((int)low[u], row_imax((int)row_at(pos[u] + to_g), (int)(Pl[u] - row_at(pos[u]))));
+    if (!r.strict) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = (pos[u] - p0) >> 2;
+            int a = j;
+            while (a > r.n && r.PK[a - 1] + (a - 1) == r.PK[j] + j) --a;
+            while (a < j && (r.g[a] | r.kmask) > (w[u] | r.kmask)) ++a;
+            w[u] = a < j ? (w[u] & ~r.kmask) | a : w[u];
+        }
+    }
+    row_lds_sync();
+    w[0] = c0 + r.lane >= r.n ? w[0] : PP_INF32;
+#pragma unroll
+    for (int u = 0; u < U; ++u) r.out[c0 + 64 * u + r.lane + 1] = w[u];
+    return trips;
 }

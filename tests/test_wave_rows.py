@@ -12,7 +12,8 @@ from test_wave_makespan import build
 pytestmark = pytest.mark.skipif(__import__("shutil").which("g++") is None, reason="needs g++")
 
 KINDS = {"free": 0, "one zero layer": 1, "half zero layers": 2, "last layer outweighs": 3, "skewed": 4,
-         "falling transfers": 5, "random transfers": 6, "all zero": 7}
+         "falling transfers": 5, "random transfers": 6, "all zero": 7,
+         "few slow cuts": 8, "few slow cuts, half zero layers": 9}
 
 
 @pytest.fixture(scope="module")
@@ -45,9 +46,11 @@ def test_rows_lane_by_lane(driver, kind):
         assert out[i] == out[i + 1] == out[i + 2], cases[i]
 
 
-@pytest.mark.parametrize("L,D,S,N", [(97, 12, 11, 30), (128, 8, 8, 40), (128, 17, 16, 20)])
+@pytest.mark.parametrize("L,D,S,N", [(97, 12, 11, 30), (128, 8, 8, 40), (128, 17, 16, 20), (300, 9, 8, 12), (192, 17, 16, 12)])
 def test_steps_do_not_depend_on_binding_links(driver, L, D, S, N):
     # all trips of the searches are counted, those of repeated rounds too: links that bind at every cut
-    # may widen the windows, but never make a cell look at its splits one by one
+    # may widen the windows (and longer rows take shorter steps then), but never make a cell look at its
+    # splits one by one
     free, falling, wild = (driver([(L, D, S, N, 5, k, 0, 0)])[0][3] for k in (0, 5, 6))
-    assert falling < 1.7 * free and wild < 1.7 * free, (free, falling, wild)
+    most = 1.7 if L <= 128 else 3.5
+    assert falling < most * free and wild < most * free, (free, falling, wild)

@@ -27,7 +27,7 @@ int main() {
         for (int l = 0; l < L; ++l) {
             ll t = 50 + upto(950);
             if (kind == 1 && l == L / 3) t = 0;                    // one layer of length zero
-            if (kind == 2 && upto(1)) t = 0;                       // half of them
+            if ((kind == 2 || kind == 9) && upto(1)) t = 0;        // half of them
             if (kind == 3 && l == L - 1) t = 2 * P[l];             // the last layer outweighs the others
             if (kind == 4) t = l < 3 * L / 4 ? 1 : 400;            // most layers in little time
             if (kind == 7) t = 0;
@@ -35,12 +35,13 @@ int main() {
         }
         const ll top = P[L] / S + 1;
         for (int i = 0; i < D * D; ++i) {
-            const ll slow = kind >= 5 ? 1 + upto(8) : 1;
+            const ll slow = kind == 5 || kind == 6 ? 1 + upto(8) : 1;
             for (int k = 0; k < L; ++k) {
                 ll x = upto(top / 8 + 1);
                 if (kind == 5) x = slow * top * (L - k) / L;       // every cut cheaper than the one before
                 if (kind == 6) x = upto(slow * top);               // links bind everywhere, in no order
                 if (kind <= 2 && k % 5 == 0) x = 3 * top;          // a few cuts that cost more than a stage
+                if (kind >= 8) x = k % 47 == 5 ? 3 * top : 1;          // one cut in 47 of those
                 X[(size_t)i * L + k] = (int)x;                     // [k]: the cut between layers k - 1 and k
             }
         }
