@@ -11,6 +11,10 @@
 #define PP_INF32 0x7fffffff
 #define PP_CAP62 ((long long)1 << 62)
 
+// DPP controls that cross the rows of 16 lanes (update_dpp).
+#define DPP_WAVE_SHL1 0x130  // lane i takes lane i + 1's value
+#define DPP_WAVE_SHR1 0x138  // lane i takes lane i - 1's value
+
 __host__ __device__ static inline size_t pp_align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Number of key bits that hold a split index 0..L-1.

@@ -2,10 +2,10 @@
 // pp_dp_row.h, up to four chunks of 64 cells side by side.
 //
 // What bounds it: the latency of the searches' LDS reads, then instruction issue (vector unit busy
-// 61 % at L = 1024, where the LDS holds three waves per SIMD; four chunks side by side give each
-// wave four reads in flight).  About 36 K vector instructions per candidate at L = 1024, S = 32,
+// 63 % at L = 1024, where the LDS holds three waves per SIMD; four chunks side by side give each
+// wave four reads in flight).  About 37 K vector instructions per candidate at L = 1024, S = 32,
 // against 125 K when every (cell, split) pair up to an exact early exit was evaluated: 2^20
-// candidates 275 -> 96 ms; L = 300, S = 16, 15 751 representatives 297 -> 210 us.  Where links bind at
+// candidates 275 -> 98 ms; L = 300, S = 16, 15 751 representatives 297 -> 203 us.  Where links bind at
 // every cut (1.25 GB/s, activations that shrink; DP alone): L = 1024, S = 16 522 -> 280 us for 500
 // candidates, L = 300, S = 16 176 -> 143 us for 2 777.  (One lane per row
 // and one step per cell with a monotone queue was measured too: 345 ms at L = 1024, a serial chain of
@@ -29,7 +29,7 @@
 // activations that shrink) L = 300, S = 16 0.54x / 0.53x / 1.23x / 1.22x / 1.23x; channel times of about a
 // stage's, in no order, L = 192, S = 64 0.81x / 0.98x / 1.13x / 1.23x / 1.23x, L = 1024, S = 16 1.88x / 1.88x /
 // 2.02x / 1.88x / 1.75x; times that seldom bind, L = 1024, S = 32 2.18x / 2.17x / 2.17x / 2.16x / 1.83x.
-#define ROW_FALLS 32
+#define ROW_FALLS 16
 struct dp_big_args {
     int NC;      // chunks of 64 cells: ceil(L / 64)
     int waves;   // working waves (each owns one backtrack table)

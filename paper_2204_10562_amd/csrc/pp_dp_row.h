@@ -30,7 +30,6 @@
 
 #include "pp_common.h"
 
-#define DPP_WAVE_SHL1 0x130  // lane i takes lane i + 1's value
 #define DPP_ROW_SHL(n) (0x100 + (n))
 
 __device__ __forceinline__ int row_imin(int a, int b) { return a < b ? a : b; }

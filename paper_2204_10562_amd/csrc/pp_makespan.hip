@@ -557,8 +557,6 @@ __global__ __launch_bounds__(64) void k_makespan_lds(mk_args a) {
             fin[(size_t)(j - 1) * W] = max(idle, ready) + dur[(size_t)(j - 1) * W];
         }
     }
-    // with fewer than 64 lanes the arg-min would need another reduction; the host only asks
-    // for it when W == 64
     emit(a, q, c, live, fq, fin[(size_t)(J - 1) * W], blockIdx.x, gridDim.x, a.t_off);
   }
 }
@@ -656,8 +654,8 @@ static int lds_lanes(int S) {
     return W;
 }
 
-// Register kernel for a.S <= 16, LDS kernel beyond.  With a.part set the LDS kernel must run
-// full waves (lds_lanes(a.S) == 64).
+// Register kernel for a.S <= 16, resources over lanes or LDS columns beyond (a.part is not set there:
+// pp_launch_makespan takes the minimum in a pass of its own).
 static int launch_makespan(const mk_args &a, hipStream_t st) {
     if (a.S <= 8) return launch_regs<0>(a, st);
     switch (a.S) {

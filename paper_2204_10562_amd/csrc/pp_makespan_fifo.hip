@@ -22,8 +22,6 @@
 // 1.52 ms.
 #include "pp_makespan.h"
 
-#define DPP_WAVE_SHL1 0x130  // lane i takes lane i + 1's value
-#define DPP_WAVE_SHR1 0x138  // lane i takes lane i - 1's value
 #define FIFO_THREADS 256
 
 // LG = a.lanes_per lanes per candidate (a power of two, at least R), lane r - 1 is resource r.

@@ -34,8 +34,6 @@
 // order 131 -> 34 us, transfers added to the stages 137 -> 22 us (64-bit in LDS before).
 #include "pp_makespan.h"
 
-#define DPP_WAVE_SHL1 0x130  // lane i takes lane i + 1's value
-#define DPP_WAVE_SHR1 0x138  // lane i takes lane i - 1's value
 #define SPLIT_NEG (-(1 << 30))
 
 __device__ __forceinline__ int smax(int a, int b) { return a > b ? a : b; }

@@ -7,8 +7,6 @@
 //                               many candidates they have lanes for
 // and prints one line per case.
 #include "../../paper_2204_10562_amd/csrc/pp_makespan_split.hip"
-#undef DPP_WAVE_SHL1
-#undef DPP_WAVE_SHR1
 #include "../../paper_2204_10562_amd/csrc/pp_makespan_fifo.hip"
 
 #include <string.h>
