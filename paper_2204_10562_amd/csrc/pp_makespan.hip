@@ -1062,8 +1062,8 @@ int pp_launch_makespan_variant(int variant, int L, int D, int S, int64_t N, int 
     // The faster kernels pay where a schedule is long enough for a second launch, and where there is a
     // pipeline.  All four schedules of 10 plans, the general kernel alone / both, us: S = 1 40 / 49 (M = 4 and
     // 32) and 10^6 plans 1018 / 1457 (M = 256); S = 2, M = 4 40 / 51; S = 3, M = 4 80 / 51; S = 2, M = 32 215 / 81.
-    // (A list that mixes in plans the readiness order leaves to the general kernel - items of zero length -
-    // pays for both: S = 8, M = 32 4.80 -> 4.93 ms for 20 000 plans, S = 2 223 -> 250 us.)
+    // (Lists with plans the readiness order leaves to the general kernel - items of zero length - S = 2, M = 32,
+    // 20 000 plans 223 / 197; S = 3, M = 4 84 / 92.)
     a.by_block = (variant != PP_SCHED_FIFO || S <= 32) && S > 1 && (long long)(4 * S - 3) * M > 24;
     if (a.by_block) {
         const int rc = variant == PP_SCHED_FIFO ? pp_launch_makespan_fifo(a, st) : pp_launch_makespan_split(a, st);

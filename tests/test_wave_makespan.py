@@ -77,3 +77,12 @@ def test_taken_where_the_times_fit(driver):
     fits = (2**30 - 1) // (100 + 4 + 64) // 12
     out, _ = driver(["taken %d 1 100 %d" % (PE, fits), "taken %d 1 100 %d" % (PE, fits + 1)])
     assert out == [[0, 64], [0, 0]]
+
+
+@pytest.mark.parametrize("S", [2, 3, 5, 9])
+def test_readiness_order_leaves_whole_workgroups(driver, S):
+    # a plan with an item of zero length goes to the general kernel, which simulates its neighbours too
+    out, _ = driver(["mixed %d %d 6 %d %d" % (FIFO, S, S + hi, hi) for hi in (20, 300, 5000)])
+    for rc, status, left, differ, parts in out:
+        assert (rc, status, differ, parts) == (0, 0, 0, 0)
+    assert 0 < out[0][2] and out[2][2] < 300

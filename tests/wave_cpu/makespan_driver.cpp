@@ -2,6 +2,8 @@
 // Reads cases from stdin, one per line:
 //   run VARIANT S M SEED HI     40 random plans of S stages with times up to HI under the schedule
 //                               VARIANT, against Alg. 1's rules written out in 64 bits
+//   mixed VARIANT S M SEED HI   the same with 300 plans of times from 0 up: how many were left, how many of
+//                               the others differ, and workgroups of the readiness order left in part
 //   taken VARIANT S M TIME      how many of 64 plans whose times are all TIME the 30-bit kernel takes
 //   launch VARIANT S N          the launches for N candidates (nothing runs): the return value, and how
 //                               many candidates they have lanes for
@@ -150,6 +152,19 @@ int main() {
             int differ = 0;
             for (int c = 0; c < p.N; ++c) differ += p.T[c] != p.want(c, (int)M);
             printf("%d %d %d\n", rc, p.status, differ);
+        } else if (!strcmp(what, "mixed")) {
+            int seed;
+            if (scanf("%d %lld", &seed, &x) != 2) return 2;
+            problem p(variant, S, 300, (int)M, seed, 0, x);
+            const int rc = p.launch();
+            int left = 0, differ = 0, parts = 0, each = 1;
+            while (each < 2 * S - 1) each <<= 1;
+            for (int c = 0; c < p.N; ++c) {
+                left += p.T[c] == MK_NOT_TAKEN;
+                differ += p.T[c] != MK_NOT_TAKEN && p.T[c] != p.want(c, (int)M);
+                parts += c % (FIFO_THREADS / each) && (p.T[c] == MK_NOT_TAKEN) != (p.T[c - 1] == MK_NOT_TAKEN);
+            }
+            printf("%d %d %d %d %d\n", rc, p.status, left, differ, parts);
         } else if (!strcmp(what, "taken")) {
             if (scanf("%lld", &x) != 1) return 2;
             problem p(variant, S, 64, (int)M, 1, x, x);
