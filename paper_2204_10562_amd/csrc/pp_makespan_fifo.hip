@@ -32,7 +32,7 @@ __global__ __launch_bounds__(FIFO_THREADS) void k_makespan_fifo(mk_args a) {
     const int tid = threadIdx.x, lane = tid & 63, per = FIFO_THREADS / LG;  // candidates per workgroup
     int Q = 1;
     while (Q < J) Q <<= 1;
-    int *so = lds, *sb = so + per * SP, *sf = sb + per * SP, *rings = sf + per;
+    int *so = lds, *sb = so + per * SP, *sf = sb + per * SP, *left = sf + per, *rings = left + 1;
     const long long c0 = a.first + (long long)blockIdx.x * per;
     for (int t = tid; t < per * S; t += FIFO_THREADS) {
         const int i = t / S, n = t - i * S;
@@ -45,6 +45,7 @@ __global__ __launch_bounds__(FIFO_THREADS) void k_makespan_fifo(mk_args a) {
         so[i * SP + n] = o;
         sb[i * SP + n] = e;
     }
+    if (tid == 0) *left = 0;
     __syncthreads();
     if (tid < per) sf[tid] = c0 + tid < a.N ? mk_check_rows(a, c0 + tid, so + tid * SP, sb + tid * SP) : 0;
     __syncthreads();
@@ -86,7 +87,9 @@ __global__ __launch_bounds__(FIFO_THREADS) void k_makespan_fifo(mk_args a) {
     // (the workgroup's candidates are taken or left together: k_makespan_variant simulates whole waves
     // of neighbours wherever one of them is left.  All four schedules, a seventh of the cuts with nothing to
     // send, 10^6 plans of 2 stages, M = 32: 1.95 ms plan by plan, 1.15 together, 1.19 in that kernel alone)
-    const bool taken = __syncthreads_and(!live || fault || (!odd && sum <= (long long)MK_SPLIT_CAP / M));
+    if (live && !fault && (odd || sum > (long long)MK_SPLIT_CAP / M)) *left = 1;
+    __syncthreads();
+    const bool taken = *left == 0;
     bool running = live && !fault && taken;
     int *ring = rings + i * Q;  // when a microbatch left its last block (a microbatch is in one place)
     const int Qm = Q - 1, jb = 2 * R - r;
@@ -163,7 +166,7 @@ int pp_launch_makespan_fifo(const mk_args &a, hipStream_t st) {
     int Q = 1;
     while (Q < J) Q <<= 1;
     const int per = FIFO_THREADS / b.lanes_per;
-    const size_t lds = (size_t)per * (2 * (a.S | 1) + 1 + Q) * 4;
+    const size_t lds = ((size_t)per * (2 * (a.S | 1) + 1 + Q) + 1) * 4;
     // A launch has fewer than 2^32 threads.  At up to 64 lanes per candidate that is fewer candidates than
     // a list may hold (all 12! orderings, 32 lanes each), so long lists take several launches.
     const long long groups = (a.N + per - 1) / per, most = ((1ll << 32) - 1) / FIFO_THREADS;
