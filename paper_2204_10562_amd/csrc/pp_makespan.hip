@@ -526,13 +526,14 @@ __global__ __launch_bounds__(64) void k_makespan_lds(mk_args a) {
     const int lane = threadIdx.x, W = blockDim.x;
     const int S = a.S;
     if (!a.by_block && launch_is_narrow(a)) return;  // k_makespan_split does this launch
-    // (by block: it has marked the candidates that it leaves to this kernel)
-    if (a.by_block && a.T_out[(long long)blockIdx.x * W * a.t_stride + a.t_off] != MK_NOT_TAKEN) return;
     const int R = 2 * S - 1, J = 2 * R - 1;
     // rows 0..J-1: duration of block j = row+1; rows J..2J-1: its latest finish time
     long long *dur = sm + lane;
     long long *fin = sm + (size_t)J * W + lane;
-    const long long c = (long long)blockIdx.x * W + lane;
+  for (long long block = blockIdx.x; block * W < a.N; block += gridDim.x) {
+    // (by block: k_makespan_split has marked the candidates that it leaves to this kernel)
+    if (a.by_block && a.T_out[block * W * a.t_stride + a.t_off] != MK_NOT_TAKEN) continue;
+    const long long c = block * W + lane;
     const bool live = c < a.N;
     long long worst;
     const int fault = gather_durations<0>(a, c, live, worst,
@@ -557,7 +558,8 @@ __global__ __launch_bounds__(64) void k_makespan_lds(mk_args a) {
             fin[(size_t)(j - 1) * W] = max(idle, ready) + dur[(size_t)(j - 1) * W];
         }
     }
-    emit(a, q, c, live, fq, fin[(size_t)(J - 1) * W], blockIdx.x, gridDim.x, a.t_off);
+    emit(a, q, c, live, fq, fin[(size_t)(J - 1) * W], block, 0, a.t_off);
+  }
   }
 }
 
@@ -671,7 +673,9 @@ static int launch_makespan(const mk_args &a, hipStream_t st) {
     int rc = pp_launch_makespan_split(b, st);
     if (rc) return rc;
     const size_t lds = (size_t)2 * (4 * a.S - 3) * W * 8;
-    unsigned grid = (unsigned)((a.N + W - 1) / W);
+    // (few workgroups, so that a launch with nothing to do ends at once: 32 768 of them took 100 us)
+    const long long blocks = (a.N + W - 1) / W;
+    const unsigned grid = (unsigned)(blocks < 4096 ? blocks : 4096);
     hipLaunchKernelGGL(k_makespan_lds, dim3(grid), dim3(W), lds, st, b);
     return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_HIP;
 }
