@@ -43,7 +43,7 @@ extern "C" int pp_partition_dp(int L, int D, int S, int64_t N, const int64_t *PF
     if (rc) return rc;
     hipStream_t st = (hipStream_t)stream;
     const int32_t *ord = NULL;
-    rc = pp_launch_pack(L, D, S, N, PF, PB, XF, XB, orderings, workspace, lay, &ord, st);
+    rc = pp_launch_pack(L, D, S, N, PF, PB, XF, XB, orderings, 0, workspace, lay, &ord, st);
     if (rc) return rc;
     return pp_launch_dp(L, D, S, N, PF, PB, XF, XB, orderings ? NULL : ord, orderings, 0, 0, 0, C_out,
                         bounds_out, workspace, lay, status, st);
@@ -67,7 +67,7 @@ extern "C" int pp_partition_dp_stages(int L, int D, int S, int64_t N, const int6
     if (rc) return rc;
     hipStream_t st = (hipStream_t)stream;
     const int32_t *ord = NULL;
-    rc = pp_launch_pack(L, D, S, N, PF, PB, XF, XB, orderings, workspace, lay, &ord, st);
+    rc = pp_launch_pack(L, D, S, N, PF, PB, XF, XB, orderings, 1, workspace, lay, &ord, st);
     if (rc) return rc;
     return pp_launch_dp(L, D, S, N, PF, PB, XF, XB, orderings ? NULL : ord, orderings, 1, 0, 0, C_out,
                         bounds_out, workspace, lay, status, st);
@@ -94,7 +94,7 @@ extern "C" int pp_best_plan_stages(int L, int D, int S, int64_t N, int nM, const
     int64_t *T = T_all ? T_all : (int64_t *)(base + sl.T);
     int32_t *bounds = (int32_t *)(base + sl.bounds);
     const int32_t *ord = NULL;
-    rc = pp_launch_pack(L, D, S, N, PF, PB, XF, XB, orderings, workspace, lay, &ord, st);
+    rc = pp_launch_pack(L, D, S, N, PF, PB, XF, XB, orderings, 1, workspace, lay, &ord, st);
     if (rc) return rc;
     // (where candidates share their DP the plans of the representatives are scheduled and
     // compared, and the others get T and C only if the caller wants the arrays)
@@ -174,7 +174,7 @@ extern "C" int pp_best_plan_multi(int L, int D, int S, int64_t N, int nM, const 
     int64_t *C = C_all ? C_all : (int64_t *)(base + lay.C);
     int32_t *bounds = (int32_t *)(base + lay.bounds);
     const int32_t *ord = NULL;
-    rc = pp_launch_pack(L, D, S, N, PF, PB, XF, XB, orderings, workspace, lay, &ord, st);
+    rc = pp_launch_pack(L, D, S, N, PF, PB, XF, XB, orderings, 0, workspace, lay, &ord, st);
     if (rc) return rc;
     // When the closed form of the DP applies, the makespan kernel builds the plans itself from
     // tables in LDS (one launch fewer that does work, and no trip to memory for the plans).

@@ -42,13 +42,16 @@ struct pp_ws_header {
     // keys (first link most significant); the share_nbad candidates with a bad ordering follow,
     // stored from the end of the array backwards (pp_share_at)
     unsigned share_nsorted, share_nbad;
-    // share_sorted != 0 (only when share_active == 0): the list holds all N candidates ordered
-    // by their first share_kdev devices, so that neighbours share the first share_kdev - 1 rows
+    // share_sorted != 0 (only when share_active == 0): the list holds the candidates ordered by
+    // their first share_kdev devices, so that neighbours share the first share_kdev - 1 rows
     unsigned share_sorted, share_kdev;
-    // share_active: the sorted representatives are cut into share_nchunks runs of about equal
-    // work (rows to compute); run w is entries start[w] .. start[w + 1] - 1 of the list
+    // share_active: the representatives left to the DP kernel are cut into share_nchunks runs of about
+    // equal work (rows to compute); run w is entries start[w] .. start[w + 1] - 1 of their list
     unsigned share_nchunks;
-    unsigned pad0[55];
+    // candidates the bands (pp_dp_band.h) leave to the DP kernel: with share_sorted the length of the
+    // list, with share_active the representatives among them (kept in a list of their own)
+    unsigned share_npend;
+    unsigned pad0[54];
     // byte 1024: work the partition DP actually did in this call, in 64 records of 128 bytes
     // (atomics that hit one cache line are served one after another, so every record has a
     // line of its own): (cell, split) pairs evaluated (rows shared between candidates are
@@ -71,6 +74,7 @@ __device__ __forceinline__ void pp_count_work(pp_ws_header *hdr, unsigned long l
 // Workspace carving, identical for pp_partition_dp and pp_best_plan.
 struct pp_ws_layout {
     size_t hdr, p32, x32, xkt, xct, bfl, ord, arg, bounds, C, T, part, total;
+    size_t band;  // the table of the bands (pp_dp_band.h), behind the backtrack tables; 0: not wanted
     // candidates that share a DP (0 = not carved: see pp_share_possible)
     size_t sh_hash, sh_rep, sh_table, sh_keys, sh_reps, sh_cnt, sh_start, sh_rows;
     long long sh_row_slots;  // DP rows (of pp_share_row_stride(L) keys) the area sh_rows holds
@@ -105,6 +109,10 @@ __device__ __forceinline__ long long pp_share_at(const pp_ws_header *hdr, const 
     return r < ns ? reps[r] : reps[N - 1 - (r - ns)];
 }
 
+// Whether the few cells of pp_dp_band.h are tried first: one lane per candidate, so lists of less than a
+// wave are left to the kernels that spread a candidate over a wave (37 candidates of 150 layers in 6 stages).
+static inline bool pp_band_wanted(int S, int64_t N) { return S >= 2 && N >= 64; }
+
 static inline pp_ws_layout pp_layout(int L, int D, int S, int64_t N) {
     pp_ws_layout w;
     size_t off = 0;
@@ -119,6 +127,9 @@ static inline pp_ws_layout pp_layout(int L, int D, int S, int64_t N) {
     w.ord = off;    off += pp_align256((size_t)N * S * 4);
     w.slots = (int)(N < PP_DP_SLOTS ? N : PP_DP_SLOTS);
     w.arg = off;    off += pp_align256((size_t)w.slots * S * (L + 128) * 2);  // rows padded to 128 cells
+    // (a backtrack table takes at most S * (L + 63) of its S * (L + 128) entries: with 64 tables and more
+    // at least 8 KiB per stage are left behind them, and the table takes less than 2.5 KiB per stage)
+    w.band = pp_band_wanted(S, N) ? w.arg + pp_align256((size_t)w.slots * S * (L + 63) * 2) : 0;
     w.bounds = off; off += pp_align256((size_t)N * S * 4);
     w.C = off;      off += pp_align256((size_t)N * 8);
     w.T = off;      off += pp_align256((size_t)N * 8);
@@ -167,9 +178,10 @@ int pp_check_sizes(int L, int D, int S, int64_t N, const int32_t *orderings);
 
 // Enqueue helpers implemented next to their kernels (all return PP_OK / PP_ERR_HIP).
 // Fills the workspace tables (and, for orderings == NULL, the explicit list of all D!
-// orderings); returns in *ord the ordering array the later kernels must read.
+// orderings); returns in *ord the ordering array the later kernels must read.  stages: what
+// pp_launch_dp will be told.
 int pp_launch_pack(int L, int D, int S, int64_t N, const int64_t *PF, const int64_t *PB,
-                   const int64_t *XF, const int64_t *XB, const int32_t *orderings, void *ws,
+                   const int64_t *XF, const int64_t *XB, const int32_t *orderings, int stages, void *ws,
                    const pp_ws_layout &lay, const int32_t **ord, hipStream_t st);
 // Exactly one of lex_ord (the library's own list of all D! orderings, known to be valid and
 // lexicographic) and user_ord (the caller's list, to be validated) is non-NULL.
@@ -197,9 +209,10 @@ int pp_launch_dp(int L, int D, int S, int64_t N, const int64_t *PF, const int64_
 // fill_part != 0: also set the arg-min partials of the workspace (lay.part) to "none".
 // run_waves (1 .. PP_DP_SLOTS): the waves of the DP kernel that will walk the list of
 // representatives; the list is cut into at most that many runs of about equal work.
-int pp_launch_share_prepare(int L, int D, int S, int64_t N, const int64_t *XF, const int64_t *XB,
-                            const int32_t *ord, int validate, int fill_part, int run_waves, void *ws,
-                            const pp_ws_layout &lay, hipStream_t st);
+// In between, the pass over the bands finishes the candidates it can (g: where the results go).
+struct dp_args;
+int pp_launch_share_prepare(const dp_args &g, int fill_part, int run_waves, void *ws, const pp_ws_layout &lay,
+                            hipStream_t st);
 // With nT > 0 also T_out [nT][N][tw] (the makespan kernel ran over the representatives as well).
 int pp_launch_share_scatter(int64_t N, int nC, int nB, int nT, int tw, int64_t *C_out,
                             int32_t *bounds_out, int64_t *T_out, void *ws, const pp_ws_layout &lay,

@@ -15,6 +15,8 @@
 // the pack kernel leaves what is needed to tell in the workspace header, and the one kernel
 // enqueued after it branches on that.
 #include "pp_common.h"
+#include "pp_dp_band.h"
+#include "pp_dp_band_table.h"
 #include "pp_dp_generic.h"
 #include "pp_dp_rows.h"
 #include "pp_dp_tile.h"
@@ -29,6 +31,8 @@ struct pack_args {
     pp_ws_header *hdr;
     int *p32, *x32, *xkt, *xct, *ord;  // ord != NULL: write all D! orderings in lexicographic order
     long long *bfl;                    // [S][L+1] partition DP without channel costs
+    int pack;                          // 0: the tables of the links are left to k_share_hash (pp_share.hip)
+    band_table_args band;
 };
 
 // x32[link*L + k] = XF + XB at cut position k (k layers before the cut), k = 1..L-1; entry 0
@@ -214,9 +218,11 @@ __device__ void flat_table(const pack_args &a, long long *sh) {
     }
 }
 
-// Blocks 0..PP_PACK_BLOCKS-1 pack a slice of the tables each and record the largest time of
+// Blocks 0..PP_PACK_BLOCKS-1 pack a slice of the tables each (where candidates may share a DP, L > 128, the kernel
+// that reads every link's times to tell them apart does it: 55 -> 16 us at L = 400, D = 64) and record the largest time of
 // their slice in the header (no atomics, nothing to initialise); further blocks, if any, write
-// the explicit list of all D! orderings.  Block PP_PACK_BLOCKS builds the channel-free DP table.
+// the explicit list of all D! orderings.  Block PP_PACK_BLOCKS builds the channel-free DP table, the one
+// after it the bands.
 __global__ __launch_bounds__(256) void k_prep(pack_args a) {
     extern __shared__ __align__(16) long long dyn[];
     __shared__ unsigned long long sh[4];
@@ -236,10 +242,12 @@ __global__ __launch_bounds__(256) void k_prep(pack_args a) {
             if (tid < 64) { a.hdr->work[tid].pairs = 0; a.hdr->work[tid].rows = 0; }
         }
         bool flat = true;
-        unsigned long long mx = pack_x(a, first, stride, flat);
-        m = mx > m ? mx : m;
-        pack_xkt(a, first, stride);
-        pack_xct(a, first, stride);
+        if (a.pack) {
+            const unsigned long long mx = pack_x(a, first, stride, flat);
+            m = mx > m ? mx : m;
+            pack_xkt(a, first, stride);
+            pack_xct(a, first, stride);
+        }
         for (int off = 32; off; off >>= 1) {
             unsigned long long o = __shfl_xor(m, off);
             m = o > m ? o : m;
@@ -254,9 +262,11 @@ __global__ __launch_bounds__(256) void k_prep(pack_args a) {
         }
     } else if (blockIdx.x == PP_PACK_BLOCKS) {
         flat_table(a, dyn);
+    } else if (blockIdx.x == PP_PACK_BLOCKS + 1) {
+        if (a.band.table) band_table(a.band, (unsigned char *)dyn);
     } else {
-        unrank_rows(a, (long long)(blockIdx.x - PP_PACK_BLOCKS - 1) * 256 + tid,
-                    (long long)(gridDim.x - PP_PACK_BLOCKS - 1) * 256);
+        unrank_rows(a, (long long)(blockIdx.x - PP_PACK_BLOCKS - 2) * 256 + tid,
+                    (long long)(gridDim.x - PP_PACK_BLOCKS - 2) * 256);
     }
 }
 
@@ -283,8 +293,27 @@ static int pp_dp_tiles(int L, int D, int S, int64_t N, const pp_ws_layout &lay) 
     return N >= least && (L > 104 ? rows > tiled : 3 * rows > 4 * tiled) ? 0 : lay.nt;
 }
 
+// How the bands of pp_dp_band.h are used.  For L > 128 the preparation of shared DPs tries them on every list of
+// a wave and more.  For L <= 128 the DP kernel finishes the candidates with the channel-free plan itself where
+// the test is cheap (band_link_bytes), which takes it 5 us of trips to memory: worth it from about 10^8 (cell,
+// split) pairs on (whole calls without / with: 36 / 42 us at 1.3e7, 31 / 36 at 4.9e7, 63 / 56 at 9.6e7, 49.6 /
+// 32.2 at 1.1e8; a list of all orderings shares two rows in three).  Where the test is not cheap, or whole rows
+// of all candidates would take so long that two launches more are little, the bands come first in launches of
+// their own (239 369 orderings, L = 104, S = 14 2072 -> 179 us; 20 317, whose links bind, L = 99, S = 37
+// 1173 -> 795; 549 239, L = 77, S = 39, where links bind so that none ends, 19.26 -> 19.6 ms).
+static int band_use(int L, int D, int S, int64_t N, int stages, bool lex, const pp_ws_layout &lay) {
+    if (!lay.band || D > 64) return BAND_USE_NOT;
+    if (!lay.nt) return lay.sh_table ? BAND_USE_INSIDE : BAND_USE_NOT;
+    const double pairs = (double)N * (S - 1) * L * L / (lex ? 3 : 1);
+    const bool cheap = band_link_bytes(D, S, stages) != 0;
+    // (the words' place is that of T)
+    const bool room = (size_t)band_link_words(D, S, stages) * 8 + (size_t)N / 8 + 8 <= (size_t)N * 8;
+    if (room && pairs >= (cheap ? 6e9 : 4e8)) return BAND_USE_ALONE;
+    return cheap && pairs >= 9e7 ? BAND_USE_INSIDE : BAND_USE_NOT;
+}
+
 int pp_launch_pack(int L, int D, int S, int64_t N, const int64_t *PF, const int64_t *PB,
-                   const int64_t *XF, const int64_t *XB, const int32_t *orderings, void *ws,
+                   const int64_t *XF, const int64_t *XB, const int32_t *orderings, int stages, void *ws,
                    const pp_ws_layout &lay, const int32_t **ord, hipStream_t st) {
     char *base = (char *)ws;
     pack_args a;
@@ -300,9 +329,20 @@ int pp_launch_pack(int L, int D, int S, int64_t N, const int64_t *PF, const int6
     a.bfl = (long long *)(base + lay.bfl);
     a.ord = orderings ? NULL : (int *)(base + lay.ord);
     *ord = orderings ? orderings : (const int32_t *)(base + lay.ord);
-    int grid = PP_PACK_BLOCKS + 1;
+    a.pack = !lay.sh_table;
+    band_table_args &t = a.band;
+    t.L = L; t.D = D; t.S = S; t.K = a.K;
+    t.PF = a.PF; t.PB = a.PB; t.XF = a.XF; t.XB = a.XB;
+    t.table = band_use(L, D, S, N, stages, orderings == NULL, lay) ? (int *)(base + lay.band) : NULL;
+    t.waves = 1;
+    t.stages = stages;
+    t.fit_limit = (1ull << (31 - a.K)) - 1;
+    int grid = PP_PACK_BLOCKS + 2;
+    size_t lds = (size_t)3 * (L + 1) * 8;
+    const size_t band_lds = band_table_lds(L, S, stages, t.waves);
+    if (t.table && lds < band_lds) lds = band_lds;
     if (a.ord) grid += (int)((N + 255) / 256 < 1024 ? (N + 255) / 256 : 1024);
-    hipLaunchKernelGGL(k_prep, dim3(grid), dim3(256), (size_t)3 * (L + 1) * 8, st, a);
+    hipLaunchKernelGGL(k_prep, dim3(grid), dim3(256), lds, st, a);
     return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_HIP;
 }
 
@@ -379,6 +419,9 @@ int pp_launch_dp(int L, int D, int S, int64_t N, const int64_t *PF, const int64_
     a.nblocks = lay.slots;
     a.bfl = (const long long *)(base + lay.bfl);
     a.defer_mmax = defer_mmax;
+    const int use = band_use(L, D, S, N, stages, lex_ord != NULL, lay);
+    a.band = use ? (const int *)(base + lay.band) : NULL;
+    a.left = NULL;
 
     int cus = 256;
     int dev = 0;
@@ -397,6 +440,12 @@ int pp_launch_dp(int L, int D, int S, int64_t N, const int64_t *PF, const int64_
         }
     };
     const int nt = pp_dp_tiles(L, D, S, N, lay);
+    if (use == BAND_USE_ALONE) {
+        unsigned long long *words = (unsigned long long *)(base + lay.T);  // (T is written once the plans are there)
+        a.left = words + band_link_words(D, S, stages);
+        const int rc = pp_launch_dp_band_alone(a, words, words + band_link_words(D, S, stages), st);
+        if (rc) return rc;
+    }
     if (lay.nt && !nt) {
         dp_rows_args t;
         t.L = L; t.D = D; t.S = S; t.K = a.K; t.N = N;
@@ -440,10 +489,11 @@ int pp_launch_dp(int L, int D, int S, int64_t N, const int64_t *PF, const int64_
     // candidates whose links have the same channel times share one DP: the kernel walks the
     // representatives the preparation finds, and their results are copied to the others
     const int run_waves = pp_dp_big_run_waves(pp_dp_big_waves(L, D, S, (int)waves, cus), S, lay.sh_row_slots);
-    int rc = pp_launch_share_prepare(L, D, S, N, XF, XB, a.ord, a.validate, keep_list, run_waves, ws, lay, st);
+    int rc = pp_launch_share_prepare(a, keep_list, run_waves, ws, lay, st);
     if (rc) return rc;
     pp_share_list list;
     list.reps = (const int *)(base + lay.sh_reps);
+    list.pend = (const int *)(base + lay.T);
     list.keys = (const int *)(base + lay.sh_keys);
     list.start = (const int *)(base + lay.sh_start);
     list.rows = (int *)(base + lay.sh_rows);

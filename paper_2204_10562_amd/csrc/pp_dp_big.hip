@@ -11,6 +11,8 @@
 // and one step per cell with a monotone queue was measured too: 345 ms at L = 1024, a serial chain of
 // LDS trips per cell.)
 //
+// Only candidates that the bands (pp_dp_band.h) have left come here where those are tried.
+//
 // Per wave in LDS: two rows of keys (the row being read, rewritten in place as g, and the row
 // being produced) and h.  Split indices go to a per-wave table in global memory while the next
 // row's g is built (coalesced), and the plan is read back from there with cache-bypassing
@@ -38,7 +40,8 @@ struct dp_big_args {
     // group of candidates with the same DP, see pp_share.hip) instead of all candidates: every
     // wave a run of neighbours, which share their first links and so their first rows (keys:
     // the key of every candidate; rows: room for row_slots saved rows of Lp + 4 keys)
-    const int *reps, *keys, *start;
+    // pend: the representatives the bands have left, the list that is really walked
+    const int *reps, *pend, *keys, *start;
     int *rows;
     long long row_slots;  // rows of Lp + 4 keys the area `rows` holds
     dp_args g;
@@ -92,26 +95,14 @@ __global__ __launch_bounds__(256, 4) void k_dp_big(dp_big_args b) {
     int *bufB = bufA + RS;
     const long long wave = (long long)blockIdx.x * wpb + wib;
 
-    for (int k = threadIdx.x; k <= Lp; k += blockDim.x) sPk[k] = (a.p32[k < L ? k : L] << K) - k;
-    if (threadIdx.x == 0) sPk[-1] = 0;
-    __syncthreads();
-    if (wave >= b.waves) return;
-    dp_row row;
-    row.h = (unsigned *)(bufB + RS);
-    row.PK = sPk;
-    row.L = L;
-    row.K = K;
-    row.kmask = kmask;
-    row.lane = lane;
-    row_begin(row);
-    int v_steps = row_first_steps(L, lane);  // lane n: steps of a search in row n
     unsigned short *arg = a.arg + (size_t)wave * b.arg_stride;
     unsigned long long pairs = 0, nrows = 0;
     const int tri = S * (S + 1) / 2;
 
     // Which candidates this wave takes: every waves-th one, or a run of consecutive entries of a
     // list the preparation left (pp_share.hip): the sorted representatives where candidates
-    // share their DP, or all candidates sorted by their first devices.  Neighbours in a list
+    // share their DP, or candidates sorted by their first devices (less those whose plans are
+    // there already).  Neighbours in a list
     // share their first rows; the wave keeps the rows that can be shared (all of them, or the
     // first kdev - 1) in its slice of the workspace.
     const bool listed = b.reps != NULL && a.hdr->share_active != 0;
@@ -120,7 +111,8 @@ __global__ __launch_bounds__(256, 4) void k_dp_big(dp_big_args b) {
     // share their DP, this wave's share of the candidates with a bad ordering that follow the
     // sorted representatives in the list (n_tail entries t_begin, t_begin + waves, ...)
     long long r_begin = wave, r_step = b.waves, nsorted = 0, t_begin = 0, n_tail = 0;
-    long long n_main = wave < a.N ? (a.N - wave + b.waves - 1) / b.waves : 0;
+    const bool working = wave < b.waves;
+    long long n_main = working && wave < a.N ? (a.N - wave + b.waves - 1) / b.waves : 0;
     unsigned pw = 1;  // lane n = 1..S-1: (classes)^(S-1-n), the weight of the key's digit n
     int keep_rows = 0;  // rows 1..keep_rows are saved
     if (listed) {
@@ -132,23 +124,37 @@ __global__ __launch_bounds__(256, 4) void k_dp_big(dp_big_args b) {
         n_main = wave < nch ? b.start[wave + 1] - r_begin : 0;
         r_step = 1;
         t_begin = nsorted + wave;
-        n_tail = t_begin < total ? (total - t_begin + b.waves - 1) / b.waves : 0;
+        n_tail = working && t_begin < total ? (total - t_begin + b.waves - 1) / b.waves : 0;
         const unsigned nc = a.hdr->share_nc;
         for (int n = lane + 1; n < S; ++n) pw *= nc;
     } else if (sorted) {
-        nsorted = a.N;
+        const long long todo = a.hdr->share_nsorted;  // (what the bands have left)
         keep_rows = (int)a.hdr->share_kdev - 1;
         keep_rows = keep_rows < S - 2 ? keep_rows : S - 2;
         keep_rows = keep_rows > 0 ? keep_rows : 0;
         long long nw = b.row_slots / (keep_rows > 0 ? keep_rows : 1);  // waves whose rows fit the area
         nw = nw < b.waves ? nw : b.waves;
         nw = nw > 1 ? nw : 1;
-        const long long chunk = (a.N + nw - 1) / nw;
+        const long long chunk = (todo + nw - 1) / nw;
         r_begin = wave * chunk;
-        n_main = r_begin < a.N ? (r_begin + chunk < a.N ? chunk : a.N - r_begin) : 0;
+        n_main = r_begin < todo ? (r_begin + chunk < todo ? chunk : todo - r_begin) : 0;
         r_step = 1;
     }
     const long long n_items = n_main + n_tail;
+    if (__syncthreads_and(n_items == 0)) return;
+    for (int k = threadIdx.x; k <= Lp; k += blockDim.x) sPk[k] = (a.p32[k < L ? k : L] << K) - k;
+    if (threadIdx.x == 0) sPk[-1] = 0;
+    __syncthreads();
+    if (!n_items) return;
+    dp_row row;
+    row.h = (unsigned *)(bufB + RS);
+    row.PK = sPk;
+    row.L = L;
+    row.K = K;
+    row.kmask = kmask;
+    row.lane = lane;
+    row_begin(row);
+    int v_steps = row_first_steps(L, lane);  // lane n: steps of a search in row n
     auto entry = [&](long long i) { return i < n_main ? r_begin + i * r_step : t_begin + (i - n_main) * b.waves; };
     // (row n >= 1 of this wave's slice at save + (n - 1) RS)
     int *save = b.rows + (size_t)((listed || sorted) && n_main ? wave : 0) * keep_rows * RS;
@@ -161,15 +167,14 @@ __global__ __launch_bounds__(256, 4) void k_dp_big(dp_big_args b) {
         c = 0; key = -1; v_o = 0;
         if (i >= n_items) return;
         const long long r = entry(i);
-        c = (listed || sorted) ? pp_share_at(a.hdr, b.reps, a.N, r) : r;
-        if (listed && r < nsorted) key = b.keys[c];
+        c = listed ? (i < n_main ? b.pend[r] : pp_share_at(a.hdr, b.reps, a.N, r)) : sorted ? b.reps[r] : r;
+        if (listed && i < n_main) key = b.keys[c];
         v_o = lane < S ? a.ord[c * S + lane] : 0;
     };
     long long c_next;
     int key_next, v_o_next;
     fetch(0, c_next, key_next, v_o_next);
     for (long long i = 0; i < n_items; ++i) {
-        const long long r = entry(i);
         const long long c = c_next;
         const int v_o = v_o_next;
         // rows 1..p of the previous candidate are this one's too: its key has the same first p
@@ -177,7 +182,7 @@ __global__ __launch_bounds__(256, 4) void k_dp_big(dp_big_args b) {
         int p = 0;
         const int key = key_next;
         fetch(i + 1, c_next, key_next, v_o_next);
-        if (listed && r < nsorted) {
+        if (listed && i < n_main) {
             if (prev_key >= 0) {
                 const bool differ = lane >= 1 && lane < S && (unsigned)key / pw != (unsigned)prev_key / pw;
                 const unsigned long long m = __ballot(differ);
@@ -412,6 +417,7 @@ int pp_launch_dp_big(const dp_args &g, int max_waves, int cus, const pp_share_li
     dp_big_args b;
     b.g = g;
     b.reps = list ? list->reps : NULL;
+    b.pend = list ? list->pend : NULL;
     b.keys = list ? list->keys : NULL;
     b.start = list ? list->start : NULL;
     b.rows = list ? list->rows : NULL;

@@ -20,6 +20,8 @@ struct dp_args {
     pp_ws_header *hdr;
     const int *p32, *x32;
     const long long *bfl;  // the partition DP with no channel cost (values, then splits), see pp_dp_flat.h
+    const int *band;       // the table of pp_dp_band.h, or NULL
+    const unsigned long long *left;  // a bit per candidate: k_dp_band has left it (NULL: it has not run)
     size_t lds_bytes;      // dynamic LDS of the launch
     // > 0: when the closed form applies and the finish times of a schedule of defer_mmax
     // microbatches fit 32 bits, leave the plans to the makespan kernel that follows
@@ -38,10 +40,10 @@ struct dp_args {
 
 // Kernel for 128 < L with 32-bit keys (pp_dp_big.hip): persistent waves, as many as fit the
 // GPU (cus compute units) but at most max_waves (the backtrack tables the workspace holds).
-// list: what pp_launch_share_prepare leaves in the workspace (representatives, every
-// candidate's key, room for saved rows), or NULL.
+// list: what pp_launch_share_prepare leaves in the workspace (representatives, those of them the bands
+// have left, every candidate's key, room for saved rows), or NULL.
 struct pp_share_list {
-    const int *reps, *keys, *start;
+    const int *reps, *pend, *keys, *start;
     int *rows;
     long long row_slots;  // rows of (128 ceil(L / 128) + 4) keys that fit the area
 };

@@ -40,6 +40,9 @@ struct dp_rows_args {
     long long chunk;  // consecutive candidates walked by one wave
     int validate;     // orderings came from the caller: check them
     int rows;         // rows a wave has room for
+    // LDS offset of a word per wave and the links' words (pp_dp_band.h; 0: no room for them); whether a workgroup's
+    // candidates are dealt out together (chunks of less than 64: the words then take the waves' place)
+    int links_at, pooled;
     int prio_left[3]; // priority k+1 while more than prio_left[k] candidates of the chunk are left
     dp_args g;        // tables, outputs and the generic fallback's arguments
 };

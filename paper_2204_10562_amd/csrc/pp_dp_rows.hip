@@ -42,6 +42,7 @@
 // 5 200 clocks with four waves per SIMD.  L = 97, S = 11, 200 003 sampled orderings, whole
 // call: 1.18 ms with all pairs, 0.96 ms here.
 #include "pp_common.h"
+#include "pp_dp_band.h"
 #include "pp_dp_flat.h"
 #include "pp_dp_row.h"
 #include "pp_dp_rows.h"
@@ -164,6 +165,7 @@ __device__ __forceinline__ int rows_compute(const rows_row &r, int n, int steps,
     return rounds;
 }
 
+template <int BANDS>
 __global__ __launch_bounds__(256) void k_dp_rows(dp_rows_args a) {
     extern __shared__ __align__(16) unsigned char smem[];
     if (pp_is_flat(a.g.hdr)) {
@@ -212,6 +214,44 @@ __global__ __launch_bounds__(256) void k_dp_rows(dp_rows_args a) {
     const long long wave = (long long)blockIdx.x * (blockDim.x >> 6) + wib;
     const long long c0 = wave * a.chunk;
     const long long c1 = c0 + a.chunk < a.N ? c0 + a.chunk : a.N;
+
+    // Candidates that the few cells of pp_dp_band.h finish come first; whole rows are computed for those left (a
+    // bit each in `left`).  Either a launch before this one has left them in memory, or the ones with the
+    // channel-free plan are finished here, one per lane: where a wave's chunk is shorter than a wave is wide, the
+    // workgroup's candidates are dealt out together.  Else the chunk is taken in pieces of up to 64.  Where more
+    // than half of a piece is left, what follows it goes without.
+    // (Not where neither can be worth it, pp_dp.hip: a kernel without this.)
+    bool whole = BANDS == BAND_USE_NOT || a.g.band[band_top_at(S, 0, S)] < 0;
+    const bool pooled = BANDS == BAND_USE_INSIDE && a.pooled;
+    unsigned long long *words = (unsigned long long *)(smem + (pooled ? 0 : a.links_at)), *reach = words + 4;
+    unsigned long long left = 0;
+    auto finish = [&](long long c, bool live) -> unsigned long long {
+        int first;
+        const unsigned long long all = __ballot(live), l = band_free_try(a.g, a.g.band, reach, c, live, first);
+        band_count(a.g, all & ~l, first, 1, c);
+        return l;
+    };
+    if (BANDS == BAND_USE_INSIDE) {
+        whole = whole || !(pooled || a.links_at) || !band_free(a.g, a.g.band);
+        if (!whole) {
+            band_links(a.g, a.g.band, reach);
+            __syncthreads();
+        }
+        if (!whole && pooled) {
+            // dealt out together, before any wave needs its part of the LDS
+            const int wpb = blockDim.x >> 6;
+            const long long first = (long long)blockIdx.x * wpb * a.chunk;
+            const int at = 64 * wib, total = (int)(a.N - first < wpb * a.chunk ? a.N - first : wpb * a.chunk);
+            const unsigned long long word = at < total ? finish(first + at + lane, at + lane < total) : 0;
+            if (lane == 0) words[wib] = word;
+            __syncthreads();
+            const int mine_at = wib * (int)a.chunk, w = mine_at >> 6, by = mine_at & 63;
+            left = words[w] >> by;
+            if (by && w + 1 < wpb) left |= words[w + 1] << (64 - by);
+            left &= (1ull << a.chunk) - 1;
+            __syncthreads();
+        }
+    }
     if (c0 >= c1) return;
 
     // row 0: one stage holding the first l layers (same for every candidate)
@@ -240,10 +280,10 @@ __global__ __launch_bounds__(256) void k_dp_rows(dp_rows_args a) {
     const unsigned long long smask = S >= 64 ? ~0ull : ((1ull << S) - 1);
     const int top_lane = (L - 1) & 63;  // the lane of cell L (in the last chunk)
 
-    // finished candidates pend0 .. pend0+pending-1 wait for their plans to be written out;
-    // lane q keeps the key of cell (S-1, L) of pending candidate q (-1: its ordering was bad)
-    long long pend0 = c0;
-    int pending = 0, v_top = 0;
+    // up to DPR_PENDING finished candidates wait for their plans to be written out; lane q keeps the key
+    // of cell (S-1, L) of the q-th of them (-1: its ordering was bad) and its place in the chunk (BAND_USE_NOT: they
+    // are neighbours, pend0 the first)
+    int pending = 0, v_top = 0, v_at = 0, pend0 = 0;
     unsigned long long pairs = 0, nrows = 0;  // work done by this wave
     int arena_used = 0;
     bool fresh = true;  // the arena was emptied: the next candidate must recompute every row
@@ -251,11 +291,18 @@ __global__ __launch_bounds__(256) void k_dp_rows(dp_rows_args a) {
     // lane n: key of cell (n, L) of the current path, i.e. the result for n+1 stages
     int v_tops = PLk;
 
+    auto remember = [&](int top, int at) __attribute__((always_inline)) {
+        if (lane == pending) {
+            v_top = top;
+            if (BANDS != BAND_USE_NOT) v_at = at;
+        }
+    };
+
     // Writes out C and the plans of all pending candidates, one per lane.
     auto flush = [&]() {
         row_lds_sync();
         const bool live = lane < pending;
-        const long long cq = pend0 + lane;
+        const long long cq = c0 + (BANDS == BAND_USE_NOT ? pend0 + lane : v_at);
         const bool bad = live && v_top < 0;
         if (__ballot(bad) && lane == 0) pp_raise(a.g.status, PP_FAULT_ORDERING);
         // xi = number of stages of the plan read back: S only, or every count 1..S
@@ -287,18 +334,30 @@ __global__ __launch_bounds__(256) void k_dp_rows(dp_rows_args a) {
         for (long long c = c0; c < c1; ++c) {
             const int d = ord[c];
             const bool bad = a.validate && (d < 0 || d >= D);
-            if (lane == pending) v_top = bad ? -1 : key;
+            remember(bad ? -1 : key, (int)(c - c0));
             if (++pending == DPR_PENDING) flush();
         }
         if (pending) flush();
         return;
     }
 
+    // Candidates by their place in the chunk: base .. end - 1 is the piece at hand.
+    const int count = (int)(c1 - c0);
+    const int piece = BANDS == BAND_USE_NOT ? count : (count + ((count + 63) >> 6) - 1) / ((count + 63) >> 6);
+    int base = 0, end_c = count;
+    bool whole_now = whole;
+    auto next = [&](int c) -> int {
+        if (BANDS == BAND_USE_NOT || whole_now) return c + 1;
+        const unsigned long long m = left >> (c - base) >> 1;
+        return m ? c + 1 + __builtin_ctzll(m) : end_c;
+    };
+    const int *ords = ord + c0 * S;
+
     // Lane n carries device o[n] of the candidate (v_o) and the link index o[n-1]*D + o[n]
     // that row n needs (v_link).
     int v_prev = 0;
     bool have_prev = false;
-    int v_o = lane < S ? ord[c0 * S + lane] : 0;
+    int v_o = 0;
 
     // Looks at candidate ordering v (previous valid one in v_prev): returns the first row to
     // compute, or -1 if the ordering is not a list of distinct devices below D.
@@ -335,22 +394,45 @@ __global__ __launch_bounds__(256) void k_dp_rows(dp_rows_args a) {
 
     // prio_until[k]: the last candidate with more than prio_left[k] candidates still to do
     // (itself included)
-    long long prio_until[3];
-    for (int k = 0; k < 3; ++k) prio_until[k] = c1 - 1 - a.prio_left[k];
+    int prio_until[3];
+    for (int k = 0; k < 3; ++k) prio_until[k] = count - 1 - a.prio_left[k];
 
-    // first candidate of the chunk (bad ones are recorded and skipped)
-    long long c = c0;
+    for (; base < count; base = end_c) {
+    end_c = count;
+    whole_now = whole;
+    if (BANDS != BAND_USE_NOT && !whole) {
+        if (BANDS == BAND_USE_ALONE) {
+            end_c = base + piece < count ? base + piece : count;
+            const unsigned long long *at = a.g.left + ((c0 + base) >> 6);
+            const int by = (int)((c0 + base) & 63), n = end_c - base;
+            left = at[0] >> by;
+            if (by + n > 64) left |= at[1] << (64 - by);
+            if (n < 64) left &= (1ull << n) - 1;
+        } else if (!pooled) {
+            end_c = base + piece < count ? base + piece : count;
+            left = finish(c0 + base + lane, base + lane < end_c);
+        }
+        if (!left) continue;
+        whole = 2 * __builtin_popcountll(left) > end_c - base;
+        have_prev = false;
+        arena_used = 0;
+        fresh = true;
+    }
+    // first candidate of the piece (bad ones are recorded and skipped)
+    int c = BANDS == BAND_USE_NOT || whole_now ? base : base + __builtin_ctzll(left);
+    v_o = lane < S ? ords[(long long)c * S + lane] : 0;
     int first = inspect(v_o);
     while (first < 0) {
-        if (lane == pending) v_top = -1;
+        remember(-1, c);
         if (++pending == DPR_PENDING) flush();
-        if (++c >= c1) break;
-        v_o = lane < S ? ord[c * S + lane] : 0;
+        c = next(c);
+        if (c >= end_c) break;
+        v_o = lane < S ? ords[(long long)c * S + lane] : 0;
         first = inspect(v_o);
     }
-    if (c >= c1) {
+    if (c >= end_c) {
         if (pending) flush();
-        return;
+        continue;
     }
     int v_link = links(v_o);
     int xk[U];
@@ -367,15 +449,16 @@ __global__ __launch_bounds__(256) void k_dp_rows(dp_rows_args a) {
         else if (c <= prio_until[1]) __builtin_amdgcn_s_setprio(2);
         else if (c <= prio_until[0]) __builtin_amdgcn_s_setprio(1);
         else __builtin_amdgcn_s_setprio(0);
-        const bool more = c + 1 < c1;
-        int v_on = (more && lane < S) ? ord[(c + 1) * S + lane] : 0;
+        int c_n = next(c);
+        const bool more = c_n < end_c;
+        int v_on = (more && lane < S) ? ords[(long long)c_n * S + lane] : 0;
         int first_n = -2, v_link_n = 0;  // next candidate: -2 none, -1 bad ordering
         bool flush_after = false;
 
         // candidate finished with key `top` in cell (S-1, L): remember it and the arena rows of
         // its path
         auto finish_candidate = [&](int top) __attribute__((always_inline)) {
-            if (lane == pending) v_top = top;
+            remember(top, c);
             if (lane < S) slots[pending * S + lane] = (unsigned char)v_cur;
             if (stages && lane < S) tops[pending * S + lane] = v_tops;
             ++pending;
@@ -481,12 +564,12 @@ __global__ __launch_bounds__(256) void k_dp_rows(dp_rows_args a) {
         if (flush_after) flush();
         // bad orderings after this candidate are recorded and skipped
         while (first_n == -1) {
-            if (lane == pending) v_top = -1;
+            remember(-1, c_n);
             if (++pending == DPR_PENDING) flush();
-            ++c;
+            c_n = next(c_n);
             first_n = -2;
-            if (c + 1 < c1) {
-                v_on = lane < S ? ord[(c + 1) * S + lane] : 0;
+            if (c_n < end_c) {
+                v_on = lane < S ? ords[(long long)c_n * S + lane] : 0;
                 first_n = inspect(v_on);  // compared with the last valid candidate
                 if (first_n >= 0) {
                     if (arena_used + (S - 1 - first_n) > arena_rows || pending + 2 > DPR_PENDING) {
@@ -499,17 +582,21 @@ __global__ __launch_bounds__(256) void k_dp_rows(dp_rows_args a) {
             }
         }
         if (first_n < 0) break;  // no candidate left
-        ++c;
+        c = c_n;
         v_o = v_on;
         v_link = v_link_n;
         first = first_n;
     }
     if (pending) flush();
+    }
     if (lane == 0) pp_count_work(a.g.hdr, pairs, nrows, (unsigned)wave);
 }
 
+static size_t rows_own_lds(int L, int S, int rows, int stages, int wpb) {
+    return (DPR_TABLE + (size_t)wpb * dpr_lds_per_wave(L, S, rows, stages) + 15) & ~(size_t)15;
+}
 static size_t rows_lds(int L, int D, int S, int rows, int stages, int wpb) {
-    size_t lds = DPR_TABLE + (size_t)wpb * dpr_lds_per_wave(L, S, rows, stages);
+    size_t lds = rows_own_lds(L, S, rows, stages, wpb);
     const size_t generic = dp_generic_lds_bytes(L);  // the int64 fallback's rows
     if (lds < generic) lds = generic;
     const size_t flat = pp_flat_lds_wanted(L, D, S, wpb);  // the closed-form body's tables
@@ -534,8 +621,24 @@ dpr_shape pp_dp_rows_shape(int L, int D, int S, int stages) {
 
 int pp_launch_dp_rows(const dp_rows_args &a, int grid, const dpr_shape &sh, hipStream_t st) {
     dp_rows_args b = a;
-    b.g.lds_bytes = sh.lds;
     b.rows = sh.rows;
-    hipLaunchKernelGGL(k_dp_rows, dim3(grid), dim3(64 * sh.wpb), sh.lds, st, b);
+    const int use = !a.g.band ? BAND_USE_NOT : a.g.left ? BAND_USE_ALONE : BAND_USE_INSIDE;
+    size_t lds = sh.lds;
+    b.links_at = b.pooled = 0;
+    if (use == BAND_USE_INSIDE) {
+        // the words of the links: in the waves' place, or behind it where that costs no workgroup
+        const size_t own = rows_own_lds(a.L, a.S, sh.rows, a.g.stages, sh.wpb), words = band_link_bytes(a.D, a.S, a.g.stages);
+        b.pooled = a.chunk < 64 && words && words <= sh.wpb * dpr_lds_per_wave(a.L, a.S, sh.rows, a.g.stages);
+        const size_t to = own + words > lds ? own + words : lds;
+        auto groups = [&](size_t bytes) { return (int)(160 * 1024 / ((bytes + 1279) / 1280 * 1280)); };
+        if (!b.pooled && words && to <= 64 * 1024 && (groups(to) >= groups(lds) || groups(to) * sh.wpb >= 16)) {
+            b.links_at = (int)own;
+            lds = to;
+        }
+    }
+    b.g.lds_bytes = lds;
+    if (use == BAND_USE_ALONE) hipLaunchKernelGGL(k_dp_rows<BAND_USE_ALONE>, dim3(grid), dim3(64 * sh.wpb), lds, st, b);
+    else if (use == BAND_USE_INSIDE) hipLaunchKernelGGL(k_dp_rows<BAND_USE_INSIDE>, dim3(grid), dim3(64 * sh.wpb), lds, st, b);
+    else hipLaunchKernelGGL(k_dp_rows<BAND_USE_NOT>, dim3(grid), dim3(64 * sh.wpb), lds, st, b);
     return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_HIP;
 }

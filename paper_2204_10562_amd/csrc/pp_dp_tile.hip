@@ -26,6 +26,7 @@
 // arena rows make up its path, and the plans of up to 64 finished candidates are read back
 // together, one candidate per lane.
 #include "pp_common.h"
+#include "pp_dp_band.h"
 #include "pp_dp_flat.h"
 #include "pp_dp_tile.h"
 
@@ -94,7 +95,7 @@ __device__ __forceinline__ void lds_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
-template <int NT>
+template <int NT, int BANDS>
 __global__ __launch_bounds__(256) void k_dp_tile(dp_tile_args a) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ dp_generic_small s_generic;
@@ -129,6 +130,44 @@ __global__ __launch_bounds__(256) void k_dp_tile(dp_tile_args a) {
     const long long wave = (long long)blockIdx.x * (blockDim.x >> 6) + wib;
     const long long c0 = wave * a.chunk;
     const long long c1 = c0 + a.chunk < a.N ? c0 + a.chunk : a.N;
+
+    // Candidates that the few cells of pp_dp_band.h finish come first; whole rows are computed for those left (a
+    // bit each in `left`).  Either a launch before this one has left them in memory, or the ones with the
+    // channel-free plan are finished here, one per lane: where a wave's chunk is shorter than a wave is wide, the
+    // workgroup's candidates are dealt out together.  Else the chunk is taken in pieces of up to 64.  Where more
+    // than half of a piece is left, what follows it goes without.
+    // (Not where neither can be worth it, pp_dp.hip: a kernel without this.)
+    bool whole = BANDS == BAND_USE_NOT || a.g.band[band_top_at(S, 0, S)] < 0;
+    const bool pooled = BANDS == BAND_USE_INSIDE && a.pooled;
+    unsigned long long *words = (unsigned long long *)(smem + (pooled ? 0 : a.links_at)), *reach = words + 4;
+    unsigned long long left = 0;
+    auto finish = [&](long long c, bool live) -> unsigned long long {
+        int first;
+        const unsigned long long all = __ballot(live), l = band_free_try(a.g, a.g.band, reach, c, live, first);
+        band_count(a.g, all & ~l, first, 1, c);
+        return l;
+    };
+    if (BANDS == BAND_USE_INSIDE) {
+        whole = whole || !(pooled || a.links_at) || !band_free(a.g, a.g.band);
+        if (!whole) {
+            band_links(a.g, a.g.band, reach);
+            __syncthreads();
+        }
+        if (!whole && pooled) {
+            // dealt out together, before any wave needs its part of the LDS
+            const int wpb = blockDim.x >> 6;
+            const long long first = (long long)blockIdx.x * wpb * a.chunk;
+            const int at = 64 * wib, total = (int)(a.N - first < wpb * a.chunk ? a.N - first : wpb * a.chunk);
+            const unsigned long long word = at < total ? finish(first + at + lane, at + lane < total) : 0;
+            if (lane == 0) words[wib] = word;
+            __syncthreads();
+            const int mine_at = wib * (int)a.chunk, w = mine_at >> 6, by = mine_at & 63;
+            left = words[w] >> by;
+            if (by && w + 1 < wpb) left |= words[w + 1] << (64 - by);
+            left &= (1ull << a.chunk) - 1;
+            __syncthreads();
+        }
+    }
     if (c0 >= c1) return;
 
     // candidate-independent part: Dp[i][j] = ((P[l] - P[k]) << K) | k, or infinite if k >= l
@@ -188,10 +227,10 @@ __global__ __launch_bounds__(256) void k_dp_tile(dp_tile_args a) {
     // where this lane stores the cells it holds after a row's reduction (b = 0 or 4 only)
     const int wofs = la + 1 + (lb >> 2) * 8 * H;
 
-    // finished candidates pend0 .. pend0+pending-1 wait for their plans to be written out;
-    // lane q keeps the key of cell (S-1, L) of pending candidate q (-1: its ordering was bad)
-    long long pend0 = c0;
-    int pending = 0, v_top = 0;
+    // up to DPT_PENDING finished candidates wait for their plans to be written out; lane q keeps the key
+    // of cell (S-1, L) of the q-th of them (-1: its ordering was bad) and its place in the chunk (BAND_USE_NOT: they
+    // are neighbours, pend0 the first)
+    int pending = 0, v_top = 0, v_at = 0, pend0 = 0;
     unsigned long long pairs = 0, nrows = 0;  // work done by this wave
     int arena_used = 0;
     bool fresh = true;  // the arena was emptied: the next candidate must recompute every row
@@ -199,11 +238,18 @@ __global__ __launch_bounds__(256) void k_dp_tile(dp_tile_args a) {
     // lane n: key of cell (n, L) of the current path, i.e. the result for n+1 stages
     int v_tops = __builtin_amdgcn_readlane(Pl[NT - 1], top_lane);
 
+    auto remember = [&](int top, int at) __attribute__((always_inline)) {
+        if (lane == pending) {
+            v_top = top;
+            if (BANDS != BAND_USE_NOT) v_at = at;
+        }
+    };
+
     // Writes out C and the plans of all pending candidates, one per lane.
     auto flush = [&]() {
         lds_sync();
         const bool live = lane < pending;
-        const long long cq = pend0 + lane;
+        const long long cq = c0 + (BANDS == BAND_USE_NOT ? pend0 + lane : v_at);
         const bool bad = live && v_top < 0;
         if (__ballot(bad) && lane == 0) pp_raise(a.g.status, PP_FAULT_ORDERING);
         // xi = number of stages of the plan read back: S only, or every count 1..S
@@ -235,18 +281,30 @@ __global__ __launch_bounds__(256) void k_dp_tile(dp_tile_args a) {
         for (long long c = c0; c < c1; ++c) {
             const int d = ord[c];
             const bool bad = a.validate && (d < 0 || d >= D);
-            if (lane == pending) v_top = bad ? -1 : key;
+            remember(bad ? -1 : key, (int)(c - c0));
             if (++pending == DPT_PENDING) flush();
         }
         if (pending) flush();
         return;
     }
 
+    // Candidates by their place in the chunk: base .. end - 1 is the piece at hand.
+    const int count = (int)(c1 - c0);
+    const int piece = BANDS == BAND_USE_NOT ? count : (count + ((count + 63) >> 6) - 1) / ((count + 63) >> 6);
+    int base = 0, end_c = count;
+    bool whole_now = whole;
+    auto next = [&](int c) -> int {
+        if (BANDS == BAND_USE_NOT || whole_now) return c + 1;
+        const unsigned long long m = left >> (c - base) >> 1;
+        return m ? c + 1 + __builtin_ctzll(m) : end_c;
+    };
+    const int *ords = ord + c0 * S;
+
     // Lane n carries device o[n] of the candidate (v_o) and the link index o[n-1]*D + o[n]
     // that row n needs (v_link).
     int v_prev = 0;
     bool have_prev = false;
-    int v_o = lane < S ? ord[c0 * S + lane] : 0;
+    int v_o = 0;
 
     // Looks at candidate ordering v (previous valid one in v_prev): returns the first row to
     // compute, or -1 if the ordering is not a list of distinct devices below D.
@@ -280,22 +338,45 @@ __global__ __launch_bounds__(256) void k_dp_tile(dp_tile_args a) {
 
     // prio_until[k]: the last candidate with more than prio_left[k] candidates still to do
     // (itself included)
-    long long prio_until[3];
-    for (int k = 0; k < 3; ++k) prio_until[k] = c1 - 1 - a.prio_left[k];
+    int prio_until[3];
+    for (int k = 0; k < 3; ++k) prio_until[k] = count - 1 - a.prio_left[k];
 
-    // first candidate of the chunk (bad ones are recorded and skipped)
-    long long c = c0;
+    for (; base < count; base = end_c) {
+    end_c = count;
+    whole_now = whole;
+    if (BANDS != BAND_USE_NOT && !whole) {
+        if (BANDS == BAND_USE_ALONE) {
+            end_c = base + piece < count ? base + piece : count;
+            const unsigned long long *at = a.g.left + ((c0 + base) >> 6);
+            const int by = (int)((c0 + base) & 63), n = end_c - base;
+            left = at[0] >> by;
+            if (by + n > 64) left |= at[1] << (64 - by);
+            if (n < 64) left &= (1ull << n) - 1;
+        } else if (!pooled) {
+            end_c = base + piece < count ? base + piece : count;
+            left = finish(c0 + base + lane, base + lane < end_c);
+        }
+        if (!left) continue;
+        whole = 2 * __builtin_popcountll(left) > end_c - base;
+        have_prev = false;
+        arena_used = 0;
+        fresh = true;
+    }
+    // first candidate of the piece (bad ones are recorded and skipped)
+    int c = BANDS == BAND_USE_NOT || whole_now ? base : base + __builtin_ctzll(left);
+    v_o = lane < S ? ords[(long long)c * S + lane] : 0;
     int first = inspect(v_o);
     while (first < 0) {
-        if (lane == pending) v_top = -1;
+        remember(-1, c);
         if (++pending == DPT_PENDING) flush();
-        if (++c >= c1) break;
-        v_o = lane < S ? ord[c * S + lane] : 0;
+        c = next(c);
+        if (c >= end_c) break;
+        v_o = lane < S ? ords[(long long)c * S + lane] : 0;
         first = inspect(v_o);
     }
-    if (c >= c1) {
+    if (c >= end_c) {
         if (pending) flush();
-        return;
+        continue;
     }
     int v_link = links(v_o);
     int xk[NT];
@@ -312,15 +393,16 @@ __global__ __launch_bounds__(256) void k_dp_tile(dp_tile_args a) {
         else if (c <= prio_until[1]) __builtin_amdgcn_s_setprio(2);
         else if (c <= prio_until[0]) __builtin_amdgcn_s_setprio(1);
         else __builtin_amdgcn_s_setprio(0);
-        const bool more = c + 1 < c1;
-        int v_on = (more && lane < S) ? ord[(c + 1) * S + lane] : 0;
+        int c_n = next(c);
+        const bool more = c_n < end_c;
+        int v_on = (more && lane < S) ? ords[(long long)c_n * S + lane] : 0;
         int first_n = -2, v_link_n = 0;  // next candidate: -2 none, -1 bad ordering
         bool flush_after = false;
 
         // candidate finished with key `top` in cell (S-1, L): remember it and the arena rows of
         // its path
         auto finish_candidate = [&](int top) __attribute__((always_inline)) {
-            if (lane == pending) v_top = top;
+            remember(top, c);
             if (lane < S) slots[pending * S + lane] = (unsigned char)v_cur;
             if (stages && lane < S) tops[pending * S + lane] = v_tops;
             ++pending;
@@ -454,12 +536,12 @@ __global__ __launch_bounds__(256) void k_dp_tile(dp_tile_args a) {
         if (flush_after) flush();
         // bad orderings after this candidate are recorded and skipped
         while (first_n == -1) {
-            if (lane == pending) v_top = -1;
+            remember(-1, c_n);
             if (++pending == DPT_PENDING) flush();
-            ++c;
+            c_n = next(c_n);
             first_n = -2;
-            if (c + 1 < c1) {
-                v_on = lane < S ? ord[(c + 1) * S + lane] : 0;
+            if (c_n < end_c) {
+                v_on = lane < S ? ords[(long long)c_n * S + lane] : 0;
                 first_n = inspect(v_on);  // compared with the last valid candidate
                 if (first_n >= 0) {
                     if (arena_used + (S - 1 - first_n) > DPT_ARENA_ROWS || pending + 2 > DPT_PENDING) {
@@ -472,18 +554,21 @@ __global__ __launch_bounds__(256) void k_dp_tile(dp_tile_args a) {
             }
         }
         if (first_n < 0) break;  // no candidate left
-        ++c;
+        c = c_n;
         v_o = v_on;
         v_link = v_link_n;
         first = first_n;
     }
     if (pending) flush();
+    }
     if (lane == 0) pp_count_work(a.g.hdr, pairs, nrows, (unsigned)wave);
 }
 
 template <int NT>
 static int launch_nt(const dp_tile_args &a, int grid, int wpb, size_t lds, hipStream_t st) {
-    hipLaunchKernelGGL(k_dp_tile<NT>, dim3(grid), dim3(64 * wpb), lds, st, a);
+    if (!a.g.band) hipLaunchKernelGGL((k_dp_tile<NT, BAND_USE_NOT>), dim3(grid), dim3(64 * wpb), lds, st, a);
+    else if (a.g.left) hipLaunchKernelGGL((k_dp_tile<NT, BAND_USE_ALONE>), dim3(grid), dim3(64 * wpb), lds, st, a);
+    else hipLaunchKernelGGL((k_dp_tile<NT, BAND_USE_INSIDE>), dim3(grid), dim3(64 * wpb), lds, st, a);
     return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_HIP;
 }
 
@@ -503,6 +588,17 @@ int pp_launch_dp_tile(const dp_tile_args &a, int nt, int grid, int wpb, hipStrea
     size_t lds;
     pp_dp_tile_shape(a.L, a.D, a.S, nt, &lds);
     dp_tile_args b = a;
+    // behind the waves' parts a word per wave and the links' words, where that costs no workgroup
+    const size_t own = ((size_t)wpb * pp_dp_tile_lds_per_wave(a.S, nt) + 15) & ~(size_t)15;
+    auto groups = [&](size_t bytes) { return (int)(160 * 1024 / ((bytes + sizeof(dp_generic_small) + 1279) / 1280 * 1280)); };
+    const size_t words = band_link_bytes(a.D, a.S, a.g.stages), to = own + words > lds ? own + words : lds;
+    b.links_at = 0;
+    const bool inside = a.g.band && !a.g.left;
+    b.pooled = inside && a.chunk < 64 && words && words <= own;
+    if (inside && !b.pooled && words && to <= 64 * 1024 && (groups(to) >= groups(lds) || groups(to) * wpb >= 16)) {
+        b.links_at = (int)own;
+        lds = to;
+    }
     b.g.lds_bytes = lds;
     switch (nt) {
 #define CASE(n) case n: return launch_nt<n>(b, grid, wpb, lds, st);

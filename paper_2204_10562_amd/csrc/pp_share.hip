@@ -7,17 +7,18 @@
 // each), so many links carry the same row X[.], and two candidates whose links have equal rows
 // position by position get the same table, bottleneck and plan.  This file finds those groups
 // on the device:
-//   1. k_share_hash     a hash of every link's forward and backward row (one wave per link),
-//                       and the table of representatives set to "none";
+//   1. k_share_hash     a hash of every link's forward and backward row (one wave per link), the link's
+//                       times packed for the DP, and the table of representatives set to "none";
 //   2. k_share_classes  link i joins the class of the lowest link with the same hash whose rows
-//                       are equal entry by entry (one wave per link);
+//                       are equal entry by entry (one wave per link), and the classes are counted;
 //   3. k_share_keys     classes numbered 0..nc-1; a candidate's key is its sequence of S-1
 //                       class numbers read as a number in base nc (first link most
 //                       significant), and the lowest candidate of every key is kept with an
 //                       atomic min (only if nc^(S-1) fits the table);
 //   4. k_share_count, k_share_reps   the table compacted, in the order of the keys, into the
 //                       list of representatives;
-//   5. k_share_cost, k_share_bounds  the list cut into runs of about equal work, one per wave
+//   5. k_dp_band        (pp_dp_band.hip) finishes the representatives whose few best cells suffice;
+//   6. k_share_cost, k_share_bounds  the others cut into runs of about equal work, one per wave
 //                       of the DP kernel.
 // The DP kernel walks the list - neighbours in it share their first links and with them the
 // first rows of the table - and k_share_scatter hands every representative's results to the
@@ -26,18 +27,23 @@
 //
 // When the keys do not fit the table (every link its own class) there is still something to
 // share: row n depends on the first n + 1 devices only, and a long sampled list holds each
-// choice of the first few devices many times.  The same kernels then sort the candidates by
-// their first k devices (D^k <= table entries; a counting sort: histogram in k_share_keys,
-// bucket offsets in k_share_count / k_share_reps, placement in k_share_place), the list holds
-// all N candidates, and the DP kernel reuses the first k - 1 rows between neighbours.  All decisions are taken on the device; when
-// the keys do not fit the table the kernels return at once and the DP runs over all candidates.
-#include "pp_common.h"
+// choice of the first few devices many times.  What the bands leave of the candidates is then
+// sorted by the first k devices (D^k <= table entries; a counting sort: histogram in k_dp_band
+// before the keys, bucket offsets in k_share_count / k_share_reps, placement in k_dp_band after
+// them), and the DP kernel reuses the first k - 1 rows between neighbours.  All decisions are taken
+// on the device.
+#include "pp_dp_band.h"
+#include "pp_share.h"
 
 struct share_args {
     int L, D, S, validate;
     long long N;
     const long long *XF, *XB;
+    int *x32;                   // [D*D*L] XF + XB (entry k: the cut after k layers)
     const int *ord;
+    dp_args g;                  // what the bands need of it: the tables
+    const int *band;            // the pack kernel's table of the bands, or NULL
+    unsigned long long *links;  // band_links' words
     pp_ws_header *hdr;
     unsigned long long *lhash;  // [D*D]
     int *lrep;                  // [D*D] lowest link with equal rows (-1 on the diagonal)
@@ -45,18 +51,21 @@ struct share_args {
     int *keys;                  // [N] key of every candidate (-1: bad ordering)
     int *reps;                  // [N] representatives (see pp_share_at)
     int *cnt;                   // [PP_SHARE_TABLE / 256] keys in use per 256 table entries
-    int *start;                 // [run_waves + 1] first list entry of every run
+    int *pend;                  // [N] representatives the bands have left
+    int *start;                 // [run_waves + 1] first entry of every run of that list
     int run_waves;
     // arg-min partials to preset (pairs of int64), or NULL
     long long *part;
     long long n_part;
+    // k_share_keys: candidates first_c .. last_c - 1; look: 1 = there are entries of an earlier launch to look at
+    long long first_c, last_c;
+    int look;
     // scatter
     int nC, nB, nT, tw, vec;
     long long *C_out, *T_out;
     int *bounds_out;
 };
 
-#define SHARE_NONE 0x7fffffff
 #define SHARE_FILL_BLOCKS 256
 
 // (a finaliser in the style of splitmix64: multiply, fold the high bits down, twice)
@@ -87,20 +96,37 @@ __global__ __launch_bounds__(256) void k_share_hash(share_args a) {
         a.hdr->share_sorted = 0;
         a.hdr->share_kdev = 0;
         a.hdr->share_nchunks = 0;
+        a.hdr->share_npend = 0;
     }
     const int i = blockIdx.x * 4 + (tid >> 6);
     if (i >= nl) return;
     const int u = i / a.D, v = i - u * a.D;
-    unsigned long long h = 0;
-    if (u != v) {
-        // the entries a plan can read: cut positions 1..L-1, stored at 0..L-2
-        const long long *xf = a.XF + (size_t)i * a.L, *xb = a.XB + (size_t)i * a.L;
-        for (int k = lane; k < a.L - 1; k += 64)
-            h += share_mix(share_mix((unsigned long long)xf[k] + 0x9E3779B97F4A7C15ull * (unsigned)(k + 1)) ^
-                           (unsigned long long)xb[k]);
-        for (int off = 32; off; off >>= 1) h += __shfl_xor(h, off);
+    const long long *xf = a.XF + (size_t)i * a.L, *xb = a.XB + (size_t)i * a.L;
+    int *x32 = a.x32 + (size_t)i * a.L;
+    unsigned long long h = 0, m = 0;
+    bool flat = true;
+    const long long first = xf[0] + xb[0];
+    // the entries a plan can read: cut positions 1..L-1, stored at 0..L-2
+    for (int k = lane; k < a.L - 1; k += 64) {
+        const long long f = xf[k], b = xb[k], x = f + b;
+        h += share_mix(share_mix((unsigned long long)f + 0x9E3779B97F4A7C15ull * (unsigned)(k + 1)) ^ (unsigned long long)b);
+        x32[k + 1] = (int)x;
+        flat &= x == first;
+        const unsigned long long ux = x < 0 ? ~0ull : (unsigned long long)x;
+        m = ux > m ? ux : m;
     }
-    if (lane == 0) a.lhash[i] = h;
+    for (int off = 32; off; off >>= 1) {
+        h += __shfl_xor(h, off);
+        const unsigned long long o = __shfl_xor(m, off);
+        m = o > m ? o : m;
+    }
+    const bool all_flat = __ballot(!flat) == 0;
+    if (lane == 0) {
+        x32[0] = 0;
+        a.lhash[i] = u != v ? h : 0;
+        atomicMax(&a.hdr->pmax[i & (PP_PACK_BLOCKS - 1)], m);
+        if (!all_flat) a.hdr->flat[i & (PP_PACK_BLOCKS - 1)] = 0;  // (set everywhere by the pack kernel)
+    }
 }
 
 __global__ __launch_bounds__(256) void k_share_classes(share_args a) {
@@ -112,6 +138,7 @@ __global__ __launch_bounds__(256) void k_share_classes(share_args a) {
         if (lane == 0) a.lrep[i] = -1;
         return;
     }
+    if (a.band) band_link_wave(a.g, a.band, i, a.links);
     const unsigned long long h = a.lhash[i];
     int rep = i;
     for (int base = 0; base < i && rep == i; base += 64) {
@@ -132,25 +159,46 @@ __global__ __launch_bounds__(256) void k_share_classes(share_args a) {
             }
         }
     }
-    if (lane == 0) a.lrep[i] = rep;
+    if (lane == 0) {
+        a.lrep[i] = rep;
+        if (rep == i) atomicAdd(&a.hdr->share_nc, 1u);
+    }
 }
+
+// Candidates of a workgroup and their keys' slots in LDS (k_share_keys, first launch).
+#define SHARE_OWN 1024
+#define SHARE_SLOT_BITS 11
+#define SHARE_SLOTS (1 << SHARE_SLOT_BITS)
 
 __global__ __launch_bounds__(256) void k_share_keys(share_args a) {
     __shared__ int s_cls[PP_SHARE_MAX_D * PP_SHARE_MAX_D];
-    __shared__ int s_cnt[256];
+    __shared__ int s_cnt[4], s_key[SHARE_SLOTS], s_low[SHARE_SLOTS];
     const int nl = a.D * a.D, D = a.D, S = a.S, tid = threadIdx.x;
+    const unsigned nc = a.hdr->share_nc, tsize = share_table_size(nc, S);
+    // otherwise: buckets of the first kdev devices (pp_dp_band.hip)
+    int kdev = 0;
+    unsigned nbuck = 1;
+    if (!tsize && a.band) nbuck = share_buckets(D, S, kdev);  // (not worth it for less than a wave of candidates)
+    if (blockIdx.x == 0 && tid == 0) {
+        a.hdr->share_tsize = tsize ? tsize : (kdev ? nbuck : 0);
+        a.hdr->share_active = tsize != 0;
+        a.hdr->share_sorted = kdev != 0;
+        a.hdr->share_kdev = (unsigned)kdev;
+    }
+    if (!tsize) return;
     // class numbers: the rank of a link's representative among the representatives
     const int per = (nl + 255) / 256, lo = tid * per, hi = lo + per < nl ? lo + per : nl;
     int cnt = 0;
     for (int i = lo; i < hi; ++i) cnt += a.lrep[i] == i;
-    s_cnt[tid] = cnt;
-    __syncthreads();
-    int before = 0, nc = 0;
-    for (int t = 0; t < 256; ++t) {
-        const int v = s_cnt[t];
-        before += t < tid ? v : 0;
-        nc += v;
+    int before = cnt;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(before, off);
+        before += (tid & 63) >= off ? o : 0;
     }
+    if ((tid & 63) == 63) s_cnt[tid >> 6] = before;
+    __syncthreads();
+    before -= cnt;
+    for (int w = 0; w < tid >> 6; ++w) before += s_cnt[w];
     for (int i = lo; i < hi; ++i)
         if (a.lrep[i] == i) s_cls[i] = before++;
     __syncthreads();
@@ -162,80 +210,61 @@ __global__ __launch_bounds__(256) void k_share_keys(share_args a) {
     __syncthreads();
     for (int i = lo; i < hi; ++i) s_cls[i] = mine[i - lo];
     __syncthreads();
-    // keys are S-1 digits in base nc
-    unsigned tsize = 1;
-    for (int n = 1; n < S; ++n) {
-        const unsigned long long t = (unsigned long long)tsize * (unsigned)nc;
-        tsize = t <= PP_SHARE_TABLE ? (unsigned)t : 0;
-    }
-    if (nc == 0) tsize = S > 1 ? 0 : 1;
-    // otherwise: buckets of the first kdev devices (at least two, or there is no row to share)
-    int kdev = 0;
-    unsigned nbuck = 1;
-    if (!tsize) {
-        while (kdev < S && (unsigned long long)nbuck * (unsigned)D <= PP_SHARE_TABLE) { nbuck *= (unsigned)D; ++kdev; }
-        if (kdev < 2 || S < 3) kdev = 0;
-    }
-    if (blockIdx.x == 0 && tid == 0) {
-        a.hdr->share_nc = (unsigned)nc;
-        a.hdr->share_tsize = tsize ? tsize : (kdev ? nbuck : 0);
-        a.hdr->share_active = tsize != 0;
-        a.hdr->share_sorted = kdev != 0;
-        a.hdr->share_kdev = (unsigned)kdev;
-    }
     const bool vec = (S & 3) == 0 && ((uintptr_t)a.ord & 15) == 0;
-    if (!tsize) {
-        if (!kdev) return;
-        // histogram of the buckets (the table starts at SHARE_NONE everywhere: counts are taken
-        // relative to that, in unsigned arithmetic)
-        for (long long c = (long long)blockIdx.x * 256 + tid; c < a.N; c += (long long)gridDim.x * 256) {
-            const int *row = a.ord + c * S;
-            unsigned key = 0;
-            for (int n = 0; n < kdev; ++n) {
-                int d = row[n];
-                d = (d < 0 || d >= D) ? 0 : d;  // (a bad row is found by the DP kernel; any bucket will do)
-                key = key * (unsigned)D + (unsigned)d;
-            }
-            a.keys[c] = (int)key;
-            atomicAdd((unsigned *)&a.table[key], 1u);
-        }
-        return;
+    // The first launch takes SHARE_OWN neighbours per workgroup and keeps the lowest of every key in LDS first: a
+    // key that many candidates have (3.5 % of sampled orderings of 4 servers of 4 devices never stay on a server)
+    // would have their atomics queue on its address.  What it has left can be looked at through the caches by
+    // the launch for the rest of the list, and is lower than any candidate there.
+    if (!a.look) {
+        for (int i = tid; i < SHARE_SLOTS; i += 256) { s_key[i] = -1; s_low[i] = SHARE_NONE; }
+        __syncthreads();
     }
-    for (long long c = (long long)blockIdx.x * 256 + tid; c < a.N; c += (long long)gridDim.x * 256) {
+    const long long from = a.first_c + (a.look ? (long long)blockIdx.x * 256 : (long long)blockIdx.x * SHARE_OWN) + tid;
+    const long long to = a.look ? a.last_c : (from - tid + SHARE_OWN < a.last_c ? from - tid + SHARE_OWN : a.last_c);
+    const long long step = a.look ? (long long)gridDim.x * 256 : 256;
+    for (long long c = from; c < to; c += step) {
         const int *row = a.ord + c * S;
         unsigned long long used = 0;
         unsigned key = 0;
         bool bad = false;
         int prev = 0;
-        auto step = [&](int n, int d) {
+        auto place = [&](int n, int d) {
             if (a.validate) {
                 if (d < 0 || d >= D) { bad = true; d = 0; }
                 bad |= (used >> d) & 1;
                 used |= 1ull << d;
             }
-            if (n) key = key * (unsigned)nc + (unsigned)s_cls[prev * D + d];
+            if (n) key = key * nc + (unsigned)s_cls[prev * D + d];
             prev = d;
         };
         if (vec) {
             // (a row is S devices of 4 bytes: 16 bytes at a time where rows are so aligned)
             for (int n = 0; n < S; n += 4) {
                 const int4 v = *(const int4 *)(row + n);
-                step(n, v.x); step(n + 1, v.y); step(n + 2, v.z); step(n + 3, v.w);
+                place(n, v.x); place(n + 1, v.y); place(n + 2, v.z); place(n + 3, v.w);
             }
         } else {
-            for (int n = 0; n < S; ++n) step(n, row[n]);
+            for (int n = 0; n < S; ++n) place(n, row[n]);
         }
         if (bad) {
             a.keys[c] = -1;
             a.reps[a.N - 1 - atomicAdd(&a.hdr->share_nbad, 1u)] = (int)c;
-        } else {
-            a.keys[c] = (int)key;
-            // (most candidates of a common key arrive after a lower one: a look first spares
-            // the atomic, which would queue behind all others on the same address)
-            if (__hip_atomic_load(&a.table[key], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > (int)c)
-                atomicMin(&a.table[key], (int)c);
+            continue;
         }
+        a.keys[c] = (int)key;
+        if (a.look) {
+            if (a.table[key] > (int)c) atomicMin(&a.table[key], (int)c);
+            continue;
+        }
+        const int slot = (int)((key * 2654435761u) >> (32 - SHARE_SLOT_BITS));
+        const int was = atomicCAS(&s_key[slot], -1, (int)key);
+        if (was == -1 || was == (int)key) atomicMin(&s_low[slot], (int)c);
+        else atomicMin(&a.table[key], (int)c);  // (another key has the slot)
     }
+    if (a.look) return;
+    __syncthreads();
+    for (int i = tid; i < SHARE_SLOTS; i += 256)
+        if (s_key[i] >= 0) atomicMin(&a.table[s_key[i]], s_low[i]);
 }
 
 // Keys in use in every block of 256 table entries.
@@ -243,6 +272,7 @@ __global__ __launch_bounds__(256) void k_share_count(share_args a) {
     __shared__ int sh[4];
     const unsigned tsize = a.hdr->share_tsize;
     const unsigned key = blockIdx.x * 256u + threadIdx.x;
+    if (a.hdr->share_sorted && !a.hdr->share_npend) return;  // (the bands have left none)
     int n;
     if (a.hdr->share_sorted) {
         // candidates in the bucket
@@ -268,6 +298,7 @@ __global__ __launch_bounds__(256) void k_share_reps(share_args a) {
     }
     const unsigned tsize = a.hdr->share_tsize;
     if (blockIdx.x * 256u >= tsize && blockIdx.x) return;
+    if (a.hdr->share_sorted && !a.hdr->share_npend) return;
     // keys in use before this block's (block 0: in all blocks, for the header)
     const int upto = blockIdx.x ? (int)blockIdx.x : PP_SHARE_TABLE / 256;
     int sum = 0;
@@ -285,8 +316,7 @@ __global__ __launch_bounds__(256) void k_share_reps(share_args a) {
     const int base = blockIdx.x ? before : 0;
     const unsigned key = blockIdx.x * 256u + tid;
     if (a.hdr->share_sorted) {
-        // every bucket's first position in the list (k_share_place hands the positions out)
-        if (blockIdx.x == 0 && tid == 0) a.hdr->share_nsorted = a.hdr->share_nreps = (unsigned)a.N;
+        // every bucket's first position in the list (k_dp_band hands the positions out)
         const int n = key < tsize ? (int)((unsigned)a.table[key] - (unsigned)SHARE_NONE) : 0;
         int incl = n;
         for (int off = 1; off < 64; off <<= 1) {
@@ -313,10 +343,13 @@ __global__ __launch_bounds__(256) void k_share_reps(share_args a) {
 // Work of representative r of the sorted list when it follows r - 1 in a run: the rows its key
 // does not share with its predecessor's (at least the last one), plus one row's worth for what
 // a candidate costs besides its rows.  A run's first entry computes all S - 1 rows.
+// (One that has ended already costs nothing.)
 __device__ __forceinline__ int share_cost(const share_args &a, long long r) {
     const int S = a.S;
+    const unsigned key = (unsigned)a.keys[a.reps[r]];
+    if (key & SHARE_ENDED) return 0;
     if (r == 0 || S < 3) return S;
-    const unsigned key = (unsigned)a.keys[a.reps[r]], prev = (unsigned)a.keys[a.reps[r - 1]];
+    const unsigned prev = (unsigned)a.keys[a.reps[r - 1]] & ~(unsigned)SHARE_ENDED;
     const unsigned nc = a.hdr->share_nc;
     unsigned pw = a.hdr->share_tsize / nc;  // weight of the first digit
     int p = 0;
@@ -324,76 +357,83 @@ __device__ __forceinline__ int share_cost(const share_args &a, long long r) {
     return S - p;
 }
 
-// Sum of share_cost over every 256 entries of the sorted list (cnt is free again by now).
+// Sum of share_cost over every 256 entries of the sorted list (cnt is free again by now), and in the bits from
+// SHARE_LEFT on how many of them are left to the DP kernel.
+#define SHARE_LEFT 20
 __global__ __launch_bounds__(256) void k_share_cost(share_args a) {
     __shared__ int sh[4];
     if (!a.hdr->share_active) return;
     const long long r = (long long)blockIdx.x * 256 + threadIdx.x;
     int c = r < (long long)a.hdr->share_nsorted ? share_cost(a, r) : 0;
+    c |= (c != 0) << SHARE_LEFT;
     for (int off = 32; off; off >>= 1) c += __shfl_xor(c, off);
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = c;
     __syncthreads();
     if (threadIdx.x == 0) a.cnt[blockIdx.x] = sh[0] + sh[1] + sh[2] + sh[3];
 }
 
-// Cuts the sorted list into runs of about total / run_waves work each (never less than S + 1, so
-// that the running sum crosses at most one boundary per entry): start[w] = first entry of run w.
+// The representatives that are left, in the order of the list, cut into runs of about total / run_waves work
+// each (never less than S + 1, so that the running sum crosses at most one boundary per entry): start[w] = first
+// entry of run w.
 __global__ __launch_bounds__(256) void k_share_bounds(share_args a) {
     __shared__ long long sh[4], s_excl[256];
+    __shared__ int shp[4], sht[4];
     if (!a.hdr->share_active) return;
     const int tid = threadIdx.x, lane = tid & 63, wib = tid >> 6;
     const long long ns = a.hdr->share_nsorted;
-    if (ns == 0) {
-        if (blockIdx.x == 0 && tid == 0) { a.hdr->share_nchunks = 0; a.start[0] = 0; }
-        return;
-    }
     if ((long long)blockIdx.x * 256 >= ns) return;
-    // work before this block, and in all
-    const int nblk = (int)((ns + 255) / 256);
+    // work and entries before this block, and in all
+    const int nblk = (int)((ns + 255) / 256), low = (1 << SHARE_LEFT) - 1;
     long long before = 0, total = 0;
+    int left_before = 0, left_total = 0;
     for (int i = tid; i < nblk; i += 256) {
-        const int v = a.cnt[i];
+        const int v = a.cnt[i] & low, p = a.cnt[i] >> SHARE_LEFT;
         total += v;
+        left_total += p;
         before += i < (int)blockIdx.x ? v : 0;
+        left_before += i < (int)blockIdx.x ? p : 0;
     }
-    for (int off = 32; off; off >>= 1) { before += __shfl_xor(before, off); total += __shfl_xor(total, off); }
-    if (lane == 0) { sh[wib] = before; s_excl[wib] = total; }
+    for (int off = 32; off; off >>= 1) {
+        before += __shfl_xor(before, off); total += __shfl_xor(total, off);
+        left_before += __shfl_xor(left_before, off); left_total += __shfl_xor(left_total, off);
+    }
+    if (lane == 0) { sh[wib] = before; s_excl[wib] = total; shp[wib] = left_before; sht[wib] = left_total; }
     __syncthreads();
     before = sh[0] + sh[1] + sh[2] + sh[3];
     total = s_excl[0] + s_excl[1] + s_excl[2] + s_excl[3];
+    left_before = shp[0] + shp[1] + shp[2] + shp[3];
+    left_total = sht[0] + sht[1] + sht[2] + sht[3];
+    if (!total) return;  // (share_nchunks and share_npend are 0)
     __syncthreads();
     long long quota = (total + a.run_waves - 1) / a.run_waves;
     quota = quota > a.S + 1 ? quota : a.S + 1;
     const long long r = (long long)blockIdx.x * 256 + tid;
     const int c = r < ns ? share_cost(a, r) : 0;
+    const unsigned long long left = __ballot(c != 0);
     long long incl = c;
     for (int off = 1; off < 64; off <<= 1) {
         const long long o = __shfl_up(incl, off);
         incl += lane >= off ? o : 0;
     }
-    if (lane == 63) sh[wib] = incl;
+    if (lane == 63) { sh[wib] = incl; shp[wib] = __builtin_popcountll(left); }
     __syncthreads();
     long long excl = before + incl - c;
-    for (int w = 0; w < wib; ++w) excl += sh[w];
+    int at = left_before + __builtin_popcountll(left & ((1ull << lane) - 1));
+    for (int w = 0; w < wib; ++w) { excl += sh[w]; at += shp[w]; }
     s_excl[tid] = excl;
     __syncthreads();
     if (r >= ns) return;
+    if (c) a.pend[at] = a.reps[r];
     const long long id = excl / quota;
     long long id_prev = -1;
     if (tid) id_prev = s_excl[tid - 1] / quota;
     else if (r) id_prev = (excl - share_cost(a, r - 1)) / quota;
-    if (id != id_prev) a.start[id] = (int)r;
+    if (id != id_prev) a.start[id] = at;
     if (r == ns - 1) {
-        a.start[id + 1] = (int)ns;
+        a.start[id + 1] = left_total;
         a.hdr->share_nchunks = (unsigned)(id + 1);
+        a.hdr->share_npend = (unsigned)left_total;
     }
-}
-
-// Counting sort, last step: every candidate takes the next free position of its bucket.
-__global__ __launch_bounds__(256) void k_share_place(share_args a) {
-    if (!a.hdr->share_sorted) return;
-    for (long long c = (long long)blockIdx.x * 256 + threadIdx.x; c < a.N; c += (long long)gridDim.x * 256)
-        a.reps[atomicAdd(&a.table[a.keys[c]], 1)] = (int)c;
 }
 
 // Every candidate that is not the representative of its key takes the representative's
@@ -403,7 +443,7 @@ __global__ __launch_bounds__(256) void k_share_scatter(share_args a) {
     for (long long c = (long long)blockIdx.x * 256 + threadIdx.x; c < a.N; c += (long long)gridDim.x * 256) {
         const int key = a.keys[c];
         if (key < 0) continue;
-        const long long r = a.table[key];
+        const long long r = a.table[key & ~SHARE_ENDED];
         if (r == c) continue;
         for (int i = 0; i < a.nC; ++i) a.C_out[c * a.nC + i] = a.C_out[r * a.nC + i];
         for (int q = 0; q < a.nT; ++q)
@@ -429,6 +469,7 @@ static share_args share_base(void *ws, const pp_ws_layout &lay) {
     a.reps = (int *)(base + lay.sh_reps);
     a.cnt = (int *)(base + lay.sh_cnt);
     a.start = (int *)(base + lay.sh_start);
+    a.pend = (int *)(base + lay.T);  // (T is written once the plans are there)
     return a;
 }
 
@@ -437,26 +478,45 @@ static long long share_grid(int64_t N) {
     return g < 4096 ? g : 4096;
 }
 
-int pp_launch_share_prepare(int L, int D, int S, int64_t N, const int64_t *XF, const int64_t *XB,
-                            const int32_t *ord, int validate, int fill_part, int run_waves, void *ws,
-                            const pp_ws_layout &lay, hipStream_t st) {
+int pp_launch_share_prepare(const dp_args &g, int fill_part, int run_waves, void *ws, const pp_ws_layout &lay,
+                            hipStream_t st) {
     if (!lay.sh_table || run_waves < 1 || run_waves > PP_DP_SLOTS) return PP_ERR_INVALID_ARG;
     share_args a = share_base(ws, lay);
+    const int D = g.D;
+    const long long N = g.N;
     if (fill_part) {
         a.part = (long long *)((char *)ws + lay.part);
         a.n_part = (long long)((N + 63) / 64) * PP_MAX_M_LIST;
     }
-    a.L = L; a.D = D; a.S = S; a.N = N; a.validate = validate;
-    a.XF = (const long long *)XF; a.XB = (const long long *)XB;
-    a.ord = ord;
+    a.L = g.L; a.D = D; a.S = g.S; a.N = N; a.validate = g.validate;
+    a.XF = g.XF; a.XB = g.XB;
+    a.x32 = (int *)((char *)ws + lay.x32);
+    a.ord = g.ord;
     a.run_waves = run_waves;
+    a.g = g;
+    a.band = g.band;
+    // (the saved rows of 64 waves and more, S - 1 of 1040 bytes and more each, hold 8 (S - 1) bytes per link of up
+    // to 64 devices, and are needed later)
+    a.links = (unsigned long long *)((char *)ws + lay.sh_rows);
     const int link_blocks = (D * D + 3) / 4;
     hipLaunchKernelGGL(k_share_hash, dim3(link_blocks + SHARE_FILL_BLOCKS), dim3(256), 0, st, a);
     hipLaunchKernelGGL(k_share_classes, dim3(link_blocks), dim3(256), 0, st, a);
-    hipLaunchKernelGGL(k_share_keys, dim3((unsigned)share_grid(N)), dim3(256), 0, st, a);
+    int rc = a.band ? pp_launch_dp_band(g, a.band, a.links, a.keys, a.table, a.reps, 1, st) : PP_OK;
+    if (rc) return rc;
+    // The keys of a long list in two launches, the first eighth alone: 10^6 candidates of 15 751 keys 87 us when
+    // every candidate looks past the caches and does its own atomic, 57 us so.
+    const long long first = N > 200000 ? N / 8 : N;
+    a.first_c = 0; a.last_c = first; a.look = 0;
+    hipLaunchKernelGGL(k_share_keys, dim3((unsigned)((first + SHARE_OWN - 1) / SHARE_OWN)), dim3(256), 0, st, a);
+    if (first < N) {
+        const long long g = share_grid(N - first);
+        a.first_c = first; a.last_c = N; a.look = 1;
+        hipLaunchKernelGGL(k_share_keys, dim3((unsigned)(g < 2048 ? g : 2048)), dim3(256), 0, st, a);
+    }
     hipLaunchKernelGGL(k_share_count, dim3(PP_SHARE_TABLE / 256), dim3(256), 0, st, a);
     hipLaunchKernelGGL(k_share_reps, dim3(PP_SHARE_TABLE / 256), dim3(256), 0, st, a);
-    hipLaunchKernelGGL(k_share_place, dim3((unsigned)share_grid(N)), dim3(256), 0, st, a);
+    rc = a.band ? pp_launch_dp_band(g, a.band, a.links, a.keys, a.table, a.reps, 0, st) : PP_OK;
+    if (rc) return rc;
     hipLaunchKernelGGL(k_share_cost, dim3((unsigned)share_grid(N)), dim3(256), 0, st, a);
     hipLaunchKernelGGL(k_share_bounds, dim3((unsigned)share_grid(N)), dim3(256), 0, st, a);
     return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_HIP;

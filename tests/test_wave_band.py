@@ -1,0 +1,51 @@
+"""The partition from a few cells of every row, run lane by lane on the CPU (its own sources, with
+UndefinedBehaviorSanitizer) against the recursion over all splits: every candidate it finishes has the true
+values and the lowest split among equal ones, with and without the links' words, for every number of stages."""
+import os
+import subprocess
+
+import pytest
+
+from test_wave_makespan import build
+
+pytestmark = pytest.mark.skipif(__import__("shutil").which("g++") is None, reason="needs g++")
+
+FREE, ZEROS, TIES, OUTLIER, EQUAL, SOME, MOST, HIGH = range(8)
+SIZES = [(3, 2, 2, 64), (5, 5, 5, 70), (17, 8, 8, 65), (64, 9, 2, 64), (40, 33, 33, 66), (88, 12, 11, 64), (128, 8, 8, 130),
+         (200, 7, 7, 64), (321, 20, 16, 64), (130, 64, 64, 64)]
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    exe = build(tmp_path_factory.mktemp("band"), "band_driver")
+
+    def ask(cases):
+        env = dict(os.environ)
+        env.pop("LD_PRELOAD", None)  # the sanitizer's runtime must come first in the library list
+        res = subprocess.run([exe], input="".join(" ".join(str(x) for x in c) + "\n" for c in cases),
+                             stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=600, env=env)
+        assert res.returncode == 0 and "runtime error" not in res.stderr, res.stderr[-2000:]
+        out = [[int(x) for x in l.split()] for l in res.stdout.splitlines()]
+        assert len(out) == len(cases)
+        return out
+    return ask
+
+
+@pytest.mark.parametrize("kind", [FREE, ZEROS, TIES, OUTLIER, EQUAL, SOME, MOST, HIGH])
+def test_bands_lane_by_lane(driver, kind):
+    cases = [(L, D, S, N, L + S, kind, stages, words) for L, D, S, N in SIZES for stages in (0, 1) for words in (0, 1)
+             if not (stages and S > 33)]
+    ended = 0
+    for case, (rc, status, differ, done, reported) in zip(cases, driver(cases)):
+        N = case[3]
+        assert rc == 0 and differ == 0, case
+        if kind == FREE:
+            # links that never bind: every candidate ends; the bad ordering is reported
+            assert (done, reported) == (N - 1, 1) and status != 0, case
+        else:
+            assert status == 0, case
+        ended += done
+    # links that bind in some rows or all leave candidates to the other kernels, but not all of them
+    assert ended > 0
+    if kind in (SOME, MOST):
+        assert ended < sum(c[3] for c in cases)

@@ -1,0 +1,122 @@
+// Runs the partition from a few cells per row (pp_dp_band.h, its own source) on the CPU: the block that finds the
+// bands, the words of the links, and the pass over the candidates.  Reads cases from stdin, one per line:
+//   L D S N SEED KIND STAGES WORDS
+// KIND: what the layer and transfer times look like (below); STAGES: plans of every number of stages; WORDS: whether
+// the words of the links are there.  Prints, per case, the return value, the status, how many results of the
+// candidates that ended differ from the recursion over all splits, how many ended, and how many candidates with a
+// bad ordering were reported.
+#include "../../paper_2204_10562_amd/csrc/pp_dp_band_table.h"
+#include "../../paper_2204_10562_amd/csrc/pp_dp_band.hip"
+
+#include <string.h>
+
+#include <algorithm>
+#include <random>
+
+alignas(16) unsigned char smem[64 * 1024];  // the kernels' LDS
+alignas(16) long long dyn[8 * 1024];
+
+static void k_band_table(band_table_args a) { band_table(a, (unsigned char *)dyn); }
+
+typedef long long ll;
+
+int main() {
+    int L, D, S, N, seed, kind, stages, words;
+    while (scanf("%d %d %d %d %d %d %d %d", &L, &D, &S, &N, &seed, &kind, &stages, &words) == 8) {
+        std::mt19937_64 g(seed);
+        auto upto = [&](ll n) { return (ll)(g() % (unsigned long long)(n + 1)); };
+        std::vector<ll> PF(L + 1), PB(L + 1, 0), P(L + 1);
+        std::vector<ll> XF((size_t)D * D * L), XB((size_t)D * D * L, 0);
+        for (int l = 0; l < L; ++l) {
+            ll t = 50 + upto(950);
+            if (kind == 1 && upto(2) == 0) t = 0;                  // a third of the layers of length zero
+            if (kind == 2) t = 1 + upto(2);                        // ties everywhere
+            if (kind == 3 && l == L / 2) t = 40000;                // one layer outweighs the others
+            if (kind == 4) t = 100;                                // equal layers
+            PF[l + 1] = P[l + 1] = P[l] + t;
+        }
+        const ll top = P[L] / S + 1;
+        for (int i = 0; i < D * D; ++i)
+            for (int k = 0; k < L; ++k) {
+                ll x = upto(top / 2);
+                if (kind == 5) x = upto(top + top / 2);            // links that bind now and then
+                if (kind == 6) x = upto(4 * top);                  // and nearly everywhere
+                if (kind == 7) x = top / 2 + upto(top);
+                XF[(size_t)i * L + k] = x;
+            }
+        std::vector<int> ord((size_t)N * S);
+        for (int c = 0; c < N; ++c) {
+            std::vector<int> dev(D);
+            for (int i = 0; i < D; ++i) dev[i] = i;
+            std::shuffle(dev.begin(), dev.end(), g);
+            std::copy(dev.begin(), dev.begin() + S, ord.begin() + (size_t)c * S);
+        }
+        const int bad = N / 3;
+        if (kind == 0) ord[(size_t)bad * S + S - 1] = ord[(size_t)bad * S];
+        static pp_ws_header hdr;
+        memset(&hdr, 0, sizeof hdr);
+        ll vmax = P[L];
+        for (ll x : XF) vmax = std::max(vmax, x);
+        hdr.pmax[3] = (unsigned long long)vmax;
+        std::vector<int> p32(L + 17, (int)P[L]), x32((size_t)D * D * L + 129, 0x55555555);
+        for (int l = 0; l <= L; ++l) p32[l] = (int)P[l];
+        for (size_t i = 0; i < (size_t)D * D * L; ++i) x32[i] = i % L ? (int)XF[i - 1] : 0;
+        const int tri = stages ? S * (S + 1) / 2 : S, nc = stages ? S : 1;
+        std::vector<int> table((size_t)S * 700, 0x7abcdef);
+        std::vector<unsigned long long> links(band_link_words(D, S, stages)), left((N + 63) / 64);
+        std::vector<ll> C((size_t)N * nc, -7);
+        std::vector<int> bounds((size_t)N * tri + 4, -7);
+        int status = 0;
+        band_table_args p = {};
+        p.L = L; p.D = D; p.S = S; p.K = pp_index_bits(L);
+        p.PF = PF.data(); p.PB = PB.data(); p.XF = XF.data(); p.XB = XB.data();
+        p.table = table.data(); p.stages = stages;
+        p.fit_limit = (1ull << (31 - p.K)) - 1;
+        const size_t need = band_table_lds(L, S, stages, p.waves);
+        if (need > sizeof dyn) return 1;
+        memset(dyn, seed & 255, sizeof dyn);
+        memset(smem, seed & 255, sizeof smem);
+        wave::launch(k_band_table, dim3(1), dim3(256), need, p);
+        dp_args a = {};
+        a.L = L; a.D = D; a.S = S; a.K = p.K; a.N = N;
+        a.validate = 1;
+        a.fit_limit = p.fit_limit;
+        a.hdr = &hdr; a.p32 = p32.data(); a.x32 = x32.data(); a.ord = ord.data();
+        a.stages = stages; a.C_out = C.data(); a.bounds_out = bounds.data(); a.status = &status;
+        a.band = table.data();
+        const int rc = pp_launch_dp_band_alone(a, words ? links.data() : NULL, left.data(), NULL);
+        int differ = 0, ended = 0, reported = 0;
+        for (int c = 0; c < N; ++c) {
+            // (without bands the pass does nothing, and the kernel behind it looks at nothing it has left)
+            if (table[band_top_at(S, 0, S)] < 0 || (left[c >> 6] >> (c & 63) & 1)) continue;
+            if (kind == 0 && c == bad) {
+                reported += C[(size_t)c * nc] == INT64_MAX;
+                continue;
+            }
+            ++ended;
+            std::vector<std::vector<ll>> W(S, std::vector<ll>(L + 1));
+            std::vector<std::vector<int>> A(S, std::vector<int>(L + 1));
+            W[0] = P;
+            for (int n = 1; n < S; ++n)
+                for (int l = 0; l <= L; ++l) {
+                    W[n][l] = INT64_MAX;
+                    for (int k = n; k < l; ++k) {
+                        const ll x = x32[((size_t)ord[(size_t)c * S + n - 1] * D + ord[(size_t)c * S + n]) * L + k];
+                        const ll v = std::max(std::max(W[n - 1][k], x), P[l] - P[k]);
+                        if (v < W[n][l]) { W[n][l] = v; A[n][l] = k; }
+                    }
+                }
+            for (int xi = stages ? 1 : S; xi <= S; ++xi) {
+                differ += C[(size_t)c * nc + (stages ? xi - 1 : 0)] != W[xi - 1][L];
+                const int *b = &bounds[(size_t)c * tri + (stages ? xi * (xi - 1) / 2 : 0)];
+                for (int n = xi - 1, e = L; n >= 0; --n) {
+                    differ += b[n] != e;
+                    e = A[n][e];
+                }
+            }
+        }
+        printf("%d %d %d %d %d\n", rc, status, differ, ended, reported);
+        fflush(stdout);
+    }
+    return 0;
+}
