@@ -13,6 +13,9 @@
 // The listing scans l' ascending, then r' ascending, and replaces its best only on strict
 // improvement: the minimiser kept is the first in (l', r') order.
 //
+// Where the cells that a good plan can use are few, k_prm_band (pp_prm_band.hip) has planned the launch when this
+// kernel starts; it does the others.
+//
 // One workgroup of two waves per candidate (persistent over candidates), one lane per cell l.  State
 // (xi, r, i) depends only on states with fewer GPUs, so states are visited by ascending i, and with
 // int32 values each wave does half of the states of an i on its own, without barriers.
@@ -38,35 +41,13 @@
 // it (L = 8, where one wave was idle: 3.2 -> 2.2 ms).
 #include "pp_common.h"
 #include "pp_dp_row.h"
+#include "pp_prm.h"
 
 #define PRM_THREADS 128
 // Fewest layers for which a cell's split is searched rather than scanned for (int32 values).  All
 // 40320 orderings of 8 GPUs, whole call, scan / search in ms: 2.60 / 2.65 at L = 32, 2.80 / 2.73 at
 // 48, 2.99 / 2.87 at 64, 4.29 / 3.68 at 72 (a second chunk of positions), 4.82 / 3.85 at 112.
 #define PRM_SEARCH_MIN_L 40
-
-struct prm_args {
-    int L, D, M;
-    int search;  // nonzero: the launch has LDS for the minima apart from the records
-    long long N;
-    const long long *fwd, *bwd, *actf, *actb, *alpha, *bw;
-    const int *ord;  // [N][D]
-    char *scratch;   // slots * slot_bytes
-    size_t slot_bytes;
-    long long *W_out;  // [N][D]: W of the best plan with xi stages at xi-1 (PP_INF64: none)
-    int *bounds_out;   // [N][D(D+1)/2]
-    int *reps_out;     // [N][D(D+1)/2]
-    long long *pre_out;  // [3][L+1]: prefix sums of fwd, bwd, alpha for the kernels that follow
-    int32_t *status;
-};
-
-__host__ __device__ static inline int prm_states(int D) { return D * (D + 1) * (D + 2) / 6; }
-
-// Index of state (i GPUs, xi stages, r replicas of the last stage), 1 <= xi <= i,
-// 1 <= r <= i - xi + 1.
-__host__ __device__ static inline int prm_sid(int i, int xi, int r) {
-    return (i - 1) * i * (i + 1) / 6 + (xi - 1) * (i + 1) - xi * (xi - 1) / 2 + (r - 1);
-}
 
 // Bytes of per-workgroup scratch: W and the minimising (l', r') of every state and cell, and
 // the minima of the bandwidth matrix over rank sets.
@@ -98,27 +79,6 @@ __device__ __forceinline__ bool prm_less(const prm_key &a, const prm_key &b) {
     if (a.v != b.v) return a.v < b.v;
     if (a.lp != b.lp) return a.lp < b.lp;
     return a.rp < b.rp;
-}
-
-__device__ __forceinline__ long long cdiv64(long long a, long long b) { return a / b + (a % b != 0); }
-
-// Quotients of whole numbers below 2^53 by double arithmetic (instead of 64-bit integer division,
-// about 100 instructions each and 14 % of the kernel's).  `inv` is the reciprocal
-// of den to 40 bits or more and the quotient is below 2^31, so the truncated product is off by one
-// at most; the remainder (exact by the fused multiply-add) says which way.
-__device__ __forceinline__ double prm_inv(double den) {
-    const double r = __builtin_amdgcn_rcp(den);
-    return __builtin_fma(r, __builtin_fma(-den, r, 1.0), r);
-}
-__device__ __forceinline__ int prm_ceil_div(double a, double den, double inv) {
-    const double q = __builtin_trunc(a * inv), rem = __builtin_fma(-q, den, a);
-    return (int)q + (rem > 0.0) + (rem > den);
-}
-__device__ __forceinline__ int prm_floor_div(double a, double den, double inv, int &rest) {
-    const double q = __builtin_trunc(a * inv), rem = __builtin_fma(-q, den, a);
-    const int up = rem >= den, down = rem < 0.0;
-    rest = (int)(rem + (down ? den : up ? -den : 0.0));
-    return (int)q + up - down;
 }
 
 // Values are int64, or int32 when every finite value of the launch is known to stay below
@@ -573,6 +533,7 @@ __device__ void prm_run(const prm_args &a, unsigned char *smem, prm_shared &sh) 
 __global__ __launch_bounds__(PRM_THREADS) void k_prm(prm_args a) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ prm_shared sh;
+    if (a.band && a.band[PRM_BAND_PARTS]) return;  // (every candidate has been planned: pp_prm_band.hip)
     const int L = a.L, D = a.D, tid = threadIdx.x, B = blockDim.x;
     const long long M = a.M;
     const int L1 = L + 1, L1p = (L1 + 1) & ~1;
@@ -747,7 +708,17 @@ extern "C" int pp_plan_replicated(int L, int D, int64_t N, int M, const int64_t 
     a.slot_bytes = prm_slot_bytes(L, D);
     a.W_out = (long long *)W; a.bounds_out = bounds; a.reps_out = reps;
     a.pre_out = (long long *)pre;
+    a.slots = lay.slots;
     a.status = status;
+    // the bands' tables lie where the kernels after k_prm write: the partial results, or the times
+    const size_t tables = prm_band_bytes(L, D);
+    a.band = tables <= lay.total - lay.part ? (int *)(base + lay.part)
+             : tables <= lay.bounds - lay.T ? (int *)(base + lay.T) : nullptr;
+    if (!prm_band_wanted(a)) a.band = nullptr;
+    if (a.band) {
+        const int rc = pp_launch_prm_band(a, st);
+        if (rc) return rc;
+    }
     size_t lds = prm_lds_bytes(L, D);
     a.search = prm_search_lds_bytes(L, D) <= 64 * 1024;
     if (a.search && prm_search_lds_bytes(L, D) > lds) lds = prm_search_lds_bytes(L, D);
