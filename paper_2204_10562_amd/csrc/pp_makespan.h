@@ -95,20 +95,25 @@ __device__ __forceinline__ int overflow_fault(long long worst, int M, int S) {
     return worst > (PP_CAP62 - 1) / ((long long)M + 4 * S - 4) ? PP_FAULT_OVERFLOW : 0;
 }
 
-// Writes T of microbatch count q, raises faults, and (if wanted) leaves the wave's minimum in
-// its slot of the partials; k_pick, launched next on the same stream, reduces the partials.
+// Writes T of microbatch count q, raises faults, and returns the wave's minimum.
+__device__ __forceinline__ tc_pair emit_T(const mk_args &a, int q, long long c, bool live, int fault, long long T, int t_off) {
+    if (live) {
+        if (fault) { T = PP_INF64; pp_raise(a.status, fault); }
+        if (a.T_out) a.T_out[((long long)q * a.N + c) * a.t_stride + t_off] = T;
+    }
+    tc_pair v = {live ? T : PP_INF64, live ? c : INT64_MAX};
+    return a.part ? wave_tc_min(v) : v;
+}
+
+// The same, and (if wanted) leaves the wave's minimum in its slot of the partials; k_pick, launched next on the
+// same stream, reduces the partials.
 // (Plain stores and a kernel boundary: earlier versions let the last wave to arrive do the
 // final reduction, but the returned atomics and arrival counters that needs cost more than
 // the schedule itself once a launch has thousands of waves.)
 __device__ __forceinline__ void emit(const mk_args &a, int q, long long c, bool live, int fault,
                                      long long T, long long wave_id, long long n_waves, int t_off) {
-    if (live) {
-        if (fault) { T = PP_INF64; pp_raise(a.status, fault); }
-        if (a.T_out) a.T_out[((long long)q * a.N + c) * a.t_stride + t_off] = T;
-    }
+    const tc_pair v = emit_T(a, q, c, live, fault, T, t_off);
     if (!a.part) return;
-    tc_pair v = {live ? T : PP_INF64, live ? c : INT64_MAX};
-    v = wave_tc_min(v);
     if ((threadIdx.x & 63) == 0 && wave_id < n_waves) a.part[(long long)q * n_waves + wave_id] = v;
 }
 

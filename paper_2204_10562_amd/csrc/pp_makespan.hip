@@ -369,7 +369,8 @@ __device__ __forceinline__ bool fused_gather(const mk_args &a, long long c, bool
 // candidates for up to MK_REGS_WAVES counts: the scattered table lookups of the gather, which
 // cost more than the schedule itself for small M, are split between them by stage and
 // exchanged through LDS (dynamic, (J + 1 + waves) * 64 * 8 bytes; none for a single wave).
-template <int S, bool SHARE = false, bool LISTED = false>
+// ONE: the launch is one workgroup, which picks the winners itself (regs_picks).
+template <int S, bool SHARE = false, bool LISTED = false, bool ONE = false>
 __device__ __forceinline__ void regs_body(const mk_args &a) {
     constexpr int R = 2 * S - 1, J = 4 * S - 3;
     extern __shared__ __align__(16) long long sh_all[];  // per group: [J+1][64] durations, [nw][64] worst
@@ -440,6 +441,19 @@ __device__ __forceinline__ void regs_body(const mk_args &a) {
     long long T;
     if (__all(narrow)) T = sweep_regs<S, int>(dur, M, [](const int (&fin)[J + 1]) { return (long long)fin[J]; });
     else T = sweep_regs<S, long long>(dur, M, [](const long long (&fin)[J + 1]) { return fin[J]; });
+    if constexpr (ONE) {
+        // (every wave comes here: there are as many counts as waves in a group)
+        const tc_pair v = emit_T(a, q, c, live, fq, T, a.t_off);
+        __syncthreads();  // what the gather exchanged has been read
+        tc_pair *best = (tc_pair *)sh_all;
+        if (lane == 0) best[wall] = v;
+        __syncthreads();  // and the plans are where write_winner reads them
+        if (g) return;
+        tc_pair u = v;
+        for (int h = 1; h < G; ++h) u = tc_min(u, best[h * nw + w]);
+        write_winner(a, q, u, lane);
+        return;
+    }
     if (!SHARE || f == 1) {
         emit(a, q, c, live, fq, T, group, (a.N + 63) / 64, a.all_xi ? S - 1 : a.t_off);
         return;
@@ -471,6 +485,21 @@ __global__ __launch_bounds__(64 * MK_REGS_WAVES * MK_REGS_GROUPS) void k_makespa
         case 6: regs_body<6>(a); break;
         case 7: regs_body<7>(a); break;
         case 8: regs_body<8>(a); break;
+    }
+}
+
+// The same for a launch of one workgroup, which writes the winners' records itself.  A kernel of its own so that
+// the plain one stays as lean as it is.
+__global__ __launch_bounds__(64 * MK_REGS_WAVES) void k_makespan_regs8_one(mk_args a) {
+    switch (a.S) {
+        case 1: regs_body<1, false, false, true>(a); break;
+        case 2: regs_body<2, false, false, true>(a); break;
+        case 3: regs_body<3, false, false, true>(a); break;
+        case 4: regs_body<4, false, false, true>(a); break;
+        case 5: regs_body<5, false, false, true>(a); break;
+        case 6: regs_body<6, false, false, true>(a); break;
+        case 7: regs_body<7, false, false, true>(a); break;
+        case 8: regs_body<8, false, false, true>(a); break;
     }
 }
 
@@ -565,6 +594,16 @@ __global__ __launch_bounds__(64) void k_makespan_lds(mk_args a) {
 
 static long long regs_waves(long long N) { return (N + 63) / 64; }
 
+// True if k_makespan_regs8 is launched as one workgroup that picks the winners, without k_pick.  The smallest calls
+// are five launches of 2 to 4 us in a row, and inside a workgroup a barrier is all that the partials need.  Whole
+// calls: 64 candidates of 8 stages, four counts 37.0 -> 35.7 us, 100 candidates, two counts 37.0 -> 35.9, all
+// orderings of 4 devices 30.5 -> 27.8.  Up to four waves, so that each still has a SIMD of its own (a wave alone
+// keeps one busy), and up to two groups: 190 candidates in three 44.1 -> 44.9.
+static bool regs_picks(const mk_args &a) {
+    const long long groups = regs_waves(a.N);
+    return a.part && a.S <= 8 && !a.all_xi && !a.rlist && groups <= 2 && groups * a.nM <= MK_REGS_WAVES;
+}
+
 // S = 0: the kernel for all S <= 8 (a.S, or every stage count 1..a.S if a.all_xi is set).
 template <int S>
 static int launch_regs(const mk_args &a, hipStream_t st) {
@@ -620,7 +659,13 @@ static int launch_regs(const mk_args &a, hipStream_t st) {
         b.groups = MK_REGS_GROUPS;
         gridx = (grid + MK_REGS_GROUPS - 1) / MK_REGS_GROUPS;
     }
+    const bool one = S == 0 && regs_picks(a);
+    if (one) {
+        b.groups = (int)grid;
+        gridx = 1;
+    }
     size_t lds_all = lds * b.groups;
+    if (one && lds_all < MK_REGS_WAVES * sizeof(tc_pair)) lds_all = MK_REGS_WAVES * sizeof(tc_pair);
     if (b.fuse) {
         const size_t need = mk_fuse_lds_bytes(a.L, a.D, a.S, nw, b.groups);
         lds_all = need > lds_all ? need : lds_all;
@@ -632,6 +677,8 @@ static int launch_regs(const mk_args &a, hipStream_t st) {
         else if (a.all_xi && a.share[a.S > 2 ? a.S - 2 : 0] > 1)
             hipLaunchKernelGGL(k_makespan_regs8_shared, dim3(grid, (a.nM + nw - 1) / nw, a.S),
                                dim3(64 * nw), lds, st, b);
+        else if (one)
+            hipLaunchKernelGGL(k_makespan_regs8_one, dim3(1), dim3(64 * nw * b.groups), lds_all, st, b);
         else
             hipLaunchKernelGGL(k_makespan_regs8, dim3(gridx, (a.nM + nw - 1) / nw, a.all_xi ? a.S : 1),
                                dim3(64 * nw * b.groups), lds_all, st, b);
@@ -739,7 +786,7 @@ int pp_launch_makespan(int L, int D, int S, int64_t N, int nM, const int *Ms, co
         return PP_OK;
     }
     int rc = launch_makespan(a, st);
-    if (rc || !part) return rc;
+    if (rc || !part || regs_picks(a)) return rc;
     // one partial per wave of 64 candidates and microbatch count
     return launch_pick(a, nM, regs_waves(N), st);
 }
