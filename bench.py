@@ -233,7 +233,7 @@ def main():
             ach = OPS_PER_PAIR * sv["pairs_executed"] / t_dpv["mean"]
             peak4 = calibration["waves_per_simd_4"] * 1e12
             roofline_dp = {
-                "bound": "alu", "kernel": "pp_partition_dp = k_prep + k_dp_rows (general path: a binary search per cell)",
+                "bound": "alu", "kernel": "pp_partition_dp = k_prep + k_dp_rows (general path: the cells of every row that a good plan can use, whole rows where those do not decide)",
                 "workload": "gpt_varied: the GPT shape with activation sizes 16 MiB x U[0.5, 2) per boundary",
                 "achieved": ach / 1e12, "peak": ALU_PEAK_OPS / 1e12, "unit": "TOP/s (32-bit integer lane-ops)",
                 "frac": ach / ALU_PEAK_OPS, "ops_per_pair": OPS_PER_PAIR,
@@ -248,7 +248,7 @@ def main():
             vi = figures.get("dp_general.valu_insts_per_launch")
             if vi:
                 roofline_dp["issue_view"] = {
-                    "valu_wave_insts_per_launch": vi, "valu_insts_per_executed_pair_lane": vi * 64 / sv["pairs_executed"],
+                    "valu_wave_insts_per_launch": vi,
                     "frac_of_spec_issue_rate": vi * 64 / t_dpv["mean"] / ALU_PEAK_OPS,
                     "frac_of_measured_issue_rate": vi * 64 / t_dpv["mean"] / peak4,
                     "valu_busy_frac": figures.get("dp_general.valu_busy_frac"), "source": "profiles/ (rocprofv3 --pmc)"}
