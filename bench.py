@@ -15,7 +15,8 @@ Objects of the line beside the contract's fields:
   roofline_dp       the general partition-DP kernel, timed on the same shape with activation
                     sizes that differ per boundary (on the GPT workload itself the transfer
                     times do not depend on the cut position and the DP runs in closed form:
-                    see "dp")
+                    see "dp"); most plans are found without evaluating pairs, so it says how the
+                    rows were settled and how busy the vector units are, not pairs per second
   calibration       the integer vector rate measured on this GPU by the calibration kernel
   cpu_baseline      the oracle on the host cores, as it stands
 """
@@ -34,7 +35,6 @@ sys.path.insert(0, ROOT)
 # published MI355X figures: 256 compute units x 4 SIMDs x 16 lanes at 2.4 GHz, one 32-bit
 # integer operation per lane per clock
 ALU_PEAK_OPS = 256 * 4 * 16 * 2.4e9
-OPS_PER_PAIR = 3      # subtract, max, min on 32-bit keys per (cell, split) pair of the DP (a step of a search: add, read, compare)
 OPS_PER_BLOCK_OP = 2  # max, add per (block, microbatch) update of the schedule
 
 
@@ -185,7 +185,8 @@ def main():
     log("  pp_partition_dp        %9.1f us (median %.1f, min %.1f)   nominal %.3e pair-evals/s  %.3e cells/s%s"
         % (t_dp["mean"] * 1e6, t_dp["median"] * 1e6, t_dp["min"] * 1e6, pairs / t_dp["mean"], N * S * L / t_dp["mean"],
            "   [closed form: transfer times do not depend on the cut position]" if closed_form else ""))
-    log("     executed %d of %d nominal pair-evals (%d rows)" % (stats["pairs_executed"], pairs, stats["rows_executed"]))
+    log("     executed %d of %d nominal pair-evals (%d rows settled: %d by the program without transfers, %d over their bands)"
+        % (stats["pairs_executed"], pairs, stats["rows_executed"], stats["free_rows"], stats["band_rows"]))
     if L > 128 and stats["share_active"]:
         log("     %d link classes: %d of the %d candidates computed, the others share their results"
             % (stats["share_classes"], stats["share_computed"], N))
@@ -229,17 +230,17 @@ def main():
             t_dpv = timed(lambda: pp.pp_partition_dp(L, D, S, N, gv.PF, gv.PB, gv.XF, gv.XB, gv.orderings, C, bounds, wsv, gv.status), reps)
             torch.cuda.synchronize()
             sv = pp.read_workspace_stats(wsv)
-            assert int(gv.status.item()) == 0 and sv["rows_executed"] > 0
-            ach = OPS_PER_PAIR * sv["pairs_executed"] / t_dpv["mean"]
+            assert int(gv.status.item()) == 0 and sv["rows_executed"] > 0  # (the closed form settles none)
+            how = {"rows_settled": sv["rows_executed"], "by_the_program_without_transfers": sv["free_rows"],
+                   "over_their_bands": sv["band_rows"], "whole": sv["rows_executed"] - sv["free_rows"] - sv["band_rows"],
+                   "pair_evals": sv["pairs_executed"], "of_which_in_bands": sv["band_pairs"], "pair_evals_nominal": pairs}
             peak4 = calibration["waves_per_simd_4"] * 1e12
             roofline_dp = {
                 "bound": "alu", "kernel": "pp_partition_dp = k_prep + k_dp_rows (general path: the cells of every row that a good plan can use, whole rows where those do not decide)",
                 "workload": "gpt_varied: the GPT shape with activation sizes 16 MiB x U[0.5, 2) per boundary",
-                "achieved": ach / 1e12, "peak": ALU_PEAK_OPS / 1e12, "unit": "TOP/s (32-bit integer lane-ops)",
-                "frac": ach / ALU_PEAK_OPS, "ops_per_pair": OPS_PER_PAIR,
+                "peak": ALU_PEAK_OPS / 1e12, "unit": "TOP/s (32-bit integer lane-ops)",
                 "peak_measured": peak4 / 1e12, "peak_measured_at": "4 waves per SIMD (the kernel's occupancy)",
-                "launch": us(t_dpv), "pair_evals_executed_per_launch": sv["pairs_executed"],
-                "pair_evals_nominal_per_launch": pairs, "rows_executed_per_launch": sv["rows_executed"],
+                "launch": us(t_dpv), "per_launch": how,
                 "dp_cells_per_s": N * S * L / t_dpv["mean"], "dp_nominal_pair_evals_per_s": pairs / t_dpv["mean"],
                 "traffic": figures.get("dp_general.traffic_bytes_per_launch"),
             }
@@ -252,10 +253,10 @@ def main():
                     "frac_of_spec_issue_rate": vi * 64 / t_dpv["mean"] / ALU_PEAK_OPS,
                     "frac_of_measured_issue_rate": vi * 64 / t_dpv["mean"] / peak4,
                     "valu_busy_frac": figures.get("dp_general.valu_busy_frac"), "source": "profiles/ (rocprofv3 --pmc)"}
-            log("  general DP kernel on gpt_varied: pp_partition_dp %.1f us (median %.1f, min %.1f); executed %d pairs (%d rows): "
-                "%.1f%% of spec peak at %d ops/pair, %.1f%% of the measured rate"
-                % (t_dpv["mean"] * 1e6, t_dpv["median"] * 1e6, t_dpv["min"] * 1e6, sv["pairs_executed"], sv["rows_executed"],
-                   100 * ach / ALU_PEAK_OPS, OPS_PER_PAIR, 100 * ach / peak4))
+            log("  general DP kernel on gpt_varied: pp_partition_dp %.1f us (median %.1f, min %.1f); of %d rows %d by the program "
+                "without transfers, %d over their bands, %d whole; %d pairs evaluated"
+                % (t_dpv["mean"] * 1e6, t_dpv["median"] * 1e6, t_dpv["min"] * 1e6, how["rows_settled"],
+                   how["by_the_program_without_transfers"], how["over_their_bands"], how["whole"], how["pair_evals"]))
             del gv, wsv
 
         # --- the stage-count search (Alg. 3's outer loop) over the same candidates
@@ -377,7 +378,7 @@ def main():
         "dp": {"entry_point": "pp_partition_dp", "closed_form": closed_form, "call": us(t_dp),
                "dp_cells_per_s": N * S * L / t_dp["mean"], "dp_nominal_pair_evals_per_s": pairs / t_dp["mean"],
                "pair_evals_executed_per_launch": stats["pairs_executed"], "pair_evals_nominal_per_launch": pairs,
-               "rows_executed_per_launch": stats["rows_executed"],
+               "rows_settled_per_launch": stats["rows_executed"],
                # candidates whose links have the same transfer times share one DP (L > 128)
                "shared": ({"link_classes": stats["share_classes"], "candidates_computed": stats["share_computed"]}
                           if L > 128 and stats["share_active"] else None)},

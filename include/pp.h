@@ -101,12 +101,23 @@ int pp_prefix_costs(int L, int D, const int64_t *fwd_us, const int64_t *bwd_us,
  * byte PP_WS_WORK on, 64 records PP_WS_WORK_STRIDE bytes apart; the uint64 at
  * the start of each record adds up (over the 64) to the number of (cell,
  * split) pairs the dynamic program actually evaluated in that call, the
- * uint64 after it to the number of DP rows it computed.  Rows that
- * consecutive candidates share (equal ordering prefixes) are computed and
- * counted once, and for L > 128, and for longer lists of 88 < L <= 128, a cell's
- * split is searched for (counted: the steps of the search and its result; for
- * L > 128 not the few splits looked at where a search has to be mended), so
- * these can be far below N * pairs-per-candidate.
+ * uint64 after it to the number of rows of the candidates' tables it settled.
+ * Rows that consecutive candidates share (equal ordering prefixes) are
+ * computed and counted once, and for L > 128, and for longer lists of
+ * 88 < L <= 128, a cell's split is searched for (counted: the steps of the
+ * search and its result; for L > 128 not the few splits looked at where a
+ * search has to be mended), so these can be far below N * pairs-per-candidate.
+ * In longer lists (and from 64 candidates on for L > 128) a candidate may be
+ * finished from the few cells of every row that a good plan can use (its
+ * band), or, where no link reaches into its values, with the plan of the
+ * program without transfer times, which the call works out once and does not
+ * count.  The next three uint64 of each record say how many of the pairs were
+ * pairs of bands (also of candidates that did not end there; some pairs of a
+ * band that cannot matter are skipped four at a time and counted all the
+ * same), how many of the rows were computed over their band alone (for every
+ * candidate and, with plans of every stage count, for every count), and how
+ * many were settled by the program without transfer times, with no pair
+ * evaluated.  The other rows were computed whole.
  *
  * For L > 128 and D <= 64 the dynamic program is computed once for every
  * group of candidates whose links have the same transfer times at every cut

@@ -323,6 +323,7 @@ def read_workspace_stats(workspace):
     rec = rec.reshape(64, PP_WS_WORK_STRIDE // 8)
     sh = workspace[PP_WS_SHARE:PP_WS_SHARE + 32].cpu().numpy().view(np.uint32)
     return dict(pairs_executed=int(rec[:, 0].sum()), rows_executed=int(rec[:, 1].sum()),
+                band_pairs=int(rec[:, 2].sum()), band_rows=int(rec[:, 3].sum()), free_rows=int(rec[:, 4].sum()),
                 share_active=int(sh[0]), share_classes=int(sh[1]), share_keys=int(sh[2]),
                 share_computed=int(sh[3]), share_sorted=int(sh[6]), share_sort_devices=int(sh[7]))
 

@@ -55,10 +55,12 @@ struct pp_ws_header {
     // byte 1024: work the partition DP actually did in this call, in 64 records of 128 bytes
     // (atomics that hit one cache line are served one after another, so every record has a
     // line of its own): (cell, split) pairs evaluated (rows shared between candidates are
-    // counted once) and DP rows computed (the single-cell last row counts too).  Zeroed by
-    // the pack kernel; the totals are the sums over the 64 records.
+    // counted once) and DP rows settled (the single-cell last row counts too); then, of those
+    // pairs, the ones of bands (pp_dp_band.h), and of those rows the ones of bands and the ones
+    // that are the channel-free program's.  Zeroed by the pack kernel; the totals are the sums
+    // over the 64 records.
     struct {
-        unsigned long long pairs, rows, pad[14];
+        unsigned long long pairs, rows, band_pairs, band_rows, free_rows, pad[11];
     } work[64];
 };
 

@@ -239,7 +239,10 @@ __global__ __launch_bounds__(256) void k_prep(pack_args a) {
             }
             long long pl = a.PF[a.L] + a.PB[a.L];
             m = pl < 0 ? ~0ull : (unsigned long long)pl;
-            if (tid < 64) { a.hdr->work[tid].pairs = 0; a.hdr->work[tid].rows = 0; }
+            if (tid < 64) {
+                auto &w = a.hdr->work[tid];
+                w.pairs = w.rows = w.band_pairs = w.band_rows = w.free_rows = 0;
+            }
         }
         bool flat = true;
         if (a.pack) {

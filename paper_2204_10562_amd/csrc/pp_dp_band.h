@@ -105,16 +105,14 @@ __device__ __forceinline__ bool band_free(const dp_args &a, const int *table) {
 
 // A wave's candidates, one per lane (c, where live; all lanes must call): reports bad orderings, and finishes the
 // candidates none of whose links reaches into its row (links: band_links' words, or NULL: there are none) with
-// the channel-free plan.  Returns the others, a bit per lane.  first: the first place where a lane's devices
-// differ from those of the lane before (work counters).
+// the channel-free plan.  Returns the others, a bit per lane.
 __device__ __forceinline__ unsigned long long band_free_try(const dp_args &a, const int *table, const unsigned long long *links,
-                                                            long long c, bool live, int &first) {
+                                                            long long c, bool live) {
     const int lane = threadIdx.x & 63, S = a.S, D = a.D, tri = S * (S + 1) / 2;
     const int *row = a.ord + c * S;
     bool bad = false;
     unsigned long long seen = 0, reach = 0;
-    int before = 0;
-    first = lane ? S : 0;
+    int before = 0, first = lane ? S : 0;  // the first place where the devices differ from those of the lane before
     auto device = [&](int n, int d) {
         const int left = __builtin_amdgcn_update_dpp(d, d, DPP_WAVE_SHR1, 0xf, 0xf, false);
         if (d != left && first == S) first = n;
@@ -171,18 +169,16 @@ __device__ __forceinline__ unsigned long long band_free_try(const dp_args &a, co
         const int e = __builtin_amdgcn_readlane(v_C, n);
         if (done) Co[n] = e;
     }
-    return __ballot(live && !bad && !done);
-}
-
-// Adds the rows of the candidates `ended` to the counters: those of neighbours in the wave that begin with the
-// same devices count once, the last row's single cell for every candidate; a row of `pairs` (cell, split) pairs.
-__device__ __forceinline__ void band_count(const dp_args &a, unsigned long long ended, int first, unsigned pairs, long long c) {
-    const int lane = threadIdx.x & 63, S = a.S;
+    // (rows of neighbours in the wave that begin with the same devices count once, the last row for everyone)
     const bool after = lane && (ended >> (lane - 1) & 1);
-    first = after && first > 1 ? first : 1;
-    int rows = ended >> lane & 1 ? 1 + band_max(0, S - 1 - first) : 0;
+    int rows = done ? 1 + band_max(0, S - 1 - (after && first > 1 ? first : 1)) : 0;
     for (int off = 32; off; off >>= 1) rows += __shfl_xor(rows, off);
-    if (lane == 0 && ended) pp_count_work(a.hdr, (unsigned long long)rows * pairs, rows, (unsigned)(c >> 6));
+    if (lane == 0) {
+        auto &w = a.hdr->work[(c >> 6) & 63];
+        atomicAdd(&w.rows, (unsigned long long)rows);
+        atomicAdd(&w.free_rows, (unsigned long long)rows);
+    }
+    return __ballot(live && !bad && !done);
 }
 
 // One link's words, by one wave.
@@ -214,19 +210,13 @@ __device__ __forceinline__ unsigned long long band_try(const dp_args &a, const i
     const int lane = threadIdx.x & 63, S = a.S, L = a.L, D = a.D, K = a.K, kmask = (1 << K) - 1;
     unsigned *args = (unsigned *)lds + lane;                                       // [S][WORDS][64]
     unsigned char *dev = lds + (size_t)S * WORDS * 256 + lane;                      // [S][64]
-    int first;
-    const unsigned long long most = band_free_try(a, table, links, c, live, first);
-    const unsigned long long all = __ballot(live);
-    if (!most) {
-        // (bad orderings among them are in nobody's way here)
-        band_count(a, all, first, 1, c);
-        return 0;
-    }
+    const unsigned long long most = band_free_try(a, table, links, c, live);
+    if (!most) return 0;
     bool open = most >> lane & 1;  // this lane's candidate has ended well so far
     for (int n = 0; n < S; ++n) dev[n * 64] = open ? (unsigned char)a.ord[c * S + n] : 0;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     const int tri = S * (S + 1) / 2;
-    unsigned cells = 0;  // (cell, split) pairs of the rows of the last stage count
+    unsigned long long pairs = 0;  // of all the lanes' bands
     int tried[BAND_LEVELS] = {}, well[BAND_LEVELS] = {};
 
     for (int xi = a.stages ? 1 : S; xi <= S; ++xi) {
@@ -260,9 +250,10 @@ __device__ __forceinline__ unsigned long long band_try(const dp_args &a, const i
                     }
             };
             fetch(1, lo_p, w_p);
-            unsigned pairs = 0;
             bool alive = todo;
-            for (int n = 1; n < xi && __ballot(alive); ++n) {
+            for (int n = 1; n < xi; ++n) {
+                const unsigned long long here_too = __ballot(alive);
+                if (!here_too) break;
                 const int here = __builtin_amdgcn_readlane(v_row, n);
                 const int lo = here & 0xffff, w = here >> 16;
                 const int v_pn = PK[lo + (lane & (CELLS - 1))];
@@ -299,7 +290,7 @@ __device__ __forceinline__ unsigned long long band_try(const dp_args &a, const i
                 }
 #pragma unroll
                 for (int q = 0; q < WORDS; ++q) args[(n * WORDS + q) * 64] = word[q];
-                pairs += (unsigned)(w * w_p);
+                pairs += (unsigned)(w * w_p * __builtin_popcountll(here_too));
                 lo_p = lo;
                 w_p = w;
                 v_pp = v_pn;
@@ -307,10 +298,10 @@ __device__ __forceinline__ unsigned long long band_try(const dp_args &a, const i
             }
             const bool ok = alive && W[0] <= top_most;
             tried[level] += __builtin_popcountll(__ballot(todo));
-            well[level] += __builtin_popcountll(__ballot(ok));
+            const int ended = __builtin_popcountll(__ballot(ok));
+            well[level] += ended;
             todo = todo && !ok;
-            if (__ballot(ok)) {
-                cells = pairs;
+            if (ended) {
                 if (ok) a.C_out[a.stages ? c * S + xi - 1 : c] = W[0] >> K;
                 int *bo = a.bounds_out + (a.stages ? c * tri + xi * (xi - 1) / 2 : c * S);
                 const bool whole = (xi & 3) == 0 && ((uintptr_t)bo & 15) == 0;
@@ -336,8 +327,15 @@ __device__ __forceinline__ unsigned long long band_try(const dp_args &a, const i
         else if (8 * well[level] < tried[level]) pace.skip[level] = 7;
     }
     const unsigned long long left = __ballot((most >> lane & 1) && !open);
-    for (int off = 32; off; off >>= 1) cells = (unsigned)band_max((int)cells, __shfl_xor((int)cells, off));
-    band_count(a, all & ~left, first, cells / (unsigned)(S > 1 ? S - 1 : 1) + 1, c);
+    // (a candidate that ended: its rows, of every stage count asked for)
+    const unsigned long long rows = (unsigned long long)(__builtin_popcountll(__ballot(open)) * (a.stages ? tri - S : S - 1));
+    if (lane == 0 && pairs) {
+        auto &w = a.hdr->work[(c >> 6) & 63];
+        atomicAdd(&w.pairs, pairs);
+        atomicAdd(&w.band_pairs, pairs);
+        atomicAdd(&w.rows, rows);
+        atomicAdd(&w.band_rows, rows);
+    }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     return left;
 }

@@ -141,12 +141,7 @@ __global__ __launch_bounds__(256) void k_dp_tile(dp_tile_args a) {
     const bool pooled = BANDS == BAND_USE_INSIDE && a.pooled;
     unsigned long long *words = (unsigned long long *)(smem + (pooled ? 0 : a.links_at)), *reach = words + 4;
     unsigned long long left = 0;
-    auto finish = [&](long long c, bool live) -> unsigned long long {
-        int first;
-        const unsigned long long all = __ballot(live), l = band_free_try(a.g, a.g.band, reach, c, live, first);
-        band_count(a.g, all & ~l, first, 1, c);
-        return l;
-    };
+    auto finish = [&](long long c, bool live) { return band_free_try(a.g, a.g.band, reach, c, live); };
     if (BANDS == BAND_USE_INSIDE) {
         whole = whole || !(pooled || a.links_at) || !band_free(a.g, a.g.band);
         if (!whole) {

@@ -82,3 +82,22 @@ def test_all_orderings_inside_and_outside_a_launch_of_their_own(ppo):
         assert st == 0 and rc == 0
         np.testing.assert_array_equal(C, C0)
         np.testing.assert_array_equal(b, b0)
+
+
+def test_work_counters(ppo):
+    """Links that reach into no value: no pair is evaluated; links that bind nearly everywhere: most rows are whole."""
+    from paper_2204_10562_amd import binding as pp
+    from paper_2204_10562_amd.problem import GpuProblem
+    for kind in ("free", "most"):
+        w = problem(kind, 9500, 128, 8, 8, 1)
+        w.orderings, w.N = None, 40320
+        g = GpuProblem(w)
+        g.prefix()
+        print("[case] work counters", kind, flush=True)
+        assert g.dp()[0] == 0
+        s = pp.read_workspace_stats(g.ws)
+        assert s["rows_executed"] > 0 and s["band_pairs"] <= s["pairs_executed"]
+        if kind == "free":
+            assert s["pairs_executed"] == 0 and s["free_rows"] == s["rows_executed"]
+        else:
+            assert s["pairs_executed"] > s["rows_executed"] > 2 * (s["free_rows"] + s["band_rows"])

@@ -19,10 +19,10 @@ SIZES = [(3, 2, 2, 64), (5, 5, 5, 70), (17, 8, 8, 65), (64, 9, 2, 64), (40, 33, 
 def driver(tmp_path_factory):
     exe = build(tmp_path_factory.mktemp("band"), "band_driver")
 
-    def ask(cases):
+    def ask(cases, *args):
         env = dict(os.environ)
         env.pop("LD_PRELOAD", None)  # the sanitizer's runtime must come first in the library list
-        res = subprocess.run([exe], input="".join(" ".join(str(x) for x in c) + "\n" for c in cases),
+        res = subprocess.run([exe, *args], input="".join(" ".join(str(x) for x in c) + "\n" for c in cases),
                              stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=600, env=env)
         assert res.returncode == 0 and "runtime error" not in res.stderr, res.stderr[-2000:]
         out = [[int(x) for x in l.split()] for l in res.stdout.splitlines()]
@@ -49,3 +49,23 @@ def test_bands_lane_by_lane(driver, kind):
     assert ended > 0
     if kind in (SOME, MOST):
         assert ended < sum(c[3] for c in cases)
+
+
+@pytest.mark.parametrize("kind", [FREE, SOME, MOST, HIGH])
+def test_work_counters(driver, kind):
+    """What did not run is not counted: no pair and no computed row for candidates with the channel-free plan or a bad
+    ordering, pairs of bands only where there was a recursion (also one that ended nothing)."""
+    cases = [(L, D, S, N, L + S, kind, stages, words) for L, D, S, N in SIZES[1:8] for stages in (0, 1) for words in (0, 1)
+             if not (stages and S > 12)]
+    for case, (_, _, _, done, _, pairs, rows, band_pairs, band_rows, free_rows) in zip(cases, driver(cases, "work")):
+        L, D, S, N, _, _, stages, words = case
+        assert pairs == band_pairs and rows == band_rows + free_rows, case
+        per = S * (S - 1) // 2 if stages else S - 1
+        assert free_rows <= done * (S - 1) and band_rows % per == 0 and band_rows <= done * per, case
+        if not words:
+            assert free_rows == 0 and band_rows == done * per and pairs >= band_rows, case
+        elif kind == FREE:
+            # every link is hidden: nothing is evaluated
+            assert pairs == 0 and free_rows >= N - 1, case
+        if pairs == 0:
+            assert band_rows == 0, case

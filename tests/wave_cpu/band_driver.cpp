@@ -4,7 +4,8 @@
 // KIND: what the layer and transfer times look like (below); STAGES: plans of every number of stages; WORDS: whether
 // the words of the links are there.  Prints, per case, the return value, the status, how many results of the
 // candidates that ended differ from the recursion over all splits, how many ended, and how many candidates with a
-// bad ordering were reported.
+// bad ordering were reported; with an argument also the work counters: pairs, rows, and those of them in bands and
+// of the channel-free program.
 #include "../../paper_2204_10562_amd/csrc/pp_dp_band_table.h"
 #include "../../paper_2204_10562_amd/csrc/pp_dp_band.hip"
 
@@ -20,7 +21,7 @@ static void k_band_table(band_table_args a) { band_table(a, (unsigned char *)dyn
 
 typedef long long ll;
 
-int main() {
+int main(int argc, char **) {
     int L, D, S, N, seed, kind, stages, words;
     while (scanf("%d %d %d %d %d %d %d %d", &L, &D, &S, &N, &seed, &kind, &stages, &words) == 8) {
         std::mt19937_64 g(seed);
@@ -115,7 +116,13 @@ int main() {
                 }
             }
         }
-        printf("%d %d %d %d %d\n", rc, status, differ, ended, reported);
+        printf("%d %d %d %d %d", rc, status, differ, ended, reported);
+        ll work[5] = {};
+        for (auto &w : hdr.work) {
+            work[0] += w.pairs; work[1] += w.rows; work[2] += w.band_pairs; work[3] += w.band_rows; work[4] += w.free_rows;
+        }
+        for (ll w : work) if (argc > 1) printf(" %lld", w);
+        printf("\n");
         fflush(stdout);
     }
     return 0;
