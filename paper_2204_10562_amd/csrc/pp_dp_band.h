@@ -340,5 +340,59 @@ __device__ __forceinline__ unsigned long long band_try(const dp_args &a, const i
     return left;
 }
 
+// How a row kernel for L <= 128 (A: dp_rows_args or dp_tile_args) passes by the candidates that bands finish: whole
+// rows are computed for those left, a bit each in `left`.  Either a launch before this one has left them in memory,
+// or the ones with the channel-free plan are finished here, one per lane: where a wave's chunk is shorter than a
+// wave is wide, the workgroup's candidates are dealt out together.  Else the chunk is taken in pieces of up to 64.
+// Where that has to be found out here and more than half of a piece is left, what follows it goes without.  (Bits
+// that are in memory are read to the end: 270 000 orderings, L = 97, S = 11, 46 % of them left 1019 -> 801 us, 83 %
+// 1216 -> 1164, all of them 1264 -> 1268.)
+// (A kernel without this where neither can be worth it, pp_dp.hip.)  Returns whether all rows are to be computed.
+template <int BANDS, typename A>
+__device__ __forceinline__ bool band_begin(const A &a, unsigned char *smem, unsigned long long *&reach, unsigned long long &left) {
+    reach = NULL;
+    left = 0;
+    if (BANDS == BAND_USE_NOT || a.g.band[band_top_at(a.S, 0, a.S)] < 0) return true;
+    if (BANDS == BAND_USE_ALONE) return false;
+    if (!(a.pooled || a.links_at) || !band_free(a.g, a.g.band)) return true;
+    unsigned long long *words = (unsigned long long *)(smem + (a.pooled ? 0 : a.links_at));
+    reach = words + 4;
+    band_links(a.g, a.g.band, reach);
+    __syncthreads();
+    if (a.pooled) {
+        // dealt out together, before any wave needs its part of the LDS
+        const int lane = threadIdx.x & 63, wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wpb = blockDim.x >> 6;
+        const long long first = (long long)blockIdx.x * wpb * a.chunk;
+        const int at = 64 * wib, total = (int)(a.N - first < wpb * a.chunk ? a.N - first : wpb * a.chunk);
+        const unsigned long long word =
+            at < total ? band_free_try(a.g, a.g.band, reach, first + at + lane, at + lane < total) : 0;
+        if (lane == 0) words[wib] = word;
+        __syncthreads();
+        const int mine_at = wib * (int)a.chunk, w = mine_at >> 6, by = mine_at & 63;
+        left = words[w] >> by;
+        if (by && w + 1 < wpb) left |= words[w + 1] << (64 - by);
+        left &= (1ull << a.chunk) - 1;
+        __syncthreads();
+    }
+    return false;
+}
+
+// The candidates base .. end - 1 of the chunk at c0: `left` of them, and where the piece ends.
+template <int BANDS, typename A>
+__device__ __forceinline__ int band_piece(const A &a, const unsigned long long *reach, long long c0, int base, int end,
+                                          unsigned long long &left) {
+    const int lane = threadIdx.x & 63;
+    if (BANDS == BAND_USE_ALONE) {
+        const unsigned long long *at = a.g.left + ((c0 + base) >> 6);
+        const int by = (int)((c0 + base) & 63), n = end - base;
+        left = at[0] >> by;
+        if (by + n > 64) left |= at[1] << (64 - by);
+        if (n < 64) left &= (1ull << n) - 1;
+    } else if (!a.pooled) {
+        left = band_free_try(a.g, a.g.band, reach, c0 + base + lane, base + lane < end);
+    }
+    return end;  // (dealt out together: the chunk is one piece)
+}
+
 // L <= 128: the bands in launches of their own, in front of the DP kernel (links: room for D * D words).
 int pp_launch_dp_band_alone(const dp_args &g, unsigned long long *links, unsigned long long *left, hipStream_t st);

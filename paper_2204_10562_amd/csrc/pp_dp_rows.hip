@@ -215,38 +215,9 @@ __global__ __launch_bounds__(256) void k_dp_rows(dp_rows_args a) {
     const long long c0 = wave * a.chunk;
     const long long c1 = c0 + a.chunk < a.N ? c0 + a.chunk : a.N;
 
-    // Candidates that the few cells of pp_dp_band.h finish come first; whole rows are computed for those left (a
-    // bit each in `left`).  Either a launch before this one has left them in memory, or the ones with the
-    // channel-free plan are finished here, one per lane: where a wave's chunk is shorter than a wave is wide, the
-    // workgroup's candidates are dealt out together.  Else the chunk is taken in pieces of up to 64.  Where more
-    // than half of a piece is left, what follows it goes without.
-    // (Not where neither can be worth it, pp_dp.hip: a kernel without this.)
-    bool whole = BANDS == BAND_USE_NOT || a.g.band[band_top_at(S, 0, S)] < 0;
-    const bool pooled = BANDS == BAND_USE_INSIDE && a.pooled;
-    unsigned long long *words = (unsigned long long *)(smem + (pooled ? 0 : a.links_at)), *reach = words + 4;
-    unsigned long long left = 0;
-    auto finish = [&](long long c, bool live) { return band_free_try(a.g, a.g.band, reach, c, live); };
-    if (BANDS == BAND_USE_INSIDE) {
-        whole = whole || !(pooled || a.links_at) || !band_free(a.g, a.g.band);
-        if (!whole) {
-            band_links(a.g, a.g.band, reach);
-            __syncthreads();
-        }
-        if (!whole && pooled) {
-            // dealt out together, before any wave needs its part of the LDS
-            const int wpb = blockDim.x >> 6;
-            const long long first = (long long)blockIdx.x * wpb * a.chunk;
-            const int at = 64 * wib, total = (int)(a.N - first < wpb * a.chunk ? a.N - first : wpb * a.chunk);
-            const unsigned long long word = at < total ? finish(first + at + lane, at + lane < total) : 0;
-            if (lane == 0) words[wib] = word;
-            __syncthreads();
-            const int mine_at = wib * (int)a.chunk, w = mine_at >> 6, by = mine_at & 63;
-            left = words[w] >> by;
-            if (by && w + 1 < wpb) left |= words[w + 1] << (64 - by);
-            left &= (1ull << a.chunk) - 1;
-            __syncthreads();
-        }
-    }
+    // candidates of the chunk that bands have finished are passed by: pieces of it and what is left of them
+    unsigned long long *reach, left;
+    bool whole = band_begin<BANDS>(a, smem, reach, left);
     if (c0 >= c1) return;
 
     // row 0: one stage holding the first l layers (same for every candidate)
@@ -396,19 +367,9 @@ __global__ __launch_bounds__(256) void k_dp_rows(dp_rows_args a) {
     end_c = count;
     whole_now = whole;
     if (BANDS != BAND_USE_NOT && !whole) {
-        if (BANDS == BAND_USE_ALONE) {
-            end_c = base + piece < count ? base + piece : count;
-            const unsigned long long *at = a.g.left + ((c0 + base) >> 6);
-            const int by = (int)((c0 + base) & 63), n = end_c - base;
-            left = at[0] >> by;
-            if (by + n > 64) left |= at[1] << (64 - by);
-            if (n < 64) left &= (1ull << n) - 1;
-        } else if (!pooled) {
-            end_c = base + piece < count ? base + piece : count;
-            left = finish(c0 + base + lane, base + lane < end_c);
-        }
+        end_c = band_piece<BANDS>(a, reach, c0, base, base + piece < count ? base + piece : count, left);
         if (!left) continue;
-        whole = 2 * __builtin_popcountll(left) > end_c - base;
+        whole = BANDS == BAND_USE_INSIDE && 2 * __builtin_popcountll(left) > end_c - base;
         have_prev = false;
         arena_used = 0;
         fresh = true;

@@ -20,10 +20,10 @@ KINDS = {"free": 0, "one zero layer": 1, "half zero layers": 2, "last layer outw
 def driver(tmp_path_factory):
     exe = build(tmp_path_factory.mktemp("rows"), "rows_driver")
 
-    def ask(cases):
+    def ask(cases, *args):
         env = dict(os.environ)
         env.pop("LD_PRELOAD", None)  # the sanitizer's runtime must come first in the library list
-        res = subprocess.run([exe], input="".join(" ".join(str(x) for x in c) + "\n" for c in cases),
+        res = subprocess.run([exe, *args], input="".join(" ".join(str(x) for x in c) + "\n" for c in cases),
                              stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=300, env=env)
         assert res.returncode == 0 and "runtime error" not in res.stderr, res.stderr[-2000:]
         out = [[int(x) for x in l.split()] for l in res.stdout.splitlines()]
@@ -54,3 +54,12 @@ def test_steps_do_not_depend_on_binding_links(driver, L, D, S, N):
     free, falling, wild = (driver([(L, D, S, N, 5, k, 0, 0)])[0][3] for k in (0, 5, 6))
     most = 1.7 if L <= 128 else 3.5
     assert falling < most * free and wild < most * free, (free, falling, wild)
+
+
+@pytest.mark.parametrize("L,D,S,N", [(89, 4, 2, 900), (97, 6, 5, 603), (128, 5, 3, 450), (90, 3, 3, 192), (128, 34, 33, 200)])
+def test_candidates_that_are_finished_already(driver, L, D, S, N):
+    """Chunks of several pieces, of which some candidates, all or none are left: those are right, and the kernel keeps its
+    hands off the others also behind a piece where most are left."""
+    cases = [(L, D, S, N, L + S, kind, stages, 85) for kind in (0, 6) for stages in (0, 1)]
+    for case, got in zip(cases, driver(cases, "left")):
+        assert got[:3] == [0, 0, 0], case
