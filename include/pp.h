@@ -107,11 +107,11 @@ int pp_prefix_costs(int L, int D, const int64_t *fwd_us, const int64_t *bwd_us,
  * 88 < L <= 128, a cell's split is searched for (counted: the steps of the
  * search and its result; for L > 128 not the few splits looked at where a
  * search has to be mended), so these can be far below N * pairs-per-candidate.
- * In longer lists (and from 64 candidates on for L > 128) a candidate may be
- * finished from the few cells of every row that a good plan can use (its
- * band), or, where no link reaches into its values, with the plan of the
- * program without transfer times, which the call works out once and does not
- * count.  The next three uint64 of each record say how many of the pairs were
+ * In lists for which whole rows take long enough (and, of the second, from 64
+ * candidates on for L > 128) a candidate may be finished from the few cells of
+ * every row that a good plan can use (its band), or, where no link reaches
+ * into its values, with the plan of the program without transfer times, which
+ * the call works out once and does not count.  The next three uint64 of each record say how many of the pairs were
  * pairs of bands (also of candidates that did not end there; some pairs of a
  * band that cannot matter are skipped four at a time and counted all the
  * same), how many of the rows were computed over their band alone (for every
@@ -125,10 +125,11 @@ int pp_prefix_costs(int L, int D, const int64_t *fwd_us, const int64_t *bwd_us,
  * whenever (number of distinct link rows)^(S-1) <= 2^20; the four uint32 at
  * byte PP_WS_SHARE then hold: 1 (0 if every candidate was computed on its
  * own), the number of distinct link rows, that power, and the number of
- * candidates computed.  Where that power is too large the candidates are
- * instead taken in the order of their first k devices (D^k <= 2^20), so that
- * consecutive ones share the first k - 1 rows: the uint32 at byte
- * PP_WS_SHARE + 24 is then 1 and the one after it k.
+ * candidates that stand for all.  Where that power is too large, lists of 64
+ * candidates and more are instead taken in the order of their first k devices
+ * (D^k <= 2^20), so that consecutive ones share the first k - 1 rows (those
+ * whose plans are there already are left out of the order): the uint32 at
+ * byte PP_WS_SHARE + 24 is then 1 and the one after it k.
  */
 #define PP_WS_WORK 1024
 #define PP_WS_WORK_STRIDE 128

@@ -296,23 +296,70 @@ static int pp_dp_tiles(int L, int D, int S, int64_t N, const pp_ws_layout &lay) 
     return N >= least && (L > 104 ? rows > tiled : 3 * rows > 4 * tiled) ? 0 : lay.nt;
 }
 
-// How the bands of pp_dp_band.h are used.  For L > 128 the preparation of shared DPs tries them on every list of
-// a wave and more.  For L <= 128 the DP kernel finishes the candidates with the channel-free plan itself where
-// the test is cheap (band_link_bytes), which takes it 5 us of trips to memory: worth it from about 10^8 (cell,
-// split) pairs on (whole calls without / with: 36 / 42 us at 1.3e7, 31 / 36 at 4.9e7, 63 / 56 at 9.6e7, 49.6 /
-// 32.2 at 1.1e8; a list of all orderings shares two rows in three).  Where the test is not cheap, or whole rows
-// of all candidates would take so long that two launches more are little, the bands come first in launches of
-// their own (239 369 orderings, L = 104, S = 14 2072 -> 179 us; 20 317, whose links bind, L = 99, S = 37
-// 1173 -> 795; 549 239, L = 77, S = 39, where links bind so that none ends, 19.26 -> 19.6 ms).
+// How the bands of pp_dp_band.h are used: where whole rows of all candidates take so long that looking for plans
+// that need none costs little if there are none.  Looking for the channel-free plan costs next to nothing where links
+// bind so often that the table's block finds nothing to be had (BAND_SAMPLE); for the recursion over the bands' cells
+// see band_cells.  (Below: whole calls of pp_partition_dp in us, without; with bands
+// and links that never bind; with bands and links that bind nearly everywhere.)
+//
+// L > 128: the preparation of shared DPs looks for the channel-free plan of every list of a wave and more: 64
+// candidates 61; 44; 64 (L = 150, S = 8), 116; 78; 140 (150, 32), 394; 94; 473 against 469 without (1024, 32).  The
+// worst are short lists with links that seldom bind, but where it matters: 76 -> 91 (300, 8), 432 -> 508 (400, 64);
+// for L <= 128 56 -> 65 (3000 candidates, 128, 16), 64 -> 72 (20 000, 128, 8).
+// With plans of every stage count the table takes 0.11 S^2 us and more: 119; 288; 143 against 140 (150, 32), but 397;
+// 227; 476 against 472 (1024, 32).
+//
+// L <= 128: the row kernel, and the tiled one of few tiles, finish the candidates with the channel-free plan themselves
+// where the links' words fit the LDS (band_link_bytes): 33; 23; 34 (6000 candidates, L = 128, S = 8), 50; 24; 53 (all 8!
+// orderings), 69; 31; 71 (10 000, 97, 11), 77; 24; 81 (60 000, 40, 8); all 7! orderings 22.5; 21.5; 23.8 are too few.
+// Otherwise in launches of their own: 63; 31; 68 (8!, L = 88), 121; 29; 127 (40 000, 88, 8), 164; 58; 173 (8000, 60,
+// 33), 81; 29; 87 (40 000, 100, 6), but 48; 28; 52 (10 000, 88, 8) and 22; 26; 26 (2600).  (With that in it, the tiled
+// kernel of more tiles has a wave per SIMD less: 175 -> 261 at 300 000, L = 64, S = 4, with links that bind.)
+static double band_rows_work(int L, int S, int64_t N, bool lex) {
+    return (double)N * (S - 1) * L / (lex ? 3 : 1);  // (a list of all orderings shares two rows in three)
+}
+
+// About what whole rows take, in us: for L > 128 a wave's trips from row to row or the cells of all, else the cells, by
+// the waves of a compute unit that the LDS of the tiled kernel has room for.
+static double band_whole_us(int L, int D, int S, int64_t N, bool lex, const pp_ws_layout &lay) {
+    const double work = band_rows_work(L, S, N, lex);
+    if (!lay.nt) {
+        const double trips = (S - 1) * (1.5 + 0.01 * L), cells = 4e-6 * work;
+        return trips > cells ? trips : cells;
+    }
+    if (!pp_dp_tiles(L, D, S, N, lay)) return 4e-6 * work;
+    size_t lds;
+    const int wpb = pp_dp_tile_shape(L, D, S, lay.nt, &lds), waves = (int)(160 * 1024 / lds) * wpb;
+    return (waves < 12 ? 50e-6 / waves : 4e-6) * work;
+}
+
+// How far N candidates are from being enough for the recursion over the bands' cells, which takes a wave some 80 + S us
+// (L > 128) or 40 + 4 S whatever comes of it, S / 2 times as much for plans of every stage count: 0 not enough; 1 if
+// the table's block finds that it probably ends most of them (a third of the time whole rows take); 2 in any case (a tenth).
+// Where it ends them: 3780 -> 316 (200 000 candidates, L = 300, S = 16), 1410 -> 626 (8000, 1024, 32), 1112 -> 542 (270 000,
+// 97, 11), 1800 -> 76 (100 000, 77, 30).  Where it does not: 668 -> 734 (270 000, 128, 8), 958 -> 1029 (40 000, 1024, 8), and
+// what the two rules keep it from: 910 -> 1067 (2000, 1024, 64), 880 -> 970 (40 000, 300, 16), 64 -> 135 (2000, 150, 8),
+// 54 -> 110 (3000, 128, 16), 60 -> 241 (300, 150, 8, every stage count).
+static int band_cells(int L, int D, int S, int64_t N, int stages, bool lex, const pp_ws_layout &lay) {
+    const double price = (lay.nt ? 40 + 4 * S : 80 + S) * (stages ? S / 2 + 1 : 1);
+    const double whole = band_whole_us(L, D, S, N, lex, lay);
+    return whole >= 10 * price ? 2 : whole >= 3 * price ? 1 : 0;
+}
+
 static int band_use(int L, int D, int S, int64_t N, int stages, bool lex, const pp_ws_layout &lay) {
     if (!lay.band || D > 64) return BAND_USE_NOT;
-    if (!lay.nt) return lay.sh_table ? BAND_USE_INSIDE : BAND_USE_NOT;
-    const double pairs = (double)N * (S - 1) * L * L / (lex ? 3 : 1);
-    const bool cheap = band_link_bytes(D, S, stages) != 0;
-    // (the words' place is that of T)
-    const bool room = (size_t)band_link_words(D, S, stages) * 8 + (size_t)N / 8 + 8 <= (size_t)N * 8;
-    if (room && pairs >= (cheap ? 6e9 : 4e8)) return BAND_USE_ALONE;
-    return cheap && pairs >= 9e7 ? BAND_USE_INSIDE : BAND_USE_NOT;
+    const double work = band_rows_work(L, S, N, lex);
+    if (!lay.nt) {
+        if (!lay.sh_table) return BAND_USE_NOT;
+        int waves = 1;
+        band_table_lds(L, S, stages, waves);
+        return !stages || band_whole_us(L, D, S, N, lex, lay) >= (double)S * S / waves ? BAND_USE_INSIDE : BAND_USE_NOT;
+    }
+    const bool room = (size_t)band_link_words(D, S, stages) * 8 + (size_t)N / 8 + 8 <= (size_t)N * 8;  // (T's place)
+    const bool inside = pp_dp_tiles(L, D, S, N, lay) <= DPT_INSIDE_NT && band_link_bytes(D, S, stages) != 0;
+    if (room && band_cells(L, D, S, N, stages, lex, lay)) return BAND_USE_ALONE;
+    if (inside) return work >= 3e6 ? BAND_USE_INSIDE : BAND_USE_NOT;
+    return room && work >= 8e6 ? BAND_USE_ALONE : BAND_USE_NOT;
 }
 
 int pp_launch_pack(int L, int D, int S, int64_t N, const int64_t *PF, const int64_t *PB,
@@ -339,6 +386,7 @@ int pp_launch_pack(int L, int D, int S, int64_t N, const int64_t *PF, const int6
     t.table = band_use(L, D, S, N, stages, orderings == NULL, lay) ? (int *)(base + lay.band) : NULL;
     t.waves = 1;
     t.stages = stages;
+    t.cells = band_cells(L, D, S, N, stages, orderings == NULL, lay);
     t.fit_limit = (1ull << (31 - a.K)) - 1;
     int grid = PP_PACK_BLOCKS + 2;
     size_t lds = (size_t)3 * (L + 1) * 8;
@@ -424,6 +472,10 @@ int pp_launch_dp(int L, int D, int S, int64_t N, const int64_t *PF, const int64_
     a.defer_mmax = defer_mmax;
     const int use = band_use(L, D, S, N, stages, lex_ord != NULL, lay);
     a.band = use ? (const int *)(base + lay.band) : NULL;
+    // (representatives are fewer than the candidates the rule has looked at)
+    a.band_all = band_cells(L, D, S, N, stages, lex_ord != NULL, lay) ? 0 : N + 1;
+    if (!a.band_all && lay.sh_table)
+        for (a.band_all = 64; a.band_all < N && !band_cells(L, D, S, a.band_all, stages, false, lay);) a.band_all *= 2;
     a.left = NULL;
 
     int cus = 256;

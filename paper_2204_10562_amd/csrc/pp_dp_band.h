@@ -49,6 +49,9 @@ __host__ __device__ static inline int band_hidden_at(int S, int xi, int n) {
     return band_C_at(S, S + 1) + (xi * (xi - 1) / 2 + n) * BAND_CELLS;
 }
 
+// Lists of at least dp_args::band_all candidates are looked at with the recursion over the bands' cells, shorter ones
+// for the channel-free plan alone.
+
 // LDS of one wave: a column of splits (4 bits a cell) and one of devices per lane.  Lists of fewer than a wave's
 // candidates are left to the other kernels (pp_band_wanted).
 __host__ __device__ static inline size_t band_lds_per_wave(int S) {
@@ -82,17 +85,21 @@ __host__ __device__ static inline size_t band_link_bytes(int D, int S, int stage
 }
 __device__ __forceinline__ void band_links(const dp_args &a, const int *table, unsigned long long *links) {
     const int S = a.S, nl = a.D * a.D, words = band_link_words(a.D, S, a.stages);
-    for (int i = threadIdx.x; i < words; i += blockDim.x) {
-        unsigned long long m = 0;
+    if (!a.stages) {
+        for (int i = threadIdx.x; i < words; i += blockDim.x) links[i] = 0;
+        __syncthreads();
+    }
+    for (int i = threadIdx.x; i < (S - 1) * nl; i += blockDim.x) {
+        const int n = i / nl + 1, link = i - (n - 1) * nl;
         if (a.stages) {
-            const int n = i / nl + 1, link = i - (n - 1) * nl;
+            unsigned long long m = 0;
             for (int xi = n + 1; xi <= S; ++xi)
                 if (band_link_reaches(a, table, xi, link, n)) m |= 1ull << (xi - 1);
-        } else {
-            for (int n = 1; n < S; ++n)
-                if (band_link_reaches(a, table, S, i, n)) m |= 1ull << n;
+            links[i] = m;
+        } else if (band_link_reaches(a, table, S, link, n)) {
+            // (a row of a link per thread: with a link per thread it is a chain of S trips to memory)
+            atomicOr(&links[link], 1ull << n);
         }
-        links[i] = m;
     }
 }
 
@@ -342,9 +349,9 @@ __device__ __forceinline__ unsigned long long band_try(const dp_args &a, const i
 
 // How a row kernel for L <= 128 (A: dp_rows_args or dp_tile_args) passes by the candidates that bands finish: whole
 // rows are computed for those left, a bit each in `left`.  Either a launch before this one has left them in memory,
-// or the ones with the channel-free plan are finished here, one per lane: where a wave's chunk is shorter than a
-// wave is wide, the workgroup's candidates are dealt out together.  Else the chunk is taken in pieces of up to 64.
-// Where that has to be found out here and more than half of a piece is left, what follows it goes without.  (Bits
+// or (k_dp_rows) the ones with the channel-free plan are finished here, one per lane: where a wave's chunk is shorter
+// than a wave is wide, the workgroup's candidates are dealt out together.  Else the chunk is taken in pieces of up to
+// 64.  Where that has to be found out here and more than half of a piece is left, what follows it goes without.  (Bits
 // that are in memory are read to the end: 270 000 orderings, L = 97, S = 11, 46 % of them left 1019 -> 801 us, 83 %
 // 1216 -> 1164, all of them 1264 -> 1268.)
 // (A kernel without this where neither can be worth it, pp_dp.hip.)  Returns whether all rows are to be computed.
@@ -354,25 +361,27 @@ __device__ __forceinline__ bool band_begin(const A &a, unsigned char *smem, unsi
     left = 0;
     if (BANDS == BAND_USE_NOT || a.g.band[band_top_at(a.S, 0, a.S)] < 0) return true;
     if (BANDS == BAND_USE_ALONE) return false;
-    if (!(a.pooled || a.links_at) || !band_free(a.g, a.g.band)) return true;
-    unsigned long long *words = (unsigned long long *)(smem + (a.pooled ? 0 : a.links_at));
-    reach = words + 4;
-    band_links(a.g, a.g.band, reach);
-    __syncthreads();
-    if (a.pooled) {
-        // dealt out together, before any wave needs its part of the LDS
-        const int lane = threadIdx.x & 63, wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wpb = blockDim.x >> 6;
-        const long long first = (long long)blockIdx.x * wpb * a.chunk;
-        const int at = 64 * wib, total = (int)(a.N - first < wpb * a.chunk ? a.N - first : wpb * a.chunk);
-        const unsigned long long word =
-            at < total ? band_free_try(a.g, a.g.band, reach, first + at + lane, at + lane < total) : 0;
-        if (lane == 0) words[wib] = word;
+    if constexpr (BANDS == BAND_USE_INSIDE) {
+        if (!(a.pooled || a.links_at) || !band_free(a.g, a.g.band)) return true;
+        unsigned long long *words = (unsigned long long *)(smem + (a.pooled ? 0 : a.links_at));
+        reach = words + 4;
+        band_links(a.g, a.g.band, reach);
         __syncthreads();
-        const int mine_at = wib * (int)a.chunk, w = mine_at >> 6, by = mine_at & 63;
-        left = words[w] >> by;
-        if (by && w + 1 < wpb) left |= words[w + 1] << (64 - by);
-        left &= (1ull << a.chunk) - 1;
-        __syncthreads();
+        if (a.pooled) {
+            // dealt out together, before any wave needs its part of the LDS
+            const int lane = threadIdx.x & 63, wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wpb = blockDim.x >> 6;
+            const long long first = (long long)blockIdx.x * wpb * a.chunk;
+            const int at = 64 * wib, total = (int)(a.N - first < wpb * a.chunk ? a.N - first : wpb * a.chunk);
+            const unsigned long long word =
+                at < total ? band_free_try(a.g, a.g.band, reach, first + at + lane, at + lane < total) : 0;
+            if (lane == 0) words[wib] = word;
+            __syncthreads();
+            const int mine_at = wib * (int)a.chunk, w = mine_at >> 6, by = mine_at & 63;
+            left = words[w] >> by;
+            if (by && w + 1 < wpb) left |= words[w + 1] << (64 - by);
+            left &= (1ull << a.chunk) - 1;
+            __syncthreads();
+        }
     }
     return false;
 }
@@ -381,17 +390,18 @@ __device__ __forceinline__ bool band_begin(const A &a, unsigned char *smem, unsi
 template <int BANDS, typename A>
 __device__ __forceinline__ int band_piece(const A &a, const unsigned long long *reach, long long c0, int base, int end,
                                           unsigned long long &left) {
-    const int lane = threadIdx.x & 63;
-    if (BANDS == BAND_USE_ALONE) {
+    if constexpr (BANDS == BAND_USE_ALONE) {
         const unsigned long long *at = a.g.left + ((c0 + base) >> 6);
         const int by = (int)((c0 + base) & 63), n = end - base;
         left = at[0] >> by;
         if (by + n > 64) left |= at[1] << (64 - by);
         if (n < 64) left &= (1ull << n) - 1;
-    } else if (!a.pooled) {
-        left = band_free_try(a.g, a.g.band, reach, c0 + base + lane, base + lane < end);
+    } else if constexpr (BANDS == BAND_USE_INSIDE) {
+        const int lane = threadIdx.x & 63;
+        // (dealt out together: the chunk is one piece)
+        if (!a.pooled) left = band_free_try(a.g, a.g.band, reach, c0 + base + lane, base + lane < end);
     }
-    return end;  // (dealt out together: the chunk is one piece)
+    return end;
 }
 
 // L <= 128: the bands in launches of their own, in front of the DP kernel (links: room for D * D words).

@@ -50,11 +50,13 @@ __global__ __launch_bounds__(64) void k_dp_band(band_args b) {
     __syncthreads();
     band_pace pace = {};
     const long long todo = PASS != BAND_SECOND ? a.N : (long long)a.hdr->share_nsorted;
+    const bool cells = todo >= a.band_all;
+    if (PASS == BAND_SECOND && !cells && !links) return;
     for (long long r = (long long)blockIdx.x * 64; r < todo; r += (long long)gridDim.x * 64) {
         const bool live = r + lane < todo;
         const long long c = live ? (PASS != BAND_SECOND ? r + lane : b.reps[r + lane]) : 0;
         unsigned long long left = __ballot(live);
-        if (use) left = band_try(a, b.band, links, PK, smem, c, live, pace);
+        if (use) left = cells ? band_try(a, b.band, links, PK, smem, c, live, pace) : band_free_try(a, b.band, links, c, live);
         if (PASS == BAND_ALONE) {
             if (lane == 0) b.left[r >> 6] = left;
             continue;

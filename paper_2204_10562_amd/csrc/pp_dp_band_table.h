@@ -14,8 +14,15 @@ struct band_table_args {
     int *table;                    // NULL: not wanted
     int waves;                     // waves that find the bands
     int stages;
+    int cells;                     // the recursion over the bands' cells is worth trying: 0 no, 1 if links allow, 2 yes
     unsigned long long fit_limit;  // of the 32-bit keys
 };
+
+// Of so many transfer times all over the table, the part that is longer than a stage says what bands are good for.
+// A candidate has the channel-free plan if none of its S - 1 cuts has one: not likely where they are more than a
+// (S - 1)th.  The recursion moves cuts to where there is none, p / (1 - p) cells away on an average, and all of its
+// cuts together have about a band to move in.
+#define BAND_SAMPLE 2  // per thread
 
 // The bands of pp_dp_band.h.  P: the prefix sums in LDS, with 0 before them
 // and a large number twice behind; inv[b]: the first k with
@@ -166,7 +173,7 @@ static inline size_t band_table_lds(int L, int S, int stages, int &waves) {
 
 __device__ inline void band_table(const band_table_args &a, unsigned char *sh) {
     const int L = a.L, S = a.S, tid = threadIdx.x;
-    int *s_longest = (int *)sh, *s_differs = s_longest + 4, *P = s_longest + 9;
+    int *s_longest = (int *)sh, *s_differs = s_longest + 4, *s_sample = s_longest + 5, *P = s_longest + 9;
     unsigned short *inv = (unsigned short *)(sh + (((size_t)(L + 12) * 4 + 15) & ~(size_t)15));
     const int nb = band_buckets(L);
     unsigned short *reach = inv + nb;
@@ -186,17 +193,29 @@ __device__ inline void band_table(const band_table_args &a, unsigned char *sh) {
         fits &= p >= q && p <= total;
         longest = band_max(longest, (int)(p - q));
     }
+    // (requested here, looked at when the buckets are there)
+    long long sample[BAND_SAMPLE];
+    if (a.cells < 2) {
+#pragma unroll
+        for (int j = 0; j < BAND_SAMPLE; ++j) {
+            const unsigned at = (unsigned)(tid * BAND_SAMPLE + j) * 2654435761u;  // (spread over links and cuts)
+            const int link = (int)((at >> 16) * (unsigned)(a.D * a.D) >> 16), k = (int)((at & 0xffff) * (unsigned)(L - 1) >> 16);
+            const size_t i = (size_t)link * L + k;
+            sample[j] = a.XF[i] + a.XB[i];
+            if (link % (a.D + 1) == 0) sample[j] = -1;  // (a device and itself)
+        }
+    }
     for (int off = 32; off; off >>= 1) longest = band_max(longest, __shfl_xor(longest, off));
     if ((tid & 63) == 0) s_longest[tid >> 6] = longest;
-    if (tid == 0) *s_differs = 0;
+    if (tid == 0) *s_differs = s_sample[0] = s_sample[1] = 0;
     __syncthreads();
+    longest = band_max(band_max(s_longest[0], s_longest[1]), band_max(s_longest[2], s_longest[3]));
     if (differs) *s_differs = 1;
-    if (!__syncthreads_and(fits) || !*s_differs) {
+    auto none = [&]() {
         for (int i = tid; i < BAND_LEVELS * S; i += 256) a.table[i] = -1;
         for (int i = tid; i < S; i += 256) a.table[band_C_at(S, i + 1)] = -1;
-        return;
-    }
-    longest = band_max(band_max(s_longest[0], s_longest[1]), band_max(s_longest[2], s_longest[3]));
+    };
+    if (!__syncthreads_and(fits) || !*s_differs) return none();
     band_model m;
     m.P = P;
     m.inv = inv;
@@ -211,7 +230,17 @@ __device__ inline void band_table(const band_table_args &a, unsigned char *sh) {
         const int from = k ? (P[k - 1] >> m.sh) + 1 : 0, to = P[k] >> m.sh;
         for (int b = from; b <= to; ++b) inv[b] = (unsigned short)k;
     }
+    if (a.cells < 2) {
+        int seen = 0, over = 0;
+#pragma unroll
+        for (int j = 0; j < BAND_SAMPLE; ++j) {
+            seen += __builtin_popcountll(__ballot(sample[j] >= 0));
+            over += __builtin_popcountll(__ballot(sample[j] > longest && sample[j] > total / S));
+        }
+        if ((tid & 63) == 0) { atomicAdd(&s_sample[0], seen); atomicAdd(&s_sample[1], over); }
+    }
     __syncthreads();
+    if (s_sample[1] * (S - 1) > (a.cells ? 3 * BAND_CELLS / 4 * (s_sample[0] - s_sample[1]) : s_sample[0])) return none();
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (wave >= a.waves) return;
     unsigned short *hi = reach + (size_t)wave * 2 * S * 64, *lo = hi + (size_t)S * 64;

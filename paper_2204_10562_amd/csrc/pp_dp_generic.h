@@ -21,6 +21,7 @@ struct dp_args {
     const int *p32, *x32;
     const long long *bfl;  // the partition DP with no channel cost (values, then splits), see pp_dp_flat.h
     const int *band;       // the table of pp_dp_band.h, or NULL
+    long long band_all;    // the fewest candidates for which the recursion over the bands is worth it (pp_dp.hip)
     const unsigned long long *left;  // a bit per candidate: k_dp_band has left it (NULL: it has not run)
     size_t lds_bytes;      // dynamic LDS of the launch
     // > 0: when the closed form applies and the finish times of a schedule of defer_mmax

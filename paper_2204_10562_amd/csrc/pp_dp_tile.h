@@ -6,6 +6,7 @@
 
 #define DPT_ARENA_ROWS 64  // backtrack rows a wave keeps before it must write plans out
 #define DPT_PENDING 64     // candidates whose plans are written out together (one per lane)
+#define DPT_INSIDE_NT 6    // most tiles with which the kernel finishes candidates with the channel-free plan itself (pp_dp.hip)
 
 struct dp_tile_args {
     int L, D, S, K;

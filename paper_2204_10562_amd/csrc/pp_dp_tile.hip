@@ -95,8 +95,8 @@ __device__ __forceinline__ void lds_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// (sixteen tiles just fit two waves per SIMD: with a few registers more 3000 orderings, L = 128, S = 8, took 41 us
-// instead of 30)
+// (sixteen tiles just fit two waves per SIMD, with 7 or 8 registers spilled: with one wave 3000 orderings, L = 128, S = 8,
+// took 41 us instead of 31)
 template <int NT, int BANDS>
 __global__ __launch_bounds__(256, NT >= 16 ? 2 : 1) void k_dp_tile(dp_tile_args a) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -526,7 +526,9 @@ template <int NT>
 static int launch_nt(const dp_tile_args &a, int grid, int wpb, size_t lds, hipStream_t st) {
     if (!a.g.band) hipLaunchKernelGGL((k_dp_tile<NT, BAND_USE_NOT>), dim3(grid), dim3(64 * wpb), lds, st, a);
     else if (a.g.left) hipLaunchKernelGGL((k_dp_tile<NT, BAND_USE_ALONE>), dim3(grid), dim3(64 * wpb), lds, st, a);
-    else hipLaunchKernelGGL((k_dp_tile<NT, BAND_USE_INSIDE>), dim3(grid), dim3(64 * wpb), lds, st, a);
+    else if constexpr (NT <= DPT_INSIDE_NT)
+        hipLaunchKernelGGL((k_dp_tile<NT, BAND_USE_INSIDE>), dim3(grid), dim3(64 * wpb), lds, st, a);
+    else return PP_ERR_INVALID_ARG;
     return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_HIP;
 }
 

@@ -43,6 +43,7 @@ struct share_args {
     const int *ord;
     dp_args g;                  // what the bands need of it: the tables
     const int *band;            // the pack kernel's table of the bands, or NULL
+    int sort;                   // lists whose keys do not fit are sorted by their first devices
     unsigned long long *links;  // band_links' words
     pp_ws_header *hdr;
     unsigned long long *lhash;  // [D*D]
@@ -178,7 +179,7 @@ __global__ __launch_bounds__(256) void k_share_keys(share_args a) {
     // otherwise: buckets of the first kdev devices (pp_dp_band.hip)
     int kdev = 0;
     unsigned nbuck = 1;
-    if (!tsize && a.band) nbuck = share_buckets(D, S, kdev);  // (not worth it for less than a wave of candidates)
+    if (!tsize && a.sort) nbuck = share_buckets(D, S, kdev);
     if (blockIdx.x == 0 && tid == 0) {
         a.hdr->share_tsize = tsize ? tsize : (kdev ? nbuck : 0);
         a.hdr->share_active = tsize != 0;
@@ -495,13 +496,14 @@ int pp_launch_share_prepare(const dp_args &g, int fill_part, int run_waves, void
     a.run_waves = run_waves;
     a.g = g;
     a.band = g.band;
+    a.sort = N >= 64;  // (no wave of the DP kernel has two candidates of a shorter list)
     // (the saved rows of 64 waves and more, S - 1 of 1040 bytes and more each, hold 8 (S - 1) bytes per link of up
     // to 64 devices, and are needed later)
     a.links = (unsigned long long *)((char *)ws + lay.sh_rows);
     const int link_blocks = (D * D + 3) / 4;
     hipLaunchKernelGGL(k_share_hash, dim3(link_blocks + SHARE_FILL_BLOCKS), dim3(256), 0, st, a);
     hipLaunchKernelGGL(k_share_classes, dim3(link_blocks), dim3(256), 0, st, a);
-    int rc = a.band ? pp_launch_dp_band(g, a.band, a.links, a.keys, a.table, a.reps, 1, st) : PP_OK;
+    int rc = a.sort ? pp_launch_dp_band(g, a.band, a.links, a.keys, a.table, a.reps, 1, st) : PP_OK;
     if (rc) return rc;
     // The keys of a long list in two launches, the first eighth alone: 10^6 candidates of 15 751 keys 87 us when
     // every candidate looks past the caches and does its own atomic, 57 us so.
@@ -515,7 +517,7 @@ int pp_launch_share_prepare(const dp_args &g, int fill_part, int run_waves, void
     }
     hipLaunchKernelGGL(k_share_count, dim3(PP_SHARE_TABLE / 256), dim3(256), 0, st, a);
     hipLaunchKernelGGL(k_share_reps, dim3(PP_SHARE_TABLE / 256), dim3(256), 0, st, a);
-    rc = a.band ? pp_launch_dp_band(g, a.band, a.links, a.keys, a.table, a.reps, 0, st) : PP_OK;
+    rc = a.sort ? pp_launch_dp_band(g, a.band, a.links, a.keys, a.table, a.reps, 0, st) : PP_OK;
     if (rc) return rc;
     hipLaunchKernelGGL(k_share_cost, dim3((unsigned)share_grid(N)), dim3(256), 0, st, a);
     hipLaunchKernelGGL(k_share_bounds, dim3((unsigned)share_grid(N)), dim3(256), 0, st, a);

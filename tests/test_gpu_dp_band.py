@@ -101,3 +101,26 @@ def test_work_counters(ppo):
             assert s["pairs_executed"] == 0 and s["free_rows"] == s["rows_executed"]
         else:
             assert s["pairs_executed"] > s["rows_executed"] > 2 * (s["free_rows"] + s["band_rows"])
+
+
+@pytest.mark.parametrize("L,D,S,N,looks", [(150, 9, 8, 300, 1), (300, 16, 16, 2000, 1), (400, 64, 64, 64, 1), (1024, 9, 8, 64, 1),
+                                           (88, 8, 8, 2600, 0), (128, 8, 8, 900, 0), (60, 40, 33, 3000, 0), (97, 12, 11, 7000, 1),
+                                           (40, 8, 8, 60000, 1), (128, 16, 16, 9000, 1)])
+def test_short_lists_whose_links_bind(ppo, L, D, S, N, looks):
+    """Nothing is tried that cannot be worth it there: the recursion over bands nowhere, and the plan of the program without
+    transfer times only where a list is long enough for it and links seldom bind."""
+    from paper_2204_10562_amd import binding as pp
+    from paper_2204_10562_amd.problem import GpuProblem
+    for kind in ("free", "most"):
+        w = problem(kind, 9600 + L + S + N, L, D, S, N)
+        g = GpuProblem(w)
+        g.prefix()
+        for stages in (False, True):
+            print("[case] short list", kind, L, D, S, N, stages, flush=True)
+            assert (g.dp_stages() if stages else g.dp())[0] == 0
+            s = pp.read_workspace_stats(g.ws)
+            assert s["band_pairs"] == s["band_rows"] == 0
+            if kind == "most":
+                assert s["free_rows"] == 0
+            elif not stages:
+                assert (s["free_rows"] > 0) == bool(looks)

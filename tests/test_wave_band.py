@@ -69,3 +69,22 @@ def test_work_counters(driver, kind):
             assert pairs == 0 and free_rows >= N - 1, case
         if pairs == 0:
             assert band_rows == 0, case
+
+
+@pytest.mark.parametrize("kind", [FREE, ZEROS, SOME, HIGH])
+def test_short_lists(driver, kind):
+    """A list too short for the recursion is looked at for the channel-free plan alone, and not at all where links bind so
+    often that hardly a candidate has it."""
+    cases = [(L, D, S, N, L + S, kind, stages, words) for L, D, S, N in SIZES[1:8] for stages in (0, 1) for words in (0, 1)
+             if not (stages and S > 12)]
+    ended = 0
+    for case, (rc, _, differ, done, reported, pairs, rows, _, _, free_rows) in zip(cases, driver(cases, "short")):
+        L, D, S, N, _, _, _, words = case
+        assert rc == 0 and differ == 0 and pairs == 0 and rows == free_rows, case
+        assert (rows > 0) == (done > 0) and (words or not done), case
+        if kind == FREE and words:
+            assert (done, reported) == (N - 1, 1), case
+        if kind == HIGH and L > 4 * S > 8:
+            assert done == reported == 0, case
+        ended += done
+    assert ended > 0 or kind in (SOME, HIGH)

@@ -5,7 +5,8 @@
 // the words of the links are there.  Prints, per case, the return value, the status, how many results of the
 // candidates that ended differ from the recursion over all splits, how many ended, and how many candidates with a
 // bad ordering were reported; with an argument also the work counters: pairs, rows, and those of them in bands and
-// of the channel-free program.
+// of the channel-free program.  The list counts as one that is long enough for the recursion, with the argument
+// "short" as one that is not.
 #include "../../paper_2204_10562_amd/csrc/pp_dp_band_table.h"
 #include "../../paper_2204_10562_amd/csrc/pp_dp_band.hip"
 
@@ -21,7 +22,8 @@ static void k_band_table(band_table_args a) { band_table(a, (unsigned char *)dyn
 
 typedef long long ll;
 
-int main(int argc, char **) {
+int main(int argc, char **argv) {
+    const bool shorter = argc > 1 && !strcmp(argv[1], "short");
     int L, D, S, N, seed, kind, stages, words;
     while (scanf("%d %d %d %d %d %d %d %d", &L, &D, &S, &N, &seed, &kind, &stages, &words) == 8) {
         std::mt19937_64 g(seed);
@@ -71,7 +73,7 @@ int main(int argc, char **) {
         band_table_args p = {};
         p.L = L; p.D = D; p.S = S; p.K = pp_index_bits(L);
         p.PF = PF.data(); p.PB = PB.data(); p.XF = XF.data(); p.XB = XB.data();
-        p.table = table.data(); p.stages = stages;
+        p.table = table.data(); p.stages = stages; p.cells = shorter ? 0 : 2;
         p.fit_limit = (1ull << (31 - p.K)) - 1;
         const size_t need = band_table_lds(L, S, stages, p.waves);
         if (need > sizeof dyn) return 1;
@@ -85,6 +87,7 @@ int main(int argc, char **) {
         a.hdr = &hdr; a.p32 = p32.data(); a.x32 = x32.data(); a.ord = ord.data();
         a.stages = stages; a.C_out = C.data(); a.bounds_out = bounds.data(); a.status = &status;
         a.band = table.data();
+        a.band_all = shorter ? N + 1 : N;
         const int rc = pp_launch_dp_band_alone(a, words ? links.data() : NULL, left.data(), NULL);
         int differ = 0, ended = 0, reported = 0;
         for (int c = 0; c < N; ++c) {
