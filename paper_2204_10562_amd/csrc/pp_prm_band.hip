@@ -148,7 +148,7 @@ __global__ __launch_bounds__(PRM_PREP_THREADS) void k_prm_prep(prm_args a) {
     };
     const int k = tid & (PRM_TRIES - 1);
     const float v = (float)(trial(k) - fixed);  // (ceil adds less than `fixed` to a stage or transfer)
-    for (int t = tid; t < 3 * 17 * PRM_TRIES; t += T) s_reach[0][0][t] = 0;
+    for (int t = tid; t < 3 * 17 * PRM_TRIES; t += T) ((int *)s_reach)[t] = 0;
     if (tid < D * (D + 1) / 2) {
         // (GPUs before, replicas) by descending GPUs before
         int q = 1;
@@ -514,8 +514,9 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
                 if (t == 0) pp_raise(a.status, PP_FAULT_ORDERING);
                 if (t < D) a.W_out[c * D + t] = PP_INF64;
                 for (int n = t; n < tri; n += LANES) { a.bounds_out[c * tri + n] = 0; a.reps_out[c * tri + n] = 0; }
-            } else if (t < D && wbest == INF) {  // (not with bands that hold a plan)
+            } else if (t < D && wbest == INF) {  // (not with bands that hold a plan; as k_prm has it)
                 a.W_out[c * D + t] = PP_INF64;
+                for (int n = t * (t + 1) / 2; n < (t + 1) * (t + 2) / 2; ++n) a.bounds_out[c * tri + n] = a.reps_out[c * tri + n] = 0;
             } else if (t < D) {
                 const int xi = t + 1;
                 a.W_out[c * D + t] = (long long)wbest;

@@ -1,0 +1,87 @@
+"""The replicated planner from the bands, run lane by lane on the CPU (its own sources, with UndefinedBehaviorSanitizer)
+against the oracle: times from a few microseconds to the limit of 32-bit values, links that bind, layers of length zero,
+both ways to share the states among waves."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2204_10562_amd import workloads
+from test_wave_makespan import build
+
+pytestmark = pytest.mark.skipif(__import__("shutil").which("g++") is None, reason="needs g++")
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    exe = build(tmp_path_factory.mktemp("prm"), "prm_driver")
+
+    def ask(problems):
+        env = dict(os.environ)
+        env.pop("LD_PRELOAD", None)  # the sanitizer's runtime must come first in the library list
+        text = "".join(" ".join(str(int(x)) for x in p) + "\n" for p in problems)
+        res = subprocess.run([exe], input=text, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=600, env=env)
+        assert res.returncode == 0 and "runtime error" not in res.stderr, res.stderr[-2000:]
+        out = [np.array([int(x) for x in l.split()], np.int64) for l in res.stdout.splitlines()]
+        assert len(out) == len(problems)
+        return out
+    return ask
+
+
+def problem(seed, L, D, N, M, times, kind):
+    w = workloads.random_small(seed, L, D, D, N, zero_frac=0.05, hi_time=times, hi_act=90 * times)
+    rng = np.random.Generator(np.random.PCG64(seed))
+    if kind == "far":  # links that bind
+        w.bw[:] = np.maximum(w.bw // 8, 1)
+    if kind == "one slow":
+        w.bw[0, D - 1] = w.bw[D - 1, 0] = 1
+    alpha = rng.integers(0, 3 * times, size=L).astype(np.int64)
+    return w, alpha, M
+
+
+def numbers(w, alpha, M, team, plant=0):
+    return np.concatenate([[w.L, w.D, w.N, M, team, plant], w.fwd, w.bwd, w.actf, w.actb, alpha, w.bw.ravel(), w.orderings.ravel()])
+
+
+def split(out, N, D):
+    tri = D * (D + 1) // 2
+    W, b, r = out[5:5 + N * D], out[5 + N * D:5 + N * (D + tri)], out[5 + N * (D + tri):]
+    return W.reshape(N, D), b.reshape(N, tri), r.reshape(N, tri)
+
+
+# (the largest times: sums next to 2^29 / M, where the bound's arithmetic in 32-bit floats is coarsest)
+SIZES = [(9, 3, 9, 3, 40), (17, 8, 9, 64, 40), (30, 4, 5, 16, 300), (34, 5, 9, 30, 5000), (60, 6, 3, 60, 900), (26, 9, 5, 24, 60),
+         (40, 3, 17, 40, 120000), (90, 5, 2, 64, 40000), (70, 4, 3, 20, 160000), (33, 13, 3, 40, 200)]
+
+
+@pytest.mark.parametrize("kind", ["near", "far", "one slow"])
+def test_plans_from_the_bands(ppo, driver, kind):
+    problems = [problem(900 + i, L, D, N, M, times, kind) for i, (L, D, N, M, times) in enumerate(SIZES)]
+    used = 0
+    for team in (1, 0):
+        for (w, alpha, M), out in zip(problems, driver([numbers(*p, team) for p in problems])):
+            status, parts, lanes, widest, tried = out[:5]
+            assert status == 0 and (tried or not parts) and widest <= parts * lanes
+            if not parts:
+                continue
+            used += 1
+            rc, _, _, W0, b0, r0 = ppo.spp_replicated(w.L, w.D, w.N, M, w.fwd, w.bwd, w.actf, w.actb, alpha, w.bw, w.orderings)
+            assert rc == 0
+            W, b, r = split(out, w.N, w.D)
+            np.testing.assert_array_equal(W, W0)
+            np.testing.assert_array_equal(b, b0)
+            np.testing.assert_array_equal(r, r0)
+    assert used >= 10 if kind == "near" else used > 0
+
+
+def test_nothing_is_left_unwritten(driver):
+    """Bands without a plan (which the kernel that finds them does not make): no plan, not what was there before."""
+    for team in (0, 1):
+        w, alpha, M = problem(950, 20, 4, 9, 16, 300, "near")
+        out, = driver([numbers(w, alpha, M, team, plant=1)])
+        assert out[1] > 0
+        W, b, r = split(out, w.N, w.D)
+        assert (W[:, 1:] == np.iinfo(np.int64).max).all() and (W[:, 0] >= 0).all()
+        assert (b[:, 1:] == 0).all() and (r[:, 1:] == 0).all()
+        assert (b[:, 0] == w.L).all() and (r[:, 0] == w.D).all()

@@ -34,6 +34,8 @@ inline uint2 make_uint2(unsigned x, unsigned y) { return {x, y}; }
 struct int4 { int x, y, z, w; };
 inline int2 make_int2(int x, int y) { return {x, y}; }
 inline int4 make_int4(int x, int y, int z, int w) { return {x, y, z, w}; }
+struct float2 { float x, y; };
+inline float2 make_float2(float x, float y) { return {x, y}; }
 typedef void *hipStream_t;
 typedef int hipError_t;
 enum { hipSuccess = 0, hipErrorInvalidConfiguration = 9 };
@@ -187,6 +189,8 @@ inline unsigned long long __builtin_amdgcn_ballot_w64(bool v) { return __ballot(
 inline int __shfl_xor(int v, int m) { return (int)wave::meet(wave::SHFL_XOR, v, m); }
 inline long long __shfl_xor(long long v, int m) { return wave::meet(wave::SHFL_XOR, v, m); }
 inline unsigned long long __shfl_xor(unsigned long long v, int m) { return (unsigned long long)wave::meet(wave::SHFL_XOR, (long long)v, m); }
+inline long long __shfl_up(long long v, int d) { return wave::meet(wave::SHFL_UP, v, d); }
+inline int __shfl(int v, int i) { return (int)wave::meet(wave::READLANE, v, i); }
 inline int __shfl_up(int v, int d) { return (int)wave::meet(wave::SHFL_UP, v, d); }
 inline int __builtin_amdgcn_update_dpp(int old, int v, int ctrl, int, int, bool) { return (int)wave::meet(wave::DPP, v, ctrl, old); }
 inline int __builtin_amdgcn_readfirstlane(int v) { return (int)wave::meet(wave::READLANE, v, 0); }
@@ -194,9 +198,15 @@ inline int __builtin_amdgcn_readlane(int v, int i) { return (int)wave::meet(wave
 inline void __builtin_amdgcn_wave_barrier() { wave::meet(wave::WAVE_BARRIER, 0); }
 #define __builtin_amdgcn_fence(...) ((void)0)
 #define __builtin_amdgcn_s_setprio(...) ((void)0)
+// (the hardware's reciprocal is off by an ulp or so: a little more here, now too large and now too small)
+inline double __builtin_amdgcn_rcp(double x) { return 1.0 / x * (1.0 + ((long long)x & 1 ? 1 : -1) * 0x1p-24); }
+inline int __popc(unsigned v) { return __builtin_popcount(v); }
+inline int __mul24(int a, int b) { return a * b; }
 inline void __syncthreads() { wave::meet(wave::BLOCK_BARRIER, 1); }
 inline int __syncthreads_and(int v) { return (int)wave::meet(wave::BLOCK_BARRIER, v); }
 #define __HIP_MEMORY_SCOPE_AGENT 0
 #define __hip_atomic_load(p, order, scope) (*(p))
 template <typename T, typename V> T atomicOr(T *p, V v) { T o = *p; *p |= (T)v; return o; }
 template <typename T, typename V> T atomicAdd(T *p, V v) { T o = *p; *p += (T)v; return o; }
+template <typename T, typename V> T atomicMax(T *p, V v) { T o = *p; if ((T)v > o) *p = (T)v; return o; }
+template <typename T, typename V> T atomicMin(T *p, V v) { T o = *p; if ((T)v < o) *p = (T)v; return o; }
