@@ -40,8 +40,8 @@ def problem(seed, L, D, N, M, times, kind):
     return w, alpha, M
 
 
-def numbers(w, alpha, M, team, plant=0):
-    return np.concatenate([[w.L, w.D, w.N, M, team, plant], w.fwd, w.bwd, w.actf, w.actb, alpha, w.bw.ravel(), w.orderings.ravel()])
+def numbers(w, alpha, M, team):
+    return np.concatenate([[w.L, w.D, w.N, M, team], w.fwd, w.bwd, w.actf, w.actb, alpha, w.bw.ravel(), w.orderings.ravel()])
 
 
 def split(out, N, D):
@@ -73,15 +73,3 @@ def test_plans_from_the_bands(ppo, driver, kind):
             np.testing.assert_array_equal(b, b0)
             np.testing.assert_array_equal(r, r0)
     assert used >= 10 if kind == "near" else used > 0
-
-
-def test_nothing_is_left_unwritten(driver):
-    """Bands without a plan (which the kernel that finds them does not make): no plan, not what was there before."""
-    for team in (0, 1):
-        w, alpha, M = problem(950, 20, 4, 9, 16, 300, "near")
-        out, = driver([numbers(w, alpha, M, team, plant=1)])
-        assert out[1] > 0
-        W, b, r = split(out, w.N, w.D)
-        assert (W[:, 1:] == np.iinfo(np.int64).max).all() and (W[:, 0] >= 0).all()
-        assert (b[:, 1:] == 0).all() and (r[:, 1:] == 0).all()
-        assert (b[:, 0] == w.L).all() and (r[:, 0] == w.D).all()

@@ -191,6 +191,7 @@ inline long long __shfl_xor(long long v, int m) { return wave::meet(wave::SHFL_X
 inline unsigned long long __shfl_xor(unsigned long long v, int m) { return (unsigned long long)wave::meet(wave::SHFL_XOR, (long long)v, m); }
 inline long long __shfl_up(long long v, int d) { return wave::meet(wave::SHFL_UP, v, d); }
 inline int __shfl(int v, int i) { return (int)wave::meet(wave::READLANE, v, i); }
+inline float __shfl(float v, int i) { return __builtin_bit_cast(float, __shfl(__builtin_bit_cast(int, v), i)); }
 inline int __shfl_up(int v, int d) { return (int)wave::meet(wave::SHFL_UP, v, d); }
 inline int __builtin_amdgcn_update_dpp(int old, int v, int ctrl, int, int, bool) { return (int)wave::meet(wave::DPP, v, ctrl, old); }
 inline int __builtin_amdgcn_readfirstlane(int v) { return (int)wave::meet(wave::READLANE, v, 0); }

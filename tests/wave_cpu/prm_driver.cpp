@@ -1,10 +1,9 @@
 // Runs the replicated planner from the bands (pp_prm_band.hip, its own source) on the CPU: the workgroup that finds the
 // bands, then the kernel that plans every candidate from them.  Reads problems from stdin as numbers:
-//   L D N M TEAM PLANT fwd[L] bwd[L] actf[L] actb[L] alpha[L] bw[D*D] ord[N*D]
-// TEAM: whether the waves of a workgroup share candidates; PLANT: the bands are emptied in between, so that there is no
-// plan of more than one stage in them.  Prints, per problem, the status, the parts of a band (0: the bands are not used),
-// the lanes per candidate, the widest band, whether times for it were tried, and, where bands are used, W, bounds and
-// replicas of every candidate.
+//   L D N M TEAM fwd[L] bwd[L] actf[L] actb[L] alpha[L] bw[D*D] ord[N*D]
+// TEAM: whether the waves of a workgroup share candidates.  Prints, per problem, the status, the parts of a band (0: the
+// bands are not used), the lanes per candidate, the widest band, whether times for it were tried, and, where bands are
+// used, W, bounds and replicas of every candidate.
 #include <hip/hip_runtime.h>
 
 #undef __shared__
@@ -28,8 +27,8 @@ static void plan(const prm_args &a, bool team) {
 }
 
 int main() {
-    int L, D, N, M, team, plant;
-    while (scanf("%d %d %d %d %d %d", &L, &D, &N, &M, &team, &plant) == 6) {
+    int L, D, N, M, team;
+    while (scanf("%d %d %d %d %d", &L, &D, &N, &M, &team) == 5) {
         auto read = [&](size_t n) {
             std::vector<ll> v(n);
             for (ll &x : v) if (scanf("%lld", &x) != 1) exit(1);
@@ -59,13 +58,11 @@ int main() {
         const int parts = band[PRM_BAND_PARTS], lanes = parts ? band[PRM_BAND_LANES] : 0;
         int widest = 0;
         for (int i = 1; parts && i < D; ++i) widest = std::max(widest, band[PRM_BAND_W + i]);
-        if (plant)
-            for (int i = 1; i < D; ++i) band[PRM_BAND_W + i] = band[PRM_BAND_W2 + i] = 0;
         plan<8>(a, team);  // (does nothing where the other has the launch)
         plan<16>(a, team);
         for (int i = 0; i < 64; ++i) if (scratch[a.slots * a.slot_bytes + i] != 0x55) return 1;
-        // (the tables behind the header are written on the way to the tries)
-        printf("%d %d %d %d %d", status, parts, lanes, widest, band[PRM_BAND_HDR] != 0x55555555);
+        // (the bands' first cells are written behind the tries)
+        printf("%d %d %d %d %d", status, parts, lanes, widest, band[PRM_BAND_LO + 1] != 0x55555555);
         for (ll x : W) if (parts) printf(" %lld", x);
         for (int x : bounds) if (parts) printf(" %d", x);
         for (int x : reps) if (parts) printf(" %d", x);
