@@ -75,7 +75,9 @@ static inline int prm_band_waves(int L, int D, int lanes) {
 }
 // Whether a launch looks for bands.  A plan of M micro-batches is some 1 / M above the ideal (the AllReduce and the
 // rounded quotients), and a band of 32 cells has room for 32 / L: with M = 4, 147 layers and 6 GPUs none is narrow
-// enough, and to look costs 23 of 242 us.
+// enough, and to look costs 23 of 242 us.  (It does as well where links are slow, but not so slow that k_prm_prep sees it
+// at once: 82 -> 104 us for 24 orderings of 4 GPUs, 60 layers, M = 16, with one link slower by 1000, 730 -> 767 for 24 of 12,
+// 75, M = 24, with one slower by 30.  Where bands are narrow the same calls take 50 and 244 us.)
 static inline bool prm_band_wanted(const prm_args &a) {
     return a.D >= 3 && a.L >= a.D && (long long)a.M * 32 >= a.L && (size_t)a.slots * a.slot_bytes >= 2 * prm_band_slot_bytes(a.D) &&
            prm_band_waves(a.L, a.D, 8) && prm_band_waves(a.L, a.D, 16);

@@ -148,6 +148,24 @@ __global__ __launch_bounds__(PRM_PREP_THREADS) void k_prm_prep(prm_args a) {
     };
     const int k = tid & (PRM_TRIES - 1);
     const float v = (float)(trial(k) - fixed);  // (ceil adds less than `fixed` to a stage or transfer)
+    // Bands are narrow only if there is a plan of D stages within the largest of the times tried.  That has one GPU a
+    // stage: where the layers between two neighbours of the cuts that can be had over the slowest link take longer, there
+    // is none, and k_prm does the launch (unless bands of all cells will do).  (The last wave; one link slower by 1000:
+    // 342 us without bands, 351; 374 with the whole look, 200 orderings of 8 GPUs, 128 layers; 861, 869; 903, 300 of 12, 75.)
+    if (wave == T / 64 - 1 && L > prm_band_cells(D, 16) + 1) {
+        const float most = __shfl(v, PRM_TRIES - 1);
+        int before = 0;  // the last cut of the chunks done, or 0 (0 and L are ends of stages, too)
+        bool none = false;
+        for (int l0 = 1; l0 <= L; l0 += 64) {
+            const int l = l0 + lane;
+            const bool cut = l == L || (l < L && slow * act[l] <= most);
+            const unsigned long long cuts = __ballot(cut), lower = cuts & ((1ull << lane) - 1);
+            const int prev = lower ? l0 + 63 - __builtin_clzll(lower) : before;
+            if (cut) none |= Md * (double)(PF[l] - PF[prev] + PB[l] - PB[prev]) > (double)most * (1.0 + 0x1p-20);
+            before = cuts ? l0 + 63 - __builtin_clzll(cuts) : before;
+        }
+        if (none) s_bad = 1;
+    }
     for (int t = tid; t < 3 * 17 * PRM_TRIES; t += T) ((int *)s_reach)[t] = 0;
     if (tid < D * (D + 1) / 2) {
         // (GPUs before, replicas) by descending GPUs before
@@ -157,6 +175,7 @@ __global__ __launch_bounds__(PRM_PREP_THREADS) void k_prm_prep(prm_args a) {
     }
     if (tid >= 1 && tid <= D) s_each[tid] = make_float2((float)(Md / tid), (float)(2.0 * (tid - 1) / tid / (double)bmin));
     __syncthreads();
+    if (s_bad) return;
     int far = 1;  // the largest power of four below L
     while (far * 4 < L) far *= 4;
     int now = 0;

@@ -73,3 +73,16 @@ def test_plans_from_the_bands(ppo, driver, kind):
             np.testing.assert_array_equal(b, b0)
             np.testing.assert_array_equal(r, r0)
     assert used >= 10 if kind == "near" else used > 0
+
+
+def test_slow_links_end_the_look_for_bands(driver):
+    """A link so slow that a plan of one GPU a stage cannot have enough cuts within any of the times that would do."""
+    for seed, L, D, M in ((960, 60, 4, 16), (961, 40, 5, 32), (962, 75, 12, 24)):
+        w, alpha, M = problem(seed, L, D, 2, M, 300, "near")
+        w.actf = w.actb = np.full(L, 20000, np.int64)
+        w.bw[:] = 2000
+        for slow in (False, True):
+            if slow:
+                w.bw[0, 1] = 1
+            out, = driver([numbers(w, alpha, M, 1)])
+            assert out[4] != slow and (not slow or out[1] == 0), (seed, slow)
