@@ -452,6 +452,8 @@ __global__ __launch_bounds__(256) void k_dp_rows(dp_rows_args a) {
                     }
                     v_link_n = links(v_on);
                     next_link = __builtin_amdgcn_readlane(v_link_n, first_n);
+                } else {
+                    flush_after = pending + 2 > DPR_PENDING;  // (and one that is bad needs a lane, too)
                 }
             }
             fetch_x(xf, next_link);

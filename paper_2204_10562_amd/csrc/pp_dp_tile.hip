@@ -395,6 +395,8 @@ __global__ __launch_bounds__(256, NT >= 16 ? 2 : 1) void k_dp_tile(dp_tile_args 
                     }
                     v_link_n = links(v_on);
                     next_link = __builtin_amdgcn_readlane(v_link_n, first_n);
+                } else {
+                    flush_after = pending + 2 > DPT_PENDING;  // (and one that is bad needs a lane, too)
                 }
             }
             fetch_x(xf, next_link);

@@ -63,3 +63,11 @@ def test_candidates_that_are_finished_already(driver, L, D, S, N):
     cases = [(L, D, S, N, L + S, kind, stages, 85) for kind in (0, 6) for stages in (0, 1)]
     for case, got in zip(cases, driver(cases, "left")):
         assert got[:3] == [0, 0, 0], case
+
+
+@pytest.mark.parametrize("L,D,S,N", [(89, 4, 2, 900), (89, 4, 3, 900), (97, 6, 5, 600), (128, 5, 3, 450), (150, 5, 3, 300)])
+def test_bad_orderings_wherever_they_stand(driver, L, D, S, N):
+    """Also behind as many finished candidates as a wave keeps before it writes their plans out."""
+    cases = [(L, D, S, N, seed, kind, stages, 85) for seed in (2, 3) for kind in (0, 6) for stages in (0, 1)]
+    for case, (rc, status, differ, _, _) in zip(cases, driver(cases, "bad")):
+        assert rc == 0 and status != 0 and differ == 0, case

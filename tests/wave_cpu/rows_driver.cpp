@@ -6,7 +6,9 @@
 // the status, how many results differ from the recursion over all splits, the steps the kernel counted, and
 // a number that depends on all votes its waves took.  With an argument (L <= 128) some candidates are finished
 // before the kernel runs, as a launch of bands leaves them: in runs of 64, nine in ten of a run left, a few or none.
-// Theirs are to stay as they are: a result of theirs that the kernel writes counts as a difference.
+// Theirs are to stay as they are: a result of theirs that the kernel writes counts as a difference.  With the argument
+// "bad" none is finished, and some orderings name a device twice, which are to have no plan: of a wave's candidates 70 after
+// every 32, or one in four.
 #include "../../paper_2204_10562_amd/csrc/pp_dp_rows.hip"
 #include "../../paper_2204_10562_amd/csrc/pp_dp_big.hip"
 
@@ -19,7 +21,8 @@ alignas(16) unsigned char smem[64 * 1024];  // the kernel's LDS
 
 typedef long long ll;
 
-int main(int argc, char **) {
+int main(int argc, char **argv) {
+    const bool bad = argc > 1 && !strcmp(argv[1], "bad");
     int L, D, S, N, seed, kind, stages, fill;
     while (scanf("%d %d %d %d %d %d %d %d", &L, &D, &S, &N, &seed, &kind, &stages, &fill) == 8) {
         std::mt19937_64 g(seed);
@@ -61,6 +64,12 @@ int main(int argc, char **) {
             }
             std::copy(dev.begin(), dev.begin() + S, ord.begin() + (size_t)c * S);
         }
+        std::vector<char> twice(N, 0);
+        for (int c = 0; bad && c < N; ++c)
+            if (seed & 1 ? !upto(3) : c % ((N + 2) / 3) % 102 >= 32) {
+                twice[c] = 1;
+                ord[(size_t)c * S + S - 1] = ord[(size_t)c * S];
+            }
         static pp_ws_header hdr;
         memset(&hdr, 0, sizeof hdr);
         ll vmax = P[L];
@@ -94,7 +103,7 @@ int main(int argc, char **) {
             t.L = L; t.D = D; t.S = S; t.K = a.K; t.N = N;
             t.validate = 1;
             t.chunk = (N + 2) / 3;
-            if (argc > 1) {
+            if (argc > 1 && !bad) {
                 std::fill(left.begin(), left.end(), 0);
                 for (int c = 0; c < N; ++c) {
                     const int often = (int[]){9, 1, 0, 10, 5}[c / 64 % 5];
@@ -112,6 +121,11 @@ int main(int argc, char **) {
             if (!(left[c >> 6] >> (c & 63) & 1)) {
                 for (int i = 0; i < nc; ++i) differ += C[(size_t)c * nc + i] != -7;
                 for (int i = 0; i < tri; ++i) differ += bounds[(size_t)c * tri + i] != -7;
+                continue;
+            }
+            if (twice[c]) {
+                for (int i = 0; i < nc; ++i) differ += C[(size_t)c * nc + i] != INT64_MAX;
+                for (int i = 0; i < tri; ++i) differ += bounds[(size_t)c * tri + i] != 0;
                 continue;
             }
             std::vector<std::vector<ll>> W(S, std::vector<ll>(L + 1));
