@@ -86,7 +86,7 @@ struct pp_ws_layout {
 
 #define PP_TILE_MAX_L 128
 // Up to here the register-tiled kernel always does the DP, beyond it and up to PP_TILE_MAX_L where
-// pp_dp_tiled says so.
+// pp_dp_tiles (pp_dp.hip) says so.
 #define PP_PAIRS_MAX_L 88
 #define PP_DP_SLOTS 4096
 // Sharing of one partition DP between the candidates whose links have the same channel times
@@ -111,8 +111,8 @@ __device__ __forceinline__ long long pp_share_at(const pp_ws_header *hdr, const 
     return r < ns ? reps[r] : reps[N - 1 - (r - ns)];
 }
 
-// Whether the few cells of pp_dp_band.h are tried first: one lane per candidate, so lists of less than a
-// wave are left to the kernels that spread a candidate over a wave (37 candidates of 150 layers in 6 stages).
+// Whether there is room for the few cells of pp_dp_band.h (band_use in pp_dp.hip says whether they are tried): one lane
+// per candidate, so lists of less than a wave are left to the kernels that spread a candidate over a wave.
 static inline bool pp_band_wanted(int S, int64_t N) { return S >= 2 && N >= 64; }
 
 static inline pp_ws_layout pp_layout(int L, int D, int S, int64_t N) {

@@ -319,8 +319,9 @@ static double band_rows_work(int L, int S, int64_t N, bool lex) {
     return (double)N * (S - 1) * L / (lex ? 3 : 1);  // (a list of all orderings shares two rows in three)
 }
 
-// About what whole rows take, in us: for L > 128 a wave's trips from row to row or the cells of all, else the cells, by
-// the waves of a compute unit that the LDS of the tiled kernel has room for.
+// About what whole rows take, in us: for L > 128 a wave's trips from row to row or the cells of all; else the cells, and
+// with the tiled kernel the latency of a row, which the waves of a compute unit that its LDS has room for share (236 ps a
+// row of 32 cells with 12 waves, 481 of 60 with 6, 614 of 77 with 5, 389 of 88 with 12).
 static double band_whole_us(int L, int D, int S, int64_t N, bool lex, const pp_ws_layout &lay) {
     const double work = band_rows_work(L, S, N, lex);
     if (!lay.nt) {
@@ -330,7 +331,7 @@ static double band_whole_us(int L, int D, int S, int64_t N, bool lex, const pp_w
     if (!pp_dp_tiles(L, D, S, N, lay)) return 4e-6 * work;
     size_t lds;
     const int wpb = pp_dp_tile_shape(L, D, S, lay.nt, &lds), waves = (int)(160 * 1024 / lds) * wpb;
-    return (waves < 12 ? 50e-6 / waves : 4e-6) * work;
+    return work / L * (4e-6 * L + 1.6e-3 / (waves > 1 ? waves : 1));
 }
 
 // How far N candidates are from being enough for the recursion over the bands' cells, which takes a wave some 80 + S us
@@ -339,7 +340,9 @@ static double band_whole_us(int L, int D, int S, int64_t N, bool lex, const pp_w
 // Where it ends them: 3780 -> 316 (200 000 candidates, L = 300, S = 16), 1410 -> 626 (8000, 1024, 32), 1112 -> 542 (270 000,
 // 97, 11), 1800 -> 76 (100 000, 77, 30).  Where it does not: 668 -> 734 (270 000, 128, 8), 958 -> 1029 (40 000, 1024, 8), and
 // what the two rules keep it from: 910 -> 1067 (2000, 1024, 64), 880 -> 970 (40 000, 300, 16), 64 -> 135 (2000, 150, 8),
-// 54 -> 110 (3000, 128, 16), 60 -> 241 (300, 150, 8, every stage count).
+// 54 -> 110 (3000, 128, 16), 60 -> 241 (300, 150, 8, every stage count).  A caller's list in sorted order, whose neighbours
+// share rows, takes less than the rule thinks, and pays the most: 257 -> 363 (500 000 sorted orderings of 8 devices, L = 128,
+// one of them with links that bind at every cut).
 static int band_cells(int L, int D, int S, int64_t N, int stages, bool lex, const pp_ws_layout &lay) {
     const double price = (lay.nt ? 40 + 4 * S : 80 + S) * (stages ? S / 2 + 1 : 1);
     const double whole = band_whole_us(L, D, S, N, lex, lay);

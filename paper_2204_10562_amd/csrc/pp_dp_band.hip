@@ -7,7 +7,7 @@
 // its places in the order of the buckets.
 //
 // What bounds it: reading the orderings and writing the plans where the channel-free plan is the answer (2^20
-// candidates of 32 stages: 268 MB in 180 us, six waves a compute unit by LDS); else the latency of a row's gather
+// candidates of 32 stages: 268 MB in 180 us, seven waves a compute unit by LDS); else the latency of a row's gather
 // (one vector load per lane from its link's row) and, with bands of many cells, the pairs: 1.5 vector instructions
 // each for 64 candidates at once.
 #include "pp_dp_band.h"

@@ -559,37 +559,37 @@ __global__ __launch_bounds__(64) void k_makespan_lds(mk_args a) {
     // rows 0..J-1: duration of block j = row+1; rows J..2J-1: its latest finish time
     long long *dur = sm + lane;
     long long *fin = sm + (size_t)J * W + lane;
-  for (long long block = blockIdx.x; block * W < a.N; block += gridDim.x) {
-    // (by block: k_makespan_split has marked the candidates that it leaves to this kernel)
-    if (a.by_block && a.T_out[block * W * a.t_stride + a.t_off] != MK_NOT_TAKEN) continue;
-    const long long c = block * W + lane;
-    const bool live = c < a.N;
-    long long worst;
-    const int fault = gather_durations<0>(a, c, live, worst,
-                                          [&](int j, long long d) { dur[(size_t)(j - 1) * W] = d; });
-  for (int q = 0; q < a.nM; ++q) {
-    const int M = a.Ms[q];
-    const int fq = (live && !fault) ? overflow_fault(worst, M, S) : fault;
-    for (int j = 1; j <= J; ++j) fin[(size_t)(j - 1) * W] = 0;
+    for (long long block = blockIdx.x; block * W < a.N; block += gridDim.x) {
+        // (by block: k_makespan_split has marked the candidates that it leaves to this kernel)
+        if (a.by_block && a.T_out[block * W * a.t_stride + a.t_off] != MK_NOT_TAKEN) continue;
+        const long long c = block * W + lane;
+        const bool live = c < a.N;
+        long long worst;
+        const int fault = gather_durations<0>(a, c, live, worst,
+                                              [&](int j, long long d) { dur[(size_t)(j - 1) * W] = d; });
+        for (int q = 0; q < a.nM; ++q) {
+            const int M = a.Ms[q];
+            const int fq = (live && !fault) ? overflow_fault(worst, M, S) : fault;
+            for (int j = 1; j <= J; ++j) fin[(size_t)(j - 1) * W] = 0;
 
-    const int sweeps = M + 2 * R - 2;
-    for (int t = 1; t <= sweeps; ++t) {
-        const int jlo = max(1, t - M + 1), jhi = min(J, t);
-        const long long finR_prev = fin[(size_t)(R - 1) * W];
-        for (int j = min(jhi, R); j >= jlo; --j) {
-            long long idle = max(fin[(size_t)(j - 1) * W], fin[(size_t)((2 * R - j) - 1) * W]);
-            long long ready = j > 1 ? fin[(size_t)((j - 1) - 1) * W] : 0;
-            fin[(size_t)(j - 1) * W] = max(idle, ready) + dur[(size_t)(j - 1) * W];
-        }
-        for (int j = jhi; j >= max(jlo, R + 1); --j) {
-            long long idle = max(fin[(size_t)(j - 1) * W], fin[(size_t)((2 * R - j) - 1) * W]);
-            long long ready = j == R + 1 ? finR_prev : fin[(size_t)((j - 1) - 1) * W];
-            fin[(size_t)(j - 1) * W] = max(idle, ready) + dur[(size_t)(j - 1) * W];
+            const int sweeps = M + 2 * R - 2;
+            for (int t = 1; t <= sweeps; ++t) {
+                const int jlo = max(1, t - M + 1), jhi = min(J, t);
+                const long long finR_prev = fin[(size_t)(R - 1) * W];
+                for (int j = min(jhi, R); j >= jlo; --j) {
+                    long long idle = max(fin[(size_t)(j - 1) * W], fin[(size_t)((2 * R - j) - 1) * W]);
+                    long long ready = j > 1 ? fin[(size_t)((j - 1) - 1) * W] : 0;
+                    fin[(size_t)(j - 1) * W] = max(idle, ready) + dur[(size_t)(j - 1) * W];
+                }
+                for (int j = jhi; j >= max(jlo, R + 1); --j) {
+                    long long idle = max(fin[(size_t)(j - 1) * W], fin[(size_t)((2 * R - j) - 1) * W]);
+                    long long ready = j == R + 1 ? finR_prev : fin[(size_t)((j - 1) - 1) * W];
+                    fin[(size_t)(j - 1) * W] = max(idle, ready) + dur[(size_t)(j - 1) * W];
+                }
+            }
+            emit(a, q, c, live, fq, fin[(size_t)(J - 1) * W], block, 0, a.t_off);
         }
     }
-    emit(a, q, c, live, fq, fin[(size_t)(J - 1) * W], block, 0, a.t_off);
-  }
-  }
 }
 
 static long long regs_waves(long long N) { return (N + 63) / 64; }
