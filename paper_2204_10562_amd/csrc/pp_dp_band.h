@@ -19,7 +19,7 @@
 // of its row's band changes nothing: a candidate of such links alone has the plan of the channel-free program,
 // which is one for all of them (band_free_try).
 //
-// 2^20 candidates of L = 1024, S = 32, the partition alone: 97.7 ms with whole rows, 0.18 ms (0.76 ms with the
+// 2^20 candidates of L = 1024, S = 32, the partition alone: 97.7 ms with whole rows, 0.21 ms (0.76 ms with the
 // recursion over the bands' cells for each); 20 011 of L = 400, S = 48 1.54 ms -> 23 us; 15 751 of L = 300, S = 16
 // 212 -> 13 us; all 8! orderings of L = 128 48 -> 15 us; 200 003 of L = 97, S = 11 894 -> 35 us.
 #pragma once

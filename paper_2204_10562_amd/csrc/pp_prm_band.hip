@@ -19,7 +19,8 @@
 // are needed: lane u holds the minimum over the links of rank u, and a suffix minimum over the lanes gives all r'.
 // With few candidates the waves of a workgroup share them, each with its part of the r of every i.
 //
-// What bounds it: instructions, three or four waves per SIMD.  All 40320 orderings of 8 GPUs, 128 layers: 3.80 ms with
+// What bounds it: instructions and the waits between them, with 2.5 waves per SIMD in flight on an average (vector units
+// busy 61 % of the time with 8 GPUs, 50 % with 12).  All 40320 orderings of 8 GPUs, 128 layers: 3.80 ms with
 // k_prm, 0.28 here; 3001 orderings of 12 GPUs, 75 layers: 1.95 -> 0.23 ms.  It was 0.51 ms for the latter's wider bands
 // (17 to 19 cells) with 32 lanes per candidate and every cell of a band in one part.
 #include "pp_prm.h"
