@@ -63,6 +63,8 @@ int main(int argc, char **argv) {
                 std::shuffle(dev.begin(), dev.end(), g);
             }
             std::copy(dev.begin(), dev.begin() + S, ord.begin() + (size_t)c * S);
+            // (one in two as the one before its neighbour: rows to share with what a wave has done before)
+            if (argc > 1 && c >= 2 && upto(1)) std::copy_n(ord.begin() + (size_t)(c - 2) * S, S, ord.begin() + (size_t)c * S);
         }
         std::vector<char> twice(N, 0);
         for (int c = 0; bad && c < N; ++c)
