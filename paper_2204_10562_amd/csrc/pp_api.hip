@@ -98,13 +98,13 @@ extern "C" int pp_best_plan_stages(int L, int D, int S, int64_t N, int nM, const
     if (rc) return rc;
     // (where candidates share their DP the plans of the representatives are scheduled and
     // compared, and the others get T and C only if the caller wants the arrays)
-    const bool listed = lay.sh_table != 0 && pp_makespan_takes_list(S);
+    const bool listed = lay.sh_table != 0;
     rc = pp_launch_dp(L, D, S, N, PF, PB, XF, XB, orderings ? NULL : ord, orderings, 1, 0, listed, C,
                       bounds, workspace, lay, status, st);
     if (rc) return rc;
     rc = pp_launch_makespan_stages(L, D, S, N, nM, M_list, PF, PB, XF, XB, ord, bounds, C, T,
-                                   status, base + sl.part, out, (const pp_ws_header *)(base + lay.hdr),
-                                   orderings == NULL, listed ? (const int32_t *)(base + lay.sh_reps) : NULL,
+                                   status, base + lay.part, out, (const pp_ws_header *)(base + lay.hdr),
+                                   listed ? (const int32_t *)(base + lay.sh_reps) : NULL,
                                    st);
     if (rc || !listed || (!T_all && !C_all)) return rc;
     return pp_launch_share_scatter(N, C_all ? S : 0, 0, T_all ? nM : 0, S, C_all, NULL, T_all, workspace,
@@ -118,7 +118,7 @@ extern "C" int pp_schedule_makespan(int L, int D, int S, int64_t N, int M, const
     int rc = pp_check_sizes(L, D, S, N, orderings);
     if (rc) return rc;
     if (M < 1 || !PF || !PB || !XF || !XB || !bounds || !T_out) return PP_ERR_INVALID_ARG;
-    return pp_launch_makespan(L, D, S, N, 1, &M, PF, PB, XF, XB, orderings, bounds, T_out, NULL,
+    return pp_launch_makespan(L, D, S, N, 1, &M, PF, PB, XF, XB, orderings, bounds, T_out,
                               status, NULL, NULL, NULL, NULL, NULL, NULL, (hipStream_t)stream);
 }
 
@@ -133,7 +133,7 @@ extern "C" int pp_schedule_makespan_multi(int L, int D, int S, int64_t N, int nM
         return PP_ERR_INVALID_ARG;
     for (int q = 0; q < nM; ++q)
         if (M_list[q] < 1) return PP_ERR_INVALID_ARG;
-    return pp_launch_makespan(L, D, S, N, nM, M_list, PF, PB, XF, XB, orderings, bounds, T_out, NULL,
+    return pp_launch_makespan(L, D, S, N, nM, M_list, PF, PB, XF, XB, orderings, bounds, T_out,
                               status, NULL, NULL, NULL, NULL, NULL, NULL, (hipStream_t)stream);
 }
 
@@ -146,7 +146,7 @@ extern "C" int pp_schedule_makespan_variant(int variant, int L, int D, int S, in
     if (rc) return rc;
     if (M < 1 || !PF || !PB || !XF || !XB || !bounds || !T_out) return PP_ERR_INVALID_ARG;
     if (variant == PP_SCHED_PE)
-        return pp_launch_makespan(L, D, S, N, 1, &M, PF, PB, XF, XB, orderings, bounds, T_out, NULL,
+        return pp_launch_makespan(L, D, S, N, 1, &M, PF, PB, XF, XB, orderings, bounds, T_out,
                                   status, NULL, NULL, NULL, NULL, NULL, NULL, (hipStream_t)stream);
     if (variant != PP_SCHED_DUPLEX && variant != PP_SCHED_GPIPE && variant != PP_SCHED_ADDITIVE &&
         variant != PP_SCHED_FIFO)
@@ -190,13 +190,13 @@ extern "C" int pp_best_plan_multi(int L, int D, int S, int64_t N, int nM, const 
     // is shared too: only the representatives are evaluated, the arg-min runs over them (a
     // representative is the lowest candidate of its group, so ties still go to the lowest
     // index), and T and C reach the other candidates only if the caller wants the arrays.
-    const bool listed = lay.sh_table != 0 && pp_makespan_takes_list(S);
+    const bool listed = lay.sh_table != 0;
     const bool can_fuse = !listed && pp_makespan_can_fuse(L, D, S);
     rc = pp_launch_dp(L, D, S, N, PF, PB, XF, XB, orderings ? NULL : ord, orderings, 0,
                       can_fuse ? fuse.mmax : 0, listed, C, bounds, workspace, lay, status, st);
     if (rc) return rc;
     rc = pp_launch_makespan(L, D, S, N, nM, M_list, PF, PB, XF, XB, ord, bounds, T_all,
-                            (int64_t *)(base + lay.T), status, C, base + lay.part, out,
+                            status, C, base + lay.part, out,
                             (const pp_ws_header *)(base + lay.hdr), can_fuse ? &fuse : NULL,
                             listed ? (const int32_t *)(base + lay.sh_reps) : NULL, st);
     if (rc || !listed || (!T_all && !C_all)) return rc;

@@ -89,6 +89,8 @@ struct pp_ws_layout {
 // pp_dp_tiles (pp_dp.hip) says so.
 #define PP_PAIRS_MAX_L 88
 #define PP_DP_SLOTS 4096
+// Most partial minima of the arg-min per microbatch count (workgroups of a schedule launch).
+#define PP_PARTS 2048
 // Sharing of one partition DP between the candidates whose links have the same channel times
 // (pp_share.hip): table entries, and the sizes it is built for.
 #define PP_SHARE_TABLE (1 << 20)
@@ -135,7 +137,7 @@ static inline pp_ws_layout pp_layout(int L, int D, int S, int64_t N) {
     w.bounds = off; off += pp_align256((size_t)N * S * 4);
     w.C = off;      off += pp_align256((size_t)N * 8);
     w.T = off;      off += pp_align256((size_t)N * 8);
-    w.part = off;   off += pp_align256((size_t)((N + 63) / 64) * 16 * PP_MAX_M_LIST);
+    w.part = off;   off += pp_align256((size_t)((N + 63) / 64 < PP_PARTS ? (N + 63) / 64 : PP_PARTS) * 16 * PP_MAX_M_LIST);
     w.sh_hash = w.sh_rep = w.sh_table = w.sh_keys = w.sh_reps = w.sh_cnt = w.sh_start = w.sh_rows = 0;
     w.sh_row_slots = 0;
     if (pp_share_possible(L, D, N)) {
@@ -161,7 +163,7 @@ static inline pp_ws_layout pp_layout(int L, int D, int S, int64_t N) {
 
 // Extra workspace of the stage-count search, carved after the common part.
 struct pp_stage_layout {
-    size_t bounds, C, T, part, total;
+    size_t bounds, C, T, total;
 };
 
 static inline pp_stage_layout pp_layout_stages(const pp_ws_layout &base, int S, int64_t N, int nM) {
@@ -170,7 +172,6 @@ static inline pp_stage_layout pp_layout_stages(const pp_ws_layout &base, int S, 
     w.bounds = off; off += pp_align256((size_t)N * (S * (S + 1) / 2) * 4);
     w.C = off;      off += pp_align256((size_t)N * S * 8);
     w.T = off;      off += pp_align256((size_t)nM * N * S * 8);
-    w.part = off;   off += pp_align256((size_t)1024 * 16 * PP_MAX_M_LIST);
     w.total = off;
     return w;
 }
@@ -194,8 +195,7 @@ int pp_launch_pack(int L, int D, int S, int64_t N, const int64_t *PF, const int6
 // the closed form applies and the times for defer_mmax microbatches fit 32 bits).
 // keep_list != 0 (only where lay.sh_table != 0): where candidates share their DP, leave the
 // results with the representatives - the caller schedules the list (rlist of
-// pp_launch_makespan) and calls pp_launch_share_scatter itself - and set every partial of the
-// arg-min in the workspace to "none".
+// pp_launch_makespan) and calls pp_launch_share_scatter itself.
 int pp_launch_dp(int L, int D, int S, int64_t N, const int64_t *PF, const int64_t *PB,
                  const int64_t *XF, const int64_t *XB, const int32_t *lex_ord,
                  const int32_t *user_ord, int stages, int defer_mmax, int keep_list,
@@ -208,12 +208,11 @@ int pp_launch_dp(int L, int D, int S, int64_t N, const int64_t *PF, const int64_
 // only, and pp_launch_share_scatter copies every representative's results (nC entries of C_out
 // and nB of bounds_out per candidate) to the candidates it stands for.  Both do nothing when
 // the class sequences do not fit the table.  Only where lay.sh_table != 0.
-// fill_part != 0: also set the arg-min partials of the workspace (lay.part) to "none".
 // run_waves (1 .. PP_DP_SLOTS): the waves of the DP kernel that will walk the list of
 // representatives; the list is cut into at most that many runs of about equal work.
 // In between, the pass over the bands finishes the candidates it can (g: where the results go).
 struct dp_args;
-int pp_launch_share_prepare(const dp_args &g, int fill_part, int run_waves, void *ws, const pp_ws_layout &lay,
+int pp_launch_share_prepare(const dp_args &g, int run_waves, void *ws, const pp_ws_layout &lay,
                             hipStream_t st);
 // With nT > 0 also T_out [nT][N][tw] (the makespan kernel ran over the representatives as well).
 int pp_launch_share_scatter(int64_t N, int nC, int nB, int nT, int tw, int64_t *C_out,
@@ -222,10 +221,9 @@ int pp_launch_share_scatter(int64_t N, int nC, int nB, int nT, int tw, int64_t *
 
 // Makespan of every candidate's plan for each of the nM microbatch counts in Ms (host array).
 // With part/C/out non-NULL the launch also finds, per microbatch count, the candidate
-// with the smallest T (lowest index on ties) and fills out[q] (one pair of int64 per wave of
-// 64 candidates and microbatch count in part).  T_out ([nM][N]) may then be NULL; T_scratch
-// ([N]) is needed for S > 16 in that case.  hdr: the workspace header the pack kernel has filled
-// for these tables (its largest time decides between 32-bit and 64-bit kernels), or NULL.
+// with the smallest T (lowest index on ties) and fills out[q] (one pair of int64 per workgroup
+// and microbatch count in part).  T_out ([nM][N]) may then be NULL.  hdr: the workspace header the pack kernel has
+// filled for these tables, or NULL.
 // fuse != NULL (pp_best_plan only, needs hdr): the partition DP kernel was told (defer_mmax of
 // pp_launch_dp) to leave the plans to the makespan kernel whenever no link's channel time
 // depends on the cut position and all finish times for fuse->mmax microbatches fit 32 bits;
@@ -240,25 +238,23 @@ struct pp_fuse_info {
     int32_t *bounds;
 };
 bool pp_makespan_can_fuse(int L, int D, int S);
-// rlist != NULL (needs hdr and part, and pp_makespan_takes_list(S)): see mk_args.
-bool pp_makespan_takes_list(int S);
+// rlist != NULL (needs hdr and part): see mk_args.
 int pp_launch_makespan(int L, int D, int S, int64_t N, int nM, const int *Ms, const int64_t *PF,
                        const int64_t *PB, const int64_t *XF, const int64_t *XB,
                        const int32_t *orderings, const int32_t *bounds, int64_t *T_out,
-                       int64_t *T_scratch, int32_t *status, const int64_t *C, void *part,
+                       int32_t *status, const int64_t *C, void *part,
                        pp_result *out, const pp_ws_header *hdr, const pp_fuse_info *fuse,
                        const int32_t *rlist, hipStream_t st);
 // Stage-count search: makespan of the plan with xi stages of every candidate for xi = 1..S
 // (bounds [N][S(S+1)/2] and C [N][S] as pp_launch_dp leaves them with stages == 1), written to
 // T_st [nM][N][S], then per microbatch count the smallest T over all (candidate, xi), lowest
-// candidate and then lowest xi on ties, into out[q].  part must hold 1024 * nM pairs of int64.
-// lex: `orderings` is the library's own list of all D! orderings in lexicographic order.
-// rlist != NULL (S <= 16, needs hdr): only the representatives are scheduled (see mk_args).
+// candidate and then lowest xi on ties, into out[q].
+// rlist != NULL (needs hdr): only the representatives are scheduled (see mk_args).
 int pp_launch_makespan_stages(int L, int D, int S, int64_t N, int nM, const int *Ms,
                               const int64_t *PF, const int64_t *PB, const int64_t *XF,
                               const int64_t *XB, const int32_t *orderings, const int32_t *bounds,
                               const int64_t *C, int64_t *T_st, int32_t *status, void *part,
-                              pp_result *out, const pp_ws_header *hdr, int lex,
+                              pp_result *out, const pp_ws_header *hdr,
                               const int32_t *rlist, hipStream_t st);
 // Makespan (Eq. 2) of the plans with replicated stages of every (candidate, stage count) and
 // the keep-the-minimum over them; arrays laid out as pp_plan_replicated documents; part holds
@@ -268,14 +264,11 @@ int pp_launch_rep_makespan(int L, int D, int64_t N, int M, const int64_t *PF, co
                            const int64_t *bw, const int32_t *orderings, const int32_t *bounds,
                            const int32_t *reps, const int64_t *W, int64_t *T_out, int32_t *status,
                            void *part, pp_rep_result *out, hipStream_t st);
-// Makespan of given plans under a comparison schedule (PP_SCHED_DUPLEX, PP_SCHED_GPIPE).
+// Makespan of given plans under a comparison schedule.
 int pp_launch_makespan_variant(int variant, int L, int D, int S, int64_t N, int M, const int64_t *PF,
                                const int64_t *PB, const int64_t *XF, const int64_t *XB,
                                const int32_t *orderings, const int32_t *bounds, int64_t *T_out,
                                int32_t *status, hipStream_t st);
-int pp_launch_argmin(int D, int S, int64_t N, const int64_t *T, const int64_t *C,
-                     const int32_t *bounds, const int32_t *orderings, void *part,
-                     pp_result *out, hipStream_t st);
 
 // Largest time in the tables (all lanes of a full wave must call; result is uniform).
 __device__ __forceinline__ unsigned long long pp_vmax(const pp_ws_header *hdr) {

@@ -547,7 +547,7 @@ int pp_launch_dp(int L, int D, int S, int64_t N, const int64_t *PF, const int64_
     // candidates whose links have the same channel times share one DP: the kernel walks the
     // representatives the preparation finds, and their results are copied to the others
     const int run_waves = pp_dp_big_run_waves(pp_dp_big_waves(L, D, S, (int)waves, cus), S, lay.sh_row_slots);
-    int rc = pp_launch_share_prepare(a, keep_list, run_waves, ws, lay, st);
+    int rc = pp_launch_share_prepare(a, run_waves, ws, lay, st);
     if (rc) return rc;
     pp_share_list list;
     list.reps = (const int *)(base + lay.sh_reps);

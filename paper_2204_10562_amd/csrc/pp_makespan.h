@@ -8,21 +8,6 @@ struct tc_pair { long long T, c; };
 struct mk_args {
     int L, D, S, nM;
     int Ms[PP_MAX_M_LIST];  // microbatch counts; the plans are evaluated once per entry
-    // k_makespan_regs: wave slot i (blockIdx.y * waves + wave) serves count Ms[order[i]]
-    unsigned char order[PP_MAX_M_LIST];
-    // k_makespan_regs8: a workgroup holds `groups` groups of waves, each group one wave per
-    // microbatch count for its own 64 candidates; wave w of group g takes slot
-    // (slot_perm >> 2 (4 g + w)) & 3 of its four
-    int groups;
-    unsigned slot_perm;
-    // k_makespan_regs8: nonzero = blockIdx.z + 1 is the number of stages xi, the plan with xi
-    // stages is read from the triangular bounds array and T goes to column xi-1 (S, bnd_off and
-    // t_off are then ignored)
-    int all_xi;
-    // With all_xi and the library's own list of all D! orderings in lexicographic order:
-    // share[xi] = (D - xi)! consecutive candidates share their first xi devices and with them
-    // the plan of xi stages, so it is scheduled once per such block (share[xi] = 1: no sharing)
-    long long share[9];
     long long N;
     const long long *PF, *PB, *XF, *XB;
     const int *orderings;  // NULL = all D! orderings, candidate index = lexicographic rank
@@ -35,20 +20,17 @@ struct mk_args {
     // stages out of rows that hold search = S_max devices and all S_max plans.
     int ord_stride, bnd_off, t_off;
     long long bnd_stride, t_stride;
-    // search > 0 (arg-min only): the N entries are (candidate, stage count) pairs, entry
-    // i = c*search + xi-1; the record of the winner is decoded accordingly
+    // search > 0: the plans of every stage count xi = 1 .. search of N candidates; the arg-min runs over the
+    // pairs, entry c*search + xi-1, and the record of the winner is decoded accordingly
     int search;
-    int variant;  // k_makespan_variant only: PP_SCHED_*
-    // k_makespan_split / k_makespan_lds launched together without a header (more than 16 stages, no
-    // workspace): nonzero = every block of 64 candidates decides for itself which of the two
-    // kernels schedules it; k_makespan_split leaves MK_NOT_TAKEN in T_out of those it does not take
+    int variant;  // PP_SCHED_*
+    // nonzero: what 32-bit sums do not hold is left to another kernel, wave by wave (MK_NOT_TAKEN in T_out)
     int by_block;
-    int lanes_per;  // lanes per candidate of k_makespan_split (1, 2, 4 or 8) and k_makespan_fifo (1 .. 64)
+    int lanes_per;  // lanes per candidate of k_makespan_fifo (1 .. 64)
     long long first;  // k_makespan_fifo: the launch's first candidate
-    // workspace header with the largest time of the tables (NULL if there is none): lets every
-    // wave of a launch take the same decision between 32-bit and 64-bit finish times
+    // workspace header (NULL if there is none)
     const pp_ws_header *hdr;
-    // k_makespan_regs8 inside pp_best_plan: nonzero = when no link's channel time depends on the
+    // k_makespan_flat inside pp_best_plan: nonzero = when no link's channel time depends on the
     // cut position and every finish time of the launch fits 32 bits (both read from hdr), the
     // partition DP kernel has left the plans to this kernel, which builds them in closed form
     // from the channel-free tables bfl (pp_dp_flat.h) and writes C_w [N] and bounds_w [N][S].
@@ -63,15 +45,15 @@ struct mk_args {
     // bandwidth matrix, and W per (candidate, stage count) (PP_INF64 = no such plan)
     const int *reps;
     const long long *PA, *actf, *actb, *bw, *W;
-    // k_makespan_regs<S> inside pp_best_plan: non-NULL = if the workspace header says that
-    // candidates share their partition DP (pp_share.hip), this is the list of the candidates
-    // that stand for all others; only they are scheduled (entry i by lane i of the launch), and
-    // the slots of the partials no wave writes hold "none" already
+    // inside pp_best_plan: non-NULL = if the workspace header says that candidates share their
+    // partition DP (pp_share.hip), this is the list of the candidates that stand for all others;
+    // only they are scheduled
     const int *rlist;
     pp_rep_result *rout;   // [nM] winner records with replica counts (instead of out)
     // arg-min (all NULL when not wanted)
-    tc_pair *part;         // [nM][waves]: every wave's minimum, reduced by k_pick
+    tc_pair *part;         // [nM][workgroups]: every workgroup's minimum, reduced by k_pick
     long long n_part;      // k_pick: partials per microbatch count
+    int pick_here;         // the launch is one workgroup, which writes the records itself
     const long long *C;
     pp_result *out;        // [nM]
 };
@@ -95,37 +77,65 @@ __device__ __forceinline__ int overflow_fault(long long worst, int M, int S) {
     return worst > (PP_CAP62 - 1) / ((long long)M + 4 * S - 4) ? PP_FAULT_OVERFLOW : 0;
 }
 
-// Writes T of microbatch count q, raises faults, and returns the wave's minimum.
-__device__ __forceinline__ tc_pair emit_T(const mk_args &a, int q, long long c, bool live, int fault, long long T, int t_off) {
-    if (live) {
-        if (fault) { T = PP_INF64; pp_raise(a.status, fault); }
-        if (a.T_out) a.T_out[((long long)q * a.N + c) * a.t_stride + t_off] = T;
-    }
-    tc_pair v = {live ? T : PP_INF64, live ? c : INT64_MAX};
-    return a.part ? wave_tc_min(v) : v;
-}
-
-// The same, and (if wanted) leaves the wave's minimum in its slot of the partials; k_pick, launched next on the
-// same stream, reduces the partials.
-// (Plain stores and a kernel boundary: earlier versions let the last wave to arrive do the
-// final reduction, but the returned atomics and arrival counters that needs cost more than
-// the schedule itself once a launch has thousands of waves.)
-__device__ __forceinline__ void emit(const mk_args &a, int q, long long c, bool live, int fault,
-                                     long long T, long long wave_id, long long n_waves, int t_off) {
-    const tc_pair v = emit_T(a, q, c, live, fault, T, t_off);
-    if (!a.part) return;
-    if ((threadIdx.x & 63) == 0 && wave_id < n_waves) a.part[(long long)q * n_waves + wave_id] = v;
-}
-
-// T of a candidate that k_makespan_split has left to k_makespan_lds (no schedule ends before 0).
+// T of a candidate that a kernel has left to the next one (no schedule ends before 0).
 #define MK_NOT_TAKEN (-1ll)
-// Largest finish time k_makespan_split works with.
+// Largest finish time the 32-bit kernels work with.
 #define MK_SPLIT_CAP 0x3fffffff
-// True if every finish time of a pipeline of S stages whose largest per-resource time is `worst`
-// stays below MK_SPLIT_CAP for M microbatches (Lemma 1, with the sweeps of the padded pipeline), and
-// the number of sweeps fits an int also where all times are zero.
-__device__ __forceinline__ bool mk_split_fits(long long worst, long long M, int S) {
-    return M + 4 * S + 64 <= MK_SPLIT_CAP && worst <= MK_SPLIT_CAP / (M + 4 * S + 64);
+// Every finish time of a pipeline of S stages whose largest per-resource time is at most this stays below
+// MK_SPLIT_CAP for M microbatches (Lemma 1, with room); -1: no such time (M next to 2^30).
+__device__ __forceinline__ int mk_split_limit(long long M, int S) {
+    const long long n = M + 4 * S + 64;
+    return n > MK_SPLIT_CAP ? -1 : (int)((unsigned)MK_SPLIT_CAP / (unsigned)n);
+}
+
+// The winner record of microbatch count q from the minimum w over all entries.
+__device__ __forceinline__ void write_winner(const mk_args &a, int q, tc_pair w, int lane) {
+    const int S = a.S;
+    const bool none = w.T == PP_INF64;
+    // the winner: candidate c with xi stages, its C at C[at_c], its bounds from bounds[at_b]
+    long long c = w.c, at_c = w.c, at_b = w.c * a.bnd_stride + a.bnd_off;
+    int xi = S;
+    if (a.search && !none) {
+        c = w.c / a.search;
+        xi = (int)(w.c - c * a.search) + 1;
+        at_b = c * ((long long)a.search * (a.search + 1) / 2) + xi * (xi - 1) / 2;
+    }
+    if (a.rout) {
+        // plan with replicated stages: xi bounds and replica counts, all D devices by rank
+        pp_rep_result *out = a.rout + q;
+        if (lane == 0) {
+            out->best_index = none ? -1 : c;
+            out->T = w.T;
+            out->W = none ? PP_INF64 : a.C[at_c];
+            out->S = none ? 0 : xi;
+        }
+        const bool in = lane < xi && !none;
+        out->bounds[lane] = in ? a.bounds[at_b + lane] : 0;
+        out->reps[lane] = in ? a.reps[at_b + lane] : 0;
+        out->order[lane] = (lane < a.D && !none) ? a.orderings[c * a.ord_stride + lane] : 0;
+        return;
+    }
+    pp_result *out = a.out + q;
+    if (lane == 0) {
+        out->best_index = none ? -1 : c;
+        out->T = w.T;
+        out->C = none ? PP_INF64 : a.C[at_c];
+        out->S = xi;
+    }
+    // lane n writes bound n and device n (lanes xi.. write zeros)
+    int b = 0, o = 0;
+    if (lane < xi && !none) {
+        b = a.bounds[at_b + lane];
+        if (a.orderings) {
+            o = a.orderings[c * a.ord_stride + lane];
+        } else {
+            unsigned long long rem = (unsigned long long)c;
+            unsigned used = 0;
+            for (int n = 0; n <= lane; ++n) o = pp_unrank_next(a.D, n, rem, used);
+        }
+    }
+    out->bounds[lane] = b;
+    out->order[lane] = o;
 }
 
 // Fault bits of a candidate whose devices and bounds lie in LDS (o: filled in for the list of all D!
@@ -159,12 +169,14 @@ __device__ __forceinline__ int mk_check_rows(const mk_args &a, long long c, int 
     return prev != L ? PP_FAULT_BOUNDS : fault;
 }
 
-// Resources over lanes (pp_makespan_split.hip): times below MK_SPLIT_CAP, a.variant any but
-// PP_SCHED_FIFO.  With a.by_block it marks the candidates it leaves alone.
-int pp_launch_makespan_split(const mk_args &a, hipStream_t st);
+// The longest path's closed form (pp_makespan_path.h) over the plans in memory, any a.variant but PP_SCHED_FIFO
+// (pp_makespan_split.hip).  With a.by_block it marks the plans it leaves alone; with a.part it leaves partials
+// for k_pick, *n_part of them per count, or picks itself (*n_part = 0).
+int pp_launch_makespan_split(const mk_args &a, hipStream_t st, long long *n_part = NULL);
 // PP_SCHED_FIFO for at most 32 stages (pp_makespan_fifo.hip); marks the candidates it leaves alone.
 int pp_launch_makespan_fifo(const mk_args &a, hipStream_t st);
 
 // The schedules of all plans with replicated stages: 1..a.D stages, a.N candidates
 // (pp_makespan_rep.hip).
 int mk_launch_replicated(const mk_args &a, hipStream_t st);
+

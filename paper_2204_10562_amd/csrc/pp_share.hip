@@ -55,9 +55,6 @@ struct share_args {
     int *pend;                  // [N] representatives the bands have left
     int *start;                 // [run_waves + 1] first entry of every run of that list
     int run_waves;
-    // arg-min partials to preset (pairs of int64), or NULL
-    long long *part;
-    long long n_part;
     // k_share_keys: candidates first_c .. last_c - 1; look: 1 = there are entries of an earlier launch to look at
     long long first_c, last_c;
     int look;
@@ -291,12 +288,6 @@ __global__ __launch_bounds__(256) void k_share_count(share_args a) {
 __global__ __launch_bounds__(256) void k_share_reps(share_args a) {
     __shared__ int sh[4], shw[4];
     const int tid = threadIdx.x, lane = tid & 63, wib = tid >> 6;
-    // (T, candidate) = "none" in every slot of the arg-min's partials: the makespan kernel that
-    // walks the list writes only the slots of the waves that have a representative
-    for (long long i = (long long)blockIdx.x * 256 + tid; i < a.n_part; i += (long long)gridDim.x * 256) {
-        a.part[2 * i] = PP_INF64;
-        a.part[2 * i + 1] = INT64_MAX;
-    }
     const unsigned tsize = a.hdr->share_tsize;
     if (blockIdx.x * 256u >= tsize && blockIdx.x) return;
     if (a.hdr->share_sorted && !a.hdr->share_npend) return;
@@ -479,16 +470,12 @@ static long long share_grid(int64_t N) {
     return g < 4096 ? g : 4096;
 }
 
-int pp_launch_share_prepare(const dp_args &g, int fill_part, int run_waves, void *ws, const pp_ws_layout &lay,
+int pp_launch_share_prepare(const dp_args &g, int run_waves, void *ws, const pp_ws_layout &lay,
                             hipStream_t st) {
     if (!lay.sh_table || run_waves < 1 || run_waves > PP_DP_SLOTS) return PP_ERR_INVALID_ARG;
     share_args a = share_base(ws, lay);
     const int D = g.D;
     const long long N = g.N;
-    if (fill_part) {
-        a.part = (long long *)((char *)ws + lay.part);
-        a.n_part = (long long)((N + 63) / 64) * PP_MAX_M_LIST;
-    }
     a.L = g.L; a.D = D; a.S = g.S; a.N = N; a.validate = g.validate;
     a.XF = g.XF; a.XB = g.XB;
     a.x32 = (int *)((char *)ws + lay.x32);

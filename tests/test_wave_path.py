@@ -1,0 +1,44 @@
+"""The closed form of the schedules, run lane by lane on the CPU from the kernel's own source: several microbatch
+counts, plans of every stage count, sums that leave 32 bits, and the minimum over the plans."""
+import os
+import subprocess
+
+import pytest
+
+from test_wave_makespan import ADDITIVE, DUPLEX, GPIPE, PE, build, pytestmark  # noqa: F401
+
+
+@pytest.fixture(scope="module")
+def exe(tmp_path_factory):
+    return build(tmp_path_factory.mktemp("path"), "path_driver")
+
+
+def ask(exe, lines):
+    env = dict(os.environ)
+    env.pop("LD_PRELOAD", None)  # the sanitizer's runtime must come first in the library list
+    res = subprocess.run([exe], input="".join(l + "\n" for l in lines), stdout=subprocess.PIPE,
+                         stderr=subprocess.PIPE, text=True, timeout=300, env=env)
+    assert res.returncode == 0, res.stderr[-2000:]
+    assert "runtime error" not in res.stderr, res.stderr[-2000:]
+    out = [[int(x) for x in l.split()] for l in res.stdout.splitlines()]
+    assert len(out) == len(lines)
+    return out
+
+
+# pipelines that fill and that do not, on both sides of M = 2R and M = K + 1; times with many zeros and
+# equal values, of 20 bits (32-bit sums), and up to 2^50 (64-bit sums)
+@pytest.mark.parametrize("variant,counts", [(PE, "1 2 3 4 5 6 7 8"), (PE, "9 14 29 30 31 64 200"), (PE, "1 40"), (DUPLEX, "1"),
+                                            (DUPLEX, "13"), (DUPLEX, "200"), (GPIPE, "7"), (ADDITIVE, "1"), (ADDITIVE, "11"), (ADDITIVE, "99")])
+def test_against_the_schedule(exe, variant, counts):
+    nM = len(counts.split())
+    lines = ["%d %d %d %d 0 %d 0 %d %s" % (variant, S, N, S + hi % 97, hi, nM, counts)
+             for S, N in ((1, 3), (2, 64), (3, 65), (4, 130), (5, 70), (8, 260), (15, 20), (33, 9), (64, 2)) for hi in (1, 4, 10**6, 2**50)]
+    for line, got in zip(lines, ask(exe, lines)):
+        assert got == [0, 0, 0, 0], line
+
+
+@pytest.mark.parametrize("S,N", [(1, 70), (2, 5), (7, 66), (8, 64), (9, 20), (17, 3)])
+def test_every_stage_count(exe, S, N):
+    lines = ["%d %d %d %d 0 %d 1 3 2 17 70" % (PE, S, N, S, hi) for hi in (1, 10**5, 2**45)]
+    for line, got in zip(lines, ask(exe, lines)):
+        assert got == [0, 0, 0, 0], line
