@@ -26,7 +26,8 @@ struct mk_args {
     int variant;  // PP_SCHED_*
     // nonzero: what 32-bit sums do not hold is left to another kernel, wave by wave (MK_NOT_TAKEN in T_out)
     int by_block;
-    int lanes_per;  // lanes per candidate of k_makespan_fifo (1 .. 64)
+    int lanes_per;  // lanes per candidate of k_makespan_fifo (1 .. 32)
+    int groups;     // candidates per workgroup of k_makespan_fifo
     long long first;  // k_makespan_fifo: the launch's first candidate
     // workspace header (NULL if there is none)
     const pp_ws_header *hdr;
