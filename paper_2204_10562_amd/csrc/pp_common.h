@@ -258,7 +258,7 @@ int pp_launch_makespan_stages(int L, int D, int S, int64_t N, int nM, const int 
                               const int32_t *rlist, hipStream_t st);
 // Makespan (Eq. 2) of the plans with replicated stages of every (candidate, stage count) and
 // the keep-the-minimum over them; arrays laid out as pp_plan_replicated documents; part holds
-// 1024 pairs of int64.
+// PP_PARTS pairs of int64.
 int pp_launch_rep_makespan(int L, int D, int64_t N, int M, const int64_t *PF, const int64_t *PB,
                            const int64_t *PA, const int64_t *actf, const int64_t *actb,
                            const int64_t *bw, const int32_t *orderings, const int32_t *bounds,

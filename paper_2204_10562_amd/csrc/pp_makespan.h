@@ -178,6 +178,6 @@ int pp_launch_makespan_split(const mk_args &a, hipStream_t st, long long *n_part
 int pp_launch_makespan_fifo(const mk_args &a, hipStream_t st);
 
 // The schedules of all plans with replicated stages: 1..a.D stages, a.N candidates
-// (pp_makespan_rep.hip).
-int mk_launch_replicated(const mk_args &a, hipStream_t st);
+// (pp_makespan_rep.hip), and partials for k_pick as pp_launch_makespan_split leaves them.
+int mk_launch_replicated(const mk_args &a, hipStream_t st, long long *n_part);
 

@@ -296,17 +296,6 @@ int pp_launch_makespan(int L, int D, int S, int64_t N, int nM, const int *Ms, co
     return launch_makespan(a, st);
 }
 
-// ---------------------------------------------------------------- stand-alone arg-min
-
-// Each wave reduces a strided share of T to a partial for k_pick.
-__global__ __launch_bounds__(64) void k_argmin(mk_args a) {
-    tc_pair v = {PP_INF64, INT64_MAX};
-    for (long long c = (long long)blockIdx.x * 64 + threadIdx.x; c < a.N; c += (long long)gridDim.x * 64)
-        v = tc_min(v, {a.T_out[c], c});
-    v = wave_tc_min(v);
-    if (threadIdx.x == 0) a.part[blockIdx.x] = v;
-}
-
 // ---------------------------------------------------------------- stage-count search
 
 int pp_launch_makespan_stages(int L, int D, int S, int64_t N, int nM, const int *Ms,
@@ -348,22 +337,12 @@ int pp_launch_rep_makespan(int L, int D, int64_t N, int M, const int64_t *PF, co
     a.bw = (const long long *)bw; a.W = (const long long *)W;
     a.orderings = orderings; a.bounds = bounds; a.reps = reps;
     a.T_out = (long long *)T_out; a.status = status;
-    a.part = NULL; a.C = NULL; a.out = NULL; a.rout = NULL;
     a.ord_stride = D; a.bnd_stride = (long long)D * (D + 1) / 2; a.t_stride = D;
-    a.S = D;
-    a.bnd_off = D * (D - 1) / 2;
-    a.t_off = D - 1;
-    int rc = mk_launch_replicated(a, st);
-    if (rc) return rc;
-    // smallest T over all (candidate, stage count) pairs, lowest c*D + xi-1 on ties
-    mk_args m = a;
-    m.S = D; m.N = N * D; m.search = D;
-    m.part = (tc_pair *)part; m.C = (const long long *)W; m.rout = out;
-    long long waves = (m.N + 63) / 64;
-    if (waves > 1024) waves = 1024;
-    hipLaunchKernelGGL(k_argmin, dim3((unsigned)waves, 1), dim3(64), 0, st, m);
-    if (hipGetLastError() != hipSuccess) return PP_ERR_HIP;
-    return launch_pick(m, 1, waves, st);
+    a.S = D; a.search = D;
+    a.part = (tc_pair *)part; a.C = (const long long *)W; a.rout = out;
+    long long n_part = 0;
+    const int rc = mk_launch_replicated(a, st, &n_part);
+    return rc || !n_part ? rc : launch_pick(a, 1, n_part, st);
 }
 
 // ---------------------------------------------------------------- schedule variants

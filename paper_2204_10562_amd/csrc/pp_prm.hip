@@ -648,7 +648,7 @@ static rep_layout rep_layout_of(int L, int D, int64_t N) {
     w.T = off;        off += pp_align256((size_t)N * D * 8);
     w.bounds = off;   off += pp_align256((size_t)N * tri * 4);
     w.reps = off;     off += pp_align256((size_t)N * tri * 4);
-    w.part = off;     off += pp_align256((size_t)1024 * 16);
+    w.part = off;     off += pp_align256((size_t)PP_PARTS * 16);
     w.total = off;
     return w;
 }

@@ -42,3 +42,17 @@ def test_every_stage_count(exe, S, N):
     lines = ["%d %d %d %d 0 %d 1 3 2 17 70" % (PE, S, N, S, hi) for hi in (1, 10**5, 2**45)]
     for line, got in zip(lines, ask(exe, lines)):
         assert got == [0, 0, 0, 0], line
+
+
+@pytest.fixture(scope="module")
+def replicated(tmp_path_factory):
+    return build(tmp_path_factory.mktemp("rep"), "rep_driver")
+
+
+# (the smallest and largest numbers of GPUs of every instance of the kernel, fewer layers than GPUs, pipelines that fill
+# and that do not; quotients of a few units, of 30 bits and beyond)
+@pytest.mark.parametrize("D,L,N", [(2, 3, 70), (4, 9, 20), (5, 4, 30), (8, 20, 66), (9, 11, 9), (12, 30, 5), (13, 40, 4), (16, 50, 3)])
+def test_replicated_stages(replicated, D, L, N):
+    lines = ["%d %d %d %d %d %d" % (D, L, M, N, D + M, hi) for M in (1, 2, 7, 25, 80) for hi in (1, 30, 10**5, 2**44)]
+    for line, got in zip(lines, ask(replicated, lines)):
+        assert got == [0, 0, 0, 0], line
