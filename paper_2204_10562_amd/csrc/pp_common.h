@@ -286,6 +286,15 @@ __device__ __forceinline__ bool pp_is_flat(const pp_ws_header *hdr) {
     return __ballot(hdr->flat[threadIdx.x & (PP_PACK_BLOCKS - 1)] != 0) == ~0ull;
 }
 
+// Largest finish time the 32-bit kernels work with.
+#define PP_TIME_CAP 0x3fffffff
+// Every finish time of a pipeline of S stages whose largest per-resource time is at most this stays below
+// PP_TIME_CAP for M microbatches (Lemma 1, with room), and it and M are below 2^24; -1: no such time.
+__device__ __forceinline__ int pp_time_limit(long long M, int S) {
+    const long long n = M + 4 * S + 64;  // (at least 69, so the limit is below 2^24)
+    return n >= 1 << 24 ? -1 : (int)((unsigned)PP_TIME_CAP / (unsigned)n);
+}
+
 __device__ __forceinline__ void pp_raise(int32_t *status, int bit) {
     if (status) atomicOr(status, bit);
 }

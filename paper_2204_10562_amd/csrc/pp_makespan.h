@@ -63,14 +63,26 @@ __device__ __forceinline__ tc_pair tc_min(tc_pair a, tc_pair b) {
     return (b.T < a.T || (b.T == a.T && b.c < a.c)) ? b : a;
 }
 
+// Over the wave's lanes: four steps within each row of 16 (quad_perm, half_mirror, mirror), then the four rows.
+template <int CTRL>
+__device__ __forceinline__ tc_pair tc_step(tc_pair v) {
+    auto from = [](long long x) {
+        const int lo = __builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true);
+        const int hi = __builtin_amdgcn_update_dpp(0, (int)(x >> 32), CTRL, 0xf, 0xf, true);
+        return (long long)((unsigned long long)(unsigned)hi << 32 | (unsigned)lo);
+    };
+    return tc_min(v, {from(v.T), from(v.c)});
+}
 __device__ __forceinline__ tc_pair wave_tc_min(tc_pair v) {
-    for (int off = 32; off; off >>= 1) {
-        tc_pair o;
-        o.T = __shfl_xor(v.T, off);
-        o.c = __shfl_xor(v.c, off);
-        v = tc_min(v, o);
-    }
-    return v;
+    v = tc_step<0x140>(tc_step<0x141>(tc_step<0x4E>(tc_step<0xB1>(v))));
+    auto row = [&](int i) {
+        auto at = [&](long long x) {
+            const int lo = __builtin_amdgcn_readlane((int)x, i), hi = __builtin_amdgcn_readlane((int)(x >> 32), i);
+            return (long long)((unsigned long long)(unsigned)hi << 32 | (unsigned)lo);
+        };
+        return tc_pair{at(v.T), at(v.c)};
+    };
+    return tc_min(tc_min(row(0), row(16)), tc_min(row(32), row(48)));
 }
 
 // The schedule is no longer than (M + 4S - 4) * C (Lemma 1): fault if that bound reaches 2^62.
@@ -80,15 +92,6 @@ __device__ __forceinline__ int overflow_fault(long long worst, int M, int S) {
 
 // T of a candidate that a kernel has left to the next one (no schedule ends before 0).
 #define MK_NOT_TAKEN (-1ll)
-// Largest finish time the 32-bit kernels work with.
-#define MK_SPLIT_CAP 0x3fffffff
-// Every finish time of a pipeline of S stages whose largest per-resource time is at most this stays below
-// MK_SPLIT_CAP for M microbatches (Lemma 1, with room); -1: no such time (M next to 2^30).
-__device__ __forceinline__ int mk_split_limit(long long M, int S) {
-    const long long n = M + 4 * S + 64;
-    return n > MK_SPLIT_CAP ? -1 : (int)((unsigned)MK_SPLIT_CAP / (unsigned)n);
-}
-
 // The winner record of microbatch count q from the minimum w over all entries.
 __device__ __forceinline__ void write_winner(const mk_args &a, int q, tc_pair w, int lane) {
     const int S = a.S;

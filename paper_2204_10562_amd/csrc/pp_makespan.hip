@@ -52,10 +52,14 @@ static int launch_pick(mk_args a, int nM, long long n_part, hipStream_t st) {
 
 // ---------------------------------------------------------------- plans in closed form, S <= 8
 
-// LDS for plans built here: B and A of the channel-free program, PF, PB, and the forward and backward channel
-// time of every link.
-__host__ __device__ static inline size_t mk_fuse_lds_bytes(int L, int D, int S) {
-    return pp_flat_table_bytes(L, S) + (size_t)2 * (L + 1) * 8 + (size_t)2 * D * D * 8;
+#define MK_FLAT_MAX_S 8
+
+// LDS for plans built here: B and A of the channel-free program, PF and PB in pairs, the forward and backward
+// channel time of every link; then per wave the words of mk_path_body, and per stage a lane's transfer times and the largest
+// channel time so far.
+__host__ __device__ static inline size_t mk_fuse_wave_bytes(int S) { return mk_path_wave_bytes(S) + (size_t)S * 64 * 12; }
+__host__ __device__ static inline size_t mk_fuse_lds_bytes(int L, int D, int S, int waves) {
+    return pp_flat_table_bytes(L, S) + mk_path_table_bytes(L) + (size_t)D * D * 8 + waves * mk_fuse_wave_bytes(S);
 }
 
 // When the plans are not in memory yet (a.fuse): if the tables say so (see mk_args), every lane builds its
@@ -63,149 +67,152 @@ __host__ __device__ static inline size_t mk_fuse_lds_bytes(int L, int D, int S) 
 // channel-free cell), lowest split from the channel-free split table or by a search in the prefix sums - and takes
 // the block durations from LDS as well, so that everything costs one trip to memory.  Returns false (nothing done)
 // if this launch reads its plans from memory.
-template <int S, int NM>
+// What bounds it: that trip, and then the latency of loops over the stages (one wave per SIMD at 8! candidates).  Loops:
+// straight-line code, which a wave runs once, waits for its instructions.
+template <int NM>
 __device__ __forceinline__ bool flat_body(const mk_args &a) {
-    constexpr int R = 2 * S - 1;
     extern __shared__ __align__(16) int rows[];
-    const int L = a.L, D = a.D, nP = L + 1, tid = threadIdx.x, lane = tid & 63, threads = blockDim.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = threads >> 6;
-    // requests first: header, this lane's row, the tables (8 pieces of 16 bytes per thread and
-    // pass; contiguous in the workspace as B then A), PF, PB, and the links' channel times
+    const int S = a.S, L = a.L, D = a.D, nP = L + 1, SP = S | 1, tid = threadIdx.x, lane = tid & 63, T = blockDim.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = T >> 6;
+    // requests first: header, the devices of this wave's candidates, the tables (contiguous in the workspace as B then
+    // A), PF, PB, and the links' channel times
     const unsigned flat_w = a.hdr->flat[lane];
     const unsigned long long vmax = a.hdr->pmax[lane];
     long long g = (long long)blockIdx.x * waves + wave;
-    long long c = g * 64 + lane;
-    int row[S];
+    int dev[MK_FLAT_MAX_S];
+    auto fetch = [&](long long at) {
 #pragma unroll
-    for (int n = 0; n < S; ++n) row[n] = c < a.N ? a.orderings[c * a.ord_stride + n] : 0;
+        for (int u = 0; u < MK_FLAT_MAX_S; ++u) {
+            const long long t = at * 64 * S + u * 64 + lane;
+            dev[u] = u < S && t < a.N * S ? a.orderings[t] : 0;
+        }
+    };
+    fetch(g);
     const size_t tab = pp_flat_table_bytes(L, S);
-    long long *sB = (long long *)rows;
-    int *sA = (int *)(sB + (size_t)S * nP);
-    long long *sPF = (long long *)((unsigned char *)rows + tab), *sPB = sPF + nP, *sxf = sPB + nP, *sxb = sxf + D * D;
-    const int n16 = (int)(tab / 16), T = threads;
+    int *sB = rows, *sA = sB + (size_t)2 * S * nP;
+    long long *PT = (long long *)((unsigned char *)rows + tab);
+    int2 *links = (int2 *)(PT + 2 * nP);
+    const int n16 = (int)(tab / 16);
     int4 first[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) first[u] = tid + u * T < n16 ? ((const int4 *)a.bfl)[tid + u * T] : make_int4(0, 0, 0, 0);
     // (what the first pass of the loops below stores)
     const long long pf0 = tid <= L ? a.PF[tid] : 0, pb0 = tid <= L ? a.PB[tid] : 0;
-    const long long xf0 = (tid < D * D && L > 1) ? a.XF[(size_t)tid * L] : 0, xb0 = (tid < D * D && L > 1) ? a.XB[(size_t)tid * L] : 0;
+    const long long xf0 = tid < D * D && L > 1 ? a.XF[(size_t)tid * L] : 0, xb0 = tid < D * D && L > 1 ? a.XB[(size_t)tid * L] : 0;
     // (lane b holds the largest time of pack block b: all below the limit = their maximum is)
-    const bool fused = __ballot(flat_w != 0) == ~0ull &&
-                       !__ballot(vmax > 0x7fffffffull / (unsigned long long)(a.fuse_mmax + 4 * S - 4));
-    if (!fused) return false;
+    const int limit = pp_time_limit(a.fuse_mmax, S);
+    if (limit < 0 || __ballot(flat_w != 0) != ~0ull || __ballot(vmax > (unsigned long long)limit)) return false;
 #pragma unroll
     for (int u = 0; u < 8; ++u)
         if (tid + u * T < n16) ((int4 *)sB)[tid + u * T] = first[u];
-    for (int base = 8 * T; base < n16; base += 8 * T) {  // (narrow workgroups: further passes)
-        int4 more[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            more[u] = base + tid + u * T < n16 ? ((const int4 *)a.bfl)[base + tid + u * T] : make_int4(0, 0, 0, 0);
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (base + tid + u * T < n16) ((int4 *)sB)[base + tid + u * T] = more[u];
-    }
+    for (int i = 8 * T + tid; i < n16; i += T) ((int4 *)sB)[i] = ((const int4 *)a.bfl)[i];  // (narrow workgroups)
     for (int i = tid; i <= L; i += T) {
-        sPF[i] = i == tid ? pf0 : a.PF[i];
-        sPB[i] = i == tid ? pb0 : a.PB[i];
+        PT[2 * i] = i == tid ? pf0 : a.PF[i];
+        PT[2 * i + 1] = i == tid ? pb0 : a.PB[i];
     }
-    for (int i = tid; i < D * D; i += T) {
-        sxf[i] = i == tid ? xf0 : (L > 1 ? a.XF[(size_t)i * L] : 0);
-        sxb[i] = i == tid ? xb0 : (L > 1 ? a.XB[(size_t)i * L] : 0);
-    }
+    for (int i = tid; i < D * D; i += T)
+        links[i] = make_int2((int)(i == tid ? xf0 : L > 1 ? a.XF[(size_t)i * L] : 0), (int)(i == tid ? xb0 : L > 1 ? a.XB[(size_t)i * L] : 0));
     int M[NM];
     bool briefly[NM];
     mk_counts<NM>(a, M);
+    mk_briefly<PP_SCHED_PE>(M, S, briefly);
     tc_pair least[NM];
 #pragma unroll
-    for (int q = 0; q < NM; ++q) {
-        briefly[q] = M[q] < 2 * R;
-        least[q] = {PP_INF64, INT64_MAX};
-    }
+    for (int q = 0; q < NM; ++q) least[q] = {PP_INF64, INT64_MAX};
     const int steps = pp_flat_steps(L);
+    int *mine = (int *)(links + D * D) + wave * (mk_fuse_wave_bytes(S) / 4), *row = mine + lane * SP;
+    int2 *stash = (int2 *)(mine + mk_path_wave_bytes(S) / 4) + lane;
+    int *most = (int *)(stash - lane + 64 * S) + lane;  // [n][64] largest channel time up to stage n
     __syncthreads();
+    const int di = 64 / S, dn = 64 - di * S, i0 = lane / S, r0 = lane - i0 * S;
     for (; g * 64 < a.N; g += (long long)gridDim.x * waves) {
-        c = g * 64 + lane;
+        const long long c = g * 64 + lane;
         const bool live = c < a.N;
-        // a caller's row is checked here (the DP kernel has not looked at it)
-        bool bad = false;
-        if (a.fuse_validate && live) {
+        {
+            int i = i0, n = r0;
 #pragma unroll
-            for (int n = 0; n < S; ++n) {
-                bad |= row[n] < 0 || row[n] >= D;
-#pragma unroll
-                for (int q = 0; q < n; ++q) bad |= row[q] == row[n];
+            for (int u = 0; u < MK_FLAT_MAX_S; ++u) {
+                if (u < S) mine[i * SP + n] = dev[u] >= 0 && dev[u] < D ? dev[u] : 0xffff;
+                n += dn;
+                i += di;
+                if (n >= S) { n -= S; ++i; }
             }
         }
-        if (bad) {
-#pragma unroll
-            for (int n = 0; n < S; ++n) row[n] = 0;
+        fetch(g + (long long)gridDim.x * waves);  // (the next group's, on their way)
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        // a caller's row is checked here (the DP kernel has not looked at it)
+        bool bad = false;
+        int run = 0, before = 0;
+        unsigned long long seen = 0;
+#pragma unroll 1
+        for (int n = 0; n < S; ++n) {
+            int d = row[n];
+            if (a.fuse_validate) {
+                bad |= d >= D || (seen >> (d & 63) & 1);  // (D <= 32)
+                seen |= 1ull << (d & 63);
+                d = d < D ? d : 0;
+            }
+            if (n) {
+                const int2 x = links[before * D + d];
+                run = run > x.x + x.y ? run : x.x + x.y;
+                stash[n * 64] = x;
+                most[n * 64] = run;
+            }
+            before = d;
         }
-        // prefix maxima of the channel times, then the plan from (S-1, L) downwards
-        long long m[S];
-        int link[S], cf[S], cb[S];
-        m[0] = 0;
-        link[0] = cf[0] = cb[0] = 0;
-#pragma unroll
-        for (int n = 1; n < S; ++n) {
-            link[n] = row[n - 1] * D + row[n];
-            const long long f = sxf[link[n]], b = sxb[link[n]];
-            cf[n] = (int)f;
-            cb[n] = (int)b;
-            m[n] = f + b;
-        }
-        // (the next group's row is on its way while this group's plans are worked out)
-        const long long cn = c + (long long)gridDim.x * waves * 64;
-#pragma unroll
-        for (int n = 0; n < S; ++n) row[n] = cn < a.N ? a.orderings[cn * a.ord_stride + n] : 0;
-#pragma unroll
-        for (int n = 1; n < S; ++n) m[n] = m[n] > m[n - 1] ? m[n] : m[n - 1];
-        int e[S];
-        long long Cval = sB[L];  // S == 1: P[L]
-        e[S - 1] = L;
-#pragma unroll
+        bad = bad && live;
+        // the plan, from (S-1, L) downwards
+        int e = L, C = 0;
+#pragma unroll 1
         for (int n = S - 1; n >= 1; --n) {
-            const long long bn = sB[(size_t)n * nP + e[n]];
-            int r = sA[(size_t)n * nP + e[n]];
-            if (n == S - 1) Cval = m[n] > bn ? m[n] : bn;
-            if (m[n] > bn) {  // the channels bind: the longest last stage that fits in m_n
-                const long long t = sB[e[n]] - m[n];
+            const int at = n * nP + e, bn = sB[2 * at], m = most[n * 64];
+            int r = sA[at];
+            if (n == S - 1) C = m > bn ? m : bn;
+            row[n] = e;
+            if (m > bn) {  // the channels bind: the longest last stage that fits in m
+                const int t = sB[2 * e] - m;
                 int pos = 0;
                 for (int st = 1 << (steps - 1); st; st >>= 1) {
                     const int idx = pos + st - 1;
-                    pos += sB[idx <= L ? idx : L] < t ? st : 0;
+                    pos += sB[2 * (idx <= L ? idx : L)] < t ? st : 0;
                 }
                 r = pos < L ? pos : L;
                 r = r > n ? r : n;
             }
-            e[n - 1] = r;
+            e = r;
         }
-        // the plan goes to memory (the winner's record is read from there)
-        if (live && blockIdx.y == 0) {
-            a.C_w[c] = bad ? PP_INF64 : Cval;
-            int *bo = a.bounds_w + c * S;
-            if (S == 8) {
-                *(int4 *)bo = bad ? make_int4(0, 0, 0, 0) : make_int4(e[0], e[1], e[2], e[3]);
-                *(int4 *)(bo + 4) = bad ? make_int4(0, 0, 0, 0) : make_int4(e[4], e[5], e[6], e[7]);
-            } else {
-#pragma unroll
-                for (int n = 0; n < S; ++n) bo[n] = bad ? 0 : e[n];
-            }
-        }
-        // (no time of the call leaves 32 bits: the low halves of the differences are the differences)
+        row[0] = e;
         mk_path<int, NM> path;
         path.start();
-        int f0 = (int)sPF[0], b0 = (int)sPB[0];
-#pragma unroll
+        int f0 = (int)PT[0], b0 = (int)PT[1];
+#pragma unroll 1
         for (int n = 0; n < S; ++n) {
-            const int f1 = (int)sPF[e[n]], b1 = (int)sPB[e[n]], F = mk_less(f1, f0), B = mk_less(b1, b0);
+            const int at = row[n];
+            const int2 x = n ? stash[n * 64] : make_int2(0, 0);
+            // (no time of the call leaves 32 bits: the low halves of the differences are the differences)
+            const int f1 = (int)PT[2 * at], b1 = (int)PT[2 * at + 1], F = mk_less(f1, f0), B = mk_less(b1, b0);
             f0 = f1;
             b0 = b1;
-            const int K = 2 * (R - 2 * n - 1);
-            if (n) path.step(cf[n], cb[n], K + 2, true, M, briefly);
-            path.step(n == S - 1 ? mk_sum(F, B) : F, n == S - 1 ? 0 : B, K, true, M, briefly);
+            if (bad) row[n] = 0;
+            mk_stage<PP_SCHED_PE>(path, n, S, F, B, x.x, x.y, M, briefly);
         }
-        if (live && bad) pp_raise(a.status, PP_FAULT_ORDERING);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        // the plans go to memory (the winner's record is read from there, maybe by this workgroup)
+        if (blockIdx.y == 0 || a.pick_here) {
+            int i = i0, n = r0;
+            for (int u = 0; u < S; ++u) {
+                const long long t = g * 64 * S + u * 64 + lane;
+                if (t < a.N * S) a.bounds_w[t] = mine[i * SP + n];
+                n += dn;
+                i += di;
+                if (n >= S) { n -= S; ++i; }
+            }
+            if (live) a.C_w[c] = bad ? PP_INF64 : (long long)C;
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (bad) pp_raise(a.status, PP_FAULT_ORDERING);
 #pragma unroll
         for (int q = 0; q < NM; ++q) {
             const int slot = (int)blockIdx.y * NM + q;
@@ -222,17 +229,7 @@ __device__ __forceinline__ bool flat_body(const mk_args &a) {
 // pp_best_plan for 2 .. 8 stages: the plans from the tables without transfers where that is possible, else from memory.
 template <int NM>
 __global__ __launch_bounds__(64 * MK_PATH_WAVES) void k_makespan_flat(mk_args a) {
-    bool done = false;
-    switch (a.S) {
-        case 2: done = flat_body<2, NM>(a); break;
-        case 3: done = flat_body<3, NM>(a); break;
-        case 4: done = flat_body<4, NM>(a); break;
-        case 5: done = flat_body<5, NM>(a); break;
-        case 6: done = flat_body<6, NM>(a); break;
-        case 7: done = flat_body<7, NM>(a); break;
-        case 8: done = flat_body<8, NM>(a); break;
-    }
-    if (!done) mk_path_body<PP_SCHED_PE, NM>(a);
+    if (!flat_body<NM>(a)) mk_path_body<PP_SCHED_PE, NM>(a);
 }
 
 static void plain_layout(mk_args &a, int S) {
@@ -242,7 +239,7 @@ static void plain_layout(mk_args &a, int S) {
 // The makespan kernel can build the plans itself (closed form, tables staged in LDS) for 2..8
 // stages when its tables fit.
 bool pp_makespan_can_fuse(int L, int D, int S) {
-    return S >= 2 && S <= 8 && D <= 32 && mk_fuse_lds_bytes(L, D, S) <= 64 * 1024;
+    return S >= 2 && S <= MK_FLAT_MAX_S && D <= 32 && mk_fuse_lds_bytes(L, D, S, 4) <= 64 * 1024;
 }
 
 // Everything of one call in one launch, and (with a.part) the winners.
@@ -250,13 +247,13 @@ static int launch_makespan(const mk_args &a, hipStream_t st) {
     long long n_part = 0;
     if (a.fuse) {
         const mk_path_launch l = mk_path_shape(a);
-        const size_t need = mk_fuse_lds_bytes(a.L, a.D, a.S), lds = need > l.lds ? need : l.lds;
+        const size_t need = mk_fuse_lds_bytes(a.L, a.D, a.S, l.waves), lds = need > l.lds ? need : l.lds;
         mk_args b = a;
         b.pick_here = l.pick;
         n_part = l.pick ? 0 : l.grid;
-        const dim3 grid(l.grid, (a.nM + MK_COUNTS - 1) / MK_COUNTS), block(64 * l.waves);
-        if (a.nM == 1) hipLaunchKernelGGL(k_makespan_flat<1>, grid, block, lds, st, b);
-        else if (a.nM == 2) hipLaunchKernelGGL(k_makespan_flat<2>, grid, block, lds, st, b);
+        const dim3 grid(l.grid, (a.nM + l.counts - 1) / l.counts), block(64 * l.waves);
+        if (l.counts == 1) hipLaunchKernelGGL(k_makespan_flat<1>, grid, block, lds, st, b);
+        else if (l.counts == 2) hipLaunchKernelGGL(k_makespan_flat<2>, grid, block, lds, st, b);
         else hipLaunchKernelGGL(k_makespan_flat<MK_COUNTS>, grid, block, lds, st, b);
         if (hipGetLastError() != hipSuccess) return PP_ERR_HIP;
     } else {

@@ -104,7 +104,7 @@ __global__ __launch_bounds__(FIFO_THREADS) void k_makespan_fifo(mk_args a) {
     s.cf = (int)cx;
     s.cb = (int)cy;
     // (anything at 2^30 or above is out already: the sum of at most 126 such cannot overflow)
-    const long long cap = MK_SPLIT_CAP;
+    const long long cap = PP_TIME_CAP;
     long long sum = (x < cap ? x : cap) + (y < cap ? y : cap) + (cx < cap ? cx : cap) + (cy < cap ? cy : cap);
     s.idle = s.free = 0;
     s.f1 = s.f2 = s.g0 = s.g1 = s.g2 = FIFO_LATE;
@@ -117,7 +117,7 @@ __global__ __launch_bounds__(FIFO_THREADS) void k_makespan_fifo(mk_args a) {
     // (the workgroup's candidates are taken or left together: k_makespan_events simulates whole waves
     // of neighbours wherever one of them is left.  All four schedules, a seventh of the cuts with nothing to
     // send, 10^6 plans of 2 stages, M = 32: 1.95 ms plan by plan, 1.15 together, 1.19 in that kernel alone)
-    const bool taken = __syncthreads_and(!ok || (!odd && sum <= (long long)MK_SPLIT_CAP / M));
+    const bool taken = __syncthreads_and(!ok || (!odd && sum <= (long long)PP_TIME_CAP / M));
     // (a sweep more than there are serves nothing, nor does a channel behind the last stage hand anything on)
     const bool first = q == 0, reaches = q + 1 < LG;
     for (int t = 0; taken && t < M + J - 1; t += 2) {

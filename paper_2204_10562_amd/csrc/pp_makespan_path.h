@@ -39,10 +39,11 @@ template <typename V> __device__ __forceinline__ V mk_less(V x, V y) {
     typedef typename mk_unsigned<V>::type U;
     return (V)((U)x - (U)y);
 }
-template <typename V> __device__ __forceinline__ V mk_times(V x, int k) {
-    typedef typename mk_unsigned<V>::type U;
-    return (V)((U)x * (U)(V)k);
+__device__ __forceinline__ long long mk_times(long long x, int k) {
+    return (long long)((unsigned long long)x * (unsigned long long)k);
 }
+// (V = int is for times and counts below 2^24, which pp_time_limit sees to: the product is one full-rate instruction)
+__device__ __forceinline__ int mk_times(int x, int k) { return (int)(((unsigned)x & 0xffffff) * ((unsigned)k & 0xffffff)); }
 template <typename V> __device__ __forceinline__ V mk_larger(V x, V y) { return x > y ? x : y; }
 
 // The walks through the resources so far, for NM microbatch counts.
@@ -94,6 +95,7 @@ struct mk_path {
 #define MK_PATH_WAVES 8     // most waves per workgroup
 #define MK_PATH_GRID 2048   // most workgroups; they go round
 #define MK_AT_ONCE 4        // stages whose transfer times a lane asks for together
+#define MK_SPREAD 4096
 #define MK_PICK_WAVES 4      // short lists of up to so many groups of 64: one workgroup schedules and picks
 
 // LDS: PF and PB in pairs, then per wave one word per stage of each of its 64 plans, in rows an odd number
@@ -116,105 +118,176 @@ __device__ __forceinline__ unsigned long long mk_rank_digits(int D, unsigned c) 
 // What a lane finds out about its plan.
 struct mk_plan_info {
     int fault;
-    bool fits;        // no sum of the call leaves the integers V
-    long long worst;  // the largest per-resource time (V = long long)
+    bool fits;        // (32 bits) no sum of the call leaves them
+    long long worst;  // (64 bits) the largest per-resource time
 };
 
-// The plan of xi stages in the wave's rows, of this lane (live: there is one).  PT: pairs (PF, PB).
+// The steps of stage n of xi through the walks: its own times, and those of the link into it.
 template <int MODE, int NM, typename V>
-__device__ __forceinline__ mk_plan_info mk_plan_path(const mk_args &a, const int *row, const long long *PT, int xi, bool live,
-                                                     const int (&M)[NM], int limit, V (&T)[NM]) {
-    constexpr bool narrow = sizeof(V) == 4;
-    const int L = a.L, D = a.D, R = MODE == PP_SCHED_ADDITIVE ? xi : 2 * xi - 1;
-    mk_path<V, NM> path;
-    path.start();
-    bool briefly[NM];
+__device__ __forceinline__ void mk_stage(mk_path<V, NM> &path, int n, int xi, V F, V B, V cf, V cb, const int (&M)[NM],
+                                         const bool (&briefly)[NM]) {
+    const bool last = n == xi - 1;
+    if (MODE == PP_SCHED_ADDITIVE) {
+        // the transfers over a stage's inbound link are part of its passes
+        const V f = mk_sum(F, cf), b = mk_sum(B, cb);
+        path.step(last ? mk_sum(f, b) : f, last ? (V)0 : b, 2 * (xi - 1 - n), true, M, briefly);
+    } else if (MODE == PP_SCHED_GPIPE) {
+        path.step(cf, cb, 0, false, M, briefly);
+        path.step(F, B, 0, false, M, briefly);
+    } else {
+        const int K = 4 * (xi - 1 - n);
+        if (n) path.step(cf, cb, K + 2, MODE != PP_SCHED_DUPLEX, M, briefly);
+        path.step(last ? mk_sum(F, B) : F, last ? (V)0 : B, K, true, M, briefly);
+    }
+}
+template <int MODE, int NM, typename V>
+__device__ __forceinline__ V mk_result(const mk_path<V, NM> &path, int q, int M) {
+    // (GPipe's order: two flow shops of M equal jobs, one after the other)
+    if (MODE == PP_SCHED_GPIPE) return mk_sum(path.sum, mk_times(mk_sum(path.A, path.B), M - 1));
+    return path.longest(q);
+}
+template <int MODE, int NM>
+__device__ __forceinline__ void mk_briefly(const int (&M)[NM], int xi, bool (&briefly)[NM]) {
+    const int R = MODE == PP_SCHED_ADDITIVE ? xi : 2 * xi - 1;
 #pragma unroll
     for (int q = 0; q < NM; ++q) briefly[q] = MODE == PP_SCHED_DUPLEX || M[q] < 2 * R;
-    struct piece { long long f[MK_AT_ONCE], b[MK_AT_ONCE]; };
-    auto bound_of = [&](int w) { const int e = (unsigned)w >> 16; return e <= L ? e : L; };
-    // transfer times into the stages n0 .. n0 + MK_AT_ONCE - 1 (before: the word of the stage before)
+}
+
+// Looks at a plan's rows stage by stage.
+struct mk_row_check {
+    unsigned long long seen;
+    int e0;
+    bool bad, torn;
+    __device__ __forceinline__ void start() { seen = 0; e0 = 0; bad = torn = false; }
+    __device__ __forceinline__ void stage(const mk_args &a, const int *row, int n, int w) {
+        const int o = w & 0xffff, e = (int)((unsigned)w >> 16);
+        bad |= o >= a.D;
+        if (a.D <= 64) {
+            bad |= (seen >> (o & 63)) & 1;
+            seen |= 1ull << (o & 63);
+        } else if (a.orderings) {
+            for (int i = 0; i < n; ++i) bad |= (row[i] & 0xffff) == o;
+        }
+        torn |= e <= e0 || e > a.L;
+        e0 = e;
+    }
+    // (a bad ordering is reported alone: its plan is not looked at)
+    __device__ __forceinline__ int fault(const mk_args &a, bool live) const {
+        return !live ? 0 : bad ? PP_FAULT_ORDERING : torn || e0 != a.L ? PP_FAULT_BOUNDS : 0;
+    }
+};
+
+// Where the times of the link between two stages lie (words of the stages; 0, which is always there, if one is no good).
+__device__ __forceinline__ size_t mk_link_at(const mk_args &a, int before, int w, bool live) {
+    const int o = w & 0xffff, o0 = before & 0xffff, e0 = (int)((unsigned)before >> 16);
+    const bool there = o < a.D && o0 < a.D && e0 >= 1 && e0 <= a.L && live;
+    // (D <= 2^10, L <= 2^11)
+    const unsigned link = (unsigned)mk_times(o0, a.D) + (unsigned)o;
+    return there ? (size_t)((link & 0xffffff) * ((unsigned)a.L & 0xffffff) + (unsigned)(e0 - 1)) : 0;
+}
+
+// The plan of xi stages in the wave's rows, of this lane (live: there is one), in 32-bit sums.  PT: pairs (PF, PB).
+// The transfer times of the next stages are on their way while these are looked at.  (In registers: with a column of LDS
+// per lane instead, and the stages in a loop of their own, fewer waves fit a compute unit: 58 -> 87 us for 131 071 plans
+// of 32 stages.)
+template <int MODE, int NM>
+__device__ __forceinline__ mk_plan_info mk_plan32(const mk_args &a, const int *row, const long long *PT, int xi,
+                                                  bool live, const int (&M)[NM], int limit, long long (&T)[NM]) {
+    mk_path<int, NM> path;
+    path.start();
+    bool briefly[NM];
+    mk_briefly<MODE>(M, xi, briefly);
+    struct piece { long long f[MK_AT_ONCE], b[MK_AT_ONCE]; int w[MK_AT_ONCE]; };
+    // (`before`: the word of the stage before)
     auto ask = [&](piece &x, int n0, int before) {
 #pragma unroll
         for (int u = 0; u < MK_AT_ONCE; ++u) {
             const int n = n0 + u;
             x.f[u] = x.b[u] = 0;
+            x.w[u] = before;
             if (n >= xi) continue;
-            const int w = row[n], o = w & 0xffff, o0 = before & 0xffff, e0 = (unsigned)before >> 16;
-            // (no branch around the loads: all of them are in flight together)
-            const bool there = o < D && o0 < D && e0 >= 1 && e0 <= L && live;
-            const size_t at = there ? (size_t)(unsigned)(o0 * D + o) * (unsigned)L + (unsigned)(e0 - 1) : 0;
-            if (n) {
-                x.f[u] = a.XF[at];
-                x.b[u] = a.XB[at];
-            }
-            before = w;
+            const int w = row[n];
+            const size_t at = mk_link_at(a, before, w, live);
+            x.w[u] = before = w;
+            if (n) { x.f[u] = a.XF[at]; x.b[u] = a.XB[at]; }
         }
         return before;
     };
     piece now, then;
-    int asked = ask(now, 0, 0), before = 0, e0 = 0;
-    bool bad = false, torn = false;
-    unsigned long long seen = 0;
-    long long pf0 = PT[0], pb0 = PT[1], worst = 0;
-    unsigned over = 0, most = 0;
+    int asked = ask(now, 0, 0);
+    mk_row_check check;
+    check.start();
+    int f0 = (int)PT[0], b0 = (int)PT[1];
+    long long p0 = PT[0] + PT[1], over = 0;
+    unsigned most = 0;
     for (int n0 = 0; n0 < xi; n0 += MK_AT_ONCE) {
         if (n0 + MK_AT_ONCE < xi) asked = ask(then, n0 + MK_AT_ONCE, asked);
 #pragma unroll
         for (int u = 0; u < MK_AT_ONCE; ++u) {
             const int n = n0 + u;
             if (n >= xi) continue;
-            const int w = row[n], o = w & 0xffff, e = bound_of(w);
-            bad |= o >= D;
-            if (D <= 64) {
-                bad |= (seen >> (o & 63)) & 1;
-                seen |= 1ull << (o & 63);
-            } else if (a.orderings) {
-                for (int i = 0; i < n; ++i) bad |= (row[i] & 0xffff) == o;
-            }
-            torn |= (int)((unsigned)w >> 16) <= e0 || (int)((unsigned)w >> 16) > L;
-            e0 = e;
-            const long long pf = PT[2 * e], pb = PT[2 * e + 1];
-            const long long F = pf - pf0, B = pb - pb0, cf = now.f[u], cb = now.b[u], s = F + B, x = cf + cb;
-            pf0 = pf;
-            pb0 = pb;
-            if (narrow) {
-                const long long all = MODE == PP_SCHED_ADDITIVE ? s + x : s | x;
-                over |= (unsigned)(all >> 31);
-                if (MODE == PP_SCHED_ADDITIVE) most = most > (unsigned)all ? most : (unsigned)all;
-                else { most = most > (unsigned)s ? most : (unsigned)s; most = most > (unsigned)x ? most : (unsigned)x; }
-            } else {
-                worst = s > worst ? s : worst;
-                worst = x > worst ? x : worst;
-            }
-            const bool last = n == xi - 1;
+            const int w = now.w[u], e1 = (int)((unsigned)w >> 16), e = e1 <= a.L ? e1 : a.L;
+            check.stage(a, row, n, w);
+            const long long pf = PT[2 * e], pb = PT[2 * e + 1], p = pf + pb, x = now.f[u] + now.b[u];
+            const int F = mk_less((int)pf, f0), B = mk_less((int)pb, b0);
+            f0 = (int)pf;
+            b0 = (int)pb;
+            // (sums of two non-negative times: what is 31 bits or less is so in its parts)
+            over |= (p - p0) | x;
+            const unsigned s = (unsigned)(p - p0);
+            p0 = p;
             if (MODE == PP_SCHED_ADDITIVE) {
-                // the transfers over a stage's inbound link are part of its passes
-                const V f = (V)(F + cf), b = (V)(B + cb);
-                path.step(last ? mk_sum(f, b) : f, last ? (V)0 : b, 2 * (R - 1 - n), true, M, briefly);
-            } else if (MODE == PP_SCHED_GPIPE) {
-                path.step((V)cf, (V)cb, 0, false, M, briefly);
-                path.step((V)F, (V)B, 0, false, M, briefly);
+                const unsigned both = s + (unsigned)x;  // (of two numbers below 2^31, or over is set)
+                over |= (long long)(both & 0x80000000u) << 1;
+                most = most > both ? most : both;
             } else {
-                const int K = 2 * (R - 2 * n - 1);
-                if (n) path.step((V)cf, (V)cb, K + 2, MODE != PP_SCHED_DUPLEX, M, briefly);
-                path.step(last ? (V)s : (V)F, last ? (V)0 : (V)B, K, true, M, briefly);
+                most = most > s ? most : s;
+                most = most > (unsigned)x ? most : (unsigned)x;
             }
+            mk_stage<MODE>(path, n, xi, F, B, (int)now.f[u], (int)now.b[u], M, briefly);
         }
         now = then;
     }
-    torn |= e0 != L;
 #pragma unroll
-    for (int q = 0; q < NM; ++q) {
-        // (GPipe's order: two flow shops of M equal jobs, one after the other)
-        if (MODE == PP_SCHED_GPIPE) T[q] = mk_sum(path.sum, mk_times(mk_sum(path.A, path.B), M[q] - 1));
-        else T[q] = path.longest(q);
-    }
+    for (int q = 0; q < NM; ++q) T[q] = mk_result<MODE>(path, q, M[q]);
     mk_plan_info i;
-    // (a bad ordering is reported alone: its plan is not looked at)
-    i.fault = !live ? 0 : bad ? PP_FAULT_ORDERING : torn ? PP_FAULT_BOUNDS : 0;
+    i.fault = check.fault(a, live);
+    i.worst = 0;
+    i.fits = !live || i.fault || (!(over >> 31) && limit >= 0 && most <= (unsigned)limit);
+    return i;
+}
+
+// The same in 64 bits.
+template <int MODE, int NM>
+__device__ __forceinline__ mk_plan_info mk_plan64(const mk_args &a, const int *row, const long long *PT, int xi, bool live,
+                                                  const int (&M)[NM], long long (&T)[NM]) {
+    mk_path<long long, NM> path;
+    path.start();
+    bool briefly[NM];
+    mk_briefly<MODE>(M, xi, briefly);
+    mk_row_check check;
+    check.start();
+    long long f0 = PT[0], b0 = PT[1], worst = 0;
+    int before = 0;
+#pragma unroll 1
+    for (int n = 0; n < xi; ++n) {
+        const int w = row[n], e1 = (int)((unsigned)w >> 16), e = e1 <= a.L ? e1 : a.L;
+        const size_t at = mk_link_at(a, before, w, live);
+        const long long cf = n ? a.XF[at] : 0, cb = n ? a.XB[at] : 0;
+        check.stage(a, row, n, w);
+        before = w;
+        const long long pf = PT[2 * e], pb = PT[2 * e + 1], F = pf - f0, B = pb - b0;
+        f0 = pf;
+        b0 = pb;
+        worst = mk_larger(worst, mk_larger(F + B, cf + cb));
+        mk_stage<MODE>(path, n, xi, F, B, cf, cb, M, briefly);
+    }
+#pragma unroll
+    for (int q = 0; q < NM; ++q) T[q] = mk_result<MODE>(path, q, M[q]);
+    mk_plan_info i;
+    i.fault = check.fault(a, live);
     i.worst = worst;
-    i.fits = !narrow || !live || i.fault || (!over && (int)most <= limit);
+    i.fits = true;
     return i;
 }
 
@@ -295,7 +368,7 @@ __device__ __forceinline__ void mk_path_body(const mk_args &a) {
             const int xi = a.search ? k + 1 : S, SP = xi | 1;
             if (a.search && xi > counts) continue;
             const int bnd_off = a.search ? xi * (xi - 1) / 2 : a.bnd_off;
-            const int limit = mk_split_limit(MODE == PP_SCHED_GPIPE ? 2ll * mmax + 4 * xi : mmax, xi);
+            const int limit = pp_time_limit(MODE == PP_SCHED_GPIPE ? 2ll * mmax + 4 * xi : mmax, xi);
             // the group's rows, entry by entry: as many loads in flight as there are stages, up to 8
             const int di = 64 / xi, dn = 64 - di * xi;
             int i = lane / xi, n = lane - i * xi;
@@ -339,16 +412,13 @@ __device__ __forceinline__ void mk_path_body(const mk_args &a) {
                 }
             }
             long long T[NM];
-            int T32[NM];
-            mk_plan_info p = mk_plan_path<MODE, NM, int>(a, row, PT, xi, live, M, limit, T32);
-#pragma unroll
-            for (int q = 0; q < NM; ++q) T[q] = T32[q];
+            mk_plan_info p = mk_plan32<MODE, NM>(a, row, PT, xi, live, M, limit, T);
             if (__ballot(!p.fits)) {
                 if (a.by_block) {
                     if (live) a.T_out[c * a.t_stride + a.t_off] = MK_NOT_TAKEN;
                     break;
                 }
-                p = mk_plan_path<MODE, NM, long long>(a, row, PT, xi, live, M, limit, T);
+                p = mk_plan64<MODE, NM>(a, row, PT, xi, live, M, T);
             }
 #pragma unroll
             for (int q = 0; q < NM; ++q) {
@@ -366,8 +436,9 @@ __device__ __forceinline__ void mk_path_body(const mk_args &a) {
     if (a.part) mk_leave_least(a, least, (tc_pair *)rows);
 }
 
-// The launch of mk_path_body: workgroups, waves in each, LDS, and whether the one workgroup picks the winners.
-struct mk_path_launch { unsigned grid; int waves; size_t lds; int pick; };
+// The launch of mk_path_body: workgroups, waves in each, counts per lane, LDS, and whether the one workgroup picks the
+// winners.
+struct mk_path_launch { unsigned grid; int waves, counts; size_t lds; int pick; };
 
 static inline mk_path_launch mk_path_shape(const mk_args &a) {
     mk_path_launch l;
@@ -375,14 +446,18 @@ static inline mk_path_launch mk_path_shape(const mk_args &a) {
     int most = (int)((64 * 1024 - table) / each);
     most = most < MK_PATH_WAVES ? most : MK_PATH_WAVES;
     const long long groups = (a.N + 63) / 64;
+    // Plans worked out from LDS: up to MK_SPREAD waves in all, the counts of a call go to different workgroups (blockIdx.y), each
+    // of which works the plans out for itself, because there are SIMDs without a wave otherwise (8! orderings, four counts
+    // 16.6 -> 14.4 us).  Not plans from memory: 131 071 of 32 stages, two counts 58 -> 105 us.
+    l.counts = a.nM == 1 || (a.fuse && groups * a.nM <= MK_SPREAD) ? 1 : a.nM == 2 ? 2 : MK_COUNTS;
     l.pick = 0;
     if (a.search) {
         l.waves = a.search < most ? a.search : most;
-        l.pick = a.part && groups == 1 && a.nM <= MK_COUNTS;
+        l.pick = a.part && groups == 1;
         l.grid = (unsigned)(groups < MK_PATH_GRID ? groups : MK_PATH_GRID);
     } else {
         // short lists: one workgroup that picks too; longer ones: a workgroup per compute unit first
-        l.pick = a.part && groups <= most && groups <= MK_PICK_WAVES && a.nM <= MK_COUNTS;
+        l.pick = a.part && groups <= most && groups <= MK_PICK_WAVES;
         const long long want = l.pick ? groups : (groups + 255) / 256;
         l.waves = (int)(want < 1 ? 1 : want < 4 || l.pick ? want : 4);
         l.waves = l.waves < most ? l.waves : most;

@@ -174,7 +174,7 @@ __device__ __forceinline__ rep_plan rep_body(const mk_args &a, const double *tab
     rep_plan out;
     out.fault = work ? fault : 0;
     out.T = mk_larger(both, brief);
-    out.fits = !narrow || !ok || (largest < (double)MK_SPLIT_CAP && worst <= limit);
+    out.fits = !narrow || !ok || (largest < (double)PP_TIME_CAP && worst <= limit);
     return out;
 }
 
@@ -250,7 +250,7 @@ __global__ __launch_bounds__(64 * REP_WAVES) void k_rep_makespan(mk_args a) {
             __builtin_amdgcn_wave_barrier();
             const bool none = live && a.W[c * D + xi - 1] == PP_INF64;  // no plan with so many stages
             rep_plan p = {};
-            const int limit = exact ? mk_split_limit(a.Ms[0], xi) : -1;
+            const int limit = exact ? pp_time_limit(a.Ms[0], xi) : -1;
             if (limit >= 0) p = rep_body<SMAX, int>(a, tab, links, mine + lane * DP, dev, live && !none, bad, xi, limit);
             if (limit < 0 || __ballot(!p.fits))
                 p = rep_body<SMAX, long long>(a, tab, links, mine + lane * DP, dev, live && !none, bad, xi, limit);

@@ -13,21 +13,18 @@ __global__ __launch_bounds__(64 * MK_PATH_WAVES) void k_makespan_split(mk_args a
     mk_path_body<MODE, NM>(a);
 }
 
-template <int MODE>
-static void launch_path(const mk_args &a, dim3 grid, dim3 block, size_t lds, hipStream_t st) {
-    if (a.nM == 1) hipLaunchKernelGGL((k_makespan_split<MODE, 1>), grid, block, lds, st, a);
-    else if (a.nM == 2) hipLaunchKernelGGL((k_makespan_split<MODE, 2>), grid, block, lds, st, a);
-    else hipLaunchKernelGGL((k_makespan_split<MODE, MK_COUNTS>), grid, block, lds, st, a);
-}
-
 int pp_launch_makespan_split(const mk_args &a, hipStream_t st, long long *n_part) {
     const mk_path_launch l = mk_path_shape(a);
     mk_args b = a;
     b.pick_here = l.pick;
     if (n_part) *n_part = l.pick ? 0 : l.grid;
-    const dim3 grid(l.grid, (a.nM + MK_COUNTS - 1) / MK_COUNTS), block(64 * l.waves);
+    const dim3 grid(l.grid, (a.nM + l.counts - 1) / l.counts), block(64 * l.waves);
     switch (a.variant) {
-        case PP_SCHED_PE: launch_path<PP_SCHED_PE>(b, grid, block, l.lds, st); break;
+        case PP_SCHED_PE:
+            if (l.counts == 1) hipLaunchKernelGGL((k_makespan_split<PP_SCHED_PE, 1>), grid, block, l.lds, st, b);
+            else if (l.counts == 2) hipLaunchKernelGGL((k_makespan_split<PP_SCHED_PE, 2>), grid, block, l.lds, st, b);
+            else hipLaunchKernelGGL((k_makespan_split<PP_SCHED_PE, MK_COUNTS>), grid, block, l.lds, st, b);
+            break;
         // (the comparison schedules take one count)
         case PP_SCHED_DUPLEX: hipLaunchKernelGGL((k_makespan_split<PP_SCHED_DUPLEX, 1>), grid, block, l.lds, st, b); break;
         case PP_SCHED_GPIPE: hipLaunchKernelGGL((k_makespan_split<PP_SCHED_GPIPE, 1>), grid, block, l.lds, st, b); break;
