@@ -29,7 +29,7 @@ struct mk_args {
     int lanes_per;  // lanes per candidate of k_makespan_fifo (1 .. 32)
     int groups;     // candidates per workgroup of k_makespan_fifo
     long long first;  // k_makespan_fifo: the launch's first candidate
-    // workspace header (NULL if there is none)
+    // workspace header, where the plans are the planner's own (C is there then); NULL: the caller's plans
     const pp_ws_header *hdr;
     // k_makespan_flat inside pp_best_plan: nonzero = when no link's channel time depends on the
     // cut position and every finish time of the launch fits 32 bits (both read from hdr), the

@@ -229,7 +229,7 @@ __device__ __forceinline__ bool flat_body(const mk_args &a) {
 // pp_best_plan for 2 .. 8 stages: the plans from the tables without transfers where that is possible, else from memory.
 template <int NM>
 __global__ __launch_bounds__(64 * MK_PATH_WAVES) void k_makespan_flat(mk_args a) {
-    if (!flat_body<NM>(a)) mk_path_body<PP_SCHED_PE, NM>(a);
+    if (!flat_body<NM>(a)) mk_path_body<PP_SCHED_PE, NM, true>(a);
 }
 
 static void plain_layout(mk_args &a, int S) {

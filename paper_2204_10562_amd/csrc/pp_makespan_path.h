@@ -101,6 +101,8 @@ struct mk_path {
 // LDS: PF and PB in pairs, then per wave one word per stage of each of its 64 plans, in rows an odd number
 // of words apart: the device, and above it the stage's bound (0xffff: none such).
 __host__ __device__ static inline size_t mk_path_table_bytes(int L) { return (size_t)(L + 1) * 16; }
+// (of the planner's own plans, whose times are known to fit, the low halves)
+__host__ __device__ static inline size_t mk_known_table_bytes(int L) { return ((size_t)(L + 2) * 8) & ~(size_t)15; }
 __host__ __device__ static inline size_t mk_path_wave_bytes(int S) { return (size_t)64 * (S | 1) * 4; }
 
 // Device n of the orderings with lexicographic rank c < 12!: dig holds their digits, 4 bits each.
@@ -257,17 +259,61 @@ __device__ __forceinline__ mk_plan_info mk_plan32(const mk_args &a, const int *r
     return i;
 }
 
-// The same in 64 bits.
+// The same of a plan whose largest time is known to fit (its C), of valid devices: nothing is checked, and of every number
+// the low half is read.
+template <int NM>
+__device__ __forceinline__ void mk_plan_known(const mk_args &a, const int *row, const int2 *PT, int xi, bool good,
+                                              const int (&M)[NM], long long (&T)[NM]) {
+    mk_path<int, NM> path;
+    path.start();
+    bool briefly[NM];
+    mk_briefly<PP_SCHED_PE>(M, xi, briefly);
+    const int *XF = (const int *)a.XF, *XB = (const int *)a.XB;
+    struct piece { int f[MK_AT_ONCE], b[MK_AT_ONCE], e[MK_AT_ONCE]; };
+    int before = 0;  // the word of the stage before
+    auto ask = [&](piece &x, int n0) {
+#pragma unroll
+        for (int u = 0; u < MK_AT_ONCE; ++u) {
+            const int n = n0 + u;
+            x.f[u] = x.b[u] = x.e[u] = 0;
+            if (n >= xi) continue;
+            const int w = row[n];
+            const unsigned link = (unsigned)mk_times(before & 0xffff, a.D) + (unsigned)(w & 0xffff);
+            const size_t at = good ? (size_t)((link & 0xffffff) * ((unsigned)a.L & 0xffffff) + ((unsigned)before >> 16) - 1) * 2 : 0;
+            if (n) { x.f[u] = XF[at]; x.b[u] = XB[at]; }
+            x.e[u] = good ? (int)((unsigned)w >> 16) : 0;
+            before = w;
+        }
+    };
+    piece now, then;
+    ask(now, 0);
+    int2 p = PT[0];
+    for (int n0 = 0; n0 < xi; n0 += MK_AT_ONCE) {
+        if (n0 + MK_AT_ONCE < xi) ask(then, n0 + MK_AT_ONCE);
+#pragma unroll
+        for (int u = 0; u < MK_AT_ONCE; ++u) {
+            const int n = n0 + u;
+            if (n >= xi) continue;
+            const int2 q = PT[now.e[u]];
+            mk_stage<PP_SCHED_PE>(path, n, xi, mk_less(q.x, p.x), mk_less(q.y, p.y), now.f[u], now.b[u], M, briefly);
+            p = q;
+        }
+        now = then;
+    }
+#pragma unroll
+    for (int q = 0; q < NM; ++q) T[q] = path.longest(q);
+}
+
+// In 64 bits.
 template <int MODE, int NM>
-__device__ __forceinline__ mk_plan_info mk_plan64(const mk_args &a, const int *row, const long long *PT, int xi, bool live,
-                                                  const int (&M)[NM], long long (&T)[NM]) {
+__device__ __forceinline__ mk_plan_info mk_plan64(const mk_args &a, const int *row, int xi, bool live, const int (&M)[NM], long long (&T)[NM]) {
     mk_path<long long, NM> path;
     path.start();
     bool briefly[NM];
     mk_briefly<MODE>(M, xi, briefly);
     mk_row_check check;
     check.start();
-    long long f0 = PT[0], b0 = PT[1], worst = 0;
+    long long f0 = a.PF[0], b0 = a.PB[0], worst = 0;
     int before = 0;
 #pragma unroll 1
     for (int n = 0; n < xi; ++n) {
@@ -276,7 +322,7 @@ __device__ __forceinline__ mk_plan_info mk_plan64(const mk_args &a, const int *r
         const long long cf = n ? a.XF[at] : 0, cb = n ? a.XB[at] : 0;
         check.stage(a, row, n, w);
         before = w;
-        const long long pf = PT[2 * e], pb = PT[2 * e + 1], F = pf - f0, B = pb - b0;
+        const long long pf = a.PF[e], pb = a.PB[e], F = pf - f0, B = pb - b0;
         f0 = pf;
         b0 = pb;
         worst = mk_larger(worst, mk_larger(F + B, cf + cb));
@@ -332,20 +378,26 @@ __device__ __forceinline__ void mk_counts(const mk_args &a, int (&M)[NM]) {
 }
 
 // A workgroup's waves take groups of 64 plans; with a.search all plans of 1 .. a.search stages of the group's
-// candidates, each wave some of the stage counts.
-template <int MODE, int NM>
+// candidates, each wave some of the stage counts.  KNOWN: the plans are those the partition program has left (MODE is
+// PP_SCHED_PE): no time of one is longer than its C, and a bad ordering's C is PP_INF64.
+template <int MODE, int NM, bool KNOWN>
 __device__ __forceinline__ void mk_path_body(const mk_args &a) {
     extern __shared__ __align__(16) int rows[];
     const int tid = threadIdx.x, lane = tid & 63, threads = blockDim.x, waves = threads >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int S = a.S, L = a.L, D = a.D;
     long long *PT = (long long *)rows;
+    int2 *PK = (int2 *)rows;
     for (int i = tid; i <= L; i += threads) {
         const long long f = a.PF[i], b = a.PB[i];
-        PT[2 * i] = f;
-        PT[2 * i + 1] = b;
+        if (KNOWN) {
+            PK[i] = make_int2((int)f, (int)b);
+        } else {
+            PT[2 * i] = f;
+            PT[2 * i + 1] = b;
+        }
     }
-    int *mine = rows + mk_path_table_bytes(L) / 4 + wave * (mk_path_wave_bytes(S) / 4);
+    int *mine = rows + (KNOWN ? mk_known_table_bytes(L) : mk_path_table_bytes(L)) / 4 + wave * (mk_path_wave_bytes(S) / 4);
     int M[NM], mmax = 1;
     mk_counts<NM>(a, M);
 #pragma unroll
@@ -369,6 +421,7 @@ __device__ __forceinline__ void mk_path_body(const mk_args &a) {
             if (a.search && xi > counts) continue;
             const int bnd_off = a.search ? xi * (xi - 1) / 2 : a.bnd_off;
             const int limit = pp_time_limit(MODE == PP_SCHED_GPIPE ? 2ll * mmax + 4 * xi : mmax, xi);
+            const long long C = KNOWN && live ? a.C[c * counts + (a.search ? xi - 1 : 0)] : 0;
             // the group's rows, entry by entry: as many loads in flight as there are stages, up to 8
             const int di = 64 / xi, dn = 64 - di * xi;
             int i = lane / xi, n = lane - i * xi;
@@ -394,7 +447,7 @@ __device__ __forceinline__ void mk_path_body(const mk_args &a) {
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             __builtin_amdgcn_wave_barrier();
             int *row = mine + lane * SP;
-            if (!a.orderings && live) {
+            if (!KNOWN && !a.orderings && live) {
                 // the list of all D! orderings: device n is the digit-th of those left
                 if (D <= 12) {
                     unsigned long long left = 0xBA9876543210ull;
@@ -412,13 +465,26 @@ __device__ __forceinline__ void mk_path_body(const mk_args &a) {
                 }
             }
             long long T[NM];
-            mk_plan_info p = mk_plan32<MODE, NM>(a, row, PT, xi, live, M, limit, T);
+            mk_plan_info p = {};
+            if (KNOWN) {
+                const bool bad = C == PP_INF64;
+                mk_plan_known<NM>(a, row, PK, xi, live && !bad, M, T);
+                p.fits = !live || bad || C <= limit;
+                if (__ballot(bad)) {
+                    mk_row_check check;
+                    check.start();
+                    for (int n = 0; n < xi; ++n) check.stage(a, row, n, row[n]);
+                    p.fault = check.fault(a, live && bad);
+                }
+            } else {
+                p = mk_plan32<MODE, NM>(a, row, PT, xi, live, M, limit, T);
+            }
             if (__ballot(!p.fits)) {
-                if (a.by_block) {
+                if (!KNOWN && a.by_block) {
                     if (live) a.T_out[c * a.t_stride + a.t_off] = MK_NOT_TAKEN;
                     break;
                 }
-                p = mk_plan64<MODE, NM>(a, row, PT, xi, live, M, T);
+                p = mk_plan64<MODE, NM>(a, row, xi, live, M, T);
             }
 #pragma unroll
             for (int q = 0; q < NM; ++q) {
@@ -442,7 +508,7 @@ struct mk_path_launch { unsigned grid; int waves, counts; size_t lds; int pick; 
 
 static inline mk_path_launch mk_path_shape(const mk_args &a) {
     mk_path_launch l;
-    const size_t table = mk_path_table_bytes(a.L), each = mk_path_wave_bytes(a.S);
+    const size_t table = a.hdr ? mk_known_table_bytes(a.L) : mk_path_table_bytes(a.L), each = mk_path_wave_bytes(a.S);
     int most = (int)((64 * 1024 - table) / each);
     most = most < MK_PATH_WAVES ? most : MK_PATH_WAVES;
     const long long groups = (a.N + 63) / 64;

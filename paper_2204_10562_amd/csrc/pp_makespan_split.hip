@@ -10,7 +10,11 @@
 
 template <int MODE, int NM>
 __global__ __launch_bounds__(64 * MK_PATH_WAVES) void k_makespan_split(mk_args a) {
-    mk_path_body<MODE, NM>(a);
+    mk_path_body<MODE, NM, false>(a);
+}
+template <int NM>
+__global__ __launch_bounds__(64 * MK_PATH_WAVES) void k_makespan_plans(mk_args a) {
+    mk_path_body<PP_SCHED_PE, NM, true>(a);
 }
 
 int pp_launch_makespan_split(const mk_args &a, hipStream_t st, long long *n_part) {
@@ -19,6 +23,13 @@ int pp_launch_makespan_split(const mk_args &a, hipStream_t st, long long *n_part
     b.pick_here = l.pick;
     if (n_part) *n_part = l.pick ? 0 : l.grid;
     const dim3 grid(l.grid, (a.nM + l.counts - 1) / l.counts), block(64 * l.waves);
+    if (a.hdr) {
+        // (inside the planner)
+        if (l.counts == 1) hipLaunchKernelGGL(k_makespan_plans<1>, grid, block, l.lds, st, b);
+        else if (l.counts == 2) hipLaunchKernelGGL(k_makespan_plans<2>, grid, block, l.lds, st, b);
+        else hipLaunchKernelGGL(k_makespan_plans<MK_COUNTS>, grid, block, l.lds, st, b);
+        return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_HIP;
+    }
     switch (a.variant) {
         case PP_SCHED_PE:
             if (l.counts == 1) hipLaunchKernelGGL((k_makespan_split<PP_SCHED_PE, 1>), grid, block, l.lds, st, b);
