@@ -51,7 +51,10 @@ struct pp_ws_header {
     // candidates the bands (pp_dp_band.h) leave to the DP kernel: with share_sorted the length of the
     // list, with share_active the representatives among them (kept in a list of their own)
     unsigned share_npend;
-    unsigned pad0[54];
+    // k_band_free (pp_dp_band.hip) has looked at every candidate: it has scheduled those with the channel-free plan,
+    // whose bits are set (pp_ws_layout::fbits) and whose bounds are not written
+    unsigned free_valid;
+    unsigned pad0[53];
     // byte 1024: work the partition DP actually did in this call, in 64 records of 128 bytes
     // (atomics that hit one cache line are served one after another, so every record has a
     // line of its own): (cell, split) pairs evaluated (rows shared between candidates are
@@ -77,6 +80,7 @@ __device__ __forceinline__ void pp_count_work(pp_ws_header *hdr, unsigned long l
 struct pp_ws_layout {
     size_t hdr, p32, x32, xkt, xct, bfl, ord, arg, bounds, C, T, part, total;
     size_t band;  // the table of the bands (pp_dp_band.h), behind the backtrack tables; 0: not wanted
+    size_t fx, fbits;  // k_band_free: transfer times at the channel-free plan's cuts, a bit per candidate (0: not carved)
     // candidates that share a DP (0 = not carved: see pp_share_possible)
     size_t sh_hash, sh_rep, sh_table, sh_keys, sh_reps, sh_cnt, sh_start, sh_rows;
     long long sh_row_slots;  // DP rows (of pp_share_row_stride(L) keys) the area sh_rows holds
@@ -138,6 +142,11 @@ static inline pp_ws_layout pp_layout(int L, int D, int S, int64_t N) {
     w.C = off;      off += pp_align256((size_t)N * 8);
     w.T = off;      off += pp_align256((size_t)N * 8);
     w.part = off;   off += pp_align256((size_t)((N + 63) / 64 < PP_PARTS ? (N + 63) / 64 : PP_PARTS) * 16 * PP_MAX_M_LIST);
+    w.fx = w.fbits = 0;
+    if (w.band && D <= 64) {
+        w.fx = off;    off += pp_align256((size_t)D * D * S * 8);
+        w.fbits = off; off += pp_align256((size_t)((N + 63) / 64) * 8);
+    }
     w.sh_hash = w.sh_rep = w.sh_table = w.sh_keys = w.sh_reps = w.sh_cnt = w.sh_start = w.sh_rows = 0;
     w.sh_row_slots = 0;
     if (pp_share_possible(L, D, N)) {
@@ -193,13 +202,21 @@ int pp_launch_pack(int L, int D, int S, int64_t N, const int64_t *PF, const int6
 // stage count xi at offset xi(xi-1)/2.
 // defer_mmax > 0: see pp_fuse_info (the plans are left to the makespan kernel that follows when
 // the closed form applies and the times for defer_mmax microbatches fit 32 bits).
+// sched != NULL (pp_best_plan with T wanted, stages == 0): the schedules that will be asked for, so that candidates with
+// the channel-free plan can be scheduled where they are found; pp_launch_makespan has to be told (pp_free_plans).
 // keep_list != 0 (only where lay.sh_table != 0): where candidates share their DP, leave the
 // results with the representatives - the caller schedules the list (rlist of
 // pp_launch_makespan) and calls pp_launch_share_scatter itself.
+#define PP_FREE_COUNTS 4
+struct pp_sched_info {
+    int nM;  // at most PP_FREE_COUNTS
+    const int *Ms;
+    int64_t *T;  // [nM][N]
+};
 int pp_launch_dp(int L, int D, int S, int64_t N, const int64_t *PF, const int64_t *PB,
                  const int64_t *XF, const int64_t *XB, const int32_t *lex_ord,
                  const int32_t *user_ord, int stages, int defer_mmax, int keep_list,
-                 int64_t *C_out, int32_t *bounds_out, void *ws, const pp_ws_layout &lay,
+                 const pp_sched_info *sched, int64_t *C_out, int32_t *bounds_out, void *ws, const pp_ws_layout &lay,
                  int32_t *status, hipStream_t st);
 // Candidates whose links have equal channel-time rows, position by position, have the same
 // partition DP (pp_share.hip).  pp_launch_share_prepare finds, on the device, one
@@ -219,6 +236,13 @@ int pp_launch_share_scatter(int64_t N, int nC, int nB, int nT, int tw, int64_t *
                             int32_t *bounds_out, int64_t *T_out, void *ws, const pp_ws_layout &lay,
                             hipStream_t st);
 
+// What k_band_free has left, where hdr->free_valid says so: a bit per candidate that it has scheduled, and their bounds.
+struct pp_free_plans {
+    const unsigned long long *bits;
+    const int *plan;
+};
+// Where k_band_free leaves its bits, and the channel-free plan (NULLs where the layout has no room for them).
+pp_free_plans pp_free_of(void *ws, const pp_ws_layout &lay, int S);
 // Makespan of every candidate's plan for each of the nM microbatch counts in Ms (host array).
 // With part/C/out non-NULL the launch also finds, per microbatch count, the candidate
 // with the smallest T (lowest index on ties) and fills out[q] (one pair of int64 per workgroup
@@ -244,7 +268,7 @@ int pp_launch_makespan(int L, int D, int S, int64_t N, int nM, const int *Ms, co
                        const int32_t *orderings, const int32_t *bounds, int64_t *T_out,
                        int32_t *status, const int64_t *C, void *part,
                        pp_result *out, const pp_ws_header *hdr, const pp_fuse_info *fuse,
-                       const int32_t *rlist, hipStream_t st);
+                       const int32_t *rlist, const pp_free_plans *done, hipStream_t st);
 // Stage-count search: makespan of the plan with xi stages of every candidate for xi = 1..S
 // (bounds [N][S(S+1)/2] and C [N][S] as pp_launch_dp leaves them with stages == 1), written to
 // T_st [nM][N][S], then per microbatch count the smallest T over all (candidate, xi), lowest

@@ -240,6 +240,7 @@ __global__ __launch_bounds__(256) void k_prep(pack_args a) {
             long long pl = a.PF[a.L] + a.PB[a.L];
             m = pl < 0 ? ~0ull : (unsigned long long)pl;
             if (tid < 64) {
+                if (tid == 0) a.hdr->free_valid = 0;
                 auto &w = a.hdr->work[tid];
                 w.pairs = w.rows = w.band_pairs = w.band_rows = w.free_rows = 0;
             }
@@ -448,10 +449,15 @@ static long long choose_chunk(int64_t N, int D, bool lex, long long simds, int w
     return best;
 }
 
+pp_free_plans pp_free_of(void *ws, const pp_ws_layout &lay, int S) {
+    if (!lay.fx) return {NULL, NULL};
+    return {(const unsigned long long *)((char *)ws + lay.fbits), (const int *)((char *)ws + lay.band) + band_plan_at(S, S)};
+}
+
 int pp_launch_dp(int L, int D, int S, int64_t N, const int64_t *PF, const int64_t *PB,
                  const int64_t *XF, const int64_t *XB, const int32_t *lex_ord,
                  const int32_t *user_ord, int stages, int defer_mmax, int keep_list,
-                 int64_t *C_out, int32_t *bounds_out, void *ws, const pp_ws_layout &lay,
+                 const pp_sched_info *sched, int64_t *C_out, int32_t *bounds_out, void *ws, const pp_ws_layout &lay,
                  int32_t *status, hipStream_t st) {
     if (keep_list && !lay.sh_table) return PP_ERR_INVALID_ARG;
     char *base = (char *)ws;
@@ -480,6 +486,17 @@ int pp_launch_dp(int L, int D, int S, int64_t N, const int64_t *PF, const int64_
     if (!a.band_all && lay.sh_table)
         for (a.band_all = 64; a.band_all < N && !band_cells(L, D, S, a.band_all, stages, false, lay);) a.band_all *= 2;
     a.left = NULL;
+    a.fx = NULL;
+    a.fbits = NULL;
+    a.fT = NULL;
+    a.f_nM = 0;
+    if (sched && sched->T && sched->nM <= PP_FREE_COUNTS && !stages && lay.fx && a.band) {
+        a.fx = (int2 *)(base + lay.fx);
+        a.fbits = (unsigned long long *)(base + lay.fbits);
+        a.fT = (long long *)sched->T;
+        a.f_nM = sched->nM;
+        for (int q = 0; q < PP_FREE_COUNTS; ++q) a.f_Ms[q] = q < sched->nM ? sched->Ms[q] : 1;
+    }
 
     int cus = 256;
     int dev = 0;

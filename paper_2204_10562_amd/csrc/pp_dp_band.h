@@ -188,13 +188,18 @@ __device__ __forceinline__ unsigned long long band_free_try(const dp_args &a, co
     return __ballot(live && !bad && !done);
 }
 
-// One link's words, by one wave.
+// One link's words, by one wave; with a.fx also its times at the channel-free plan's cuts, the sign bit of the first saying that
+// the link reaches into the row.
 __device__ __forceinline__ void band_link_wave(const dp_args &a, const int *table, int link, unsigned long long *links) {
     const int lane = threadIdx.x & 63, S = a.S;
     if (S < 2 || !band_free(a, table)) return;
     if (!a.stages) {
         const unsigned long long rows = __ballot(lane >= 1 && lane < S && band_link_reaches(a, table, S, link, lane));
         if (lane == 0) links[link] = rows;
+        if (a.fx && lane >= 1 && lane < S) {
+            const size_t at = (size_t)link * a.L + (table[band_plan_at(S, S) + lane - 1] - 1);
+            a.fx[(size_t)lane * a.D * a.D + link] = make_int2((int)a.XF[at] | (rows >> lane & 1 ? (int)0x80000000 : 0), (int)a.XB[at]);
+        }
     } else if (lane >= 1 && lane < S) {
         unsigned long long m = 0;
         for (int xi = lane + 1; xi <= S; ++xi)

@@ -22,6 +22,11 @@ struct dp_args {
     const long long *bfl;  // the partition DP with no channel cost (values, then splits), see pp_dp_flat.h
     const int *band;       // the table of pp_dp_band.h, or NULL
     long long band_all;    // the fewest candidates for which the recursion over the bands is worth it (pp_dp.hip)
+    // k_band_free: where it works (fx NULL: it does not), the T it writes and for which counts
+    int2 *fx;                        // [S][D*D] transfer times of every link at the channel-free plan's cuts
+    unsigned long long *fbits;
+    long long *fT;
+    int f_nM, f_Ms[PP_FREE_COUNTS];
     const unsigned long long *left;  // a bit per candidate: k_dp_band has left it (NULL: it has not run)
     size_t lds_bytes;      // dynamic LDS of the launch
     // > 0: when the closed form applies and the finish times of a schedule of defer_mmax

@@ -50,6 +50,9 @@ struct mk_args {
     // partition DP (pp_share.hip), this is the list of the candidates that stand for all others;
     // only they are scheduled
     const int *rlist;
+    // plans that k_band_free has scheduled (pp_free_plans), or NULL
+    const unsigned long long *free_bits;
+    const int *free_plan;
     pp_rep_result *rout;   // [nM] winner records with replica counts (instead of out)
     // arg-min (all NULL when not wanted)
     tc_pair *part;         // [nM][workgroups]: every workgroup's minimum, reduced by k_pick
@@ -92,6 +95,12 @@ __device__ __forceinline__ int overflow_fault(long long worst, int M, int S) {
 
 // T of a candidate that a kernel has left to the next one (no schedule ends before 0).
 #define MK_NOT_TAKEN (-1ll)
+// Whether k_band_free has scheduled candidate c.  (It has not looked at any where candidates share their DP.)
+__device__ __forceinline__ bool mk_has_free(const mk_args &a) { return a.free_bits && a.hdr->free_valid; }
+__device__ __forceinline__ bool mk_is_free(const mk_args &a, long long c) {
+    return mk_has_free(a) && (a.free_bits[c >> 6] >> (c & 63) & 1);
+}
+
 // The winner record of microbatch count q from the minimum w over all entries.
 __device__ __forceinline__ void write_winner(const mk_args &a, int q, tc_pair w, int lane) {
     const int S = a.S;
@@ -129,7 +138,7 @@ __device__ __forceinline__ void write_winner(const mk_args &a, int q, tc_pair w,
     // lane n writes bound n and device n (lanes xi.. write zeros)
     int b = 0, o = 0;
     if (lane < xi && !none) {
-        b = a.bounds[at_b + lane];
+        b = mk_is_free(a, c) ? a.free_plan[lane] : a.bounds[at_b + lane];
         if (a.orderings) {
             o = a.orderings[c * a.ord_stride + lane];
         } else {

@@ -227,9 +227,15 @@ __device__ __forceinline__ bool flat_body(const mk_args &a) {
 }
 
 // pp_best_plan for 2 .. 8 stages: the plans from the tables without transfers where that is possible, else from memory.
-template <int NM>
+template <int NM, bool FREE>
 __global__ __launch_bounds__(64 * MK_PATH_WAVES) void k_makespan_flat(mk_args a) {
-    if (!flat_body<NM>(a)) mk_path_body<PP_SCHED_PE, NM, true>(a);
+    if (!flat_body<NM>(a)) mk_path_body<PP_SCHED_PE, NM, true, FREE>(a);
+}
+template <bool FREE>
+static void launch_flat(const mk_args &a, int counts, dim3 grid, dim3 block, size_t lds, hipStream_t st) {
+    if (counts == 1) hipLaunchKernelGGL((k_makespan_flat<1, FREE>), grid, block, lds, st, a);
+    else if (counts == 2) hipLaunchKernelGGL((k_makespan_flat<2, FREE>), grid, block, lds, st, a);
+    else hipLaunchKernelGGL((k_makespan_flat<MK_COUNTS, FREE>), grid, block, lds, st, a);
 }
 
 static void plain_layout(mk_args &a, int S) {
@@ -252,9 +258,8 @@ static int launch_makespan(const mk_args &a, hipStream_t st) {
         b.pick_here = l.pick;
         n_part = l.pick ? 0 : l.grid;
         const dim3 grid(l.grid, (a.nM + l.counts - 1) / l.counts), block(64 * l.waves);
-        if (l.counts == 1) hipLaunchKernelGGL(k_makespan_flat<1>, grid, block, lds, st, b);
-        else if (l.counts == 2) hipLaunchKernelGGL(k_makespan_flat<2>, grid, block, lds, st, b);
-        else hipLaunchKernelGGL(k_makespan_flat<MK_COUNTS>, grid, block, lds, st, b);
+        if (b.free_bits) launch_flat<true>(b, l.counts, grid, block, lds, st);
+        else launch_flat<false>(b, l.counts, grid, block, lds, st);
         if (hipGetLastError() != hipSuccess) return PP_ERR_HIP;
     } else {
         const int rc = pp_launch_makespan_split(a, st, &n_part);
@@ -268,7 +273,7 @@ int pp_launch_makespan(int L, int D, int S, int64_t N, int nM, const int *Ms, co
                        const int32_t *orderings, const int32_t *bounds, int64_t *T_out,
                        int32_t *status, const int64_t *C, void *part,
                        pp_result *out, const pp_ws_header *hdr, const pp_fuse_info *fuse,
-                       const int32_t *rlist, hipStream_t st) {
+                       const int32_t *rlist, const pp_free_plans *done, hipStream_t st) {
     if (rlist && (!hdr || !part)) return PP_ERR_INVALID_ARG;
     mk_args a = {};
     a.rlist = rlist;
@@ -282,6 +287,10 @@ int pp_launch_makespan(int L, int D, int S, int64_t N, int nM, const int *Ms, co
     a.T_out = (long long *)T_out; a.status = status;
     a.part = (tc_pair *)part; a.C = (const long long *)C; a.out = out;
     a.hdr = hdr;
+    if (done && hdr && T_out) {
+        a.free_bits = done->bits;
+        a.free_plan = done->plan;
+    }
     if (fuse && hdr && !rlist && pp_makespan_can_fuse(L, D, S)) {
         a.fuse = 1;
         a.fuse_mmax = fuse->mmax;

@@ -379,8 +379,9 @@ __device__ __forceinline__ void mk_counts(const mk_args &a, int (&M)[NM]) {
 
 // A workgroup's waves take groups of 64 plans; with a.search all plans of 1 .. a.search stages of the group's
 // candidates, each wave some of the stage counts.  KNOWN: the plans are those the partition program has left (MODE is
-// PP_SCHED_PE): no time of one is longer than its C, and a bad ordering's C is PP_INF64.
-template <int MODE, int NM, bool KNOWN>
+// PP_SCHED_PE): no time of one is longer than its C, and a bad ordering's C is PP_INF64.  FREE: k_band_free may have scheduled
+// some of them.
+template <int MODE, int NM, bool KNOWN, bool FREE = false>
 __device__ __forceinline__ void mk_path_body(const mk_args &a) {
     extern __shared__ __align__(16) int rows[];
     const int tid = threadIdx.x, lane = tid & 63, threads = blockDim.x, waves = threads >> 6;
@@ -404,6 +405,7 @@ __device__ __forceinline__ void mk_path_body(const mk_args &a) {
     for (int q = 0; q < NM; ++q) mmax = M[q] > mmax ? M[q] : mmax;
     const bool listed = a.rlist && a.hdr->share_active;
     const long long todo = listed ? a.hdr->share_nreps : a.N, groups = (todo + 63) / 64;
+    const bool has_free = FREE && mk_has_free(a);
     const int counts = a.search ? a.search : 1, per = a.search ? 1 : waves;
     tc_pair least[NM];
 #pragma unroll
@@ -414,6 +416,17 @@ __device__ __forceinline__ void mk_path_body(const mk_args &a) {
         const bool live = at < todo;
         const long long c = !live ? 0 : listed ? pp_share_at(a.hdr, a.rlist, a.N, at) : at;
         const int held = (int)(todo - g * 64 < 64 ? todo - g * 64 : 64);  // plans of this group
+        // (those that are scheduled already: their T is read)
+        const unsigned long long ended = FREE && has_free ? a.free_bits[g] : 0;
+        const bool done = FREE && (ended >> lane & 1);
+        if (FREE && ended && !__ballot(live && !done)) {
+#pragma unroll
+            for (int q = 0; q < NM; ++q) {
+                const int slot = (int)blockIdx.y * NM + q;
+                if (slot < a.nM && live) least[q] = tc_min(least[q], {a.T_out[(long long)slot * a.N + c], c});
+            }
+            continue;
+        }
         // (every other round of stage counts backwards: the waves' shares are alike)
         for (int turn = 0; turn * waves < counts || !a.search; ++turn) {
             const int k = turn * waves + (turn & 1 ? waves - 1 - wave : wave);
@@ -467,9 +480,9 @@ __device__ __forceinline__ void mk_path_body(const mk_args &a) {
             long long T[NM];
             mk_plan_info p = {};
             if (KNOWN) {
-                const bool bad = C == PP_INF64;
-                mk_plan_known<NM>(a, row, PK, xi, live && !bad, M, T);
-                p.fits = !live || bad || C <= limit;
+                const bool bad = C == PP_INF64 && !done;
+                mk_plan_known<NM>(a, row, PK, xi, live && !bad && !done, M, T);
+                p.fits = !live || bad || done || C <= limit;
                 if (__ballot(bad)) {
                     mk_row_check check;
                     check.start();
@@ -484,12 +497,16 @@ __device__ __forceinline__ void mk_path_body(const mk_args &a) {
                     if (live) a.T_out[c * a.t_stride + a.t_off] = MK_NOT_TAKEN;
                     break;
                 }
-                p = mk_plan64<MODE, NM>(a, row, xi, live, M, T);
+                p = mk_plan64<MODE, NM>(a, row, xi, live && !done, M, T);
             }
 #pragma unroll
             for (int q = 0; q < NM; ++q) {
                 const int slot = (int)blockIdx.y * NM + q;
                 if (slot >= a.nM || !live) continue;
+                if (FREE && done) {
+                    least[q] = tc_min(least[q], {a.T_out[(long long)slot * a.N + c], c});
+                    continue;
+                }
                 // (what the 32-bit sums took has no time that long)
                 const int fault = p.fault ? p.fault : p.worst ? overflow_fault(p.worst, M[q], xi) : 0;
                 if (fault) { T[q] = PP_INF64; pp_raise(a.status, fault); }

@@ -12,9 +12,17 @@ template <int MODE, int NM>
 __global__ __launch_bounds__(64 * MK_PATH_WAVES) void k_makespan_split(mk_args a) {
     mk_path_body<MODE, NM, false>(a);
 }
-template <int NM>
+// (FREE in a kernel of its own: with four counts the other has 121 registers, four waves per SIMD, and takes 28 us for
+// the plans of every stage count of 8! orderings, 41 with 131)
+template <int NM, bool FREE>
 __global__ __launch_bounds__(64 * MK_PATH_WAVES) void k_makespan_plans(mk_args a) {
-    mk_path_body<PP_SCHED_PE, NM, true>(a);
+    mk_path_body<PP_SCHED_PE, NM, true, FREE>(a);
+}
+template <bool FREE>
+static void launch_plans(const mk_args &a, const mk_path_launch &l, dim3 grid, dim3 block, hipStream_t st) {
+    if (l.counts == 1) hipLaunchKernelGGL((k_makespan_plans<1, FREE>), grid, block, l.lds, st, a);
+    else if (l.counts == 2) hipLaunchKernelGGL((k_makespan_plans<2, FREE>), grid, block, l.lds, st, a);
+    else hipLaunchKernelGGL((k_makespan_plans<MK_COUNTS, FREE>), grid, block, l.lds, st, a);
 }
 
 int pp_launch_makespan_split(const mk_args &a, hipStream_t st, long long *n_part) {
@@ -25,9 +33,8 @@ int pp_launch_makespan_split(const mk_args &a, hipStream_t st, long long *n_part
     const dim3 grid(l.grid, (a.nM + l.counts - 1) / l.counts), block(64 * l.waves);
     if (a.hdr) {
         // (inside the planner)
-        if (l.counts == 1) hipLaunchKernelGGL(k_makespan_plans<1>, grid, block, l.lds, st, b);
-        else if (l.counts == 2) hipLaunchKernelGGL(k_makespan_plans<2>, grid, block, l.lds, st, b);
-        else hipLaunchKernelGGL(k_makespan_plans<MK_COUNTS>, grid, block, l.lds, st, b);
+        if (b.free_bits) launch_plans<true>(b, l, grid, block, st);
+        else launch_plans<false>(b, l, grid, block, st);
         return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_HIP;
     }
     switch (a.variant) {
