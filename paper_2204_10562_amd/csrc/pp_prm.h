@@ -63,11 +63,17 @@ static inline size_t prm_band_bytes(int L, int D) { return (PRM_BAND_HDR + (size
 __host__ __device__ static inline int prm_band_cells(int D, int lanes) { return D > 12 ? 24 : 2 * lanes; }
 // Ints of a row of Gmin, [stages before]: a multiple of 4, neighbouring rows in other banks.
 __host__ __device__ static inline int prm_band_row(int D) { return ((D + 2) & ~3) | 4; }
-// Bytes of a wave's states, per part.
-__host__ __device__ static inline size_t prm_band_slot_bytes(int D) { return (size_t)prm_states(D) * 64 * 6; }
+// Bytes of a wave's states, per part; behind them the minima over the last stage's replicas, [GPUs, stages].
+__host__ __device__ static inline size_t prm_band_slot_bytes(int D) {
+    return (size_t)prm_states(D) * 64 * 6 + (size_t)(D * (D - 1) / 2) * 64 * 4;
+}
+// What a wave keeps for reading plans back: per (GPUs i, replicas r) a candidate's minimum over the links inside the last
+// stage, and per i a bit for every r whose channels are hidden.
+__host__ __device__ static inline int prm_band_back_ints(int D, int lanes) { return (64 / lanes) * (D * (D + 1) / 2) + 17; }
 static inline size_t prm_band_lds_bytes(int L, int D, int lanes, int waves) {
-    const size_t wave = (size_t)(64 / lanes) * prm_band_cells(D, lanes) * (16 + prm_band_row(D) * 4) + 64 * 4;
-    return (size_t)(L + 1) * (24 + 8 * D) + 16 + waves * wave + (size_t)D * D * 4 + PRM_BAND_HDR * 4;
+    const size_t wave = (size_t)(64 / lanes) * prm_band_cells(D, lanes) * (16 + prm_band_row(D) * 4) + 64 * 4 +
+                        (size_t)prm_band_back_ints(D, lanes) * 4;
+    return (size_t)(L + 1) * (24 + 8 * D) + 16 + waves * wave + (size_t)D * D * 4 + PRM_BAND_HDR * 4 + (size_t)(D + 1) * 8 + 8;
 }
 // Waves of a workgroup: they share the tables that no candidate changes.
 static inline int prm_band_waves(int L, int D, int lanes) {

@@ -13,16 +13,18 @@
 //
 // 8 or 16 lanes per candidate, one per cell, so that a wave has eight or four candidates; wider bands in two parts, and
 // only those states that are wide.  The states on i GPUs by ascending i.  For each (r, i) the minima over r' of every
-// cut come first, for all numbers of stages at once (the channel term of a cut and r' is worked out once, the states
-// on i - r GPUs are read from the wave's scratch memory), go to LDS by cut, and are then read for every cell with the
+// cut come first, for all numbers of stages at once.  Where the channels are hidden behind the stages, as they nearly always are
+// (what follows from the work before and after a cut bounds every value from below), these are the minima over the last
+// stage's replicas that the states have left behind; else the channel term of every cut and r' is worked out and the states
+// on i - r GPUs are read from the wave's scratch memory.  They go to LDS by cut, and are then read for every cell with the
 // cut's last stage, again for all numbers of stages.  The GPUs' bandwidth minima are taken from the ordering as they
-// are needed: lane u holds the minimum over the links of rank u, and a suffix minimum over the lanes gives all r'.
-// With few candidates the waves of a workgroup share them, each with its part of the r of every i.
+// are needed: lane u holds the minimum over the links of rank u, which grow by a rank at a time, and a suffix minimum over
+// the lanes gives all r'.  With few candidates the waves of a workgroup share them, each with its part of the r of every i.
 //
-// What bounds it: instructions and the waits between them, with 2.5 waves per SIMD in flight on an average (vector units
-// busy 61 % of the time with 8 GPUs, 50 % with 12).  All 40320 orderings of 8 GPUs, 128 layers: 3.80 ms with
-// k_prm, 0.28 here; 3001 orderings of 12 GPUs, 75 layers: 1.95 -> 0.23 ms.  It was 0.51 ms for the latter's wider bands
-// (17 to 19 cells) with 32 lanes per candidate and every cell of a band in one part.
+// What bounds it: trips to the scratch memory, which the waves in flight (2.5 per SIMD) spread over more than the caches hold,
+// and instructions.  All 40320 orderings of 8 GPUs, 128 layers: 3.80 ms with k_prm, 0.275 with every channel term and
+// every minimum over r', 0.227 now; 3001 orderings of 12 GPUs, 75 layers: 1.95, 0.226, 0.199 ms.  (Plans were read back with
+// the minima over their links worked out again and a trip to memory per r' tried: 30 % of the first one's time.)
 #include "pp_prm.h"
 #include "pp_dp_row.h"
 
@@ -280,30 +282,6 @@ struct prm_band_wave {
     const double *PA, *AF, *AB;
     const int *bw;       // [D][D]
     const int *o;        // [LANES] the candidate's devices
-    // bandwidth minima of the links from rank u (the lane's) to the ranks [p, p + r), both ways, then over u .. p - 1
-    __device__ __forceinline__ void links(int p, int r, int &mf, int &mb) const {
-        mf = mb = PP_INF32;
-        const int ou = o[t];
-        for (int v = p; v < p + r; ++v) {
-            const int ov = o[v];
-            mf = row_imin(mf, bw[ou * D + ov]);
-            mb = row_imin(mb, bw[ov * D + ou]);
-        }
-        mf = row_suffix_min<LANES>(t < p ? mf : PP_INF32, t);
-        mb = row_suffix_min<LANES>(t < p ? mb : PP_INF32, t);
-    }
-    // r times the minimum over the ordered pairs of ranks [n - r, n)
-    __device__ __forceinline__ double inside(int n, int r) const {
-        if (r < 2) return 1.0;
-        int m = PP_INF32;
-        const int ou = o[t];
-        const bool in = t >= n - r && t < n;
-        for (int v = n - r; v < n; ++v) {
-            const int x = bw[ou * D + o[v]];
-            m = in && v != t ? row_imin(m, x) : m;
-        }
-        return (double)r * (double)row_min<LANES>(m);
-    }
     __device__ __forceinline__ prm_rec rec(int r, int l, double den, double inv) const {
         const int2 x = ut[(r - 1) * L1 + l];
         prm_rec q = {x.x, 0, x.y};
@@ -326,6 +304,8 @@ struct prm_band_lds {
     const double *PA, *AF, *AB;
     const int2 *ut;
     const int *bw, *band;
+    const float2 *hide;  // [i] most bytes over a cut of the states on i GPUs, there and back; no value of theirs is less
+    int *back;   // prm_band_back_ints: the minima, then the bits (of a team: the first wave's)
     int4 *rows;  // [candidate of the wave][cells] records of the cuts
     int *gs;     // [candidate of the wave][cells][prm_band_row] Gmin by cut and stages before
     int *os;     // [64] devices
@@ -343,6 +323,9 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
     const unsigned NS64 = (unsigned)prm_states(D) * 64;
     int *Wt = (int *)(a.scratch + (size_t)wave * parts * prm_band_slot_bytes(D));  // [part][state][64]
     unsigned short *At = (unsigned short *)(Wt + (size_t)NS64 * parts);            // the cut
+    int *Gt = (int *)(At + (size_t)NS64 * parts);                                  // [part][GPUs, stages][64]
+    const int gsize = D * (D - 1) / 2 * 64;
+    int *within = lds.back + group / LANES * tri, *hides = lds.back + EACH * tri;
     int4 *rows = lds.rows + group / LANES * prm_band_cells(D, LANES);
     const int ROW = prm_band_row(D);
     int *gs = lds.gs + group / LANES * prm_band_cells(D, LANES) * ROW;
@@ -372,15 +355,34 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
         row_lds_sync();
         lds.os[lane] = d;
         row_lds_sync();
+        // (the minima over r begin above everything; the one stage on all GPUs has one r)
+        for (int k = TEAM ? wib : 0; k < parts * (gsize / 64); k += TEAM ? team : 1) Gt[k * 64 + lane] = INF;
         // ---- states by ascending number of GPUs; i == D: cell L alone, lane xi - 1 keeps the best r
         int wbest = INF, rbest = 0, lbest = 0;
+        const int ou = w.o[t];
+        int inner = INF;  // of the links between rank t and those after it, both ways
+        if (TEAM) {
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+            __syncthreads();
+        }
         for (int i = 1; i <= D; ++i) {
             const bool top = i == D;
+            // the links of rank i - 1 join: from rank t on, the minimum over the pairs of ranks t .. i - 1
+            const int on = w.o[i - 1];
+            inner = t < i - 1 ? row_imin(inner, row_imin(w.bw[ou * D + on], w.bw[on * D + ou])) : INF;
+            const int inside = row_suffix_min<LANES>(inner, t);
+            int out_f = INF, out_b = INF;  // of the links between rank t and the last r ranks, there and back
             const int lo = top ? L : band[PRM_BAND_LO + i], wd = top ? 1 : band[PRM_BAND_W + i];
             for (int r = 1; r <= i; ++r) {
-                if (TEAM && turn_of(r) != wib) continue;
                 const int n0 = i - r;  // GPUs of the sub-problem
-                const double den = w.inside(i, r), inv = prm_inv(den);
+                const int od = w.o[n0];
+                out_f = row_imin(out_f, w.bw[ou * D + od]);
+                out_b = row_imin(out_b, w.bw[od * D + ou]);
+                if (TEAM && turn_of(r) != wib) continue;
+                // r times the minimum over the ordered pairs of the last stage's ranks
+                const int links = __shfl(inside, group + n0);
+                const double den = r < 2 ? 1.0 : (double)r * (double)links, inv = prm_inv(den);
+                if (t == 0) within[i * (i - 1) / 2 + r - 1] = links;
                 if (n0 == 0) {
                     for (int c0 = 0; c0 < wd; c0 += LANES) {
                         const int v = w.last(none, w.rec(r, row_imin(lo + c0 + t, L), den, inv));
@@ -388,17 +390,18 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
                             if (t == 0) { wbest = v; rbest = D; }
                         } else if (c0 + t < wd) {
                             Wt[(unsigned)(c0 / LANES) * NS64 + prm_sid(i, 1, i) * 64 + lane] = v;
+                            atomicMin(Gt + (c0 / LANES) * gsize + i * (i - 1) / 2 * 64 + lane, v);
                         }
                     }
                     continue;
                 }
                 const int lo_p = band[PRM_BAND_LO + n0], w_p = band[PRM_BAND_W + n0];
-                const prm_rec qL = w.rec(r, L, den, inv);
-                int mf, mb;
-                w.links(n0, r, mf, mb);
+                const prm_rec qL = top ? w.rec(r, L, den, inv) : none;
+                // from rank t on to the last r ranks, both ways
+                const int mf = row_suffix_min<LANES>(t < n0 ? out_f : INF, t), mb = row_suffix_min<LANES>(t < n0 ? out_b : INF, t);
                 if (top) {
                     // two stages: any cut, the first stage on all n0 GPUs
-                    const double den0 = w.inside(n0, n0), inv0 = prm_inv(den0);
+                    const double den0 = n0 < 2 ? 1.0 : (double)n0 * (double)within[n0 * (n0 - 1) / 2 + n0 - 1], inv0 = prm_inv(den0);
                     const int f0 = __shfl(mf, group), b0 = __shfl(mb, group);  // (from rank 0 on: r' = n0)
                     const int lo2 = band[PRM_BAND_LO2 + n0], w2 = band[PRM_BAND_W2 + n0];
                     int best = INF, at = 0;
@@ -413,7 +416,13 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
                     if (t == 1 && m < wbest) { wbest = m; rbest = r; lbest = k; }
                     if (n0 < 2) continue;  // (three stages need two GPUs before the last)
                 }
-                // Gmin of every cut and number of stages: over r' of max(W(l', xi - 1, r', n0), X[r'])
+                // Gmin of every cut and number of stages: over r' of max(W(l', xi - 1, r', n0), X[r']).  Where no X[r'] of
+                // any cut is more than any value of these states can be (M P[l] / i, which follows from the work before and
+                // after the cut), max with it changes no value, and the minima over r' are there already.  (In float, with
+                // room for its roundings and the two quotients'.)
+                const float most = (float)a.M * lds.hide[n0].x / ((float)((n0 - t) * r) * (float)row_imin(mf, mb));
+                const bool hidden = !__ballot(t < n0 && !(most * 1.0001f + (float)(2 * a.M) < lds.hide[i].y));
+                if (hidden && lane == 0) atomicOr(&hides[i], 1 << r);
                 row_lds_sync();
                 for (int c0 = 0; c0 < w_p; c0 += LANES) {
                     const int lp = row_imin(lo_p + c0 + t, L);  // the lane's cut
@@ -424,8 +433,15 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
                     int g[LANES];  // [xi - 2]
 #pragma unroll
                     for (int s = 0; s < LANES; ++s) g[s] = INF;
+                    if (hidden) {
+                        // (past the L1 cache: atomics leave them in the next one)
+                        const int *Gp = Gt + (c0 / LANES) * gsize + n0 * (n0 - 1) / 2 * 64;
+#pragma unroll
+                        for (int s = 0; s < LANES; ++s)
+                            if (s < n0) g[s] = __hip_atomic_load(Gp + s * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
 #pragma unroll 1
-                    for (int rp = 1; rp <= n0; ++rp) {
+                    for (int rp = hidden ? n0 + 1 : 1; rp <= n0; ++rp) {
                         const int x = w.channel(lp, rp * r, __shfl(mf, group + n0 - rp), __shfl(mb, group + n0 - rp));
                         // (the states of s + 1 stages on n0 GPUs begin at that of one replica; one stage has all n0)
                         int v[LANES];
@@ -508,11 +524,15 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
                             const unsigned k = to + ((s + 1) * (i + 1) - (s + 1) * (s + 2) / 2) * 64;  // xi = s + 2
                             Wt[k] = best[s];
                             At[k] = (unsigned short)(lo_p + at[s]);
+                            atomicMin(Gt + (c0 / LANES) * gsize + (i * (i - 1) / 2 + s + 1) * 64 + lane, best[s]);
                         }
                     }
                 }
             }
-            if (TEAM) __syncthreads();
+            if (TEAM) {
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+                __syncthreads();
+            }
         }
         if (TEAM) {
             // the best of all waves, of equal ones the fewest replicas
@@ -550,31 +570,39 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
                     const int n0 = n - r, nrp = n0 - (s - 1);
                     int rp = n0;
                     if (s > 1) {
-                        double den = 1.0;
-                        if (r > 1) {
-                            int m = INF;
-                            for (int p = n0; p < n; ++p)
-                                for (int q = n0; q < n; ++q)
-                                    if (p != q) m = row_imin(m, w.bw[w.o[p] * D + w.o[q]]);
-                            den = (double)r * (double)m;
-                        }
+                        const double den = r < 2 ? 1.0 : (double)r * (double)within[n * (n - 1) / 2 + r - 1];
                         const double inv = prm_inv(den);
                         const int y = w.last(w.rec(r, lp, den, inv), w.rec(r, l, den, inv));
                         const int cell = lp - band[PRM_BAND_LO + n0], place = cell / LANES * (int)NS64 + cell % LANES + group;
                         const int *Ws = Wt + prm_sid(n0, s, 1) * 64 + place;
-                        int mf = INF, mb = INF;
-                        for (rp = 1; rp < nrp; ++rp) {
-                            const int ou = w.o[n0 - rp];
-                            for (int q = n0; q < n; ++q) {
-                                mf = row_imin(mf, w.bw[ou * D + w.o[q]]);
-                                mb = row_imin(mb, w.bw[w.o[q] * D + ou]);
+                        int mf = INF, mb = INF, before = 0;
+                        const bool hidden = hides[n] >> r & 1;
+                        bool found = false;
+                        // (four values in flight; the last r' is the one if no other is)
+                        for (int r0 = 1; !found; r0 += 4) {
+                            int four[4];
+#pragma unroll
+                            for (int u = 0; u < 4; ++u)
+                                four[u] = __hip_atomic_load(Ws + (row_imin(r0 + u, nrp) - 1) * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) {
+                                if (found) continue;
+                                rp = r0 + u;
+                                before = four[u];
+                                int x = 0;
+                                if (!hidden && rp < nrp) {
+                                    const int oq = w.o[n0 - rp];
+                                    for (int q = n0; q < n; ++q) {
+                                        mf = row_imin(mf, w.bw[oq * D + w.o[q]]);
+                                        mb = row_imin(mb, w.bw[w.o[q] * D + oq]);
+                                    }
+                                    x = w.channel(lp, rp * r, mf, mb);
+                                }
+                                found = rp >= nrp || row_imax(row_imax(before, x), y) == v;
                             }
-                            const int x = w.channel(lp, rp * r, mf, mb);
-                            const int before = __hip_atomic_load(Ws + (rp - 1) * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            if (row_imax(row_imax(before, x), y) == v) break;
                         }
                         const int at = prm_sid(n0, s, rp) * 64 + place;
-                        v = __hip_atomic_load(Wt + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        v = before;
                         const unsigned *word = (const unsigned *)((uintptr_t)(At + at) & ~(uintptr_t)3);
                         const unsigned two = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         l = lp;
@@ -589,12 +617,16 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
                 }
             }
         }
+        if (!TEAM || wib == 0) {
+            row_lds_sync();
+            if (lane < 17) hides[lane] = 0;
+        }
         if (TEAM) __syncthreads();  // (the next candidates' states take these ones' place)
     }
 }
 
 template <int LANES, bool TEAM>
-__global__ __launch_bounds__(256, LANES == 8 && !TEAM ? 4 : 3) void k_prm_band(prm_args a) {
+__global__ __launch_bounds__(256, 3) void k_prm_band(prm_args a) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int parts = a.band[PRM_BAND_PARTS];
     if (!parts || a.band[PRM_BAND_LANES] != LANES) return;
@@ -608,7 +640,9 @@ __global__ __launch_bounds__(256, LANES == 8 && !TEAM ? 4 : 3) void k_prm_band(p
     int4 *rows = (int4 *)(((uintptr_t)(ut + D * L1) + 15) & ~(uintptr_t)15);
     constexpr int EACH = 64 / LANES;
     int *gs = (int *)(rows + (B >> 6) * EACH * prm_band_cells(D, LANES)), *os = gs + (B >> 6) * EACH * prm_band_cells(D, LANES) * prm_band_row(D);
-    int *bw = os + B, *band = bw + D * D;
+    int *back = os + B, *bw = back + (B >> 6) * prm_band_back_ints(D, LANES), *band = bw + D * D;
+    float2 *hide = (float2 *)(((uintptr_t)(band + PRM_BAND_HDR) + 7) & ~(uintptr_t)7);
+    for (int i = tid; i < (B >> 6) * prm_band_back_ints(D, LANES); i += B) back[i] = 0;
     for (int l = tid; l < L1; l += B) {
         PA[l] = (double)a.pre_out[2 * L1 + l];
         AF[l] = l >= 1 && l < L ? (double)a.actf[l - 1] : 0.0;
@@ -618,8 +652,20 @@ __global__ __launch_bounds__(256, LANES == 8 && !TEAM ? 4 : 3) void k_prm_band(p
     for (int i = tid; i < D * D; i += B) bw[i] = i / D == i % D ? PP_INF32 : (int)a.bw[i];
     for (int i = tid; i < PRM_BAND_HDR; i += B) band[i] = a.band[i];
     __syncthreads();
+    if (tid >= 1 && tid <= D) {
+        const int lo = tid < D ? band[PRM_BAND_LO + tid] : L, w = tid < D ? band[PRM_BAND_W + tid] : 0;
+        double f = 0.0, b = 0.0;
+        for (int k = lo; k < lo + w && k <= L; ++k) {
+            f = AF[k] > f ? AF[k] : f;
+            b = AB[k] > b ? AB[k] : b;
+        }
+        const double work = (double)(a.pre_out[lo] + a.pre_out[L1 + lo]);
+        hide[tid] = make_float2((float)(f + b), (float)((double)a.M * work / tid * 0.9999));
+    }
+    __syncthreads();
     prm_band_lds lds;
-    lds.PA = PA; lds.AF = AF; lds.AB = AB; lds.ut = ut; lds.bw = bw; lds.band = band;
+    lds.PA = PA; lds.AF = AF; lds.AB = AB; lds.ut = ut; lds.bw = bw; lds.band = band; lds.hide = hide;
+    lds.back = back + (TEAM ? 0 : wib) * prm_band_back_ints(D, LANES);
     lds.rows = rows + wib * EACH * prm_band_cells(D, LANES);
     lds.gs = gs + wib * EACH * prm_band_cells(D, LANES) * prm_band_row(D);
     lds.os = os + 64 * wib;
