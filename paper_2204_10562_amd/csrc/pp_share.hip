@@ -55,9 +55,7 @@ struct share_args {
     int *pend;                  // [N] representatives the bands have left
     int *start;                 // [run_waves + 1] first entry of every run of that list
     int run_waves;
-    // k_share_keys: candidates first_c .. last_c - 1; look: 1 = there are entries of an earlier launch to look at
-    long long first_c, last_c;
-    int look;
+    long long first_c, last_c;  // k_share_keys: candidates first_c .. last_c - 1
     // scatter
     int nC, nB, nT, tw, vec;
     long long *C_out, *T_out;
@@ -168,9 +166,14 @@ __global__ __launch_bounds__(256) void k_share_classes(share_args a) {
 #define SHARE_SLOT_BITS 11
 #define SHARE_SLOTS (1 << SHARE_SLOT_BITS)
 
-__global__ __launch_bounds__(256) void k_share_keys(share_args a) {
-    __shared__ int s_cls[PP_SHARE_MAX_D * PP_SHARE_MAX_D];
-    __shared__ int s_cnt[4], s_key[SHARE_SLOTS], s_low[SHARE_SLOTS];
+// LOOK: the launch for the rest of a list, T = 256 threads (the dynamic LDS holds the class of every link); else a thread
+// per candidate of a workgroup, T = SHARE_OWN.  What bounds it: the atomics on the table, and for the rest of a list the
+// orderings' bytes (56 MB in 22 us; 28 with one load of a row in flight).
+template <bool LOOK>
+__global__ __launch_bounds__(LOOK ? 256 : SHARE_OWN) void k_share_keys(share_args a) {
+    constexpr int T = LOOK ? 256 : SHARE_OWN;
+    extern __shared__ int s_cls[];
+    __shared__ int s_cnt[T / 64], s_key[LOOK ? 1 : SHARE_SLOTS], s_low[LOOK ? 1 : SHARE_SLOTS];
     const int nl = a.D * a.D, D = a.D, S = a.S, tid = threadIdx.x;
     const unsigned nc = a.hdr->share_nc, tsize = share_table_size(nc, S);
     // otherwise: buckets of the first kdev devices (pp_dp_band.hip)
@@ -185,7 +188,7 @@ __global__ __launch_bounds__(256) void k_share_keys(share_args a) {
     }
     if (!tsize) return;
     // class numbers: the rank of a link's representative among the representatives
-    const int per = (nl + 255) / 256, lo = tid * per, hi = lo + per < nl ? lo + per : nl;
+    const int per = (nl + T - 1) / T, lo = tid * per < nl ? tid * per : nl, hi = lo + per < nl ? lo + per : nl;
     int cnt = 0;
     for (int i = lo; i < hi; ++i) cnt += a.lrep[i] == i;
     int before = cnt;
@@ -200,7 +203,7 @@ __global__ __launch_bounds__(256) void k_share_keys(share_args a) {
     for (int i = lo; i < hi; ++i)
         if (a.lrep[i] == i) s_cls[i] = before++;
     __syncthreads();
-    int mine[(PP_SHARE_MAX_D * PP_SHARE_MAX_D + 255) / 256];
+    int mine[(PP_SHARE_MAX_D * PP_SHARE_MAX_D + T - 1) / T];
     for (int i = lo; i < hi; ++i) {
         const int r = a.lrep[i];
         mine[i - lo] = r >= 0 ? s_cls[r] : 0;
@@ -213,14 +216,11 @@ __global__ __launch_bounds__(256) void k_share_keys(share_args a) {
     // key that many candidates have (3.5 % of sampled orderings of 4 servers of 4 devices never stay on a server)
     // would have their atomics queue on its address.  What it has left can be looked at through the caches by
     // the launch for the rest of the list, and is lower than any candidate there.
-    if (!a.look) {
-        for (int i = tid; i < SHARE_SLOTS; i += 256) { s_key[i] = -1; s_low[i] = SHARE_NONE; }
+    if (!LOOK) {
+        for (int i = tid; i < SHARE_SLOTS; i += T) { s_key[i] = -1; s_low[i] = SHARE_NONE; }
         __syncthreads();
     }
-    const long long from = a.first_c + (a.look ? (long long)blockIdx.x * 256 : (long long)blockIdx.x * SHARE_OWN) + tid;
-    const long long to = a.look ? a.last_c : (from - tid + SHARE_OWN < a.last_c ? from - tid + SHARE_OWN : a.last_c);
-    const long long step = a.look ? (long long)gridDim.x * 256 : 256;
-    for (long long c = from; c < to; c += step) {
+    for (long long c = a.first_c + (long long)blockIdx.x * T + tid; c < a.last_c; c += (long long)gridDim.x * T) {
         const int *row = a.ord + c * S;
         unsigned long long used = 0;
         unsigned key = 0;
@@ -237,9 +237,17 @@ __global__ __launch_bounds__(256) void k_share_keys(share_args a) {
         };
         if (vec) {
             // (a row is S devices of 4 bytes: 16 bytes at a time where rows are so aligned)
-            for (int n = 0; n < S; n += 4) {
-                const int4 v = *(const int4 *)(row + n);
-                place(n, v.x); place(n + 1, v.y); place(n + 2, v.z); place(n + 3, v.w);
+            // (four of them in flight)
+            for (int n0 = 0; n0 < S; n0 += 16) {
+                int4 v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[u] = *(const int4 *)(row + (n0 + 4 * u < S ? n0 + 4 * u : n0));
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int n = n0 + 4 * u;
+                    if (n >= S) continue;
+                    place(n, v[u].x); place(n + 1, v[u].y); place(n + 2, v[u].z); place(n + 3, v[u].w);
+                }
             }
         } else {
             for (int n = 0; n < S; ++n) place(n, row[n]);
@@ -250,7 +258,7 @@ __global__ __launch_bounds__(256) void k_share_keys(share_args a) {
             continue;
         }
         a.keys[c] = (int)key;
-        if (a.look) {
+        if (LOOK) {
             if (a.table[key] > (int)c) atomicMin(&a.table[key], (int)c);
             continue;
         }
@@ -259,9 +267,9 @@ __global__ __launch_bounds__(256) void k_share_keys(share_args a) {
         if (was == -1 || was == (int)key) atomicMin(&s_low[slot], (int)c);
         else atomicMin(&a.table[key], (int)c);  // (another key has the slot)
     }
-    if (a.look) return;
+    if (LOOK) return;
     __syncthreads();
-    for (int i = tid; i < SHARE_SLOTS; i += 256)
+    for (int i = tid; i < SHARE_SLOTS; i += T)
         if (s_key[i] >= 0) atomicMin(&a.table[s_key[i]], s_low[i]);
 }
 
@@ -437,6 +445,18 @@ __global__ __launch_bounds__(256) void k_share_scatter(share_args a) {
         if (key < 0) continue;
         const long long r = a.table[key & ~SHARE_ENDED];
         if (r == c) continue;
+        if (a.nC <= 1 && a.tw == 1 && a.nT <= 4 && !a.nB) {
+            // (all loads before the first store: one trip to memory)
+            const long long C = a.nC ? a.C_out[r] : 0;
+            long long t[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) t[q] = q < a.nT ? a.T_out[q * a.N + r] : 0;
+            if (a.nC) a.C_out[c] = C;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (q < a.nT) a.T_out[q * a.N + c] = t[q];
+            continue;
+        }
         for (int i = 0; i < a.nC; ++i) a.C_out[c * a.nC + i] = a.C_out[r * a.nC + i];
         for (int q = 0; q < a.nT; ++q)
             for (int i = 0; i < a.tw; ++i) a.T_out[(q * a.N + c) * a.tw + i] = a.T_out[(q * a.N + r) * a.tw + i];
@@ -492,15 +512,15 @@ int pp_launch_share_prepare(const dp_args &g, int run_waves, void *ws, const pp_
     hipLaunchKernelGGL(k_share_classes, dim3(link_blocks), dim3(256), 0, st, a);
     int rc = a.sort ? pp_launch_dp_band(g, a.band, a.links, a.keys, a.table, a.reps, 1, st) : PP_OK;
     if (rc) return rc;
-    // The keys of a long list in two launches, the first eighth alone: 10^6 candidates of 15 751 keys 87 us when
-    // every candidate looks past the caches and does its own atomic, 57 us so.
-    const long long first = N > 200000 ? N / 8 : N;
-    a.first_c = 0; a.last_c = first; a.look = 0;
-    hipLaunchKernelGGL(k_share_keys, dim3((unsigned)((first + SHARE_OWN - 1) / SHARE_OWN)), dim3(256), 0, st, a);
+    // The keys of a long list in two launches, the first sixteenth alone: 10^6 candidates of 15 751 keys 87 us when
+    // every candidate looks past the caches and does its own atomic, 19 + 26 us so (an eighth 30 + 22, a thirty-second 13 + 28).
+    const long long first = N > 200000 ? N / 16 : N;
+    a.first_c = 0; a.last_c = first;
+    hipLaunchKernelGGL(k_share_keys<false>, dim3((unsigned)((first + SHARE_OWN - 1) / SHARE_OWN)), dim3(SHARE_OWN), (size_t)D * D * 4, st, a);
     if (first < N) {
         const long long g = share_grid(N - first);
-        a.first_c = first; a.last_c = N; a.look = 1;
-        hipLaunchKernelGGL(k_share_keys, dim3((unsigned)(g < 2048 ? g : 2048)), dim3(256), 0, st, a);
+        a.first_c = first; a.last_c = N;
+        hipLaunchKernelGGL(k_share_keys<true>, dim3((unsigned)(g < 2048 ? g : 2048)), dim3(256), (size_t)D * D * 4, st, a);
     }
     hipLaunchKernelGGL(k_share_count, dim3(PP_SHARE_TABLE / 256), dim3(256), 0, st, a);
     hipLaunchKernelGGL(k_share_reps, dim3(PP_SHARE_TABLE / 256), dim3(256), 0, st, a);
