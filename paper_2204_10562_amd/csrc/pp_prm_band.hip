@@ -355,16 +355,14 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
         row_lds_sync();
         lds.os[lane] = d;
         row_lds_sync();
-        // (the minima over r begin above everything; the one stage on all GPUs has one r)
-        for (int k = TEAM ? wib : 0; k < parts * (gsize / 64); k += TEAM ? team : 1) Gt[k * 64 + lane] = INF;
+        // the minima over r begin above everything.  (Of a team, other waves first touch them for two GPUs, behind a barrier; that
+        // of one GPU is stored.)
+        for (int k = TEAM ? wib : 0; k < parts * (gsize / 64); k += TEAM ? team : 1)
+            if (k % (gsize / 64)) Gt[k * 64 + lane] = INF;
         // ---- states by ascending number of GPUs; i == D: cell L alone, lane xi - 1 keeps the best r
         int wbest = INF, rbest = 0, lbest = 0;
         const int ou = w.o[t];
         int inner = INF;  // of the links between rank t and those after it, both ways
-        if (TEAM) {
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-            __syncthreads();
-        }
         for (int i = 1; i <= D; ++i) {
             const bool top = i == D;
             // the links of rank i - 1 join: from rank t on, the minimum over the pairs of ranks t .. i - 1
@@ -390,7 +388,8 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
                             if (t == 0) { wbest = v; rbest = D; }
                         } else if (c0 + t < wd) {
                             Wt[(unsigned)(c0 / LANES) * NS64 + prm_sid(i, 1, i) * 64 + lane] = v;
-                            atomicMin(Gt + (c0 / LANES) * gsize + i * (i - 1) / 2 * 64 + lane, v);
+                            if (i == 1) Gt[(c0 / LANES) * gsize + lane] = v;
+                            else atomicMin(Gt + (c0 / LANES) * gsize + i * (i - 1) / 2 * 64 + lane, v);
                         }
                     }
                     continue;
@@ -659,10 +658,10 @@ __global__ __launch_bounds__(256, 3) void k_prm_band(prm_args a) {
             f = AF[k] > f ? AF[k] : f;
             b = AB[k] > b ? AB[k] : b;
         }
-        const double work = (double)(a.pre_out[lo] + a.pre_out[L1 + lo]);
-        hide[tid] = make_float2((float)(f + b), (float)((double)a.M * work / tid * 0.9999));
+        // (ut for one replica is M times the work before the cell)
+        hide[tid] = make_float2((float)(f + b), (float)ut[lo].x / (float)tid * 0.9999f);
     }
-    __syncthreads();
+    if (!TEAM) __syncthreads();  // (a team looks there behind the barrier of its first states)
     prm_band_lds lds;
     lds.PA = PA; lds.AF = AF; lds.AB = AB; lds.ut = ut; lds.bw = bw; lds.band = band; lds.hide = hide;
     lds.back = back + (TEAM ? 0 : wib) * prm_band_back_ints(D, LANES);
