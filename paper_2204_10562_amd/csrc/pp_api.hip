@@ -192,16 +192,16 @@ extern "C" int pp_best_plan_multi(int L, int D, int S, int64_t N, int nM, const 
     // index), and T and C reach the other candidates only if the caller wants the arrays.
     const bool listed = lay.sh_table != 0;
     const bool can_fuse = !listed && pp_makespan_can_fuse(L, D, S);
-    const pp_sched_info sched = {nM, M_list, T_all};
+    pp_sched_info sched = {nM, M_list, T_all, false};
     const pp_free_plans done = pp_free_of(workspace, lay, S);
     rc = pp_launch_dp(L, D, S, N, PF, PB, XF, XB, orderings ? NULL : ord, orderings, 0,
-                      can_fuse ? fuse.mmax : 0, listed, T_all && nM <= PP_FREE_COUNTS ? &sched : NULL, C, bounds,
+                      can_fuse ? fuse.mmax : 0, listed, nM <= PP_FREE_COUNTS ? &sched : NULL, C, bounds,
                       workspace, lay, status, st);
     if (rc) return rc;
     rc = pp_launch_makespan(L, D, S, N, nM, M_list, PF, PB, XF, XB, ord, bounds, T_all,
                             status, C, base + lay.part, out,
                             (const pp_ws_header *)(base + lay.hdr), can_fuse ? &fuse : NULL,
-                            listed ? (const int32_t *)(base + lay.sh_reps) : NULL, done.bits ? &done : NULL, st);
+                            listed ? (const int32_t *)(base + lay.sh_reps) : NULL, sched.looked ? &done : NULL, st);
     if (rc || !listed || (!T_all && !C_all)) return rc;
     return pp_launch_share_scatter(N, C_all ? 1 : 0, 0, T_all ? nM : 0, 1, C_all, NULL, T_all, workspace,
                                    lay, st);

@@ -80,7 +80,9 @@ __device__ __forceinline__ void pp_count_work(pp_ws_header *hdr, unsigned long l
 struct pp_ws_layout {
     size_t hdr, p32, x32, xkt, xct, bfl, ord, arg, bounds, C, T, part, total;
     size_t band;  // the table of the bands (pp_dp_band.h), behind the backtrack tables; 0: not wanted
-    size_t fx, fbits;  // k_band_free: transfer times at the channel-free plan's cuts, a bit per candidate (0: not carved)
+    // k_band_free: transfer times at the channel-free plan's cuts, a bit per candidate, and a minimum per 64 candidates and
+    // microbatch count (0: not carved)
+    size_t fx, fbits, fleast;
     // candidates that share a DP (0 = not carved: see pp_share_possible)
     size_t sh_hash, sh_rep, sh_table, sh_keys, sh_reps, sh_cnt, sh_start, sh_rows;
     long long sh_row_slots;  // DP rows (of pp_share_row_stride(L) keys) the area sh_rows holds
@@ -93,6 +95,8 @@ struct pp_ws_layout {
 // pp_dp_tiles (pp_dp.hip) says so.
 #define PP_PAIRS_MAX_L 88
 #define PP_DP_SLOTS 4096
+// Most microbatch counts of a call for which k_band_free schedules (pp_sched_info).
+#define PP_FREE_COUNTS 4
 // Most partial minima of the arg-min per microbatch count (workgroups of a schedule launch).
 #define PP_PARTS 2048
 // Sharing of one partition DP between the candidates whose links have the same channel times
@@ -142,10 +146,11 @@ static inline pp_ws_layout pp_layout(int L, int D, int S, int64_t N) {
     w.C = off;      off += pp_align256((size_t)N * 8);
     w.T = off;      off += pp_align256((size_t)N * 8);
     w.part = off;   off += pp_align256((size_t)((N + 63) / 64 < PP_PARTS ? (N + 63) / 64 : PP_PARTS) * 16 * PP_MAX_M_LIST);
-    w.fx = w.fbits = 0;
+    w.fx = w.fbits = w.fleast = 0;
     if (w.band && D <= 64) {
         w.fx = off;    off += pp_align256((size_t)D * D * S * 8);
         w.fbits = off; off += pp_align256((size_t)((N + 63) / 64) * 8);
+        w.fleast = off; off += pp_align256((size_t)((N + 63) / 64) * 8 * PP_FREE_COUNTS);
     }
     w.sh_hash = w.sh_rep = w.sh_table = w.sh_keys = w.sh_reps = w.sh_cnt = w.sh_start = w.sh_rows = 0;
     w.sh_row_slots = 0;
@@ -202,21 +207,21 @@ int pp_launch_pack(int L, int D, int S, int64_t N, const int64_t *PF, const int6
 // stage count xi at offset xi(xi-1)/2.
 // defer_mmax > 0: see pp_fuse_info (the plans are left to the makespan kernel that follows when
 // the closed form applies and the times for defer_mmax microbatches fit 32 bits).
-// sched != NULL (pp_best_plan with T wanted, stages == 0): the schedules that will be asked for, so that candidates with
+// sched != NULL (pp_best_plan, stages == 0): the schedules that will be asked for, so that candidates with
 // the channel-free plan can be scheduled where they are found; pp_launch_makespan has to be told (pp_free_plans).
 // keep_list != 0 (only where lay.sh_table != 0): where candidates share their DP, leave the
 // results with the representatives - the caller schedules the list (rlist of
 // pp_launch_makespan) and calls pp_launch_share_scatter itself.
-#define PP_FREE_COUNTS 4
 struct pp_sched_info {
     int nM;  // at most PP_FREE_COUNTS
     const int *Ms;
-    int64_t *T;  // [nM][N]
+    int64_t *T;  // [nM][N] or NULL
+    bool looked;  // set where k_band_free may be launched
 };
 int pp_launch_dp(int L, int D, int S, int64_t N, const int64_t *PF, const int64_t *PB,
                  const int64_t *XF, const int64_t *XB, const int32_t *lex_ord,
                  const int32_t *user_ord, int stages, int defer_mmax, int keep_list,
-                 const pp_sched_info *sched, int64_t *C_out, int32_t *bounds_out, void *ws, const pp_ws_layout &lay,
+                 pp_sched_info *sched, int64_t *C_out, int32_t *bounds_out, void *ws, const pp_ws_layout &lay,
                  int32_t *status, hipStream_t st);
 // Candidates whose links have equal channel-time rows, position by position, have the same
 // partition DP (pp_share.hip).  pp_launch_share_prepare finds, on the device, one
@@ -236,9 +241,11 @@ int pp_launch_share_scatter(int64_t N, int nC, int nB, int nT, int tw, int64_t *
                             int32_t *bounds_out, int64_t *T_out, void *ws, const pp_ws_layout &lay,
                             hipStream_t st);
 
-// What k_band_free has left, where hdr->free_valid says so: a bit per candidate that it has scheduled, and their bounds.
+// What k_band_free has left, where hdr->free_valid says so: a bit per candidate that it has scheduled, per microbatch count and 64
+// candidates the least time of those (time * 64 + place in the 64, -1: none of them), and their bounds.
 struct pp_free_plans {
     const unsigned long long *bits;
+    const long long *least;  // [nM][(N + 63) / 64]
     const int *plan;
 };
 // Where k_band_free leaves its bits, and the channel-free plan (NULLs where the layout has no room for them).

@@ -450,14 +450,15 @@ static long long choose_chunk(int64_t N, int D, bool lex, long long simds, int w
 }
 
 pp_free_plans pp_free_of(void *ws, const pp_ws_layout &lay, int S) {
-    if (!lay.fx) return {NULL, NULL};
-    return {(const unsigned long long *)((char *)ws + lay.fbits), (const int *)((char *)ws + lay.band) + band_plan_at(S, S)};
+    if (!lay.fx) return {NULL, NULL, NULL};
+    return {(const unsigned long long *)((char *)ws + lay.fbits), (const long long *)((char *)ws + lay.fleast),
+            (const int *)((char *)ws + lay.band) + band_plan_at(S, S)};
 }
 
 int pp_launch_dp(int L, int D, int S, int64_t N, const int64_t *PF, const int64_t *PB,
                  const int64_t *XF, const int64_t *XB, const int32_t *lex_ord,
                  const int32_t *user_ord, int stages, int defer_mmax, int keep_list,
-                 const pp_sched_info *sched, int64_t *C_out, int32_t *bounds_out, void *ws, const pp_ws_layout &lay,
+                 pp_sched_info *sched, int64_t *C_out, int32_t *bounds_out, void *ws, const pp_ws_layout &lay,
                  int32_t *status, hipStream_t st) {
     if (keep_list && !lay.sh_table) return PP_ERR_INVALID_ARG;
     char *base = (char *)ws;
@@ -488,12 +489,15 @@ int pp_launch_dp(int L, int D, int S, int64_t N, const int64_t *PF, const int64_
     a.left = NULL;
     a.fx = NULL;
     a.fbits = NULL;
-    a.fT = NULL;
+    a.fT = a.fleast = NULL;
     a.f_nM = 0;
-    if (sched && sched->T && sched->nM <= PP_FREE_COUNTS && !stages && lay.fx && a.band) {
+    // (bands of a launch of their own: k_dp_rows looks at the candidates itself)
+    if (sched && sched->nM <= PP_FREE_COUNTS && !stages && lay.fx && (use == BAND_USE_ALONE || (a.band && lay.sh_table))) {
+        sched->looked = true;
         a.fx = (int2 *)(base + lay.fx);
         a.fbits = (unsigned long long *)(base + lay.fbits);
         a.fT = (long long *)sched->T;
+        a.fleast = (long long *)(base + lay.fleast);
         a.f_nM = sched->nM;
         for (int q = 0; q < PP_FREE_COUNTS; ++q) a.f_Ms[q] = q < sched->nM ? sched->Ms[q] : 1;
     }

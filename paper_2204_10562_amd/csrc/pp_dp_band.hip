@@ -95,7 +95,7 @@ __global__ __launch_bounds__(64) void k_dp_band(band_args b) {
 // k_dp_band (a bit per candidate that is not).
 // What bounds it: instruction issue (71 vector instructions per stage), then the orderings' bytes.  2^20 candidates of 32
 // stages, one count: 127 us, where the look for the plan (which also wrote 134 MB of bounds) took 215 and the schedules, whose
-// transfer times lie a cache line apart in [link][cut], 388; the whole call 720 -> 269 us.  20 011 of 48 stages 167 -> 142,
+// transfer times lie a cache line apart in [link][cut], 388; the whole call 720 -> 260 us.  20 011 of 48 stages 167 -> 142,
 // 200 003 of 11, two counts 75 -> 59.
 template <int NM>
 __global__ __launch_bounds__(256) void k_band_free(band_args b) {
@@ -194,12 +194,27 @@ __global__ __launch_bounds__(256) void k_band_free(band_args b) {
             a.C_out[c] = C;
 #pragma unroll
             for (int q = 0; q < NM; ++q)
-                if (q < a.f_nM) a.fT[(long long)q * a.N + c] = path.longest(q);
+                if (q < a.f_nM && a.fT) a.fT[(long long)q * a.N + c] = path.longest(q);
         }
         // (rows of neighbours in the wave that begin with the same devices count once, the last row for everyone)
         const bool after = lane && (ended >> (lane - 1) & 1);
         int rows = done ? 1 + band_max(0, S - 1 - (after && differs > 1 ? differs : 1)) : 0;
-        for (int off = 32; off; off >>= 1) rows += __shfl_xor(rows, off);
+        // (and the least time of the group, lowest candidate first; a loop, because what a wave runs once waits for its
+        // instructions: unrolled, 20 011 candidates of 48 stages take 26.2 instead of 25.3 us)
+        int T[NM], least[NM];
+#pragma unroll
+        for (int q = 0; q < NM; ++q) least[q] = T[q] = done ? path.longest(q) : 0x7fffffff;
+#pragma unroll 1
+        for (int off = 32; off; off >>= 1) {
+            rows += __shfl_xor(rows, off);
+#pragma unroll
+            for (int q = 0; q < NM; ++q) least[q] = band_min(least[q], __shfl_xor(least[q], off));
+        }
+#pragma unroll
+        for (int q = 0; q < NM; ++q) {
+            const unsigned long long at = __ballot(T[q] == least[q]) & ended;
+            if (q < a.f_nM && lane == 0) a.fleast[q * groups + g] = at ? (long long)least[q] << 6 | __builtin_ctzll(at) : -1;
+        }
         if (lane == 0) {
             a.fbits[g] = ended;
             if (rows) {

@@ -25,7 +25,7 @@ struct dp_args {
     // k_band_free: where it works (fx NULL: it does not), the T it writes and for which counts
     int2 *fx;                        // [S][D*D] transfer times of every link at the channel-free plan's cuts
     unsigned long long *fbits;
-    long long *fT;
+    long long *fT, *fleast;  // fT: or NULL
     int f_nM, f_Ms[PP_FREE_COUNTS];
     const unsigned long long *left;  // a bit per candidate: k_dp_band has left it (NULL: it has not run)
     size_t lds_bytes;      // dynamic LDS of the launch

@@ -52,6 +52,7 @@ struct mk_args {
     const int *rlist;
     // plans that k_band_free has scheduled (pp_free_plans), or NULL
     const unsigned long long *free_bits;
+    const long long *free_least;
     const int *free_plan;
     pp_rep_result *rout;   // [nM] winner records with replica counts (instead of out)
     // arg-min (all NULL when not wanted)

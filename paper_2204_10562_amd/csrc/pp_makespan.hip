@@ -287,8 +287,9 @@ int pp_launch_makespan(int L, int D, int S, int64_t N, int nM, const int *Ms, co
     a.T_out = (long long *)T_out; a.status = status;
     a.part = (tc_pair *)part; a.C = (const long long *)C; a.out = out;
     a.hdr = hdr;
-    if (done && hdr && T_out) {
+    if (done && hdr && part) {
         a.free_bits = done->bits;
+        a.free_least = done->least;
         a.free_plan = done->plan;
     }
     if (fuse && hdr && !rlist && pp_makespan_can_fuse(L, D, S)) {

@@ -389,7 +389,32 @@ __device__ __forceinline__ void mk_path_body(const mk_args &a) {
     const int S = a.S, L = a.L, D = a.D;
     long long *PT = (long long *)rows;
     int2 *PK = (int2 *)rows;
-    for (int i = tid; i <= L; i += threads) {
+    const bool listed = a.rlist && a.hdr->share_active;
+    const long long todo = listed ? a.hdr->share_nreps : a.N, groups = (todo + 63) / 64;
+    const bool has_free = FREE && mk_has_free(a);
+    const int counts = a.search ? a.search : 1, per = a.search ? 1 : waves;
+    tc_pair least[NM];
+#pragma unroll
+    for (int q = 0; q < NM; ++q) least[q] = {PP_INF64, INT64_MAX};
+    bool idle = FREE && has_free;
+    if (FREE && has_free) {
+        // (of the plans that are scheduled already, a minimum per 64 candidates; where they are all of this workgroup's, it
+        // needs no tables: 2^20 candidates of 32 stages, the T of each read instead and the tables always: 15.0, so 10.6 us)
+        for (long long i = tid; i < groups; i += threads) {
+            const long long g = (i / waves * gridDim.x + blockIdx.x) * waves + i % waves;
+            if (g >= groups) break;
+            idle = idle && a.free_bits[g] == ~0ull >> (todo - g * 64 < 64 ? 64 - (todo - g * 64) : 0);
+        }
+        for (long long g = (long long)blockIdx.x * threads + tid; g < groups; g += (long long)gridDim.x * threads)
+#pragma unroll
+            for (int q = 0; q < NM; ++q) {
+                const int slot = (int)blockIdx.y * NM + q;
+                const long long v = slot < a.nM ? a.free_least[slot * groups + g] : -1;
+                if (v >= 0) least[q] = tc_min(least[q], {v >> 6, g * 64 + (v & 63)});
+            }
+        idle = __syncthreads_and(idle);
+    }
+    for (int i = idle ? L + 1 : tid; i <= L; i += threads) {
         const long long f = a.PF[i], b = a.PB[i];
         if (KNOWN) {
             PK[i] = make_int2((int)f, (int)b);
@@ -403,30 +428,15 @@ __device__ __forceinline__ void mk_path_body(const mk_args &a) {
     mk_counts<NM>(a, M);
 #pragma unroll
     for (int q = 0; q < NM; ++q) mmax = M[q] > mmax ? M[q] : mmax;
-    const bool listed = a.rlist && a.hdr->share_active;
-    const long long todo = listed ? a.hdr->share_nreps : a.N, groups = (todo + 63) / 64;
-    const bool has_free = FREE && mk_has_free(a);
-    const int counts = a.search ? a.search : 1, per = a.search ? 1 : waves;
-    tc_pair least[NM];
-#pragma unroll
-    for (int q = 0; q < NM; ++q) least[q] = {PP_INF64, INT64_MAX};
     __syncthreads();
-    for (long long g = (long long)blockIdx.x * per + (a.search ? 0 : wave); g < groups; g += (long long)gridDim.x * per) {
+    for (long long g = idle ? groups : (long long)blockIdx.x * per + (a.search ? 0 : wave); g < groups; g += (long long)gridDim.x * per) {
         const long long at = g * 64 + lane;
         const bool live = at < todo;
         const long long c = !live ? 0 : listed ? pp_share_at(a.hdr, a.rlist, a.N, at) : at;
         const int held = (int)(todo - g * 64 < 64 ? todo - g * 64 : 64);  // plans of this group
-        // (those that are scheduled already: their T is read)
         const unsigned long long ended = FREE && has_free ? a.free_bits[g] : 0;
         const bool done = FREE && (ended >> lane & 1);
-        if (FREE && ended && !__ballot(live && !done)) {
-#pragma unroll
-            for (int q = 0; q < NM; ++q) {
-                const int slot = (int)blockIdx.y * NM + q;
-                if (slot < a.nM && live) least[q] = tc_min(least[q], {a.T_out[(long long)slot * a.N + c], c});
-            }
-            continue;
-        }
+        if (FREE && ended && !__ballot(live && !done)) continue;
         // (every other round of stage counts backwards: the waves' shares are alike)
         for (int turn = 0; turn * waves < counts || !a.search; ++turn) {
             const int k = turn * waves + (turn & 1 ? waves - 1 - wave : wave);
@@ -502,11 +512,7 @@ __device__ __forceinline__ void mk_path_body(const mk_args &a) {
 #pragma unroll
             for (int q = 0; q < NM; ++q) {
                 const int slot = (int)blockIdx.y * NM + q;
-                if (slot >= a.nM || !live) continue;
-                if (FREE && done) {
-                    least[q] = tc_min(least[q], {a.T_out[(long long)slot * a.N + c], c});
-                    continue;
-                }
+                if (slot >= a.nM || !live || (FREE && done)) continue;
                 // (what the 32-bit sums took has no time that long)
                 const int fault = p.fault ? p.fault : p.worst ? overflow_fault(p.worst, M[q], xi) : 0;
                 if (fault) { T[q] = PP_INF64; pp_raise(a.status, fault); }
