@@ -624,8 +624,9 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
     }
 }
 
-template <int LANES, bool TEAM>
-__global__ __launch_bounds__(256, 3) void k_prm_band(prm_args a) {
+// FOUR: four workgroups per compute unit at the price of spills, see prm_band_launch.
+template <int LANES, bool TEAM, bool FOUR = false>
+__global__ __launch_bounds__(256, FOUR ? 4 : 3) void k_prm_band(prm_args a) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int parts = a.band[PRM_BAND_PARTS];
     if (!parts || a.band[PRM_BAND_LANES] != LANES) return;
@@ -685,7 +686,13 @@ static void prm_band_launch(const prm_args &a, hipStream_t st) {
     const bool team = sets < 1536;
     sets = sets < room ? sets : room;
     sets = sets < 8192 ? sets : 8192;
-    if (team)
+    // (165 registers: three teams of four waves at once on each of the 256 compute units.  Where that leaves a second round for
+    // the last few and LDS has room for a fourth, the kernel in 128: 7428 orderings of 6 GPUs, 32 layers 103.5 -> 87.6 us;
+    // elsewhere its spills cost 1 to 5 %: 5500 of 8 110 -> 115, 9000 of 5, two rounds either way, 90 -> 93.)
+    const bool four = team && LANES == 8 && wpb == 4 && sets > 3 * 256 && sets <= 4 * 256 && 4 * lds <= 160 * 1024;
+    if (four)
+        hipLaunchKernelGGL((k_prm_band<LANES, true, LANES == 8>), dim3((unsigned)sets), dim3(64 * wpb), lds, st, a);
+    else if (team)
         hipLaunchKernelGGL((k_prm_band<LANES, true>), dim3((unsigned)sets), dim3(64 * wpb), lds, st, a);
     else
         hipLaunchKernelGGL((k_prm_band<LANES, false>), dim3((unsigned)((sets + wpb - 1) / wpb)), dim3(64 * wpb), lds, st, a);
