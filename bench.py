@@ -10,8 +10,10 @@ the arg-min.  Inputs are resident in HBM before the timed region.  Prints ONE JS
 on stdout; details go to stderr.
 
 Objects of the line beside the contract's fields:
-  roofline          the kernel that dominates the step (the makespan launch over all
-                    microbatch counts), timed alone through pp_schedule_makespan_multi
+  roofline          the schedules over all microbatch counts, timed alone through
+                    pp_schedule_makespan_multi (inside the step the kernel that dominates it builds
+                    the plans as well); a closed form, so the rate is that of issued instructions and
+                    "nominal" that of the recurrence's block updates it stands for
   roofline_dp       the general partition-DP kernel, timed on the same shape with activation
                     sizes that differ per boundary (on the GPT workload itself the transfer
                     times do not depend on the cut position and the DP runs in closed form:
@@ -35,7 +37,7 @@ sys.path.insert(0, ROOT)
 # published MI355X figures: 256 compute units x 4 SIMDs x 16 lanes at 2.4 GHz, one 32-bit
 # integer operation per lane per clock
 ALU_PEAK_OPS = 256 * 4 * 16 * 2.4e9
-OPS_PER_BLOCK_OP = 2  # max, add per (block, microbatch) update of the schedule
+OPS_PER_BLOCK_OP = 2  # max, add per (block, microbatch) update of the schedule's recurrence (nominal: T is found in closed form)
 
 
 def log(*a):
@@ -191,10 +193,9 @@ def main():
         log("     %d link classes: %d of the %d candidates computed, the others share their results"
             % (stats["share_classes"], stats["share_computed"], N))
     for M in Ms:
-        log("  pp_schedule_makespan M=%-3d %7.1f us   %.3e block-ops/s" % (M, t_mk[M]["mean"] * 1e6, N * M * (4 * S - 3) / t_mk[M]["mean"]))
-    log("  pp_schedule_makespan_multi %6.1f us (median %.1f, min %.1f)   %.3e block-ops/s = %.1f%% of int32 VALU peak at %d ops/block-op"
-        % (t_mkm["mean"] * 1e6, t_mkm["median"] * 1e6, t_mkm["min"] * 1e6, block_ops / t_mkm["mean"],
-           100 * OPS_PER_BLOCK_OP * block_ops / t_mkm["mean"] / ALU_PEAK_OPS, OPS_PER_BLOCK_OP))
+        log("  pp_schedule_makespan M=%-3d %7.1f us   %.3e nominal block-ops/s" % (M, t_mk[M]["mean"] * 1e6, N * M * (4 * S - 3) / t_mk[M]["mean"]))
+    log("  pp_schedule_makespan_multi %6.1f us (median %.1f, min %.1f)   %.3e nominal block-ops/s"
+        % (t_mkm["mean"] * 1e6, t_mkm["median"] * 1e6, t_mkm["min"] * 1e6, block_ops / t_mkm["mean"]))
     for M in Ms:
         log("  pp_best_plan M=%-3d      %9.1f us   %.3e plans/s" % (M, t_best[M]["mean"] * 1e6, N / t_best[M]["mean"]))
     log("  pp_best_plan_multi     %9.1f us   %.3e plans/s" % (t_multi["mean"] * 1e6, N * len(Ms) / t_multi["mean"]))
@@ -366,7 +367,9 @@ def main():
                                 "sample": "first %d candidates, all %d microbatch counts, %.1f s wall" % (n_one, len(Ms), one_wall)}
         log("  oracle on 1 host thread: %.3e plans/s (%s)" % (cpu["single_thread"]["value"], cpu["single_thread"]["sample"]))
 
-    achieved = OPS_PER_BLOCK_OP * block_ops / t_mkm["mean"]
+    # vector instructions issued (counter run, the GPT workload) against one per lane and clock
+    mk_insts = figures.get("makespan.valu_insts_per_launch") if w.name == "gpt" else None
+    achieved = None if mk_insts is None else mk_insts * 64 / t_mkm["mean"]
     line = {
         "metric": "candidate plans evaluated/sec (partition DP + makespan + argmin), L=%d, D=%d" % (L, D),
         "value": plans_per_s, "unit": "plans/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
@@ -387,12 +390,14 @@ def main():
                    "GB_per_s": prefix_bytes / t_prefix["mean"] / 1e9, "hbm_peak_GB_per_s": 8000},
         "makespan": {"per_M": [{"M": M, "us": t_mk[M]["mean"] * 1e6, "block_ops_per_s": N * M * (4 * S - 3) / t_mk[M]["mean"]} for M in Ms],
                      "all_M_one_launch_block_ops_per_s": block_ops / t_mkm["mean"]},
-        "roofline": {"bound": "alu", "kernel": ("pp_schedule_makespan_multi (the makespan launch of the step: all %d microbatch counts)" % len(Ms)
-                                               if not (L > 128 and stats["share_active"]) else
-                                               "pp_schedule_makespan_multi over all %d candidates, stand-alone (inside the step only the "
-                                               "%d representatives are scheduled)" % (N, stats["share_computed"])),
-                     "achieved": achieved / 1e12, "peak": ALU_PEAK_OPS / 1e12, "unit": "TOP/s (32-bit integer lane-ops)",
-                     "frac": achieved / ALU_PEAK_OPS, "traffic": figures.get("makespan.traffic_bytes_per_launch"),
+        "roofline": {"bound": "alu", "kernel": "pp_schedule_makespan_multi (k_makespan_split, all %d microbatch counts of all %d candidates%s)"
+                                               % (len(Ms), N, "; inside the step only the %d representatives are scheduled" % stats["share_computed"]
+                                                  if L > 128 and stats["share_active"] else ""),
+                     "achieved": None if achieved is None else achieved / 1e12, "peak": ALU_PEAK_OPS / 1e12,
+                     "unit": "TOP/s (32-bit integer lane-ops issued)", "frac": None if achieved is None else achieved / ALU_PEAK_OPS,
+                     "valu_busy_frac": figures.get("makespan.valu_busy_frac") if w.name == "gpt" else None,
+                     "traffic": figures.get("makespan.traffic_bytes_per_launch") if w.name == "gpt" else None,
+                     "nominal": OPS_PER_BLOCK_OP * block_ops / t_mkm["mean"] / 1e12,
                      "launch": us(t_mkm), "launch_us": t_mkm["mean"] * 1e6, "block_ops_per_launch": block_ops,
                      "ops_per_block_op": OPS_PER_BLOCK_OP,
                      "peak_measured": None if calibration is None else calibration["waves_per_simd_2"]},
