@@ -144,8 +144,9 @@ __device__ __forceinline__ void mk_stage(mk_path<V, NM> &path, int n, int xi, V 
 }
 template <int MODE, int NM, typename V>
 __device__ __forceinline__ V mk_result(const mk_path<V, NM> &path, int q, int M) {
-    // (GPipe's order: two flow shops of M equal jobs, one after the other)
-    if (MODE == PP_SCHED_GPIPE) return mk_sum(path.sum, mk_times(mk_sum(path.A, path.B), M - 1));
+    // (GPipe's order: two flow shops of M equal jobs, one after the other.  A and B, of different resources maybe, fit 24 bits
+    // each and their sum may not.)
+    if (MODE == PP_SCHED_GPIPE) return mk_sum(path.sum, mk_sum(mk_times(path.A, M - 1), mk_times(path.B, M - 1)));
     return path.longest(q);
 }
 template <int MODE, int NM>

@@ -100,3 +100,25 @@ def test_variants_faults(ppo, G):
     b = torch.from_numpy(bounds.reshape(-1)).to(g.dev)
     with pytest.raises(pp.PPError):
         pp.pp_schedule_makespan_variant(9, 20, 5, 4, 32, 3, g.PF, g.PB, g.XF, g.XB, g.orderings, b, T, g.status)
+
+
+@pytest.mark.parametrize("S,M", [(2, 2), (2, 12), (3, 5), (4, 8), (6, 3), (6, 200)])
+def test_variants_next_to_the_limit_of_32_bits(ppo, G, S, M):
+    # the largest forward and the largest backward time on different stages, both next to what 24-bit products take
+    L, N = S + 3, 70
+    rng = np.random.Generator(np.random.PCG64(S + M))
+    bounds = random_bounds(rng, N, S, L)
+    for variant in (0, 1, 2, 3, 4):
+        limit = (2**30 - 1) // ((2 * M + 8 * S if variant == 2 else M + 4 * S) + 64)
+        for time in (limit // 2, limit, limit + 1):
+            w = workloads.random_small(S, L, S, S, N, hi_time=7, hi_act=500)
+            w.fwd[:], w.bwd[:] = 0, 0
+            w.fwd[0] = w.bwd[-1] = time
+            tables = oracle_tables(ppo, w)
+            g = G(w)
+            g.set_tables(*tables)
+            say("variant limit", variant, S, M, time)
+            st, T = g.makespan_variant(variant, M, bounds)
+            rc, T0 = ppo.schedule_makespan_variant(variant, L, S, S, N, M, *tables, w.orderings, bounds)
+            assert st == 0 and rc == 0
+            np.testing.assert_array_equal(T, T0)

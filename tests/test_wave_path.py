@@ -37,6 +37,23 @@ def test_against_the_schedule(exe, variant, counts):
         assert got == [0, 0, 0, 0], line
 
 
+# times next to the largest that 32-bit sums and 24-bit products take (2^30 over M + 4 S + 64, twice M and 4 S more in
+# GPipe's order), where the largest forward and the largest backward time lie on different resources
+@pytest.mark.parametrize("variant,counts", [(PE, "1"), (PE, "3 40"), (PE, "2 5 9 70"), (DUPLEX, "2"), (DUPLEX, "31"), (GPIPE, "1"), (GPIPE, "2"),
+                                            (GPIPE, "3"), (GPIPE, "5"), (GPIPE, "8"), (GPIPE, "12"), (GPIPE, "33"), (ADDITIVE, "2"),
+                                            (ADDITIVE, "25")])
+def test_times_next_to_the_limit(exe, variant, counts):
+    Ms = [int(m) for m in counts.split()]
+    lines = []
+    for S, N in ((1, 2), (2, 20), (3, 40), (4, 64), (6, 65), (9, 20), (20, 10)):
+        n = max(Ms) * (2 if variant == GPIPE else 1) + 4 * S * (2 if variant == GPIPE else 1) + 64
+        limit = (2**30 - 1) // n
+        lines += ["%d %d %d %d -1 %d 0 %d %s" % (variant, S, N, seed, hi, len(Ms), counts)
+                  for seed in range(1, 6) for hi in (limit // 2, limit - 1, limit, limit + 1)]
+    for line, got in zip(lines, ask(exe, lines)):
+        assert got == [0, 0, 0, 0], line
+
+
 @pytest.mark.parametrize("S,N", [(1, 70), (2, 5), (7, 66), (8, 64), (9, 20), (17, 3)])
 def test_every_stage_count(exe, S, N):
     lines = ["%d %d %d %d 0 %d 1 3 2 17 70" % (PE, S, N, S, hi) for hi in (1, 10**5, 2**45)]

@@ -2,7 +2,9 @@
 // case per line:
 //   VARIANT S N SEED LO HI SEARCH NM M...   N random plans of S stages (SEARCH: of every stage count up to S)
 //                                           with times from LO to HI, under NM microbatch counts, against Alg. 1's rules
-//                                           written out in 64 bits, and the minimum over the plans
+//                                           written out in 64 bits, and the minimum over the plans; LO < 0: nothing takes
+//                                           any time but two layers, one of them forward and the other backward, and the transfers over
+//                                           one cut each way, all of which take HI
 // and prints the return value, the status word, how many T differ and how many minima.
 #define main makespan_main
 #include "makespan_driver.cpp"
@@ -12,7 +14,14 @@ int main() {
     int variant, S, N, seed, search, nM;
     ll lo, hi;
     while (scanf("%d %d %d %d %lld %lld %d %d", &variant, &S, &N, &seed, &lo, &hi, &search, &nM) == 8) {
-        problem p(variant, S, N, 1, seed, lo, hi);
+        problem p(variant, S, N, 1, seed, lo < 0 ? 0 : lo, lo < 0 ? 0 : hi);
+        if (lo < 0) {
+            std::mt19937_64 g(seed + 2);
+            const int f = g() % p.L, b = g() % p.L, cf = g() % p.L, cb = g() % p.L;
+            for (int l = f + 1; l <= p.L; ++l) p.PF[l] = hi;
+            for (int l = b + 1; l <= p.L; ++l) p.PB[l] = hi;
+            for (int x = 0; x < p.D * p.D; ++x) p.XF[(size_t)x * p.L + cf] = p.XB[(size_t)x * p.L + cb] = hi;
+        }
         const int tri = search ? S * (S + 1) / 2 : S, xs = search ? S : 1;
         for (int q = 0; q < nM; ++q) if (scanf("%d", &p.a.Ms[q]) != 1) return 2;
         std::vector<int> e;
