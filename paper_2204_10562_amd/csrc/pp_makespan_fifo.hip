@@ -120,7 +120,9 @@ __global__ __launch_bounds__(FIFO_THREADS) void k_makespan_fifo(mk_args a) {
     const bool taken = __syncthreads_and(!ok || (!odd && sum <= (long long)PP_TIME_CAP / M));
     // (a sweep more than there are serves nothing, nor does a channel behind the last stage hand anything on)
     const bool first = q == 0, reaches = q + 1 < LG;
-    for (int t = 0; taken && t < M + J - 1; t += 2) {
+    // (a wave without a plan has nothing to sweep; one that has one has items of positive length, so M is below 2^30)
+    const int sweeps = taken && __ballot(ok) ? M + J - 1 : 0;
+    for (int t = 0; t < sweeps; t += 2) {
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
             // the stage's forward item, which the channel before has let go in the last sweep

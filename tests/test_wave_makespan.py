@@ -86,3 +86,18 @@ def test_readiness_order_leaves_whole_workgroups(driver, S):
     for rc, status, left, differ, parts in out:
         assert (rc, status, differ, parts) == (0, 0, 0, 0)
     assert 0 < out[0][2] and out[2][2] < 300
+
+
+@pytest.mark.parametrize("S", [2, 4, 9, 32])
+def test_readiness_order_without_a_good_plan_does_no_sweep(driver, S):
+    # every plan of a workgroup is bad, or there are few: nothing runs, whatever M is
+    lines = ["faulty %d %d %d %d %d" % (FIFO, S, M, N, N) for M in (200000, 2**30, 2**31 - 1) for N in (1, 3, 700)]
+    out, errors = driver(lines, timeout=20)
+    for line, got in zip(lines, out):
+        assert got == [0, 4, 0, 0], line
+    # bad plans among good ones change nothing for these
+    lines = ["faulty %d %d 7 %d %d" % (FIFO, S, N, bad) for N, bad in ((2, 1), (70, 69), (300, 2), (300, 290))]
+    out, more = driver(lines)
+    for line, got in zip(lines, out):
+        assert got == [0, 4, 0, 0], line
+    assert "runtime error" not in errors + more, (errors + more)[-2000:]

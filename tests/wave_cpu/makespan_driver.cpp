@@ -5,6 +5,8 @@
 //   mixed VARIANT S M SEED HI   the same with 300 plans of times from 0 up: how many were left, how many of
 //                               the others differ, and workgroups of the readiness order left in part
 //   taken VARIANT S M TIME      how many of 64 plans whose times are all TIME the 30-bit kernel takes
+//   faulty VARIANT S M N BAD    N plans of which the first BAD have a bad ordering: how many of these have a time, and
+//                               how many of the others (a second's work if M is large) have another one than they should
 //   launch VARIANT S N          the launches for N candidates (nothing runs): the return value, and how
 //                               many candidates they have lanes for
 // and prints one line per case.
@@ -172,6 +174,17 @@ int main() {
             int taken = 0;
             for (int c = 0; c < p.N; ++c) taken += p.T[c] != MK_NOT_TAKEN;
             printf("%d %d\n", rc, taken);
+        } else if (!strcmp(what, "faulty")) {
+            int N, bad;
+            if (scanf("%d %d", &N, &bad) != 2) return 2;
+            problem p(variant, S, N, (int)M, 5, 1, 9);
+            for (int c = 0; c < bad; ++c) p.o[(size_t)c * S + S - 1] = c & 1 ? -1 : S;
+            const int rc = p.launch();
+            int timed = 0, differ = 0;
+            for (int c = 0; c < N; ++c)
+                if (c < bad) timed += p.T[c] != PP_INF64;
+                else differ += p.T[c] != MK_NOT_TAKEN && p.T[c] != p.want(c, (int)M);
+            printf("%d %d %d %d\n", rc, p.status, timed, differ);
         } else {
             problem p(variant, S, 1, 8, 1, 1, 1);
             p.a.N = M;
