@@ -449,6 +449,7 @@ __device__ __forceinline__ void mk_path_body(const mk_args &a) {
             // the group's rows, entry by entry: as many loads in flight as there are stages, up to 8
             const int di = 64 / xi, dn = 64 - di * xi;
             int i = lane / xi, n = lane - i * xi;
+            bool odd = false;  // a bound that is none (not of plans that are scheduled already, which have none in memory)
             __builtin_amdgcn_wave_barrier();
             for (int t0 = 0; t0 < xi; t0 += 8) {
                 int o[8], e[8], to[8];
@@ -457,16 +458,18 @@ __device__ __forceinline__ void mk_path_body(const mk_args &a) {
                     const long long ci = listed ? (long long)__shfl((int)c, i & 63) : g * 64 + i;
                     to[u] = t0 + u < xi && i < held ? i * SP + n : -1;
                     o[u] = to[u] >= 0 && a.orderings ? a.orderings[ci * a.ord_stride + n] : 0;
-                    e[u] = to[u] >= 0 ? a.bounds[ci * a.bnd_stride + bnd_off + n] : 0;
+                    e[u] = to[u] < 0 ? 0 : FREE && (ended >> (i & 63) & 1) ? L : a.bounds[ci * a.bnd_stride + bnd_off + n];
                     n += dn;
                     i += di;
                     if (n >= xi) { n -= xi; ++i; }
                 }
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
-                    if (to[u] >= 0)
-                        mine[to[u]] = (o[u] >= 0 && o[u] < D ? o[u] : 0xffff) |
-                                      (int)((unsigned)(e[u] >= 1 && e[u] <= L ? e[u] : 0xffff) << 16);
+                    if (to[u] >= 0) {
+                        const bool in = e[u] >= 1 && e[u] <= L;
+                        odd |= !in;
+                        mine[to[u]] = (o[u] >= 0 && o[u] < D ? o[u] : 0xffff) | (int)((unsigned)(in ? e[u] : 0xffff) << 16);
+                    }
             }
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             __builtin_amdgcn_wave_barrier();
@@ -491,15 +494,18 @@ __device__ __forceinline__ void mk_path_body(const mk_args &a) {
             long long T[NM];
             mk_plan_info p = {};
             if (KNOWN) {
+                // (the rows of a wave are looked at only where one of its orderings is bad, or a bound is none: then C is not
+                // what it should be, and the plan reads nothing)
                 const bool bad = C == PP_INF64 && !done;
-                mk_plan_known<NM>(a, row, PK, xi, live && !bad && !done, M, T);
-                p.fits = !live || bad || done || C <= limit;
-                if (__ballot(bad)) {
+                if (__ballot(bad || odd)) {
                     mk_row_check check;
                     check.start();
                     for (int n = 0; n < xi; ++n) check.stage(a, row, n, row[n]);
-                    p.fault = check.fault(a, live && bad);
+                    p.fault = check.fault(a, live && !done);
                 }
+                const bool good = live && !bad && !done && !p.fault;
+                mk_plan_known<NM>(a, row, PK, xi, good, M, T);
+                p.fits = !live || done || p.fault || C <= limit;
             } else {
                 p = mk_plan32<MODE, NM>(a, row, PT, xi, live, M, limit, T);
             }
