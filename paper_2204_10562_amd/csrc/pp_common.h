@@ -80,8 +80,8 @@ __device__ __forceinline__ void pp_count_work(pp_ws_header *hdr, unsigned long l
 struct pp_ws_layout {
     size_t hdr, p32, x32, xkt, xct, bfl, ord, arg, bounds, C, T, part, total;
     size_t band;  // the table of the bands (pp_dp_band.h), behind the backtrack tables; 0: not wanted
-    // k_band_free: transfer times at the channel-free plan's cuts, a bit per candidate, and a minimum per 64 candidates and
-    // microbatch count (0: not carved)
+    // k_band_free: the links' words and, behind them, their transfer times at the channel-free plan's cuts; a bit per candidate;
+    // a minimum per 64 candidates and microbatch count.  All in places that are needed later, or no longer (0: no room).
     size_t fx, fbits, fleast;
     // candidates that share a DP (0 = not carved: see pp_share_possible)
     size_t sh_hash, sh_rep, sh_table, sh_keys, sh_reps, sh_cnt, sh_start, sh_rows;
@@ -146,12 +146,6 @@ static inline pp_ws_layout pp_layout(int L, int D, int S, int64_t N) {
     w.C = off;      off += pp_align256((size_t)N * 8);
     w.T = off;      off += pp_align256((size_t)N * 8);
     w.part = off;   off += pp_align256((size_t)((N + 63) / 64 < PP_PARTS ? (N + 63) / 64 : PP_PARTS) * 16 * PP_MAX_M_LIST);
-    w.fx = w.fbits = w.fleast = 0;
-    if (w.band && D <= 64) {
-        w.fx = off;    off += pp_align256((size_t)D * D * S * 8);
-        w.fbits = off; off += pp_align256((size_t)((N + 63) / 64) * 8);
-        w.fleast = off; off += pp_align256((size_t)((N + 63) / 64) * 8 * PP_FREE_COUNTS);
-    }
     w.sh_hash = w.sh_rep = w.sh_table = w.sh_keys = w.sh_reps = w.sh_cnt = w.sh_start = w.sh_rows = 0;
     w.sh_row_slots = 0;
     if (pp_share_possible(L, D, N)) {
@@ -170,6 +164,17 @@ static inline pp_ws_layout pp_layout(int L, int D, int S, int64_t N) {
         if (nr > (size_t)w.slots * (S > 1 ? S - 1 : 1)) nr = (size_t)w.slots * (S > 1 ? S - 1 : 1);
         w.sh_row_slots = (long long)nr;
         w.sh_rows = off;  off += pp_align256(nr * row);
+    }
+    // The bits and minima lie in the upper part of T's place, whose lower half holds the list or the bits of the candidates
+    // that are left (4 N + 7 + 40 (N / 64 + 1) <= 8 N); the links' times are not needed any more when the DP kernels begin, and lie in
+    // what these then fill: the saved rows (64 waves' and more, S - 1 of 1040 bytes and more each, hold 8 S bytes per
+    // link of up to 64 devices), or the backtrack tables (from 253 candidates on always).
+    w.fx = w.fbits = w.fleast = 0;
+    const size_t free_room = w.sh_rows ? off - w.sh_rows : (size_t)w.slots * S * (L + 63) * 2;
+    if (w.band && D <= 64 && free_room >= (size_t)D * D * S * 8) {
+        w.fx = w.sh_rows ? w.sh_rows : w.arg;
+        w.fbits = w.T + (((size_t)N * 4 + 7) & ~(size_t)7);
+        w.fleast = w.fbits + (size_t)((N + 63) / 64) * 8;
     }
     w.total = off;
     return w;

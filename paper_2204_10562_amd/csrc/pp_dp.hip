@@ -359,7 +359,7 @@ static int band_use(int L, int D, int S, int64_t N, int stages, bool lex, const 
         band_table_lds(L, S, stages, waves);
         return !stages || band_whole_us(L, D, S, N, lex, lay) >= (double)S * S / waves ? BAND_USE_INSIDE : BAND_USE_NOT;
     }
-    const bool room = (size_t)band_link_words(D, S, stages) * 8 + (size_t)N / 8 + 8 <= (size_t)N * 8;  // (T's place)
+    const bool room = (size_t)band_link_words(D, S, stages) * 8 + (size_t)N / 8 + 8 <= (size_t)N * 8;  // (in T's place)
     const bool inside = pp_dp_tiles(L, D, S, N, lay) <= DPT_INSIDE_NT && band_link_bytes(D, S, stages) != 0;
     if (room && band_cells(L, D, S, N, stages, lex, lay)) return BAND_USE_ALONE;
     if (inside) return work >= 3e6 ? BAND_USE_INSIDE : BAND_USE_NOT;
@@ -520,9 +520,12 @@ int pp_launch_dp(int L, int D, int S, int64_t N, const int64_t *PF, const int64_
     };
     const int nt = pp_dp_tiles(L, D, S, N, lay);
     if (use == BAND_USE_ALONE) {
-        unsigned long long *words = (unsigned long long *)(base + lay.T);  // (T is written once the plans are there)
-        a.left = words + band_link_words(D, S, stages);
-        const int rc = pp_launch_dp_band_alone(a, words, words + band_link_words(D, S, stages), st);
+        // (in T's place; with the links' times, where these are)
+        unsigned long long *left = (unsigned long long *)(base + lay.T), *words = left;
+        if (a.fx) words = (unsigned long long *)a.fx;
+        else left += band_link_words(D, S, stages);
+        a.left = left;
+        const int rc = pp_launch_dp_band_alone(a, words, left, st);
         if (rc) return rc;
     }
     if (lay.nt && !nt) {

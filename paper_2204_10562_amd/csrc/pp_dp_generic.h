@@ -23,7 +23,7 @@ struct dp_args {
     const int *band;       // the table of pp_dp_band.h, or NULL
     long long band_all;    // the fewest candidates for which the recursion over the bands is worth it (pp_dp.hip)
     // k_band_free: where it works (fx NULL: it does not), the T it writes and for which counts
-    int2 *fx;                        // [S][D*D] transfer times of every link at the channel-free plan's cuts
+    int2 *fx;                        // [S][D*D] transfer times of every link at the channel-free plan's cuts (row 0: the links' words)
     unsigned long long *fbits;
     long long *fT, *fleast;  // fT: or NULL
     int f_nM, f_Ms[PP_FREE_COUNTS];

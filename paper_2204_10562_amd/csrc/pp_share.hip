@@ -481,7 +481,7 @@ static share_args share_base(void *ws, const pp_ws_layout &lay) {
     a.reps = (int *)(base + lay.sh_reps);
     a.cnt = (int *)(base + lay.sh_cnt);
     a.start = (int *)(base + lay.sh_start);
-    a.pend = (int *)(base + lay.T);  // (T is written once the plans are there)
+    a.pend = (int *)(base + lay.T);
     return a;
 }
 
@@ -505,7 +505,7 @@ int pp_launch_share_prepare(const dp_args &g, int run_waves, void *ws, const pp_
     a.band = g.band;
     a.sort = N >= 64;  // (no wave of the DP kernel has two candidates of a shorter list)
     // (the saved rows of 64 waves and more, S - 1 of 1040 bytes and more each, hold 8 (S - 1) bytes per link of up
-    // to 64 devices, and are needed later)
+    // to 64 devices, and are needed later; with g.fx the links' times lie behind the words)
     a.links = (unsigned long long *)((char *)ws + lay.sh_rows);
     const int link_blocks = (D * D + 3) / 4;
     hipLaunchKernelGGL(k_share_hash, dim3(link_blocks + SHARE_FILL_BLOCKS), dim3(256), 0, st, a);

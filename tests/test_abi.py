@@ -51,6 +51,35 @@ def test_workspace_bytes_host_function(libpp):
     assert binding.pp_workspace_bytes(4, 8, 5, 1) == 0   # S > L
 
 
+def areas(L, D, S, N):
+    """The workspace's areas: the header, the tables, a list of orderings, the backtrack tables, per candidate bounds, C and one
+    more number, 16 partial minima of 16 bytes per 64 candidates, and for L > 128 what candidates that share a DP need."""
+    up = lambda n: (n + 255) // 256 * 256  # noqa: E731
+    nt, slots = ((L + 7) // 8 if L <= 128 else 0), min(N, 4096)
+    total = 1024 + 64 * 128 + up(4 * (L + 17)) + up(4 * D * D * L) + up(32 * D * D * nt) + up(64 * D * D * ((nt + 1) // 2))
+    total += up(12 * S * (L + 1)) + up(4 * N * S) + up(2 * slots * S * (L + 128)) + up(4 * N * S) + 2 * up(8 * N)
+    total += up((N + 63) // 64 * 256)
+    if L > 128 and D <= 64:
+        row = 4 * (128 * ((L + 127) // 128) + 4)
+        rows = min(2048 * max(1, S - 1), (64 << 20) // row, slots * max(1, S - 1))
+        total += up(8 * D * D) + up(4 * D * D) + (4 << 20) + 2 * up(4 * N) + (16 << 10) + up(4 * 4098) + up(rows * row)
+    return total
+
+
+def test_workspace_holds_nothing_beyond_its_areas(libpp):
+    from paper_2204_10562_amd import binding
+    for L, D, S, N in [(88, 64, 16, 5000), (88, 64, 64, 1000)]:
+        # (pp_best_plan_static takes these)
+        assert binding.pp_workspace_bytes(L, D, S, N) <= binding.PP_STATIC_WORKSPACE_BYTES
+    for L in (1, 2, 16, 88, 97, 128, 129, 150, 400, 1024):
+        for D in (1, 2, 5, 8, 16, 33, 48, 64, 65, 100):
+            for S in sorted({1, 2, min(8, D, L), min(64, D, L)}):
+                if S > D or S > L:
+                    continue
+                for N in (1, 63, 64, 65, 300, 5000, 131072, 200003, 1 << 20):
+                    assert 0 < binding.pp_workspace_bytes(L, D, S, N) <= areas(L, D, S, N), (L, D, S, N)
+
+
 def test_strerror(libpp):
     assert libpp.pp_strerror(0) == b"ok"
     for code in (-1, -2, -3):

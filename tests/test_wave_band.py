@@ -88,3 +88,12 @@ def test_short_lists(driver, kind):
             assert done == reported == 0, case
         ended += done
     assert ended > 0 or kind in (SOME, HIGH)
+
+
+def test_places_of_the_channel_free_plans(driver):
+    cases = [(L, D, S, N) for L in (2, 16, 88, 128, 129, 131, 400, 1025) for D in (2, 3, 8, 33, 47, 63, 64)
+             for S in sorted({2, min(3, D, L), min(D, L, 64)}) for N in list(range(64, 200)) + [252, 253, 999, 4095, 4097, 200003, 1 << 20]
+             if S <= min(L, D)]
+    for (L, D, S, N), (room, clash) in zip(cases, driver(cases, "layout")):
+        # (a list of 64 or more; L <= 128: what the bands' own launches are made for has a thousand candidates)
+        assert not clash and (room or (L <= 128 and N < 253)), (L, D, S, N)

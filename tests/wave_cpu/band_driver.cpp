@@ -6,7 +6,8 @@
 // candidates that ended differ from the recursion over all splits, how many ended, and how many candidates with a
 // bad ordering were reported; with an argument also the work counters: pairs, rows, and those of them in bands and
 // of the channel-free program.  The list counts as one that is long enough for the recursion, with the argument
-// "short" as one that is not.
+// "short" as one that is not.  With the argument "layout" the cases are L D S N, and what is printed is whether
+// there is room for what k_band_free leaves, and whether a part of it lies where something else is at that time.
 #include "../../paper_2204_10562_amd/csrc/pp_dp_band_table.h"
 #include "../../paper_2204_10562_amd/csrc/pp_dp_band.hip"
 
@@ -25,6 +26,18 @@ typedef long long ll;
 int main(int argc, char **argv) {
     const bool shorter = argc > 1 && !strcmp(argv[1], "short");
     int L, D, S, N, seed, kind, stages, words;
+    if (argc > 1 && !strcmp(argv[1], "layout")) {
+        while (scanf("%d %d %d %d", &L, &D, &S, &N) == 4) {
+            const pp_ws_layout w = pp_layout(L, D, S, N);
+            const size_t groups = (N + 63) / 64, lower = w.sh_rows ? (size_t)N * 4 : groups * 8;  // the list, or the bits
+            const size_t times = w.fx + (size_t)D * D * S * 8;
+            bool clash = w.fbits < w.T + lower || w.fleast < w.fbits + groups * 8 || w.fleast + groups * 8 * PP_FREE_COUNTS > w.part;
+            clash |= w.sh_rows ? w.fx != w.sh_rows || times > w.total : w.fx != w.arg || times > w.band;
+            clash |= (w.fx | w.fbits | w.fleast) & 7;
+            printf("%d %d\n", w.fx != 0, w.fx && clash);
+        }
+        return 0;
+    }
     while (scanf("%d %d %d %d %d %d %d %d", &L, &D, &S, &N, &seed, &kind, &stages, &words) == 8) {
         std::mt19937_64 g(seed);
         auto upto = [&](ll n) { return (ll)(g() % (unsigned long long)(n + 1)); };
