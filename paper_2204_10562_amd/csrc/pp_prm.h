@@ -52,28 +52,26 @@ __device__ __forceinline__ int prm_floor_div(double a, double den, double inv, i
 // The bands (pp_prm_band.hip): ints of the header, then [D][L+1] pairs.
 #define PRM_BAND_PARTS 0  // nonzero: every candidate is planned from bands of up to so many times a candidate's lanes,
 #define PRM_BAND_LANES 1  // of which there are 8 or 16
-#define PRM_BAND_LO 16    // [i] first cell of the states on i GPUs, and cells, in plans of three stages or more
+#define PRM_BAND_MOST 1   // [i >= 1] (in LDS) float: most bytes over a cut of the states on i GPUs, there and back
+#define PRM_BAND_LO 16    // [i >= 1] first cell of the states on i GPUs, and cells, in plans of three stages or more
 #define PRM_BAND_W 32
 #define PRM_BAND_LO2 48   // the same of the cuts of plans of two
 #define PRM_BAND_W2 64
 #define PRM_BAND_HDR 80
 static inline size_t prm_band_bytes(int L, int D) { return (PRM_BAND_HDR + (size_t)D * (L + 1) * 2) * 4; }
 // Most cells of a band with so many lanes per candidate: twice as many, or what lets three workgroups share the LDS
-// of a compute unit (60 layers, 3000 orderings of 16 GPUs: 986 us for the call with two of them, 530 with three).
+// of a compute unit (60 layers, 3000 orderings of 16 GPUs: 649 us for the call with two of them, 399 with three).
 __host__ __device__ static inline int prm_band_cells(int D, int lanes) { return D > 12 ? 24 : 2 * lanes; }
 // Ints of a row of Gmin, [stages before]: a multiple of 4, neighbouring rows in other banks.
 __host__ __device__ static inline int prm_band_row(int D) { return ((D + 2) & ~3) | 4; }
-// Bytes of a wave's states, per part; behind them the minima over the last stage's replicas, [GPUs, stages].
+// Bytes of a wave's states, per part (those on all GPUs are not kept); behind them the minima over the last stage's
+// replicas, [GPUs, stages], and those over the links of ranks, [GPUs], which reading plans back takes.
 __host__ __device__ static inline size_t prm_band_slot_bytes(int D) {
-    return (size_t)prm_states(D) * 64 * 6 + (size_t)(D * (D - 1) / 2) * 64 * 4;
+    return (size_t)prm_states(D - 1) * 64 * 6 + (size_t)(D * (D - 1) / 2 + D + 1) * 64 * 4;
 }
-// What a wave keeps for reading plans back: per (GPUs i, replicas r) a candidate's minimum over the links inside the last
-// stage, and per i a bit for every r whose channels are hidden.
-__host__ __device__ static inline int prm_band_back_ints(int D, int lanes) { return (64 / lanes) * (D * (D + 1) / 2) + 17; }
 static inline size_t prm_band_lds_bytes(int L, int D, int lanes, int waves) {
-    const size_t wave = (size_t)(64 / lanes) * prm_band_cells(D, lanes) * (16 + prm_band_row(D) * 4) + 64 * 4 +
-                        (size_t)prm_band_back_ints(D, lanes) * 4;
-    return (size_t)(L + 1) * (24 + 8 * D) + 16 + waves * wave + (size_t)D * D * 4 + PRM_BAND_HDR * 4 + (size_t)(D + 1) * 8 + 8;
+    const size_t wave = (size_t)(64 / lanes) * prm_band_cells(D, lanes) * (16 + prm_band_row(D) * 4) + 64 * 4;
+    return (size_t)(L + 1) * (24 + 8 * D) + 16 + waves * wave + (size_t)D * D * 4 + PRM_BAND_HDR * 4;
 }
 // Waves of a workgroup: they share the tables that no candidate changes.
 static inline int prm_band_waves(int L, int D, int lanes) {

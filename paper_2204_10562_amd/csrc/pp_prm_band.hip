@@ -273,6 +273,8 @@ __device__ __forceinline__ int row_suffix_min(int v, int t) {
     return LANES == 8 ? v : row_imin(v, __builtin_amdgcn_update_dpp(v, v, 0x108, 0xf, 0xf, false));
 }
 
+#define PRM_BAND_HIDDEN 0x8000  // with a cut: no r' before it has channels that matter (L < 2^15)
+
 struct prm_rec { int u, ra, oh; };  // M (QF + QB) + QA, remainder of the AllReduce quotient, one-hot remainders
 
 template <int LANES>
@@ -304,8 +306,6 @@ struct prm_band_lds {
     const double *PA, *AF, *AB;
     const int2 *ut;
     const int *bw, *band;
-    const float2 *hide;  // [i] most bytes over a cut of the states on i GPUs, there and back; no value of theirs is less
-    int *back;   // prm_band_back_ints: the minima, then the bits (of a team: the first wave's)
     int4 *rows;  // [candidate of the wave][cells] records of the cuts
     int *gs;     // [candidate of the wave][cells][prm_band_row] Gmin by cut and stages before
     int *os;     // [64] devices
@@ -320,12 +320,12 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
     const int tri = D * (D + 1) / 2;
     const int *band = lds.band;
     const int parts = __builtin_amdgcn_readfirstlane(band[PRM_BAND_PARTS]);
-    const unsigned NS64 = (unsigned)prm_states(D) * 64;
+    const unsigned NS64 = (unsigned)prm_states(D - 1) * 64;
     int *Wt = (int *)(a.scratch + (size_t)wave * parts * prm_band_slot_bytes(D));  // [part][state][64]
-    unsigned short *At = (unsigned short *)(Wt + (size_t)NS64 * parts);            // the cut
+    unsigned short *At = (unsigned short *)(Wt + (size_t)NS64 * parts);            // the cut, and PRM_BAND_HIDDEN
     int *Gt = (int *)(At + (size_t)NS64 * parts);                                  // [part][GPUs, stages][64]
+    int *In = Gt + (size_t)(D * (D - 1) / 2) * 64 * parts;  // [GPUs i][64] minima over the links between the ranks from one on up to i
     const int gsize = D * (D - 1) / 2 * 64;
-    int *within = lds.back + group / LANES * tri, *hides = lds.back + EACH * tri;
     int4 *rows = lds.rows + group / LANES * prm_band_cells(D, LANES);
     const int ROW = prm_band_row(D);
     int *gs = lds.gs + group / LANES * prm_band_cells(D, LANES) * ROW;
@@ -360,15 +360,19 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
         for (int k = TEAM ? wib : 0; k < parts * (gsize / 64); k += TEAM ? team : 1)
             if (k % (gsize / 64)) Gt[k * 64 + lane] = INF;
         // ---- states by ascending number of GPUs; i == D: cell L alone, lane xi - 1 keeps the best r
-        int wbest = INF, rbest = 0, lbest = 0;
+        int wbest = INF, rbest = 0, lbest = 0;  // (lbest: the cut, and PRM_BAND_HIDDEN)
         const int ou = w.o[t];
         int inner = INF;  // of the links between rank t and those after it, both ways
+        int whole = INF;  // of those between the first t ranks
         for (int i = 1; i <= D; ++i) {
             const bool top = i == D;
             // the links of rank i - 1 join: from rank t on, the minimum over the pairs of ranks t .. i - 1
             const int on = w.o[i - 1];
             inner = t < i - 1 ? row_imin(inner, row_imin(w.bw[ou * D + on], w.bw[on * D + ou])) : INF;
-            const int inside = row_suffix_min<LANES>(inner, t);
+            const int inside = row_suffix_min<LANES>(inner, t), first_i = __shfl(inside, group);
+            whole = t == i ? first_i : whole;
+            if (!TEAM || wib == 0) In[(unsigned)i * 64 + lane] = inside;
+            const float least = (float)lds.ut[top ? L : band[PRM_BAND_LO + i]].x / (float)i * 0.9999f;  // (see hidden)
             int out_f = INF, out_b = INF;  // of the links between rank t and the last r ranks, there and back
             const int lo = top ? L : band[PRM_BAND_LO + i], wd = top ? 1 : band[PRM_BAND_W + i];
             for (int r = 1; r <= i; ++r) {
@@ -380,7 +384,6 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
                 // r times the minimum over the ordered pairs of the last stage's ranks
                 const int links = __shfl(inside, group + n0);
                 const double den = r < 2 ? 1.0 : (double)r * (double)links, inv = prm_inv(den);
-                if (t == 0) within[i * (i - 1) / 2 + r - 1] = links;
                 if (n0 == 0) {
                     for (int c0 = 0; c0 < wd; c0 += LANES) {
                         const int v = w.last(none, w.rec(r, row_imin(lo + c0 + t, L), den, inv));
@@ -400,7 +403,8 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
                 const int mf = row_suffix_min<LANES>(t < n0 ? out_f : INF, t), mb = row_suffix_min<LANES>(t < n0 ? out_b : INF, t);
                 if (top) {
                     // two stages: any cut, the first stage on all n0 GPUs
-                    const double den0 = n0 < 2 ? 1.0 : (double)n0 * (double)within[n0 * (n0 - 1) / 2 + n0 - 1], inv0 = prm_inv(den0);
+                    const int links0 = __shfl(whole, group + n0);
+                    const double den0 = n0 < 2 ? 1.0 : (double)n0 * (double)links0, inv0 = prm_inv(den0);
                     const int f0 = __shfl(mf, group), b0 = __shfl(mb, group);  // (from rank 0 on: r' = n0)
                     const int lo2 = band[PRM_BAND_LO2 + n0], w2 = band[PRM_BAND_W2 + n0];
                     int best = INF, at = 0;
@@ -417,11 +421,10 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
                 }
                 // Gmin of every cut and number of stages: over r' of max(W(l', xi - 1, r', n0), X[r']).  Where no X[r'] of
                 // any cut is more than any value of these states can be (M P[l] / i, which follows from the work before and
-                // after the cut), max with it changes no value, and the minima over r' are there already.  (In float, with
-                // room for its roundings and the two quotients'.)
-                const float most = (float)a.M * lds.hide[n0].x / ((float)((n0 - t) * r) * (float)row_imin(mf, mb));
-                const bool hidden = !__ballot(t < n0 && !(most * 1.0001f + (float)(2 * a.M) < lds.hide[i].y));
-                if (hidden && lane == 0) atomicOr(&hides[i], 1 << r);
+                // after the cut; ut for one replica is M times the work before it), max with it changes no value, and the minima
+                // over r' are there already.  (In float, with room for its roundings and the two quotients'.)
+                const float most = (float)a.M * __int_as_float(band[PRM_BAND_MOST + n0]) / ((float)((n0 - t) * r) * (float)row_imin(mf, mb));
+                const bool hidden = !__ballot(t < n0 && !(most * 1.0001f + (float)(2 * a.M) < least));
                 row_lds_sync();
                 for (int c0 = 0; c0 < w_p; c0 += LANES) {
                     const int lp = row_imin(lo_p + c0 + t, L);  // the lane's cut
@@ -484,7 +487,7 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
                         at = v < best ? lo_p + j : at;
                         best = row_imin(v, best);
                     }
-                    if (on && best < wbest) { wbest = best; rbest = r; lbest = at; }
+                    if (on && best < wbest) { wbest = best; rbest = r; lbest = hidden ? at | PRM_BAND_HIDDEN : at; }
                     continue;
                 }
                 // every cell of the states: the best cut
@@ -517,12 +520,13 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
                     }
                     if (c0 + t < wd) {
                         const unsigned to = (unsigned)(c0 / LANES) * NS64 + prm_sid(i, 1, r) * 64 + lane;
+                        const int base = hidden ? lo_p | PRM_BAND_HIDDEN : lo_p;
 #pragma unroll
                         for (int s = 0; s < LANES - 1; ++s) {
                             if (s >= n0) continue;
                             const unsigned k = to + ((s + 1) * (i + 1) - (s + 1) * (s + 2) / 2) * 64;  // xi = s + 2
                             Wt[k] = best[s];
-                            At[k] = (unsigned short)(lo_p + at[s]);
+                            At[k] = (unsigned short)(base + at[s]);
                             atomicMin(Gt + (c0 / LANES) * gsize + (i * (i - 1) / 2 + s + 1) * 64 + lane, best[s]);
                         }
                     }
@@ -561,21 +565,19 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
                 const int xi = t + 1;
                 a.W_out[c * D + t] = (long long)wbest;
                 int *bo = a.bounds_out + c * tri + xi * (xi - 1) / 2, *ro = a.reps_out + c * tri + xi * (xi - 1) / 2;
-                int l = L, n = D, r = rbest, lp = lbest, v = wbest;
+                int l = L, n = D, r = rbest, cut = lbest, v = wbest;
                 bo[xi - 1] = L;
                 ro[xi - 1] = r;
                 for (int s = xi - 1; s >= 1; --s) {
                     // layers [lp, l) on r replicas as stage s; r' of the stage before: the first one whose value reaches v
-                    const int n0 = n - r, nrp = n0 - (s - 1);
+                    const int n0 = n - r, nrp = n0 - (s - 1), lp = cut & ~PRM_BAND_HIDDEN;
+                    const bool hidden = cut & PRM_BAND_HIDDEN;
                     int rp = n0;
                     if (s > 1) {
-                        const double den = r < 2 ? 1.0 : (double)r * (double)within[n * (n - 1) / 2 + r - 1];
-                        const double inv = prm_inv(den);
-                        const int y = w.last(w.rec(r, lp, den, inv), w.rec(r, l, den, inv));
+                        const int links = __hip_atomic_load(In + (n * 64 + group + n0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         const int cell = lp - band[PRM_BAND_LO + n0], place = cell / LANES * (int)NS64 + cell % LANES + group;
                         const int *Ws = Wt + prm_sid(n0, s, 1) * 64 + place;
-                        int mf = INF, mb = INF, before = 0;
-                        const bool hidden = hides[n] >> r & 1;
+                        int mf = INF, mb = INF, before = 0, y = 0;
                         bool found = false;
                         // (four values in flight; the last r' is the one if no other is)
                         for (int r0 = 1; !found; r0 += 4) {
@@ -583,6 +585,10 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
 #pragma unroll
                             for (int u = 0; u < 4; ++u)
                                 four[u] = __hip_atomic_load(Ws + (row_imin(r0 + u, nrp) - 1) * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            if (r0 == 1) {
+                                const double den = r < 2 ? 1.0 : (double)r * (double)links, inv = prm_inv(den);
+                                y = w.last(w.rec(r, lp, den, inv), w.rec(r, l, den, inv));
+                            }
 #pragma unroll
                             for (int u = 0; u < 4; ++u) {
                                 if (found) continue;
@@ -605,7 +611,7 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
                         const unsigned *word = (const unsigned *)((uintptr_t)(At + at) & ~(uintptr_t)3);
                         const unsigned two = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         l = lp;
-                        lp = (int)((uintptr_t)(At + at) & 2 ? two >> 16 : two & 0xffff);
+                        cut = (int)((uintptr_t)(At + at) & 2 ? two >> 16 : two & 0xffff);
                     } else {
                         l = lp;
                     }
@@ -615,10 +621,6 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
                     ro[s - 1] = r;
                 }
             }
-        }
-        if (!TEAM || wib == 0) {
-            row_lds_sync();
-            if (lane < 17) hides[lane] = 0;
         }
         if (TEAM) __syncthreads();  // (the next candidates' states take these ones' place)
     }
@@ -640,9 +642,7 @@ __global__ __launch_bounds__(256, FOUR ? 4 : 3) void k_prm_band(prm_args a) {
     int4 *rows = (int4 *)(((uintptr_t)(ut + D * L1) + 15) & ~(uintptr_t)15);
     constexpr int EACH = 64 / LANES;
     int *gs = (int *)(rows + (B >> 6) * EACH * prm_band_cells(D, LANES)), *os = gs + (B >> 6) * EACH * prm_band_cells(D, LANES) * prm_band_row(D);
-    int *back = os + B, *bw = back + (B >> 6) * prm_band_back_ints(D, LANES), *band = bw + D * D;
-    float2 *hide = (float2 *)(((uintptr_t)(band + PRM_BAND_HDR) + 7) & ~(uintptr_t)7);
-    for (int i = tid; i < (B >> 6) * prm_band_back_ints(D, LANES); i += B) back[i] = 0;
+    int *bw = os + B, *band = bw + D * D;
     for (int l = tid; l < L1; l += B) {
         PA[l] = (double)a.pre_out[2 * L1 + l];
         AF[l] = l >= 1 && l < L ? (double)a.actf[l - 1] : 0.0;
@@ -652,20 +652,18 @@ __global__ __launch_bounds__(256, FOUR ? 4 : 3) void k_prm_band(prm_args a) {
     for (int i = tid; i < D * D; i += B) bw[i] = i / D == i % D ? PP_INF32 : (int)a.bw[i];
     for (int i = tid; i < PRM_BAND_HDR; i += B) band[i] = a.band[i];
     __syncthreads();
-    if (tid >= 1 && tid <= D) {
-        const int lo = tid < D ? band[PRM_BAND_LO + tid] : L, w = tid < D ? band[PRM_BAND_W + tid] : 0;
+    if (tid >= 1 && tid < D) {
+        const int lo = band[PRM_BAND_LO + tid], w = band[PRM_BAND_W + tid];
         double f = 0.0, b = 0.0;
         for (int k = lo; k < lo + w && k <= L; ++k) {
             f = AF[k] > f ? AF[k] : f;
             b = AB[k] > b ? AB[k] : b;
         }
-        // (ut for one replica is M times the work before the cell)
-        hide[tid] = make_float2((float)(f + b), (float)ut[lo].x / (float)tid * 0.9999f);
+        band[PRM_BAND_MOST + tid] = __float_as_int((float)(f + b));
     }
     if (!TEAM) __syncthreads();  // (a team looks there behind the barrier of its first states)
     prm_band_lds lds;
-    lds.PA = PA; lds.AF = AF; lds.AB = AB; lds.ut = ut; lds.bw = bw; lds.band = band; lds.hide = hide;
-    lds.back = back + (TEAM ? 0 : wib) * prm_band_back_ints(D, LANES);
+    lds.PA = PA; lds.AF = AF; lds.AB = AB; lds.ut = ut; lds.bw = bw; lds.band = band;
     lds.rows = rows + wib * EACH * prm_band_cells(D, LANES);
     lds.gs = gs + wib * EACH * prm_band_cells(D, LANES) * prm_band_row(D);
     lds.os = os + 64 * wib;

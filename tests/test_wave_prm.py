@@ -86,3 +86,12 @@ def test_slow_links_end_the_look_for_bands(driver):
                 w.bw[0, 1] = 1
             out, = driver([numbers(w, alpha, M, 1)])
             assert out[4] != slow and (not slow or out[1] == 0), (seed, slow)
+
+
+def test_room_for_bands(driver):
+    """Up to which number of layers there are bands, workgroups of four waves, and three workgroups (of 16 lanes a candidate)
+    to a compute unit: what the tables of a workgroup and the states of its waves take of the LDS decides it."""
+    rooms = {6: (667, 433, 433, 516), 8: (545, 353, 353, 420), 12: (396, 255, 255, 305),
+             14: (197, 0, 194, 197), 16: (175, 0, 171, 175)}
+    for (D, room), out in zip(rooms.items(), driver([[0, D, 0, 0, 0] for D in rooms])):
+        assert tuple(out) == room, D

@@ -202,6 +202,8 @@ inline void __builtin_amdgcn_wave_barrier() { wave::meet(wave::WAVE_BARRIER, 0);
 // (the hardware's reciprocal is off by an ulp or so: a little more here, now too large and now too small)
 inline double __builtin_amdgcn_rcp(double x) { return 1.0 / x * (1.0 + ((long long)x & 1 ? 1 : -1) * 0x1p-24); }
 inline int __popc(unsigned v) { return __builtin_popcount(v); }
+inline int __float_as_int(float v) { return __builtin_bit_cast(int, v); }
+inline float __int_as_float(int v) { return __builtin_bit_cast(float, v); }
 inline int __mul24(int a, int b) { return a * b; }
 inline void __syncthreads() { wave::meet(wave::BLOCK_BARRIER, 1); }
 inline int __syncthreads_and(int v) { return (int)wave::meet(wave::BLOCK_BARRIER, v); }

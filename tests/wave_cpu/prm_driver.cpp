@@ -3,7 +3,9 @@
 //   L D N M TEAM fwd[L] bwd[L] actf[L] actb[L] alpha[L] bw[D*D] ord[N*D]
 // TEAM: whether the waves of a workgroup share candidates.  Prints, per problem, the status, the parts of a band (0: the
 // bands are not used), the lanes per candidate, the widest band, whether times for it were tried, and, where bands are
-// used, W, bounds and replicas of every candidate.
+// used, W, bounds and replicas of every candidate.  With L = 0 the last number of layers up to which there can be bands
+// of D devices, up to which a workgroup has four waves (8 and 16 lanes a candidate), and up to which three of those with 16
+// lanes share the 160 KB of a compute unit.
 #include <hip/hip_runtime.h>
 
 #undef __shared__
@@ -29,6 +31,18 @@ static void plan(const prm_args &a, bool team) {
 int main() {
     int L, D, N, M, team;
     while (scanf("%d %d %d %d %d", &L, &D, &N, &M, &team) == 5) {
+        if (L == 0) {
+            int last = 0, four8 = 0, four16 = 0, three = 0;
+            for (int l = D; l <= 1024; ++l) {
+                const int w8 = prm_band_waves(l, D, 8), w16 = prm_band_waves(l, D, 16);
+                if (w8 && w16) last = l;
+                if (w8 == 4) four8 = l;
+                if (w16 == 4) four16 = l;
+                if (w8 && w16 && 3 * prm_band_lds_bytes(l, D, 16, w16) <= 160 * 1024) three = l;
+            }
+            printf("%d %d %d %d\n", last, four8, four16, three);
+            continue;
+        }
         auto read = [&](size_t n) {
             std::vector<ll> v(n);
             for (ll &x : v) if (scanf("%lld", &x) != 1) exit(1);
