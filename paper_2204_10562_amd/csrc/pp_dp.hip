@@ -20,6 +20,7 @@
 #include "pp_dp_generic.h"
 #include "pp_dp_rows.h"
 #include "pp_dp_tile.h"
+#include "pp_share.h"
 
 // ---------------------------------------------------------------- pack
 
@@ -491,8 +492,11 @@ int pp_launch_dp(int L, int D, int S, int64_t N, const int64_t *PF, const int64_
     a.fbits = NULL;
     a.fT = a.fleast = NULL;
     a.f_nM = 0;
-    // (bands of a launch of their own: k_dp_rows looks at the candidates itself)
-    if (sched && sched->nM <= PP_FREE_COUNTS && !stages && lay.fx && (use == BAND_USE_ALONE || (a.band && lay.sh_table))) {
+    // (Bands of a launch of their own: k_dp_rows looks at the candidates itself.  L > 128: not where candidates share their DP
+    // whatever the links are, because k_band_free would find that and leave: 3 us of 67 to 105 for 2 or 3 of 12 to 30 devices.
+    // With more stages only the device knows; where they don't share, it saves 1 to 8 us of lists as short as 64.)
+    const bool shared = lay.sh_table && share_table_size((unsigned)(D * D), S) != 0;
+    if (sched && sched->nM <= PP_FREE_COUNTS && !stages && lay.fx && (use == BAND_USE_ALONE || (a.band && lay.sh_table && !shared))) {
         sched->looked = true;
         a.fx = (int2 *)(base + lay.fx);
         a.fbits = (unsigned long long *)(base + lay.fbits);

@@ -9,7 +9,7 @@
 #define SHARE_ENDED 0x40000000
 
 // Keys of S - 1 digits in base nc: how many there are, 0 if they do not fit the table.
-__device__ __forceinline__ unsigned share_table_size(unsigned nc, int S) {
+__host__ __device__ __forceinline__ unsigned share_table_size(unsigned nc, int S) {
     if (nc == 0) return S > 1 ? 0 : 1;
     unsigned tsize = 1;
     for (int n = 1; n < S && tsize; ++n) {

@@ -54,3 +54,30 @@ def test_free_plans(ppo, kind, L, D, S, N):
                         np.testing.assert_array_equal(T[q], t)
                 if want:
                     np.testing.assert_array_equal(C[keep], C0[keep])
+
+
+@pytest.mark.parametrize("L,D,S,N,looks", [(150, 9, 3, 400, False), (300, 32, 3, 400, False), (300, 33, 3, 400, True), (200, 10, 4, 400, False),
+                                           (200, 11, 4, 400, True), (129, 64, 2, 64, False), (128, 11, 9, 150000, True)])
+def test_no_launch_for_nothing(L, D, S, N, looks):
+    """The look for channel-free plans to schedule (up to four counts) is not launched where candidates share their
+    program whatever the links are: D * D kinds of links make at most 2^20 sequences."""
+    import ctypes
+
+    import torch
+    from paper_2204_10562_amd import binding as pp
+    from paper_2204_10562_amd.problem import GpuProblem
+    g = GpuProblem(problem("free", L + D, L, D, S, N))
+    assert g.prefix() == 0
+    out = torch.zeros(5 * pp.RESULT_BYTES, dtype=torch.uint8, device=g.dev)
+    ws = g.workspace()
+    hip = ctypes.CDLL("libamdhip64.so")
+    launches = []
+    for nM in (4, 5):
+        print("[case] launches", L, D, S, N, nM, flush=True)
+        graph = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(graph):
+            pp.pp_best_plan_multi(L, D, S, N, [2, 19, 5, 40, 11][:nM], g.PF, g.PB, g.XF, g.XB, g.orderings, out, None, None, ws, g.status)
+        n = ctypes.c_size_t(0)
+        assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+        launches.append(n.value)
+    assert launches[0] - launches[1] == looks, launches
