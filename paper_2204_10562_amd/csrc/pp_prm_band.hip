@@ -312,14 +312,16 @@ struct prm_band_lds {
     int *best;   // [3][64], one for the workgroup: the best plans of another wave
 };
 
-// TEAM: the waves of the workgroup share candidates, each with its part of the r of every i.
-template <int LANES, bool TEAM>
+// TEAM: the waves of the workgroup share candidates, each with its part of the r of every i.  STAGES: a multiple of 4, and no
+// state has more stages before its last.
+template <int LANES, bool TEAM, int STAGES>
 __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_lds &lds, int wave, int waves, int wib, int team) {
     constexpr int EACH = 64 / LANES;  // candidates of a wave
     const int L = a.L, D = a.D, L1 = L + 1, lane = threadIdx.x & 63, t = lane & (LANES - 1), group = lane - t;
     const int tri = D * (D + 1) / 2;
     const int *band = lds.band;
-    const int parts = __builtin_amdgcn_readfirstlane(band[PRM_BAND_PARTS]);
+    auto number = [&](int k) { return __builtin_amdgcn_readfirstlane(band[k]); };
+    const int parts = number(PRM_BAND_PARTS);
     const unsigned NS64 = (unsigned)prm_states(D - 1) * 64;
     int *Wt = (int *)(a.scratch + (size_t)wave * parts * prm_band_slot_bytes(D));  // [part][state][64]
     unsigned short *At = (unsigned short *)(Wt + (size_t)NS64 * parts);            // the cut, and PRM_BAND_HIDDEN
@@ -372,9 +374,9 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
             const int inside = row_suffix_min<LANES>(inner, t), first_i = __shfl(inside, group);
             whole = t == i ? first_i : whole;
             if (!TEAM || wib == 0) In[(unsigned)i * 64 + lane] = inside;
-            const float least = (float)lds.ut[top ? L : band[PRM_BAND_LO + i]].x / (float)i * 0.9999f;  // (see hidden)
             int out_f = INF, out_b = INF;  // of the links between rank t and the last r ranks, there and back
-            const int lo = top ? L : band[PRM_BAND_LO + i], wd = top ? 1 : band[PRM_BAND_W + i];
+            const int lo = top ? L : number(PRM_BAND_LO + i), wd = top ? 1 : number(PRM_BAND_W + i);
+            const float least = (float)lds.ut[lo].x / (float)i * 0.9999f;  // (see hidden)
             for (int r = 1; r <= i; ++r) {
                 const int n0 = i - r;  // GPUs of the sub-problem
                 const int od = w.o[n0];
@@ -397,7 +399,7 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
                     }
                     continue;
                 }
-                const int lo_p = band[PRM_BAND_LO + n0], w_p = band[PRM_BAND_W + n0];
+                const int lo_p = number(PRM_BAND_LO + n0), w_p = number(PRM_BAND_W + n0);
                 const prm_rec qL = top ? w.rec(r, L, den, inv) : none;
                 // from rank t on to the last r ranks, both ways
                 const int mf = row_suffix_min<LANES>(t < n0 ? out_f : INF, t), mb = row_suffix_min<LANES>(t < n0 ? out_b : INF, t);
@@ -406,7 +408,7 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
                     const int links0 = __shfl(whole, group + n0);
                     const double den0 = n0 < 2 ? 1.0 : (double)n0 * (double)links0, inv0 = prm_inv(den0);
                     const int f0 = __shfl(mf, group), b0 = __shfl(mb, group);  // (from rank 0 on: r' = n0)
-                    const int lo2 = band[PRM_BAND_LO2 + n0], w2 = band[PRM_BAND_W2 + n0];
+                    const int lo2 = number(PRM_BAND_LO2 + n0), w2 = number(PRM_BAND_W2 + n0);
                     int best = INF, at = 0;
                     for (int j = 0; j < w2; j += LANES) {
                         const int k = row_imin(lo2 + j + t, L - 1);
@@ -432,23 +434,34 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
                     const prm_rec qp = w.rec(r, lp, den, inv);
                     if (cut) rows[c0 + t] = make_int4(qp.u, qp.ra, qp.oh, top ? w.last(qp, qL) : 0);
                     const int *Wp = Wt + (unsigned)(c0 / LANES) * NS64 + prm_sid(n0, 1, 1) * 64;
-                    int g[LANES];  // [xi - 2]
-#pragma unroll
-                    for (int s = 0; s < LANES; ++s) g[s] = INF;
+                    // (a block of four numbers of stages to the wave's LDS; a number has cuts from itself on)
+                    auto leave = [&](int s, int g0, int g1, int g2, int g3) {
+                        if (cut)
+                            *(int4 *)(gs + (c0 + t) * ROW + s) =
+                                make_int4(lp > s ? g0 : INF, lp > s + 1 ? g1 : INF, lp > s + 2 ? g2 : INF, lp > s + 3 ? g3 : INF);
+                    };
                     if (hidden) {
                         // (past the L1 cache: atomics leave them in the next one)
                         const int *Gp = Gt + (c0 / LANES) * gsize + n0 * (n0 - 1) / 2 * 64;
+                        int g[STAGES];
 #pragma unroll
-                        for (int s = 0; s < LANES; ++s)
-                            if (s < n0) g[s] = __hip_atomic_load(Gp + s * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        for (int s = 0; s < STAGES; ++s)
+                            g[s] = s < n0 ? __hip_atomic_load(Gp + s * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : INF;
+#pragma unroll
+                        for (int s = 0; s < STAGES; s += 4)
+                            if (s < n0) leave(s, g[s], g[s + 1], g[s + 2], g[s + 3]);
+                        continue;
                     }
+                    int g[STAGES];  // [xi - 2]
+#pragma unroll
+                    for (int s = 0; s < STAGES; ++s) g[s] = INF;
 #pragma unroll 1
-                    for (int rp = hidden ? n0 + 1 : 1; rp <= n0; ++rp) {
+                    for (int rp = 1; rp <= n0; ++rp) {
                         const int x = w.channel(lp, rp * r, __shfl(mf, group + n0 - rp), __shfl(mb, group + n0 - rp));
                         // (the states of s + 1 stages on n0 GPUs begin at that of one replica; one stage has all n0)
-                        int v[LANES];
+                        int v[STAGES];
 #pragma unroll
-                        for (int s = 0; s < LANES; s += 4) {
+                        for (int s = 0; s < STAGES; s += 4) {
                             if (s > n0 - rp) continue;
                             // (of a block, also what belongs to the states after these: not used)
                             v[s] = Wp[(s * (n0 + 1) - s * (s + 1) / 2 + rp - 1) * 64 + lane];
@@ -457,7 +470,7 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
                             v[s + 3] = Wp[((s + 3) * (n0 + 1) - (s + 3) * (s + 4) / 2 + rp - 1) * 64 + lane];
                         }
 #pragma unroll
-                        for (int s = 0; s < LANES; s += 4) {
+                        for (int s = 0; s < STAGES; s += 4) {
                             if (s > n0 - rp) continue;
                             if (s) g[s] = row_imin(g[s], row_imax(v[s], x));
                             else if (rp == n0) g[0] = row_imax(v[0], x);
@@ -467,15 +480,8 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
                         }
                     }
 #pragma unroll
-                    for (int s = 0; s < LANES; s += 4) {
-                        if (s >= n0 || !cut) continue;
-                        int4 q;
-                        q.x = lp > s ? g[s] : INF;
-                        q.y = lp > s + 1 ? g[s + 1] : INF;
-                        q.z = lp > s + 2 ? g[s + 2] : INF;
-                        q.w = lp > s + 3 ? g[s + 3] : INF;
-                        *(int4 *)(gs + (c0 + t) * ROW + s) = q;
-                    }
+                    for (int s = 0; s < STAGES; s += 4)
+                        if (s < n0) leave(s, g[s], g[s + 1], g[s + 2], g[s + 3]);
                 }
                 row_lds_sync();
                 if (top) {
@@ -494,16 +500,16 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
                 for (int c0 = 0; c0 < wd; c0 += LANES) {
                     const int l = row_imin(lo + c0 + t, L);  // the lane's cell
                     const prm_rec ql = w.rec(r, l, den, inv);
-                    int best[LANES], at[LANES];
+                    int best[STAGES], at[STAGES];
 #pragma unroll
-                    for (int s = 0; s < LANES; ++s) { best[s] = INF; at[s] = 0; }
+                    for (int s = 0; s < STAGES; ++s) { best[s] = INF; at[s] = 0; }
 #pragma unroll 1
                     for (int j = 0; j < w_p; ++j) {
                         const int4 q = rows[j];
                         const prm_rec qj = {q.x, q.y, q.z};
                         const int last = lo_p + j < l ? w.last(qj, ql) : INF;
 #pragma unroll
-                        for (int s = 0; s < LANES; s += 4) {
+                        for (int s = 0; s < STAGES; s += 4) {
                             if (s >= n0) continue;
                             const int4 g = *(const int4 *)(gs + j * ROW + s);
                             const int v0 = row_imax(g.x, last), v1 = row_imax(g.y, last);
@@ -522,7 +528,7 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
                         const unsigned to = (unsigned)(c0 / LANES) * NS64 + prm_sid(i, 1, r) * 64 + lane;
                         const int base = hidden ? lo_p | PRM_BAND_HIDDEN : lo_p;
 #pragma unroll
-                        for (int s = 0; s < LANES - 1; ++s) {
+                        for (int s = 0; s < (STAGES < LANES ? STAGES : LANES - 1); ++s) {
                             if (s >= n0) continue;
                             const unsigned k = to + ((s + 1) * (i + 1) - (s + 1) * (s + 2) / 2) * 64;  // xi = s + 2
                             Wt[k] = best[s];
@@ -626,9 +632,12 @@ __device__ __forceinline__ void prm_band_run(const prm_args &a, const prm_band_l
     }
 }
 
-// FOUR: four workgroups per compute unit at the price of spills, see prm_band_launch.
-template <int LANES, bool TEAM, bool FOUR = false>
-__global__ __launch_bounds__(256, FOUR ? 4 : 3) void k_prm_band(prm_args a) {
+// Registers: eight numbers of stages at once take 141; in 128, four waves per SIMD instead of three, a few are spilled.  Teams lose less
+// by that than by a round more (7428 orderings of 6 GPUs, 32 layers 96.5 -> 80.6 us, 8150 of 8, 60 layers 145 -> 116; of 8,
+// 120 layers, with LDS for two workgroups either way, 207.5 -> 208.3), other launches do not (200 000 of 7, 100 layers 1208 -> 1227).
+// With four numbers of stages, which is enough for up to 5 GPUs, 122: 200 000 orderings of 4, 40 layers 279 -> 260 us.
+template <int LANES, bool TEAM, int STAGES>
+__global__ __launch_bounds__(256, LANES == 8 && (TEAM || STAGES < 8) ? 4 : 3) void k_prm_band(prm_args a) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int parts = a.band[PRM_BAND_PARTS];
     if (!parts || a.band[PRM_BAND_LANES] != LANES) return;
@@ -669,7 +678,7 @@ __global__ __launch_bounds__(256, FOUR ? 4 : 3) void k_prm_band(prm_args a) {
     lds.os = os + 64 * wib;
     lds.best = (int *)rows;
     const int wave = TEAM ? blockIdx.x : blockIdx.x * (B >> 6) + wib;
-    if (wave < waves) prm_band_run<LANES, TEAM>(a, lds, wave, waves, wib, B >> 6);
+    if (wave < waves) prm_band_run<LANES, TEAM, STAGES>(a, lds, wave, waves, wib, B >> 6);
 }
 
 // The launch for LANES lanes per candidate.
@@ -684,16 +693,12 @@ static void prm_band_launch(const prm_args &a, hipStream_t st) {
     const bool team = sets < 1536;
     sets = sets < room ? sets : room;
     sets = sets < 8192 ? sets : 8192;
-    // (165 registers: three teams of four waves at once on each of the 256 compute units.  Where that leaves a second round for
-    // the last few and LDS has room for a fourth, the kernel in 128: 7428 orderings of 6 GPUs, 32 layers 103.5 -> 87.6 us;
-    // elsewhere its spills cost 1 to 5 %: 5500 of 8 110 -> 115, 9000 of 5, two rounds either way, 90 -> 93.)
-    const bool four = team && LANES == 8 && wpb == 4 && sets > 3 * 256 && sets <= 4 * 256 && 4 * lds <= 160 * 1024;
-    if (four)
-        hipLaunchKernelGGL((k_prm_band<LANES, true, LANES == 8>), dim3((unsigned)sets), dim3(64 * wpb), lds, st, a);
-    else if (team)
-        hipLaunchKernelGGL((k_prm_band<LANES, true>), dim3((unsigned)sets), dim3(64 * wpb), lds, st, a);
-    else
-        hipLaunchKernelGGL((k_prm_band<LANES, false>), dim3((unsigned)((sets + wpb - 1) / wpb)), dim3(64 * wpb), lds, st, a);
+    const dim3 grid((unsigned)(team ? sets : (sets + wpb - 1) / wpb)), block(64 * wpb);
+    constexpr int FEW = LANES == 8 ? 4 : LANES;
+    if (a.D <= 5 && team) hipLaunchKernelGGL((k_prm_band<LANES, true, FEW>), grid, block, lds, st, a);
+    else if (a.D <= 5) hipLaunchKernelGGL((k_prm_band<LANES, false, FEW>), grid, block, lds, st, a);
+    else if (team) hipLaunchKernelGGL((k_prm_band<LANES, true, LANES>), grid, block, lds, st, a);
+    else hipLaunchKernelGGL((k_prm_band<LANES, false, LANES>), grid, block, lds, st, a);
 }
 
 int pp_launch_prm_band(const prm_args &a, hipStream_t st) {

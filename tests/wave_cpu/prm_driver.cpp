@@ -24,8 +24,11 @@ static void plan(const prm_args &a, bool team) {
     const int wpb = prm_band_waves(a.L, a.D, LANES);
     const size_t lds = prm_band_lds_bytes(a.L, a.D, LANES, wpb);
     if (lds > sizeof smem) abort();
-    if (team) wave::launch(k_prm_band<LANES, true>, dim3(2), dim3(64 * wpb), lds, a);
-    else wave::launch(k_prm_band<LANES, false>, dim3(2), dim3(64 * wpb), lds, a);
+    constexpr int FEW = LANES == 8 ? 4 : LANES;
+    if (a.D <= 5 && team) wave::launch(k_prm_band<LANES, true, FEW>, dim3(2), dim3(64 * wpb), lds, a);
+    else if (a.D <= 5) wave::launch(k_prm_band<LANES, false, FEW>, dim3(2), dim3(64 * wpb), lds, a);
+    else if (team) wave::launch(k_prm_band<LANES, true, LANES>, dim3(2), dim3(64 * wpb), lds, a);
+    else wave::launch(k_prm_band<LANES, false, LANES>, dim3(2), dim3(64 * wpb), lds, a);
 }
 
 int main() {
