@@ -24,7 +24,7 @@ struct mk_args {
     // pairs, entry c*search + xi-1, and the record of the winner is decoded accordingly
     int search;
     int variant;  // PP_SCHED_*
-    // nonzero: what 32-bit sums do not hold is left to another kernel, wave by wave (MK_NOT_TAKEN in T_out)
+    // k_makespan_events: nonzero = only the candidates that k_makespan_fifo has marked (MK_NOT_TAKEN in T_out)
     int by_block;
     int lanes_per;  // lanes per candidate of k_makespan_fifo (1 .. 32)
     int groups;     // candidates per workgroup of k_makespan_fifo
@@ -94,7 +94,7 @@ __device__ __forceinline__ int overflow_fault(long long worst, int M, int S) {
     return worst > (PP_CAP62 - 1) / ((long long)M + 4 * S - 4) ? PP_FAULT_OVERFLOW : 0;
 }
 
-// T of a candidate that a kernel has left to the next one (no schedule ends before 0).
+// T of a candidate that k_makespan_fifo has left to k_makespan_events (no schedule ends before 0).
 #define MK_NOT_TAKEN (-1ll)
 // Whether k_band_free has scheduled candidate c.  (It has not looked at any where candidates share their DP.)
 __device__ __forceinline__ bool mk_has_free(const mk_args &a) { return a.free_bits && a.hdr->free_valid; }
@@ -184,8 +184,8 @@ __device__ __forceinline__ int mk_check_rows(const mk_args &a, long long c, int 
 }
 
 // The longest path's closed form (pp_makespan_path.h) over the plans in memory, any a.variant but PP_SCHED_FIFO
-// (pp_makespan_split.hip).  With a.by_block it marks the plans it leaves alone; with a.part it leaves partials
-// for k_pick, *n_part of them per count, or picks itself (*n_part = 0).
+// (pp_makespan_split.hip).  With a.part it leaves partials for k_pick, *n_part of them per count, or picks itself
+// (*n_part = 0).
 int pp_launch_makespan_split(const mk_args &a, hipStream_t st, long long *n_part = NULL);
 // PP_SCHED_FIFO for at most 32 stages (pp_makespan_fifo.hip); marks the candidates it leaves alone.
 int pp_launch_makespan_fifo(const mk_args &a, hipStream_t st);

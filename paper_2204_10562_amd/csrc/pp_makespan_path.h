@@ -523,13 +523,7 @@ __device__ __forceinline__ void mk_path_body(const mk_args &a) {
             } else {
                 p = mk_plan32<MODE, NM>(a, row, PT, xi, live, M, limit, T);
             }
-            if (__ballot(!p.fits)) {
-                if (!KNOWN && a.by_block) {
-                    if (live) a.T_out[c * a.t_stride + a.t_off] = MK_NOT_TAKEN;
-                    break;
-                }
-                p = mk_plan64<MODE, NM>(a, row, xi, live && !done, M, T);
-            }
+            if (__ballot(!p.fits)) p = mk_plan64<MODE, NM>(a, row, xi, live && !done, M, T);
 #pragma unroll
             for (int q = 0; q < NM; ++q) {
                 const int slot = (int)blockIdx.y * NM + q;

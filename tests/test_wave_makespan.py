@@ -62,21 +62,25 @@ def test_readiness_order_takes_long_lists(driver, S, N):
 @pytest.mark.parametrize("variant", [PE, DUPLEX, GPIPE, ADDITIVE])
 @pytest.mark.parametrize("S", [1, 4, 17, 64])
 def test_microbatch_counts_next_to_the_largest_int(driver, variant, S):
-    # left to the 64-bit kernel, whatever the times: neither the limit on the times nor a number of
-    # sweeps may wrap around
-    Ms = [2**31 - 1 - d for d in (0, 1, 2 * S, 4 * S + 32, 4 * S + 33)] + [2**30, 2**30 - 1, 2**30 - 64]
-    lines = ["taken %d %d %d %d" % (variant, S, M, time) for M in Ms for time in (0, 1, 7)]
-    out, errors = driver(lines, timeout=60)
+    # (64-bit sums, whatever the times: neither the limit on the times nor a product may wrap around)
+    Ms = [2**31 - 1 - d for d in (0, 1, 2 * S, 4 * S + 32, 4 * S + 33)] + [2**30, 2**30 - 1, 2**30 - 64, 2**24, 2**24 - 1]
+    Ms += [2**24 - d for d in (4 * S + 63, 4 * S + 64, 4 * S + 65)]
+    lines = ["long %d %d %d %d" % (variant, S, M, time) for M in Ms for time in (0, 1, 7)]
+    out, errors = driver(lines, timeout=120)
     for line, got in zip(lines, out):
-        assert got == [0, 0], line
+        assert got == [0, 0, 0], line
     assert "runtime error" not in errors, errors[-2000:]
 
 
-def test_taken_where_the_times_fit(driver):
-    # one stage of all layers against the limit: 6 + 6 layers' times in 30 bits with the padded sweeps
-    fits = (2**30 - 1) // (100 + 4 + 64) // 12
-    out, _ = driver(["taken %d 1 100 %d" % (PE, fits), "taken %d 1 100 %d" % (PE, fits + 1)])
-    assert out == [[0, 64], [0, 0]]
+@pytest.mark.parametrize("variant", [PE, DUPLEX, GPIPE, ADDITIVE])
+@pytest.mark.parametrize("M", [1, 2, 100, 5000, 10**6])
+def test_where_the_times_stop_to_fit(driver, variant, M):
+    # one stage of all six layers, forward and backward, against the limit: in 30 bits with the padded sweeps; and 64-bit sums
+    fits = (2**30 - 1) // ((2 * M + 4 if variant == GPIPE else M) + 4 + 64) // 12
+    times = sorted({max(t, 0) for t in (fits - 1, fits, fits + 1, 2 * fits, 2**24 // 12, 2**24 // 12 + 1, 2**40)})
+    out, errors = driver(["long %d 1 %d %d" % (variant, M, t) for t in times])
+    assert out == [[0, 0, 0]] * len(times), times
+    assert "runtime error" not in errors, errors[-2000:]
 
 
 @pytest.mark.parametrize("S", [2, 3, 5, 9])

@@ -4,7 +4,9 @@
 //                               VARIANT, against Alg. 1's rules written out in 64 bits
 //   mixed VARIANT S M SEED HI   the same with 300 plans of times from 0 up: how many were left, how many of
 //                               the others differ, and workgroups of the readiness order left in part
-//   taken VARIANT S M TIME      how many of 64 plans whose times are all TIME the 30-bit kernel takes
+//   long VARIANT S M TIME       random plans whose layers' times and transfers are all TIME, under any M: T is the largest of
+//                               functions that are linear in M, so that it grows by the longest of its resources' times per
+//                               microbatch from where it does so once
 //   faulty VARIANT S M N BAD    N plans of which the first BAD have a bad ordering: how many of these have a time, and
 //                               how many of the others (a second's work if M is large) have another one than they should
 //   launch VARIANT S N          the launches for N candidates (nothing runs): the return value, and how
@@ -118,7 +120,6 @@ struct problem {
         a.orderings = o.data(); a.bounds = e.data(); a.T_out = T.data(); a.status = &status;
         a.ord_stride = S; a.bnd_stride = S; a.t_stride = 1;
         a.variant = variant;
-        a.by_block = 1;
     }
     ll want(int c, int M) const {
         const int R = 2 * S - 1, J = 2 * R - 1;
@@ -136,6 +137,20 @@ struct problem {
             }
         }
         return reference(a.variant, S, M, d, lastF, lastB);
+    }
+    // What T grows by per microbatch in a pipeline that is long enough.
+    ll slope(int c) const {
+        ll most = 0, A = 0, B = 0;
+        for (int n = 0; n < S; ++n) {
+            const int e1 = e[c * S + n], e0 = n ? e[c * S + n - 1] : 0;
+            const size_t at = n ? ((size_t)o[c * S + n - 1] * D + o[c * S + n]) * L + e0 - 1 : 0;
+            const ll F = PF[e1] - PF[e0], Bk = PB[e1] - PB[e0], cf = n ? XF[at] : 0, cb = n ? XB[at] : 0;
+            A = std::max(A, std::max(F, cf));
+            B = std::max(B, std::max(Bk, cb));
+            most = std::max(most, a.variant == PP_SCHED_ADDITIVE ? F + Bk + cf + cb
+                                  : std::max(F + Bk, a.variant == PP_SCHED_DUPLEX ? std::max(cf, cb) : cf + cb));
+        }
+        return a.variant == PP_SCHED_GPIPE ? A + B : most;
     }
     int launch() { return a.variant == PP_SCHED_FIFO ? pp_launch_makespan_fifo(a, NULL) : pp_launch_makespan_split(a, NULL); }
 };
@@ -167,13 +182,17 @@ int main() {
                 parts += c % (FIFO_THREADS / each) && (p.T[c] == MK_NOT_TAKEN) != (p.T[c - 1] == MK_NOT_TAKEN);
             }
             printf("%d %d %d %d %d\n", rc, p.status, left, differ, parts);
-        } else if (!strcmp(what, "taken")) {
+        } else if (!strcmp(what, "long")) {
             if (scanf("%lld", &x) != 1) return 2;
-            problem p(variant, S, 64, (int)M, 1, x, x);
+            problem p(variant, S, 6, (int)M, 1, x, x);
             const int rc = p.launch();
-            int taken = 0;
-            for (int c = 0; c < p.N; ++c) taken += p.T[c] != MK_NOT_TAKEN;
-            printf("%d %d\n", rc, taken);
+            int differ = 0;
+            for (int c = 0; c < p.N; ++c) {
+                ll near = 4 * S, slope = p.slope(c);
+                while (near < M && p.want(c, (int)near + 1) - p.want(c, (int)near) != slope) near *= 2;
+                differ += p.T[c] != (near < M ? p.want(c, (int)near) + (M - near) * slope : p.want(c, (int)M));
+            }
+            printf("%d %d %d\n", rc, p.status, differ);
         } else if (!strcmp(what, "faulty")) {
             int N, bad;
             if (scanf("%d %d", &N, &bad) != 2) return 2;

@@ -40,7 +40,6 @@ int main() {
         std::vector<tc_pair> part(PP_PARTS * PP_MAX_M_LIST);
         std::vector<pp_result> out(PP_MAX_M_LIST);
         p.a.nM = nM;
-        p.a.by_block = 0;
         p.a.search = search ? S : 0;
         p.a.bounds = e.data();
         p.a.bnd_stride = tri;

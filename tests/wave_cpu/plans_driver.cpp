@@ -82,7 +82,7 @@ int main() {
         std::vector<pp_result> out(PP_MAX_M_LIST);
         p.a.XF = guarded(p.XF);
         p.a.XB = guarded(p.XB);
-        p.a.nM = nM; p.a.by_block = 0; p.a.search = search ? S : 0;
+        p.a.nM = nM; p.a.search = search ? S : 0;
         p.a.orderings = p.o.data(); p.a.bounds = e.data(); p.a.bnd_stride = tri; p.a.t_stride = xs;
         p.a.T_out = T.data(); p.a.C = C.data(); p.a.part = part.data(); p.a.out = out.data(); p.a.hdr = &hdr;
         if (free_some) { p.a.free_bits = bits.data(); p.a.free_least = least.data(); p.a.free_plan = plan.data(); }
