@@ -77,7 +77,7 @@ def test_microbatch_counts_next_to_the_largest_int(driver, variant, S):
 def test_where_the_times_stop_to_fit(driver, variant, M):
     # one stage of all six layers, forward and backward, against the limit: in 30 bits with the padded sweeps; and 64-bit sums
     fits = (2**30 - 1) // ((2 * M + 4 if variant == GPIPE else M) + 4 + 64) // 12
-    times = sorted({max(t, 0) for t in (fits - 1, fits, fits + 1, 2 * fits, 2**24 // 12, 2**24 // 12 + 1, 2**40)})
+    times = sorted({max(t, 0) for t in (fits - 1, fits, fits + 1, 2 * fits, 2**24 // 12, 2**24 // 12 + 1, 2**35)})  # (12 * 2^35 * 10^6 < 2^62)
     out, errors = driver(["long %d 1 %d %d" % (variant, M, t) for t in times])
     assert out == [[0, 0, 0]] * len(times), times
     assert "runtime error" not in errors, errors[-2000:]
