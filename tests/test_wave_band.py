@@ -71,6 +71,24 @@ def test_work_counters(driver, kind):
             assert band_rows == 0, case
 
 
+@pytest.mark.parametrize("kind", [FREE, ZEROS, TIES, OUTLIER, SOME, MOST])
+def test_scheduled_where_they_are_found(driver, kind):
+    """One to four counts; a group of 64 in part and several; rows of two to 64 devices, multiples of four and not; and in the first
+    kind a bad ordering."""
+    cases = [(L, D, S, N, seed, kind, 0, 1) for L, D, S, N in SIZES + [(30, 3, 3, 191), (60, 5, 5, 257), (64, 8, 4, 129), (97, 6, 6, 300)]
+             for seed in (L + S, L + S + 1, L + S + 3)]
+    found = 0
+    for case, (rc, _, differ, done, reported, scheduled, times, minima, both) in zip(cases, driver(cases, "free")):
+        S, N = case[2:4]
+        assert (rc, differ, times, minima, both) == (0, 0, 0, 0, 0), case
+        if kind == FREE:
+            # (a link may reach into the values of a row without binding in the plan: with as many stages as 64, now and then)
+            assert (done, reported) == (N - 1, 1) and (scheduled == N - 1 if S < 64 else 2 * scheduled > N), case
+        found += scheduled
+        assert scheduled <= done
+    assert found > 0
+
+
 @pytest.mark.parametrize("kind", [FREE, ZEROS, SOME, HIGH])
 def test_short_lists(driver, kind):
     """A list too short for the recursion is looked at for the channel-free plan alone, and not at all where links bind so

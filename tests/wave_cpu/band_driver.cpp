@@ -8,23 +8,23 @@
 // of the channel-free program.  The list counts as one that is long enough for the recursion, with the argument
 // "short" as one that is not.  With the argument "layout" the cases are L D S N, and what is printed is whether
 // there is room for what k_band_free leaves, and whether a part of it lies where something else is at that time.
+// With the argument "free" (STAGES 0, WORDS 1) the candidates with the channel-free plan are also scheduled where they are
+// found, and printed are how many of these there are, how many of their T differ from Alg. 1's rules for the plan of the recursion, how many
+// minima of 64 are wrong, and how many candidates have both been scheduled and left something (bounds, or a bit for the DP kernel).
+#define main makespan_main
+#include "makespan_driver.cpp"
+#undef main
+
 #include "../../paper_2204_10562_amd/csrc/pp_dp_band_table.h"
 #include "../../paper_2204_10562_amd/csrc/pp_dp_band.hip"
-
-#include <string.h>
-
-#include <algorithm>
-#include <random>
 
 alignas(16) unsigned char smem[64 * 1024];  // the kernels' LDS
 alignas(16) long long dyn[8 * 1024];
 
 static void k_band_table(band_table_args a) { band_table(a, (unsigned char *)dyn); }
 
-typedef long long ll;
-
 int main(int argc, char **argv) {
-    const bool shorter = argc > 1 && !strcmp(argv[1], "short");
+    const bool shorter = argc > 1 && !strcmp(argv[1], "short"), frees = argc > 1 && !strcmp(argv[1], "free");
     int L, D, S, N, seed, kind, stages, words;
     if (argc > 1 && !strcmp(argv[1], "layout")) {
         while (scanf("%d %d %d %d", &L, &D, &S, &N) == 4) {
@@ -67,16 +67,21 @@ int main(int argc, char **argv) {
             std::shuffle(dev.begin(), dev.end(), g);
             std::copy(dev.begin(), dev.begin() + S, ord.begin() + (size_t)c * S);
         }
+        // (half of some layers' times, and of transfers, the other way)
+        for (int l = 0; frees && l < L; ++l) PB[l + 1] = PB[l] + (P[l + 1] - P[l]) / (2 + l % 3);
+        for (int l = 0; l <= L; ++l) PF[l] = P[l] - PB[l];
+        std::vector<ll> X = XF;
+        for (size_t i = 0; frees && i < XF.size(); ++i) { XB[i] = X[i] / (2 + i % 3); XF[i] = X[i] - XB[i]; }
         const int bad = N / 3;
         if (kind == 0) ord[(size_t)bad * S + S - 1] = ord[(size_t)bad * S];
         static pp_ws_header hdr;
         memset(&hdr, 0, sizeof hdr);
         ll vmax = P[L];
-        for (ll x : XF) vmax = std::max(vmax, x);
+        for (ll x : X) vmax = std::max(vmax, x);
         hdr.pmax[3] = (unsigned long long)vmax;
         std::vector<int> p32(L + 17, (int)P[L]), x32((size_t)D * D * L + 129, 0x55555555);
         for (int l = 0; l <= L; ++l) p32[l] = (int)P[l];
-        for (size_t i = 0; i < (size_t)D * D * L; ++i) x32[i] = i % L ? (int)XF[i - 1] : 0;
+        for (size_t i = 0; i < (size_t)D * D * L; ++i) x32[i] = i % L ? (int)X[i - 1] : 0;
         const int tri = stages ? S * (S + 1) / 2 : S, nc = stages ? S : 1;
         std::vector<int> table((size_t)S * 700, 0x7abcdef);
         std::vector<unsigned long long> links(band_link_words(D, S, stages)), left((N + 63) / 64);
@@ -101,8 +106,20 @@ int main(int argc, char **argv) {
         a.stages = stages; a.C_out = C.data(); a.bounds_out = bounds.data(); a.status = &status;
         a.band = table.data();
         a.band_all = shorter ? N + 1 : N;
+        a.PF = PF.data(); a.PB = PB.data(); a.XF = XF.data(); a.XB = XB.data();
+        const int groups = (N + 63) / 64, nM = 1 + seed % PP_FREE_COUNTS, Ms[] = {2 + seed % 5, 19, 5, 40};
+        std::vector<int2> fx((size_t)D * D * S);
+        std::vector<unsigned long long> bits(groups, 0);
+        std::vector<ll> T((size_t)nM * N, -7), least((size_t)nM * groups, -7);
+        if (frees) {
+            a.fx = fx.data(); a.fbits = bits.data(); a.fT = T.data(); a.fleast = least.data();
+            a.f_nM = nM;
+            for (int q = 0; q < PP_FREE_COUNTS; ++q) a.f_Ms[q] = q < nM ? Ms[q] : 1;
+        }
         const int rc = pp_launch_dp_band_alone(a, words ? links.data() : NULL, left.data(), NULL);
-        int differ = 0, ended = 0, reported = 0;
+        int differ = 0, ended = 0, reported = 0, scheduled = 0, times = 0, minima = 0, both = 0;
+        const int *plan = table.data() + band_plan_at(S, S);
+        std::vector<ll> lowest((size_t)nM * groups, -1);
         for (int c = 0; c < N; ++c) {
             // (without bands the pass does nothing, and the kernel behind it looks at nothing it has left)
             if (table[band_top_at(S, 0, S)] < 0 || (left[c >> 6] >> (c & 63) & 1)) continue;
@@ -123,6 +140,35 @@ int main(int argc, char **argv) {
                         if (v < W[n][l]) { W[n][l] = v; A[n][l] = k; }
                     }
                 }
+            if (hdr.free_valid && (bits[c >> 6] >> (c & 63) & 1)) {
+                ++scheduled;
+                both += left[c >> 6] >> (c & 63) & 1;
+                for (int n = 0; n < S; ++n) both += bounds[(size_t)c * S + n] != -7;
+                differ += C[c] != W[S - 1][L];
+                for (int n = S - 1, e = L; n >= 0; --n) {
+                    differ += plan[n] != e;
+                    e = A[n][e];
+                }
+                const int R = 2 * S - 1;
+                std::vector<ll> d(2 * R + 1, 0);
+                for (int n = 0; n < S; ++n) {
+                    const int e0 = n ? plan[n - 1] : 0, r = 2 * n + 1;
+                    const ll F = PF[plan[n]] - PF[e0], B = PB[plan[n]] - PB[e0];
+                    d[r] = n == S - 1 ? F + B : F;
+                    if (n < S - 1) d[2 * R - r] = B;
+                    if (!n) continue;
+                    const size_t at = ((size_t)ord[(size_t)c * S + n - 1] * D + ord[(size_t)c * S + n]) * L + e0 - 1;
+                    d[r - 1] = XF[at];
+                    d[2 * R - r + 1] = XB[at];
+                }
+                for (int q = 0; q < nM; ++q) {
+                    const ll t = reference(PP_SCHED_PE, S, Ms[q], d, 0, 0), v = t << 6 | (c & 63);
+                    times += T[(size_t)q * N + c] != t;
+                    ll &l = lowest[(size_t)q * groups + (c >> 6)];
+                    if (l < 0 || v < l) l = v;
+                }
+                continue;
+            }
             for (int xi = stages ? 1 : S; xi <= S; ++xi) {
                 differ += C[(size_t)c * nc + (stages ? xi - 1 : 0)] != W[xi - 1][L];
                 const int *b = &bounds[(size_t)c * tri + (stages ? xi * (xi - 1) / 2 : 0)];
@@ -132,7 +178,13 @@ int main(int argc, char **argv) {
                 }
             }
         }
+        for (int i = 0; hdr.free_valid && i < nM * groups; ++i) minima += least[i] != lowest[i];
         printf("%d %d %d %d %d", rc, status, differ, ended, reported);
+        if (frees) {
+            printf(" %d %d %d %d\n", scheduled, times, minima, both);
+            fflush(stdout);
+            continue;
+        }
         ll work[5] = {};
         for (auto &w : hdr.work) {
             work[0] += w.pairs; work[1] += w.rows; work[2] += w.band_pairs; work[3] += w.band_rows; work[4] += w.free_rows;
