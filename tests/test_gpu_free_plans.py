@@ -13,7 +13,7 @@ SIZES = [
     (60, 8, 8, 60001), (97, 11, 3, 200003), (97, 12, 11, 30011), (100, 9, 7, 150000), (128, 16, 16, 20000), (77, 33, 31, 9001),
     (129, 6, 5, 64), (150, 9, 9, 65), (257, 12, 11, 3000), (200, 20, 18, 4500), (300, 64, 64, 300), (140, 4, 2, 777)]
 # (the kernel of the rows looks for them itself, or candidates share their program)
-ELSEWHERE = [(128, 16, 16, 20000), (129, 6, 5, 64), (140, 4, 2, 777)]
+ELSEWHERE = [(97, 11, 3, 200003), (97, 12, 11, 30011), (128, 16, 16, 20000), (129, 6, 5, 64), (140, 4, 2, 777)]
 
 
 @pytest.mark.parametrize("L,D,S,N", SIZES)
