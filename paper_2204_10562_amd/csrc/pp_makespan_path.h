@@ -261,29 +261,30 @@ __device__ __forceinline__ mk_plan_info mk_plan32(const mk_args &a, const int *r
 }
 
 // The same of a plan whose largest time is known to fit (its C), of valid devices: nothing is checked, and of every number
-// the low half is read.
+// the low half is read.  What it returns is negative if one of the bounds is none (it is taken for L).
 template <int NM>
-__device__ __forceinline__ void mk_plan_known(const mk_args &a, const int *row, const int2 *PT, int xi, bool good,
-                                              const int (&M)[NM], long long (&T)[NM]) {
+__device__ __forceinline__ int mk_plan_known(const mk_args &a, const int *row, const int2 *PT, int xi, bool good,
+                                             const int (&M)[NM], long long (&T)[NM]) {
     mk_path<int, NM> path;
     path.start();
     bool briefly[NM];
     mk_briefly<PP_SCHED_PE>(M, xi, briefly);
     const int *XF = (const int *)a.XF, *XB = (const int *)a.XB;
     struct piece { int f[MK_AT_ONCE], b[MK_AT_ONCE], e[MK_AT_ONCE]; };
-    int before = 0;  // the word of the stage before
+    int before = 0, cut = 0, all = 0;  // the device and the bound of the stage before; the words together
     auto ask = [&](piece &x, int n0) {
 #pragma unroll
         for (int u = 0; u < MK_AT_ONCE; ++u) {
             const int n = n0 + u;
             x.f[u] = x.b[u] = x.e[u] = 0;
             if (n >= xi) continue;
-            const int w = row[n];
-            const unsigned link = (unsigned)mk_times(before & 0xffff, a.D) + (unsigned)(w & 0xffff);
-            const size_t at = good ? (size_t)((link & 0xffffff) * ((unsigned)a.L & 0xffffff) + ((unsigned)before >> 16) - 1) * 2 : 0;
+            const int w = row[n], e = (int)((unsigned)w >> 16);
+            const unsigned link = (unsigned)mk_times(before, a.D) + (unsigned)(w & 0xffff);
+            const size_t at = good ? (size_t)((link & 0xffffff) * ((unsigned)a.L & 0xffffff) + (unsigned)cut - 1) * 2 : 0;
             if (n) { x.f[u] = XF[at]; x.b[u] = XB[at]; }
-            x.e[u] = good ? (int)((unsigned)w >> 16) : 0;
-            before = w;
+            all |= w;
+            before = w & 0xffff;
+            cut = x.e[u] = good ? e < a.L ? e : a.L : 0;
         }
     };
     piece now, then;
@@ -303,6 +304,7 @@ __device__ __forceinline__ void mk_plan_known(const mk_args &a, const int *row, 
     }
 #pragma unroll
     for (int q = 0; q < NM; ++q) T[q] = path.longest(q);
+    return good ? all : 0;
 }
 
 // In 64 bits.
@@ -417,25 +419,30 @@ __device__ __forceinline__ void mk_path_body(const mk_args &a) {
             }
         idle = __syncthreads_and(idle);
     }
-    // (16 loads in flight: 2000 plans of 8 stages, 2000 layers, a wave to a workgroup, three counts 29.6 us for the call with two, 24.3 so)
-    for (int i0 = idle ? L + 1 : tid; i0 <= L; i0 += 8 * threads) {
-        long long f[8], b[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int i = i0 + u * threads <= L ? i0 + u * threads : L;
-            f[u] = a.PF[i];
-            b[u] = a.PB[i];
+    auto table = [&](int i, long long f, long long b) {
+        if (KNOWN) {
+            PK[i] = make_int2((int)f, (int)b);
+        } else {
+            PT[2 * i] = f;
+            PT[2 * i + 1] = b;
         }
+    };
+    if (L < 4 * threads) {
+        for (int i = idle ? L + 1 : tid; i <= L; i += threads) table(i, a.PF[i], a.PB[i]);
+    } else {
+        // (of many layers 16 loads in flight: 2000 plans of 8 stages, 2000 layers, a wave to a workgroup, three counts 29.6 us for the
+        // call with two, 24.3 so; of few, more code to fetch: the plans of every stage count of 8!, 128 layers 28.6 and 29.4)
+        for (int i0 = idle ? L + 1 : tid; i0 <= L; i0 += 8 * threads) {
+            long long f[8], b[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int i = i0 + u * threads;
-            if (i > L) continue;
-            if (KNOWN) {
-                PK[i] = make_int2((int)f[u], (int)b[u]);
-            } else {
-                PT[2 * i] = f[u];
-                PT[2 * i + 1] = b[u];
+            for (int u = 0; u < 8; ++u) {
+                const int i = i0 + u * threads <= L ? i0 + u * threads : L;
+                f[u] = a.PF[i];
+                b[u] = a.PB[i];
             }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (i0 + u * threads <= L) table(i0 + u * threads, f[u], b[u]);
         }
     }
     int *mine = rows + (KNOWN ? mk_known_table_bytes(L) : mk_path_table_bytes(L)) / 4 + wave * (mk_path_wave_bytes(S) / 4);
@@ -463,7 +470,6 @@ __device__ __forceinline__ void mk_path_body(const mk_args &a) {
             // the group's rows, entry by entry: as many loads in flight as there are stages, up to 8
             const int di = 64 / xi, dn = 64 - di * xi;
             int i = lane / xi, n = lane - i * xi;
-            bool odd = false;  // a bound that is none (not of plans that are scheduled already, which have none in memory)
             __builtin_amdgcn_wave_barrier();
             for (int t0 = 0; t0 < xi; t0 += 8) {
                 int o[8], e[8], to[8];
@@ -472,18 +478,16 @@ __device__ __forceinline__ void mk_path_body(const mk_args &a) {
                     const long long ci = listed ? (long long)__shfl((int)c, i & 63) : g * 64 + i;
                     to[u] = t0 + u < xi && i < held ? i * SP + n : -1;
                     o[u] = to[u] >= 0 && a.orderings ? a.orderings[ci * a.ord_stride + n] : 0;
-                    e[u] = to[u] < 0 ? 0 : FREE && (ended >> (i & 63) & 1) ? L : a.bounds[ci * a.bnd_stride + bnd_off + n];
+                    e[u] = to[u] >= 0 ? a.bounds[ci * a.bnd_stride + bnd_off + n] : 0;
                     n += dn;
                     i += di;
                     if (n >= xi) { n -= xi; ++i; }
                 }
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
-                    if (to[u] >= 0) {
-                        const bool in = e[u] >= 1 && e[u] <= L;
-                        odd |= !in;
-                        mine[to[u]] = (o[u] >= 0 && o[u] < D ? o[u] : 0xffff) | (int)((unsigned)(in ? e[u] : 0xffff) << 16);
-                    }
+                    if (to[u] >= 0)
+                        mine[to[u]] = (o[u] >= 0 && o[u] < D ? o[u] : 0xffff) |
+                                      (int)((unsigned)(e[u] >= 1 && e[u] <= L ? e[u] : 0xffff) << 16);
             }
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             __builtin_amdgcn_wave_barrier();
@@ -508,17 +512,15 @@ __device__ __forceinline__ void mk_path_body(const mk_args &a) {
             long long T[NM];
             mk_plan_info p = {};
             if (KNOWN) {
-                // (the rows of a wave are looked at only where one of its orderings is bad, or a bound is none: then C is not
-                // what it should be, and the plan reads nothing)
+                // (the rows of a wave are looked at only where one of its orderings is bad, whose C says so, or a bound is none)
                 const bool bad = C == PP_INF64 && !done;
-                if (__ballot(bad || odd)) {
+                const int all = mk_plan_known<NM>(a, row, PK, xi, live && !bad && !done, M, T);
+                if (__ballot(bad || all < 0)) {
                     mk_row_check check;
                     check.start();
                     for (int n = 0; n < xi; ++n) check.stage(a, row, n, row[n]);
                     p.fault = check.fault(a, live && !done);
                 }
-                const bool good = live && !bad && !done && !p.fault;
-                mk_plan_known<NM>(a, row, PK, xi, good, M, T);
                 p.fits = !live || done || p.fault || C <= limit;
             } else {
                 p = mk_plan32<MODE, NM>(a, row, PT, xi, live, M, limit, T);
