@@ -99,7 +99,7 @@ struct mk_path {
 #define MK_PICK_WAVES 4      // short lists of up to so many groups of 64: one workgroup schedules and picks
 
 // LDS: PF and PB in pairs, then per wave one word per stage of each of its 64 plans, in rows an odd number
-// of words apart: the device, and above it the stage's bound (0xffff: none such).
+// of words apart: the device (0xffff: none such), and above it the stage's bound (none such: L and the sign bit).
 __host__ __device__ static inline size_t mk_path_table_bytes(int L) { return (size_t)(L + 1) * 16; }
 // (of the planner's own plans, whose times are known to fit, the low halves)
 __host__ __device__ static inline size_t mk_known_table_bytes(int L) { return ((size_t)(L + 2) * 8) & ~(size_t)15; }
@@ -278,13 +278,13 @@ __device__ __forceinline__ int mk_plan_known(const mk_args &a, const int *row, c
             const int n = n0 + u;
             x.f[u] = x.b[u] = x.e[u] = 0;
             if (n >= xi) continue;
-            const int w = row[n], e = (int)((unsigned)w >> 16);
+            const int w = row[n];
             const unsigned link = (unsigned)mk_times(before, a.D) + (unsigned)(w & 0xffff);
             const size_t at = good ? (size_t)((link & 0xffffff) * ((unsigned)a.L & 0xffffff) + (unsigned)cut - 1) * 2 : 0;
             if (n) { x.f[u] = XF[at]; x.b[u] = XB[at]; }
             all |= w;
             before = w & 0xffff;
-            cut = x.e[u] = good ? e < a.L ? e : a.L : 0;
+            cut = x.e[u] = good ? w >> 16 & 0x7fff : 0;
         }
     };
     piece now, then;
@@ -392,8 +392,10 @@ __device__ __forceinline__ void mk_path_body(const mk_args &a) {
     const int S = a.S, L = a.L, D = a.D;
     long long *PT = (long long *)rows;
     int2 *PK = (int2 *)rows;
-    const bool listed = a.rlist && a.hdr->share_active;
-    const long long todo = listed ? a.hdr->share_nreps : a.N, groups = (todo + 63) / 64;
+    // (one trip to memory for what the header says)
+    const unsigned active = a.rlist ? a.hdr->share_active : 0, nreps = a.rlist ? a.hdr->share_nreps : 0;
+    const bool listed = active;
+    const long long todo = listed ? nreps : a.N, groups = (todo + 63) / 64;
     const bool has_free = FREE && mk_has_free(a);
     const int counts = a.search ? a.search : 1, per = a.search ? 1 : waves;
     tc_pair least[NM];
@@ -487,7 +489,7 @@ __device__ __forceinline__ void mk_path_body(const mk_args &a) {
                 for (int u = 0; u < 8; ++u)
                     if (to[u] >= 0)
                         mine[to[u]] = (o[u] >= 0 && o[u] < D ? o[u] : 0xffff) |
-                                      (int)((unsigned)(e[u] >= 1 && e[u] <= L ? e[u] : 0xffff) << 16);
+                                      (int)((unsigned)(e[u] >= 1 && e[u] <= L ? e[u] : 0x8000 | L) << 16);
             }
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             __builtin_amdgcn_wave_barrier();
