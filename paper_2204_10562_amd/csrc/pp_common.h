@@ -78,7 +78,10 @@ __device__ __forceinline__ void pp_count_work(pp_ws_header *hdr, unsigned long l
 
 // Workspace carving, identical for pp_partition_dp and pp_best_plan.
 struct pp_ws_layout {
-    size_t hdr, p32, x32, xkt, xct, bfl, ord, arg, bounds, C, T, part, total;
+    size_t hdr, p32, x32, xkt, xct, bfl, ord, arg, bounds, C, part, total;
+    // 8 bytes per candidate: what the bands leave to the DP kernel, as bits behind the links' words or as a list, and k_band_free's
+    // bits and minima
+    size_t left;
     size_t band;  // the table of the bands (pp_dp_band.h), behind the backtrack tables; 0: not wanted
     // k_band_free: the links' words and, behind them, their transfer times at the channel-free plan's cuts; a bit per candidate;
     // a minimum per 64 candidates and microbatch count.  All in places that are needed later, or no longer (0: no room).
@@ -95,7 +98,8 @@ struct pp_ws_layout {
 // pp_dp_tiles (pp_dp.hip) says so.
 #define PP_PAIRS_MAX_L 88
 #define PP_DP_SLOTS 4096
-// Most microbatch counts of a call for which k_band_free schedules (pp_sched_info).
+// Most microbatch counts of a call for which k_band_free schedules (pp_sched_info): what a lane works on at once.  Calls with more
+// write the bounds and read them again (2^20 candidates of 32 stages, four counts 285 us, five 1190; 200 003 of 11 65 and 100).
 #define PP_FREE_COUNTS 4
 // Most partial minima of the arg-min per microbatch count (workgroups of a schedule launch).
 #define PP_PARTS 2048
@@ -144,7 +148,7 @@ static inline pp_ws_layout pp_layout(int L, int D, int S, int64_t N) {
     w.band = pp_band_wanted(S, N) ? w.arg + pp_align256((size_t)w.slots * S * (L + 63) * 2) : 0;
     w.bounds = off; off += pp_align256((size_t)N * S * 4);
     w.C = off;      off += pp_align256((size_t)N * 8);
-    w.T = off;      off += pp_align256((size_t)N * 8);
+    w.left = off;   off += pp_align256((size_t)N * 8);
     w.part = off;   off += pp_align256((size_t)((N + 63) / 64 < PP_PARTS ? (N + 63) / 64 : PP_PARTS) * 16 * PP_MAX_M_LIST);
     w.sh_hash = w.sh_rep = w.sh_table = w.sh_keys = w.sh_reps = w.sh_cnt = w.sh_start = w.sh_rows = 0;
     w.sh_row_slots = 0;
@@ -165,7 +169,7 @@ static inline pp_ws_layout pp_layout(int L, int D, int S, int64_t N) {
         w.sh_row_slots = (long long)nr;
         w.sh_rows = off;  off += pp_align256(nr * row);
     }
-    // The bits and minima lie in the upper part of T's place, whose lower half holds the list or the bits of the candidates
+    // The bits and minima lie in the upper part of w.left, whose lower half holds the list or the bits of the candidates
     // that are left (4 N + 7 + 40 (N / 64 + 1) <= 8 N); the links' times are not needed any more when the DP kernels begin, and lie in
     // what these then fill: the saved rows (64 waves' and more, S - 1 of 1040 bytes and more each, hold 8 S bytes per
     // link of up to 64 devices), or the backtrack tables (from 253 candidates on always).
@@ -173,7 +177,7 @@ static inline pp_ws_layout pp_layout(int L, int D, int S, int64_t N) {
     const size_t free_room = w.sh_rows ? off - w.sh_rows : (size_t)w.slots * S * (L + 63) * 2;
     if (w.band && D <= 64 && free_room >= (size_t)D * D * S * 8) {
         w.fx = w.sh_rows ? w.sh_rows : w.arg;
-        w.fbits = w.T + (((size_t)N * 4 + 7) & ~(size_t)7);
+        w.fbits = w.left + (((size_t)N * 4 + 7) & ~(size_t)7);
         w.fleast = w.fbits + (size_t)((N + 63) / 64) * 8;
     }
     w.total = off;

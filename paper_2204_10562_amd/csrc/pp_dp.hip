@@ -360,7 +360,7 @@ static int band_use(int L, int D, int S, int64_t N, int stages, bool lex, const 
         band_table_lds(L, S, stages, waves);
         return !stages || band_whole_us(L, D, S, N, lex, lay) >= (double)S * S / waves ? BAND_USE_INSIDE : BAND_USE_NOT;
     }
-    const bool room = (size_t)band_link_words(D, S, stages) * 8 + (size_t)N / 8 + 8 <= (size_t)N * 8;  // (in T's place)
+    const bool room = (size_t)band_link_words(D, S, stages) * 8 + (size_t)N / 8 + 8 <= (size_t)N * 8;  // (in lay.left)
     const bool inside = pp_dp_tiles(L, D, S, N, lay) <= DPT_INSIDE_NT && band_link_bytes(D, S, stages) != 0;
     if (room && band_cells(L, D, S, N, stages, lex, lay)) return BAND_USE_ALONE;
     if (inside) return work >= 3e6 ? BAND_USE_INSIDE : BAND_USE_NOT;
@@ -524,8 +524,8 @@ int pp_launch_dp(int L, int D, int S, int64_t N, const int64_t *PF, const int64_
     };
     const int nt = pp_dp_tiles(L, D, S, N, lay);
     if (use == BAND_USE_ALONE) {
-        // (in T's place; with the links' times, where these are)
-        unsigned long long *left = (unsigned long long *)(base + lay.T), *words = left;
+        // (in lay.left; with the links' times, where these are)
+        unsigned long long *left = (unsigned long long *)(base + lay.left), *words = left;
         if (a.fx) words = (unsigned long long *)a.fx;
         else left += band_link_words(D, S, stages);
         a.left = left;
@@ -579,7 +579,7 @@ int pp_launch_dp(int L, int D, int S, int64_t N, const int64_t *PF, const int64_
     if (rc) return rc;
     pp_share_list list;
     list.reps = (const int *)(base + lay.sh_reps);
-    list.pend = (const int *)(base + lay.T);
+    list.pend = (const int *)(base + lay.left);
     list.keys = (const int *)(base + lay.sh_keys);
     list.start = (const int *)(base + lay.sh_start);
     list.rows = (int *)(base + lay.sh_rows);

@@ -7,7 +7,7 @@
 // and down(p), or what is like it, is the largest over q (2 S - 1 peaks by up to S ends, three instructions each).
 //
 // What bounds it: instruction issue: about 100 instructions per stage for its times (quotients in doubles), as many
-// for the minima over the links, and the walks.  40 320 orderings of 8 GPUs, plans of 1 .. 8 stages, M = 64: 134 -> 33 us
+// for the minima over the links, and the walks.  40 320 orderings of 8 GPUs, plans of 1 .. 8 stages, M = 64: 134 -> 35 us
 // (64-bit integer quotients and a sweep over all blocks per microbatch before); 3001 of 12 GPUs 58 -> 33 us.
 #include <limits.h>
 

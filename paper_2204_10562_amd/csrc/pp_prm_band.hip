@@ -23,7 +23,7 @@
 //
 // What bounds it: trips to the scratch memory, which the waves in flight (2.5 per SIMD) spread over more than the caches hold,
 // and instructions.  All 40320 orderings of 8 GPUs, 128 layers: 3.80 ms with k_prm, 0.275 with every channel term and
-// every minimum over r', 0.227 now; 3001 orderings of 12 GPUs, 75 layers: 1.95, 0.226, 0.199 ms.  (Plans were read back with
+// every minimum over r', 0.196 now; 3001 orderings of 12 GPUs, 75 layers: 1.95, 0.226, 0.173 ms.  (Plans were read back with
 // the minima over their links worked out again and a trip to memory per r' tried: 30 % of the first one's time.)
 #include "pp_prm.h"
 #include "pp_dp_row.h"

@@ -481,7 +481,7 @@ static share_args share_base(void *ws, const pp_ws_layout &lay) {
     a.reps = (int *)(base + lay.sh_reps);
     a.cnt = (int *)(base + lay.sh_cnt);
     a.start = (int *)(base + lay.sh_start);
-    a.pend = (int *)(base + lay.T);
+    a.pend = (int *)(base + lay.left);
     return a;
 }
 

@@ -31,7 +31,7 @@ int main(int argc, char **argv) {
             const pp_ws_layout w = pp_layout(L, D, S, N);
             const size_t groups = (N + 63) / 64, lower = w.sh_rows ? (size_t)N * 4 : groups * 8;  // the list, or the bits
             const size_t times = w.fx + (size_t)D * D * S * 8;
-            bool clash = w.fbits < w.T + lower || w.fleast < w.fbits + groups * 8 || w.fleast + groups * 8 * PP_FREE_COUNTS > w.part;
+            bool clash = w.fbits < w.left + lower || w.fleast < w.fbits + groups * 8 || w.fleast + groups * 8 * PP_FREE_COUNTS > w.part;
             clash |= w.sh_rows ? w.fx != w.sh_rows || times > w.total : w.fx != w.arg || times > w.band;
             clash |= (w.fx | w.fbits | w.fleast) & 7;
             printf("%d %d\n", w.fx != 0, w.fx && clash);
